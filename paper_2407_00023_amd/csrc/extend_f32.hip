@@ -4,109 +4,162 @@
 // cached prefix reused losslessly (Sec. 3.2, Sec. 5): extend row i of request r sees the
 // P_r cached prefix tokens (rows of the pool named by slot_idx) and extend tokens 0..i.
 //
-// One wavefront computes one output row (one extend token, one query head).  Keys are
-// taken 64 at a time: lane j forms the score of key j, the wave reduces max and sum for
-// the online softmax, then lane d accumulates output element d over the 64 keys.
+// A workgroup computes the output rows of one extend token for up to kHeads query heads of one KV head.  D / 4 lanes
+// share a key (16 bytes of its K row and of its V row each, so that rows are read whole and coalesced); the
+// workgroup's 1,024 / D groups take keys in turn, each with an online softmax of its own, joined at the end.
+// At the sizes this path serves (some hundred rows, some hundred keys) what bounds it is the chain of dependent memory
+// round trips, not the arithmetic: a group's K and V rows are asked for together, kUnroll keys at a time, the slot ids
+// of the next keys ahead of them, and the token's request is found by one comparison per lane instead of a search.
+// (One wave per row, keys lane by lane, V row by row behind the scores: 28 us for 97 tokens x 4 heads over 96 keys.)
 #include "common.h"
 
 namespace pa {
 
-template <int D>
-__global__ __launch_bounds__(256) void extend_f32_kernel(
-    const float* __restrict__ q_ext, const float* __restrict__ k_ext, const float* __restrict__ v_ext,
-    const float* __restrict__ pool, const int32_t* __restrict__ slot_idx, const int32_t* __restrict__ slot_offsets,
-    const int32_t* __restrict__ prefix_len, const int32_t* __restrict__ ext_len,
-    const int32_t* __restrict__ ext_offsets, int B, int64_t T, int Hq, int Hkv, int page_size, int64_t num_slots,
-    float scale, float* __restrict__ out) {
-    constexpr int DPL = D / 64;  // output elements per lane
-    const int lane = threadIdx.x & 63;
-    const int64_t row = blockIdx.x * 4ll + (threadIdx.x >> 6);  // (extend token, head)
-    if (row >= T * Hq) return;
-    const int64_t t = row / Hq;
-    const int h = static_cast<int>(row - t * Hq);
-    const int g = h / (Hq / Hkv);
-
-    // request of extend token t: last r with ext_offsets[r] <= t
+// The request of extend token t: how many of ext_offsets[1 .. B) are <= t.
+__device__ __forceinline__ int request_of(const int32_t* __restrict__ ext_offsets, int B, int64_t t) {
+    constexpr int kDirect = 256;  // up to this many: all offsets in one round trip; beyond, a search
+    if (B <= kDirect) {
+        int r = 0;
+#pragma unroll
+        for (int c = 0; c < kDirect; c += 64) {
+            const int k = c + static_cast<int>(threadIdx.x & 63);
+            r += __popcll(__ballot(k >= 1 && k < B && ext_offsets[k] <= t));
+        }
+        return r;
+    }
     int lo = 0, hi = B;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (ext_offsets[mid] <= t) lo = mid; else hi = mid;
     }
-    const int r = lo;
-    const int i = static_cast<int>(t - ext_offsets[r]);
-    if (i >= ext_len[r]) return;  // inconsistent offsets: produce nothing rather than read out of range
-    const int P = prefix_len[r];
-    const int nvis = P + i + 1;
-    const int32_t* __restrict__ slots = slot_idx + slot_offsets[r];
+    return lo;
+}
+
+template <int D, int kHeads>
+__global__ __launch_bounds__(256) void extend_f32_kernel(
+    const float* __restrict__ q_ext, const float* __restrict__ k_ext, const float* __restrict__ v_ext,
+    const float* __restrict__ pool, const int32_t* __restrict__ slot_idx, const int32_t* __restrict__ slot_offsets,
+    const int32_t* __restrict__ prefix_len, const int32_t* __restrict__ ext_len,
+    const int32_t* __restrict__ ext_offsets, int B, int Hq, int Hkv, int page_size, int64_t num_slots,
+    float scale, float* __restrict__ out) {
+    constexpr int kLanes = D / 4;            // lanes of a group: one 16-byte piece of a row each
+    constexpr int kGroups = 256 / kLanes;    // keys in work at once
+    constexpr int kUnroll = 4;               // keys a group asks for together
+    __shared__ float4 s_acc[4][kHeads][kLanes];
+    __shared__ float s_m[4][kHeads], s_l[4][kHeads];
+    const int tid = threadIdx.x, c = tid % kLanes, group = tid / kLanes;
+    const int64_t t = blockIdx.x;
+    const int G = Hq / Hkv, g = blockIdx.y;
+    const int h0 = g * G + blockIdx.z * kHeads, n_heads = min(kHeads, (g + 1) * G - h0);
+
+    const int r = request_of(ext_offsets, B, t);
     const int64_t e0 = ext_offsets[r];
+    const int i = static_cast<int>(t - e0);
+    const int P = prefix_len[r];
+    const int32_t* __restrict__ slots = slot_idx + slot_offsets[r];
+    if (i >= ext_len[r]) return;  // inconsistent offsets: produce nothing rather than read out of range
+    const int nvis = P + i + 1;
+    const unsigned last_slot = static_cast<unsigned>(min(num_slots, int64_t{INT32_MAX})) - 1u;
 
-    float qreg[DPL];
+    float4 q[kHeads], acc[kHeads];
+    float m[kHeads], l[kHeads];
 #pragma unroll
-    for (int x = 0; x < DPL; ++x) qreg[x] = q_ext[(t * Hq + h) * D + x * 64 + lane] * scale;
-
-    float m = -INFINITY, l = 0.f;
-    float acc[DPL];
+    for (int x = 0; x < kHeads; ++x) {
+        const float4 v = reinterpret_cast<const float4*>(q_ext + (t * Hq + h0 + min(x, n_heads - 1)) * D)[c];
+        q[x] = make_float4(v.x * scale, v.y * scale, v.z * scale, v.w * scale);
+        acc[x] = make_float4(0.f, 0.f, 0.f, 0.f);
+        m[x] = -INFINITY;
+        l[x] = 0.f;
+    }
+    // (keys past the end repeat the last visible one with probability 0: the lanes of a group stay together)
+    auto slot_of = [&](int j) { return j < P ? slots[j] : 0; };
+    int32_t sl[kUnroll];
 #pragma unroll
-    for (int x = 0; x < DPL; ++x) acc[x] = 0.f;
-
-    for (int j0 = 0; j0 < nvis; j0 += 64) {
-        const int j = j0 + lane;
-        const bool vis = j < nvis;
-        // element offsets of this lane's key row and value row; lanes past the end read a valid
-        // dummy row (extend token 0 of the request) so that the whole wave stays convergent
-        const float* kp = k_ext;
-        int64_t koff = (e0 * Hkv + g) * static_cast<int64_t>(D), voff = koff;
-        if (vis) {
+    for (int u = 0; u < kUnroll; ++u) sl[u] = slot_of(min(u * kGroups + group, nvis - 1));
+    for (int j0 = 0; j0 < nvis; j0 += kGroups * kUnroll) {
+        float4 k[kUnroll], v[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int j = min(j0 + u * kGroups + group, nvis - 1);
+            const float *kp, *vp;
             if (j < P) {
-                int64_t sl = slots[j];
-                sl = sl < 0 ? 0 : (sl >= num_slots ? num_slots - 1 : sl);
-                kp = pool;
-                koff = pool_row(sl, 0, g, Hkv, D, page_size);
-                voff = pool_row(sl, 1, g, Hkv, D, page_size);
+                const unsigned s = min(static_cast<unsigned>(max(sl[u], 0)), last_slot);  // never outside the pool
+                const unsigned page = s / static_cast<unsigned>(page_size), o = s - page * static_cast<unsigned>(page_size);
+                const int64_t row = (static_cast<int64_t>(page) * 2 * Hkv + g) * page_size + o;
+                kp = pool + row * D;
+                vp = kp + static_cast<int64_t>(Hkv) * page_size * D;
             } else {
-                koff = voff = ((e0 + (j - P)) * Hkv + g) * static_cast<int64_t>(D);
+                const int64_t row = (e0 + (j - P)) * Hkv + g;
+                kp = k_ext + row * D;
+                vp = v_ext + row * D;
             }
+            k[u] = reinterpret_cast<const float4*>(kp)[c];
+            v[u] = reinterpret_cast<const float4*>(vp)[c];
         }
-        float s = 0.f;
-        {
-            const float4* k4 = reinterpret_cast<const float4*>(kp + koff);
 #pragma unroll
-            for (int c = 0; c < D / 4; ++c) {
-                const float4 kk = k4[c];
-                const int d = 4 * c;
-                s += __shfl(qreg[d / 64], d % 64) * kk.x;
-                s += __shfl(qreg[(d + 1) / 64], (d + 1) % 64) * kk.y;
-                s += __shfl(qreg[(d + 2) / 64], (d + 2) % 64) * kk.z;
-                s += __shfl(qreg[(d + 3) / 64], (d + 3) % 64) * kk.w;
+        for (int u = 0; u < kUnroll; ++u) sl[u] = slot_of(min(j0 + (kUnroll + u) * kGroups + group, nvis - 1));
+#pragma unroll
+        for (int x = 0; x < kHeads; ++x) {
+            float s[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                float d = q[x].x * k[u].x + q[x].y * k[u].y + q[x].z * k[u].z + q[x].w * k[u].w;
+#pragma unroll
+                for (int off = 1; off < kLanes; off <<= 1) d += __shfl_xor(d, off);
+                s[u] = j0 + u * kGroups + group < nvis ? d : -INFINITY;
             }
-        }
-        if (!vis) s = -INFINITY;
-        float cm = s;
+            float mx = m[x];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) cm = fmaxf(cm, __shfl_xor(cm, off));
-        const float m_new = fmaxf(m, cm);
-        const float alpha = expf(m - m_new);  // first chunk: exp(-inf) = 0
-        const float p = vis ? expf(s - m_new) : 0.f;
-        float ps = p;
+            for (int u = 0; u < kUnroll; ++u) mx = fmaxf(mx, s[u]);
+            const float ref = mx == -INFINITY ? 0.f : mx;  // (a group that has seen no key yet)
+            const float alpha = expf(m[x] - ref);
+            m[x] = mx;
+            l[x] *= alpha;
+            acc[x].x *= alpha; acc[x].y *= alpha; acc[x].z *= alpha; acc[x].w *= alpha;
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off);
-        l = l * alpha + ps;
-        m = m_new;
-#pragma unroll
-        for (int x = 0; x < DPL; ++x) acc[x] *= alpha;
-        const int cnt = min(64, nvis - j0);
-        for (int jj = 0; jj < cnt; ++jj) {
-            const float pj = __shfl(p, jj);
-            const bool in_pool = (j0 + jj) < P;
-            const long long vo = __shfl(static_cast<long long>(voff), jj);
-            const float* vrow = (in_pool ? pool : v_ext) + vo;
-#pragma unroll
-            for (int x = 0; x < DPL; ++x) acc[x] += pj * vrow[x * 64 + lane];
+            for (int u = 0; u < kUnroll; ++u) {
+                const float p = expf(s[u] - ref);
+                l[x] += p;
+                acc[x].x += p * v[u].x; acc[x].y += p * v[u].y; acc[x].z += p * v[u].z; acc[x].w += p * v[u].w;
+            }
         }
     }
-    const float inv = 1.f / l;
+    // join the groups: those of a wave by exchange, then the four waves through LDS
+    const int wave = tid >> 6, lane = tid & 63;
 #pragma unroll
-    for (int x = 0; x < DPL; ++x) out[(t * Hq + h) * D + x * 64 + lane] = acc[x] * inv;
+    for (int x = 0; x < kHeads; ++x) {
+#pragma unroll
+        for (int off = kLanes; off < 64; off <<= 1) {
+            const float mo = __shfl_xor(m[x], off), mn = fmaxf(m[x], mo), ref = mn == -INFINITY ? 0.f : mn;
+            const float a = expf(m[x] - ref), b = expf(mo - ref);
+            l[x] = l[x] * a + __shfl_xor(l[x], off) * b;
+            acc[x].x = acc[x].x * a + __shfl_xor(acc[x].x, off) * b;
+            acc[x].y = acc[x].y * a + __shfl_xor(acc[x].y, off) * b;
+            acc[x].z = acc[x].z * a + __shfl_xor(acc[x].z, off) * b;
+            acc[x].w = acc[x].w * a + __shfl_xor(acc[x].w, off) * b;
+            m[x] = mn;
+        }
+        if (lane < kLanes) s_acc[wave][x][c] = acc[x];
+        if (lane == 0) {
+            s_m[wave][x] = m[x];
+            s_l[wave][x] = l[x];
+        }
+    }
+    __syncthreads();
+    for (int y = tid; y < n_heads * D; y += 256) {
+        const int x = y / D, d = y % D;
+        float mx = s_m[0][x];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) mx = fmaxf(mx, s_m[w][x]);
+        float num = 0.f, den = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float a = expf(s_m[w][x] - mx);  // (some group has seen key 0, so the maximum is finite)
+            num += a * reinterpret_cast<const float*>(&s_acc[w][x][0])[d];
+            den += a * s_l[w][x];
+        }
+        out[(t * Hq + h0 + x) * D + d] = num / den;
+    }
 }
 
 }  // namespace pa
@@ -116,17 +169,23 @@ int pa_extend_attention_f32(const void* q_ext, const void* k_ext, const void* v_
                             const int32_t* slot_idx, const int32_t* slot_offsets, const int32_t* prefix_len,
                             const int32_t* ext_len, const int32_t* ext_offsets, int B, int64_t T, int Hq, int Hkv, int D,
                             int page_size, int64_t num_slots, float scale, void* out, hipStream_t stream) {
-    const int64_t rows = T * Hq;
-    const dim3 grid(static_cast<unsigned>((rows + 3) / 4)), block(256);
-#define PA_LAUNCH_F32(DD)                                                                                        \
-    hipLaunchKernelGGL(pa::extend_f32_kernel<DD>, grid, block, 0, stream, static_cast<const float*>(q_ext),      \
+    // query heads a workgroup takes at once: all of a KV head's up to four (they share its K and V rows)
+    const int G = Hq / Hkv, per_wg = G >= 3 ? 4 : G;
+    PA_REQUIRE(Hkv <= 65535 && (G + per_wg - 1) / per_wg <= 65535, "pa_extend_attention: too many heads (%d, %d)", Hq, Hkv);
+    const dim3 grid(static_cast<unsigned>(T), static_cast<unsigned>(Hkv), static_cast<unsigned>((G + per_wg - 1) / per_wg)), block(256);
+#define PA_LAUNCH_F32(DD, HH)                                                                                    \
+    hipLaunchKernelGGL((pa::extend_f32_kernel<DD, HH>), grid, block, 0, stream, static_cast<const float*>(q_ext), \
                        static_cast<const float*>(k_ext), static_cast<const float*>(v_ext),                       \
                        static_cast<const float*>(kv_pool), slot_idx, slot_offsets, prefix_len, ext_len,          \
-                       ext_offsets, B, T, Hq, Hkv, page_size, num_slots, scale, static_cast<float*>(out))
+                       ext_offsets, B, Hq, Hkv, page_size, num_slots, scale, static_cast<float*>(out))
     {
         pa::ProfScope prof(pa::kProfExtendF32, stream);
-        if (D == 64) PA_LAUNCH_F32(64);
-        else PA_LAUNCH_F32(128);
+        if (D == 64 && per_wg == 1) PA_LAUNCH_F32(64, 1);
+        else if (D == 64 && per_wg == 2) PA_LAUNCH_F32(64, 2);
+        else if (D == 64) PA_LAUNCH_F32(64, 4);
+        else if (per_wg == 1) PA_LAUNCH_F32(128, 1);
+        else if (per_wg == 2) PA_LAUNCH_F32(128, 2);
+        else PA_LAUNCH_F32(128, 4);
     }
 #undef PA_LAUNCH_F32
     PA_HIP(hipGetLastError());
