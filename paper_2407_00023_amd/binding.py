@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libprefixattn (argument marshalling only).
+"""Thin binding of libprefixattn (argument marshalling only): ctypes, and a native module for the three hot-path calls.
 
 Every function below forwards to the C entry point of the same name (``pa_`` prefix
 dropped); all computation happens in the HIP kernels of the library.  PyTorch supplies
@@ -22,6 +22,7 @@ if not os.path.exists(LIB_PATH):
         "There is no CPU fallback.")
 
 _lib = C.CDLL(LIB_PATH)
+from . import _calls  # noqa: E402  (links to the library just loaded; built with it)
 
 F32, BF16 = 0, 1
 _DTYPES = {torch.float32: F32, torch.bfloat16: BF16}
@@ -83,6 +84,9 @@ class PrefixAttnError(RuntimeError):
         super().__init__(f"{where} failed with code {code}: {_lib.pa_last_error().decode()}")
 
 
+_calls.setup(PrefixAttnError)
+
+
 def _check(rc: int, where: str):
     if rc != 0:
         raise PrefixAttnError(rc, where)
@@ -94,7 +98,7 @@ def _ptr(t: Optional[torch.Tensor]):
 
 def _stream(stream) -> C.c_void_p:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 
@@ -323,58 +327,9 @@ def extend_workspace_bytes(B: int, T: int, max_kv_len: int, Hq: int, Hkv: int, D
     return n
 
 
-def match_prefixes(tree: Tree, tokens: torch.Tensor, offsets: torch.Tensor, prefix_len: Optional[torch.Tensor] = None,
-                   slot_idx: Optional[torch.Tensor] = None, stream=None):
-    """-> (prefix_len int32 [B], slot_idx int32 like tokens).  Asynchronous on the stream."""
-    _dev_i32(tokens, "tokens"), _dev_i32(offsets, "offsets")
-    B = offsets.numel() - 1
-    if prefix_len is None:
-        prefix_len = torch.empty(B, dtype=torch.int32, device=tokens.device)
-    if slot_idx is None:
-        slot_idx = torch.empty_like(tokens)
-    _dev_i32(prefix_len, "prefix_len"), _dev_i32(slot_idx, "slot_idx")
-    if prefix_len.numel() < B or slot_idx.numel() < tokens.numel():
-        raise ValueError("output tensors too small")
-    _check(_lib.pa_match_prefixes(tree._h, _ptr(tokens), _ptr(offsets), B, _ptr(prefix_len), _ptr(slot_idx),
-                                  _stream(stream)), "pa_match_prefixes")
-    return prefix_len, slot_idx
-
-
-def extend_attention(q_ext: torch.Tensor, k_ext: torch.Tensor, v_ext: torch.Tensor, kv_pool: torch.Tensor,
-                     slot_idx: torch.Tensor, slot_offsets: torch.Tensor, prefix_len: torch.Tensor,
-                     ext_len: torch.Tensor, ext_offsets: torch.Tensor, scale: float, *, page_size: int,
-                     num_slots: int, max_kv_len: int, out: Optional[torch.Tensor] = None,
-                     workspace: Optional[torch.Tensor] = None, stream=None, kv8: bool = False) -> torch.Tensor:
-    """q_ext [T,Hq,D], k_ext/v_ext [T,Hkv,D] -> out [T,Hq,D].  Asynchronous on the stream."""
-    T, Hq, D = q_ext.shape
-    Hkv = k_ext.shape[1]
-    dt = _code(q_ext.dtype, kv8)
-    for name, t in (("q_ext", q_ext), ("k_ext", k_ext), ("v_ext", v_ext)):
-        if not (t.is_cuda and t.is_contiguous() and t.dtype == q_ext.dtype):
-            raise TypeError(f"{name} must be a contiguous CUDA tensor of dtype {q_ext.dtype}")
-    if k_ext.shape != (T, Hkv, D) or v_ext.shape != k_ext.shape:
-        raise ValueError("k_ext / v_ext shape mismatch")
-    for name, t in (("slot_idx", slot_idx), ("slot_offsets", slot_offsets), ("prefix_len", prefix_len),
-                    ("ext_len", ext_len), ("ext_offsets", ext_offsets)):
-        _dev_i32(t, name)
-    B = prefix_len.numel()
-    if slot_offsets.numel() != B + 1 or ext_offsets.numel() != B + 1 or ext_len.numel() != B:
-        raise ValueError("per-request arrays disagree on B")
-    if kv_pool.numel() * kv_pool.element_size() < kv_pool_bytes(num_slots, Hkv, D, q_ext.dtype, page_size, kv8):
-        raise ValueError("kv_pool smaller than pa_kv_pool_bytes")
-    if out is None:
-        out = torch.empty_like(q_ext)
-    elif out.shape != q_ext.shape or out.dtype != q_ext.dtype or not out.is_contiguous() or not out.is_cuda:
-        raise ValueError("bad out tensor")
-    need = extend_workspace_bytes(B, T, max_kv_len, Hq, Hkv, D, q_ext.dtype)
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q_ext.device)
-    wbytes = workspace.numel() * workspace.element_size()
-    _check(_lib.pa_extend_attention(_ptr(q_ext), _ptr(k_ext), _ptr(v_ext), _ptr(kv_pool), _ptr(slot_idx),
-                                    _ptr(slot_offsets), _ptr(prefix_len), _ptr(ext_len), _ptr(ext_offsets), B, T,
-                                    max_kv_len, Hq, Hkv, D, page_size, num_slots, dt, float(scale), _ptr(out),
-                                    _ptr(workspace), wbytes, _stream(stream)), "pa_extend_attention")
-    return out
+# The three calls of the hot path marshal their tensors in native code (csrc/calls.cpp): through ctypes they cost the host
+# 38 us a step, as much as the GPU takes for a small batch.
+match_prefixes, extend_attention, append_kv = _calls.match_prefixes, _calls.extend_attention, _calls.append_kv
 
 
 def extend_attention_static(q_ext: torch.Tensor, k_ext: torch.Tensor, v_ext: torch.Tensor, kv_pool: torch.Tensor,
@@ -402,20 +357,6 @@ def extend_status(workspace: torch.Tensor, stream=None) -> None:
 def extend_set_row_sharing(on: bool) -> None:
     """Process-wide: False gives every request row tiles of its own (for slot lists that do not come from one prefix tree)."""
     _check(_lib.pa_extend_set_row_sharing(1 if on else 0), "pa_extend_set_row_sharing")
-
-
-def append_kv(kv_pool: torch.Tensor, new_slots: torch.Tensor, k_ext: torch.Tensor, v_ext: torch.Tensor, *,
-              page_size: int, num_slots: int, stream=None, kv8: bool = False) -> None:
-    T, Hkv, D = k_ext.shape
-    _dev_i32(new_slots, "new_slots")
-    if new_slots.numel() != T or v_ext.shape != k_ext.shape or v_ext.dtype != k_ext.dtype:
-        raise ValueError("append_kv: shape mismatch")
-    if not (k_ext.is_cuda and v_ext.is_cuda and k_ext.is_contiguous() and v_ext.is_contiguous()):
-        raise TypeError("k_ext / v_ext must be contiguous CUDA tensors")
-    if kv_pool.numel() * kv_pool.element_size() < kv_pool_bytes(num_slots, Hkv, D, k_ext.dtype, page_size, kv8):
-        raise ValueError("kv_pool smaller than pa_kv_pool_bytes")
-    _check(_lib.pa_append_kv(_ptr(kv_pool), _ptr(new_slots), _ptr(k_ext), _ptr(v_ext), T, Hkv, D, page_size,
-                             num_slots, _code(k_ext.dtype, kv8), _stream(stream)), "pa_append_kv")
 
 
 def gather_kv(kv_pool: torch.Tensor, slots: torch.Tensor, *, Hkv: int, D: int, dtype: torch.dtype, page_size: int,

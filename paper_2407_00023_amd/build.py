@@ -1,15 +1,18 @@
-"""Build libprefixattn.so for gfx950 with hipcc (in-tree, next to this file)."""
+"""Build libprefixattn.so for gfx950 with hipcc, and the Python module of the hot-path calls with g++ (in-tree, next to
+this file)."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libprefixattn.so")
+CALLS = os.path.join(HERE, "_calls.so")
 SOURCES = ["tree.cpp", "sched.cpp", "profile.cpp", "match.hip", "kvpool.hip", "extend.cpp", "extend_f32.hip", "extend_bf16.hip", "calib.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 code generation
@@ -26,6 +29,26 @@ def _hipcc() -> str:
         if os.path.sep not in c or os.path.exists(c):
             return c
     return "hipcc"
+
+
+def _compile_calls() -> str:
+    """The host-only Python module _calls (csrc/calls.cpp) against the torch that is installed."""
+    import torch
+    t = os.path.dirname(torch.__file__)
+    obj = os.path.join(OBJ, "calls.o")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+                           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                           "-I" + os.path.join(t, "include"), "-I" + os.path.join(t, "include", "torch", "csrc", "api", "include"),
+                           "-I/opt/rocm/include", "-I" + sysconfig.get_paths()["include"],
+                           "-c", os.path.join(CSRC, "calls.cpp"), "-o", obj])
+    return obj
+
+
+def _link_calls(obj: str) -> None:
+    import torch
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    subprocess.check_call(["g++", "-shared", "-fPIC", obj, "-o", CALLS, "-L" + HERE, "-l:libprefixattn.so", "-L" + lib, "-lc10",
+                           "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-Wl,-rpath,$ORIGIN"])
 
 
 def build(verbose: bool = False) -> str:
@@ -45,9 +68,11 @@ def build(verbose: bool = False) -> str:
             print(err, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=6) as ex:
+    with ThreadPoolExecutor(max_workers=7) as ex:
+        calls = ex.submit(_compile_calls)
         objs = list(ex.map(compile_one, SOURCES))
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
+    _link_calls(calls.result())
     return LIB
 
 
