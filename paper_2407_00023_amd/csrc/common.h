@@ -32,45 +32,57 @@ inline bool shape_ok(int Hq, int Hkv, int D) {
     return Hkv > 0 && Hq > 0 && Hq % Hkv == 0 && (D == 64 || D == 128);
 }
 
-// Entry of the positional index of the flattened tree (see DeviceTree).
+// What the positional index of the flattened tree holds of a node (see DeviceTree).
 struct __attribute__((aligned(32))) PathEntry {
-    unsigned long long hash;  // of the token path up to and including the first token of the node's edge
-    int32_t depth;            // depth of that token
-    int32_t node;             // -1 = empty entry
-    int32_t edge_start;       // index of the node's first edge token in edge_tok / edge_slot
+    unsigned long long hash;     // of the token path up to and including the first token of the node's edge
+    unsigned long long endhash;  // ... and the last one
+    int32_t depth;               // depth of the first one; -1: the node is gone
+    int32_t edge_start;          // index of the node's first edge token in edge_tok / edge_slot
     int32_t edge_len;
     int32_t parent;
+};
+struct PathSlot {
+    uint32_t tag;  // path_tag of the node's (hash, depth)
+    int32_t node;  // -1: empty; kGoneNode: the node was removed
+};
+constexpr int32_t kGoneNode = -2;
+
+// Entry of the child table of the flattened tree: all that a walk needs to know of the child, so that a step of it is
+// one round trip to memory.
+struct __attribute__((aligned(32))) ChildEntry {
+    unsigned long long key;      // (parent node id << 32) | first token of the child's edge; kEmptyKey, kDeletedKey
+    int32_t node;
+    int32_t edge_start;          // index of the first edge token in edge_tok / edge_slot
+    unsigned long long endhash;  // hash of the path up to and including the edge's last token
+    int32_t edge_len;
     int32_t pad;
 };
 
 // Flattened radix tree in device memory.
-//   Node n (0 = the empty virtual root) owns edge tokens edge_tok[node_start[n] .. +node_len[n])
-//   and, in parallel, the KV slot of each of those tokens in edge_slot.
-//   Children are found through one open-addressing hash table for the whole tree:
-//   key = (parent node id << 32) | first token of the child's edge, value = child node id;
-//   linear probing, empty key = all ones, capacity a power of two (mask = capacity - 1).
+//   Every node but the empty virtual root 0 owns a run of edge tokens in edge_tok and, in parallel, the KV slot of each
+//   of those tokens in edge_slot.
+//   Children are found through one open-addressing hash table for the whole tree; linear probing, empty key = all
+//   ones, capacity a power of two (mask = capacity - 1), at least 64.
 struct DeviceTree {
     const int32_t* edge_tok;
     const int32_t* edge_slot;
-    const int32_t* node_start;
-    const int32_t* node_len;
-    const unsigned long long* ht_key;
-    const int32_t* ht_val;
+    const ChildEntry* child;
     uint32_t ht_mask;
     int32_t n_nodes;
     int32_t n_tokens;  // edge tokens of all nodes together (as of the upload)
     // Second index, by position: a node is also reachable through the hash of the whole token path from
     // the root up to and including the FIRST token of its edge, together with the depth of that token.
     // A prompt can therefore look up every node boundary on its path at once from its own prefix hashes.
-    //   ph_entry: open addressing, linear probing, empty = node -1, mask = ph_mask; one 32-byte entry holds
-    //             everything a lookup needs, so that a probe is a single memory round trip
-    //   node_endhash[n] = hash of the path up to and including the LAST token of the node's edge
-    const PathEntry* ph_entry;
-    const unsigned long long* node_endhash;
+    //   path_slot: buckets of four slots (one read settles most lookups), the bucket from path_bucket, the next
+    //              bucket where one is full; ph_mask = slots - 1, a power of two less one
+    //   path[n]:   the node's entry (node 0: the root, endhash 0)
+    const PathSlot* path_slot;
+    const PathEntry* path;
     uint32_t ph_mask;
 };
 
 constexpr unsigned long long kEmptyKey = ~0ull;
+constexpr unsigned long long kDeletedKey = ~0ull - 1;  // child table: an entry that was removed (never a real key)
 
 // 64-bit mix (splitmix64 finaliser) used identically by the host builder and the device lookup.
 __host__ __device__ inline uint32_t hash_key(unsigned long long k) {
@@ -85,9 +97,15 @@ constexpr unsigned long long kPathHashBase = 0x9E3779B97F4A7C15ull;  // odd
 __host__ __device__ inline unsigned long long path_hash_push(unsigned long long h, int32_t tok) {
     return h * kPathHashBase + (static_cast<unsigned long long>(static_cast<uint32_t>(tok)) + 1ull);
 }
-__host__ __device__ inline uint32_t path_slot(unsigned long long h, int32_t depth) {
-    return hash_key(h ^ (static_cast<unsigned long long>(static_cast<uint32_t>(depth)) * 0xD6E8FEB86659FD93ull));
+// 64 mixed bits of (path hash, depth): the low half picks the bucket, the high half is the tag kept in the slot.
+__host__ __device__ inline unsigned long long path_mix(unsigned long long h, int32_t depth) {
+    unsigned long long k = h ^ (static_cast<unsigned long long>(static_cast<uint32_t>(depth)) * 0xD6E8FEB86659FD93ull);
+    k ^= k >> 30; k *= 0xbf58476d1ce4e5b9ull;
+    k ^= k >> 27; k *= 0x94d049bb133111ebull;
+    return k ^ (k >> 31);
 }
+__host__ __device__ inline uint32_t path_bucket(unsigned long long mix, uint32_t mask) { return static_cast<uint32_t>(mix) & mask & ~3u; }
+__host__ __device__ inline uint32_t path_tag(unsigned long long mix) { return static_cast<uint32_t>(mix >> 32); }
 
 // Pool layout: [page][K=0 | V=1][kv head][token in page][D] elements.
 // Element index of the first element of (slot, which, head).

@@ -33,7 +33,7 @@ int fail(int code, const char* fmt, ...) {
 struct FlatLayout {
     int64_t tok_cap = 0, node_cap = 0;
     uint64_t tab_cap = 0;  // entries of each hash table, a power of two
-    size_t o_tok = 0, o_slot = 0, o_start = 0, o_len = 0, o_key = 0, o_val = 0, o_phe = 0, o_end = 0, total = 0;
+    size_t o_tok = 0, o_slot = 0, o_child = 0, o_pslot = 0, o_path = 0, total = 0;
     void set(int64_t tokens, int64_t nodes, uint64_t table) {
         auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
         tok_cap = tokens;
@@ -41,17 +41,12 @@ struct FlatLayout {
         tab_cap = table;
         o_tok = 0;
         o_slot = o_tok + up(static_cast<size_t>(tokens) * 4);
-        o_start = o_slot + up(static_cast<size_t>(tokens) * 4);
-        o_len = o_start + up(static_cast<size_t>(nodes) * 4);
-        o_key = o_len + up(static_cast<size_t>(nodes) * 4);
-        o_val = o_key + up(table * 8);
-        o_phe = o_val + up(table * 4);
-        o_end = o_phe + up(table * sizeof(PathEntry));
-        total = o_end + up(static_cast<size_t>(nodes) * 8);
+        o_child = o_slot + up(static_cast<size_t>(tokens) * 4);
+        o_pslot = o_child + up(table * sizeof(ChildEntry));
+        o_path = o_pslot + up(table * sizeof(PathSlot));
+        total = o_path + up(static_cast<size_t>(nodes) * sizeof(PathEntry));
     }
 };
-
-constexpr unsigned long long kDeletedKey = ~0ull - 1;  // child table: an entry that was removed (never a real key)
 
 struct Node {
     std::vector<int32_t> tok;   // edge tokens leading into this node
@@ -103,6 +98,7 @@ struct pa_tree {
     int64_t arena_end = 0, arena_holes = 0;  // tokens of the token array in use (live or dead), dead ones
     int64_t table_used = 0;                  // entries of each hash table in use (live or deleted)
     std::vector<int32_t> ht_pos, phe_pos, end_depth;  // per node: its entry in either table, depth of its last token
+    std::vector<int32_t> flat_start, flat_len;        // per node: where its edge lies in the token array
     std::vector<std::pair<size_t, size_t>> dirty;     // (offset, bytes) changed in h_stage since the last upload
     int64_t n_full_uploads = 0, n_incremental_uploads = 0, last_upload_bytes = 0;
     std::mutex mu;
@@ -157,17 +153,16 @@ static int32_t split_node(pa_tree* t, int32_t c, int32_t k) {
 
 // ---- keeping the flat form in step with the tree ----------------------------------------------------------------
 struct FlatView {
-    int32_t *tok, *slot, *start, *len, *val;
-    unsigned long long *key, *end;
-    PathEntry* phe;
+    int32_t *tok, *slot, *start, *len;  // (start, len: for the host only)
+    ChildEntry* child;
+    PathSlot* pslot;
+    PathEntry* path;
 };
 static FlatView flat_view(pa_tree* t) {
     unsigned char* b = static_cast<unsigned char*>(t->h_stage);
     const FlatLayout& f = t->flat;
-    return {reinterpret_cast<int32_t*>(b + f.o_tok),   reinterpret_cast<int32_t*>(b + f.o_slot),
-            reinterpret_cast<int32_t*>(b + f.o_start), reinterpret_cast<int32_t*>(b + f.o_len),
-            reinterpret_cast<int32_t*>(b + f.o_val),   reinterpret_cast<unsigned long long*>(b + f.o_key),
-            reinterpret_cast<unsigned long long*>(b + f.o_end), reinterpret_cast<PathEntry*>(b + f.o_phe)};
+    return {reinterpret_cast<int32_t*>(b + f.o_tok), reinterpret_cast<int32_t*>(b + f.o_slot), t->flat_start.data(), t->flat_len.data(),
+            reinterpret_cast<ChildEntry*>(b + f.o_child), reinterpret_cast<PathSlot*>(b + f.o_pslot), reinterpret_cast<PathEntry*>(b + f.o_path)};
 }
 template <class T>
 static void mark(pa_tree* t, const T* first, size_t count) {
@@ -191,24 +186,26 @@ static int32_t child_table_put(pa_tree* t, FlatView& v, int32_t parent, int32_t 
     const uint64_t mask = t->flat.tab_cap - 1;
     const unsigned long long key = (static_cast<unsigned long long>(static_cast<uint32_t>(parent)) << 32) | static_cast<uint32_t>(first_tok);
     uint64_t h = hash_key(key) & mask;
-    while (v.key[h] != kEmptyKey) h = (h + 1) & mask;  // (deleted entries are not reused: a probe for a key stops at the first empty one)
-    v.key[h] = key;
-    v.val[h] = node;
-    mark(t, v.key + h, 1);
-    mark(t, v.val + h, 1);
+    while (v.child[h].key != kEmptyKey) h = (h + 1) & mask;  // (deleted entries are not reused: a probe for a key stops at the first empty one)
+    v.child[h] = {key, node, v.start[node], v.path[node].endhash, v.len[node], 0};
+    mark(t, v.child + h, 1);
     return static_cast<int32_t>(h);
 }
+// Node `node` (its place, length and end hash known) enters the positional index.
 static int32_t path_table_put(pa_tree* t, FlatView& v, unsigned long long hash, int32_t depth, int32_t node, int32_t parent) {
-    const uint64_t mask = t->flat.tab_cap - 1;
-    uint64_t at = path_slot(hash, depth) & mask;
-    while (v.phe[at].node != -1) at = (at + 1) & mask;
-    v.phe[at].hash = hash;
-    v.phe[at].depth = depth;
-    v.phe[at].node = node;
-    v.phe[at].edge_start = v.start[node];
-    v.phe[at].edge_len = v.len[node];
-    v.phe[at].parent = parent;
-    mark(t, v.phe + at, 1);
+    const uint32_t mask = static_cast<uint32_t>(t->flat.tab_cap - 1);
+    const unsigned long long mix = path_mix(hash, depth);
+    uint32_t at = path_bucket(mix, mask);
+    while (v.pslot[at].node != -1) at = (at + 1) & mask;  // (the bucket's slots fill in order, then those of the next one)
+    v.pslot[at] = {path_tag(mix), node};
+    PathEntry& e = v.path[node];
+    e.hash = hash;
+    e.depth = depth;
+    e.edge_start = v.start[node];
+    e.edge_len = v.len[node];
+    e.parent = parent;
+    mark(t, v.pslot + at, 1);
+    mark(t, &e, 1);
     return static_cast<int32_t>(at);
 }
 static unsigned long long hash_through(unsigned long long h, const std::vector<int32_t>& tok, size_t from, size_t to) {
@@ -235,12 +232,9 @@ static void mirror_new_leaf(pa_tree* t, int32_t c) {
     v.start[c] = static_cast<int32_t>(t->arena_end);
     v.len[c] = static_cast<int32_t>(len);
     t->arena_end += len;
-    const unsigned long long first_hash = path_hash_push(v.end[p], nd.tok[0]);
-    v.end[c] = hash_through(first_hash, nd.tok, 1, nd.tok.size());
+    const unsigned long long first_hash = path_hash_push(v.path[p].endhash, nd.tok[0]);
+    v.path[c].endhash = hash_through(first_hash, nd.tok, 1, nd.tok.size());
     t->end_depth[c] = t->end_depth[p] + static_cast<int32_t>(len);
-    mark(t, v.start + c, 1);
-    mark(t, v.len + c, 1);
-    mark(t, v.end + c, 1);
     t->ht_pos[c] = child_table_put(t, v, p, nd.tok[0], c);
     t->phe_pos[c] = path_table_put(t, v, first_hash, t->end_depth[p], c, p);
     ++t->table_used;
@@ -262,25 +256,24 @@ static void mirror_split(pa_tree* t, int32_t c, int32_t h, int32_t k) {
     v.len[h] = k;
     v.start[c] += k;
     v.len[c] -= k;
-    v.end[h] = hash_through(v.end[p], head.tok, 0, head.tok.size());
+    v.path[h] = v.path[c];
+    v.path[h].endhash = hash_through(v.path[p].endhash, head.tok, 0, head.tok.size());
+    v.path[h].edge_len = k;
+    mark(t, v.path + h, 1);
     t->end_depth[h] = t->end_depth[p] + k;
-    mark(t, v.start + h, 1);
-    mark(t, v.len + h, 1);
-    mark(t, v.end + h, 1);
-    mark(t, v.start + c, 1);
-    mark(t, v.len + c, 1);
     // the entries that led to c lead to the head now (same keys: same parent, same first token, same depth)
     t->ht_pos[h] = t->ht_pos[c];
-    v.val[t->ht_pos[h]] = h;
-    mark(t, v.val + t->ht_pos[h], 1);
+    ChildEntry& ch = v.child[t->ht_pos[h]];
+    ch.node = h;
+    ch.edge_len = k;
+    ch.endhash = v.path[h].endhash;
+    mark(t, &ch, 1);
     t->phe_pos[h] = t->phe_pos[c];
-    PathEntry& eh = v.phe[t->phe_pos[h]];
-    eh.node = h;
-    eh.edge_len = k;
-    mark(t, &eh, 1);
+    v.pslot[t->phe_pos[h]].node = h;
+    mark(t, v.pslot + t->phe_pos[h], 1);
     // and the tail gets entries of its own under the head
     t->ht_pos[c] = child_table_put(t, v, h, tail.tok[0], c);
-    t->phe_pos[c] = path_table_put(t, v, path_hash_push(v.end[h], tail.tok[0]), t->end_depth[h], c, h);
+    t->phe_pos[c] = path_table_put(t, v, path_hash_push(v.path[h].endhash, tail.tok[0]), t->end_depth[h], c, h);
     ++t->table_used;
 }
 
@@ -290,12 +283,13 @@ static void mirror_trim(pa_tree* t, int32_t c, int32_t removed) {
     FlatView v = flat_view(t);
     const Node& nd = t->nodes[c];
     v.len[c] = static_cast<int32_t>(nd.tok.size());
-    v.end[c] = hash_through(v.end[nd.parent], nd.tok, 0, nd.tok.size());
+    v.path[c].endhash = hash_through(v.path[nd.parent].endhash, nd.tok, 0, nd.tok.size());
     t->end_depth[c] -= removed;
-    v.phe[t->phe_pos[c]].edge_len = v.len[c];
-    mark(t, v.len + c, 1);
-    mark(t, v.end + c, 1);
-    mark(t, v.phe + t->phe_pos[c], 1);
+    v.path[c].edge_len = v.len[c];
+    v.child[t->ht_pos[c]].edge_len = v.len[c];
+    v.child[t->ht_pos[c]].endhash = v.path[c].endhash;
+    mark(t, v.child + t->ht_pos[c], 1);
+    mark(t, v.path + c, 1);
     t->arena_holes += removed;
 }
 
@@ -304,14 +298,13 @@ static void mirror_remove(pa_tree* t, int32_t c, int32_t removed) {
     if (!mirror_open(t)) return;
     FlatView v = flat_view(t);
     v.len[c] = 0;
-    mark(t, v.len + c, 1);
-    v.key[t->ht_pos[c]] = kDeletedKey;
-    mark(t, v.key + t->ht_pos[c], 1);
-    PathEntry& e = v.phe[t->phe_pos[c]];  // stays in its probe chain, matches nothing: no position is negative
-    e.node = 0;
-    e.depth = -1;
-    e.edge_len = 0;
-    mark(t, &e, 1);
+    v.child[t->ht_pos[c]].key = kDeletedKey;
+    mark(t, v.child + t->ht_pos[c], 1);
+    v.pslot[t->phe_pos[c]].node = kGoneNode;  // (its slot stays taken, so that a full bucket goes on saying so)
+    mark(t, v.pslot + t->phe_pos[c], 1);
+    v.path[c].depth = -1;
+    v.path[c].edge_len = 0;
+    mark(t, v.path + c, 1);
     t->arena_holes += removed;
     // a token array that is mostly dead is compacted by the next full rebuild
     if (t->arena_holes > 4096 && 2 * t->arena_holes > t->arena_end) t->mirror_ok = false;
@@ -815,24 +808,22 @@ extern "C" int pa_tree_upload(pa_tree* tree, void* stream_) {
         }
         tree->h_cap = f.total;
     }
-    pa::FlatView v = pa::flat_view(tree);
     try {
+        tree->flat_start.assign(static_cast<size_t>(f.node_cap), 0);
+        tree->flat_len.assign(static_cast<size_t>(f.node_cap), 0);
         tree->ht_pos.assign(static_cast<size_t>(f.node_cap), -1);
         tree->phe_pos.assign(static_cast<size_t>(f.node_cap), -1);
         tree->end_depth.assign(static_cast<size_t>(f.node_cap), 0);
     } catch (const std::bad_alloc&) {
         return pa::fail(PA_ENOMEM, "pa_tree_upload: out of host memory");
     }
+    pa::FlatView v = pa::flat_view(tree);
     const uint64_t mask = cap - 1;
     for (uint64_t i = 0; i < cap; ++i) {
-        v.key[i] = pa::kEmptyKey;
-        v.val[i] = -1;
+        v.child[i] = {pa::kEmptyKey, -1, 0, 0ull, 0, 0};
     }
-    std::memset(v.start, 0, static_cast<size_t>(f.node_cap) * 4);
-    std::memset(v.len, 0, static_cast<size_t>(f.node_cap) * 4);
-    std::memset(v.end, 0, static_cast<size_t>(f.node_cap) * 8);
-    std::memset(v.phe, 0, cap * sizeof(pa::PathEntry));
-    for (uint64_t i = 0; i < cap; ++i) v.phe[i].node = -1;
+    std::memset(v.path, 0, static_cast<size_t>(f.node_cap) * sizeof(pa::PathEntry));
+    for (uint64_t i = 0; i < cap; ++i) v.pslot[i] = {0u, -1};
 
     int64_t cursor = 0, entries = 0;
     for (int64_t i = 0; i < nn; ++i) {
@@ -848,9 +839,9 @@ extern "C" int pa_tree_upload(pa_tree* tree, void* stream_) {
             const unsigned long long key =
                 (static_cast<unsigned long long>(static_cast<uint32_t>(i)) << 32) | static_cast<uint32_t>(kv.first);
             uint64_t h = pa::hash_key(key) & mask;
-            while (v.key[h] != pa::kEmptyKey) h = (h + 1) & mask;
-            v.key[h] = key;
-            v.val[h] = kv.second;
+            while (v.child[h].key != pa::kEmptyKey) h = (h + 1) & mask;
+            v.child[h].key = key;  // (the rest once every node has its place and its hash, below)
+            v.child[h].node = kv.second;
             tree->ht_pos[static_cast<size_t>(kv.second)] = static_cast<int32_t>(h);
             ++entries;
         }
@@ -863,7 +854,6 @@ extern "C" int pa_tree_upload(pa_tree* tree, void* stream_) {
         struct Item { int32_t node; int32_t parent; int32_t depth; unsigned long long hash; };  // depth, hash: of the path BEFORE the node's edge
         std::vector<Item> stack;
         stack.push_back({0, -1, 0, 0ull});
-        v.end[0] = 0ull;
         while (!stack.empty()) {
             const Item it = stack.back();
             stack.pop_back();
@@ -871,17 +861,13 @@ extern "C" int pa_tree_upload(pa_tree* tree, void* stream_) {
             unsigned long long h = it.hash;
             if (it.node != 0) {
                 const unsigned long long key = pa::path_hash_push(h, nd.tok[0]);
-                uint64_t at = pa::path_slot(key, it.depth) & mask;
-                while (v.phe[at].node != -1) at = (at + 1) & mask;
-                v.phe[at].hash = key;
-                v.phe[at].depth = it.depth;
-                v.phe[at].node = it.node;
-                v.phe[at].edge_start = v.start[it.node];
-                v.phe[at].edge_len = v.len[it.node];
-                v.phe[at].parent = it.parent;
+                const unsigned long long mix = pa::path_mix(key, it.depth);
+                uint32_t at = pa::path_bucket(mix, static_cast<uint32_t>(mask));
+                while (v.pslot[at].node != -1) at = (at + 1) & static_cast<uint32_t>(mask);
+                v.pslot[at] = {pa::path_tag(mix), it.node};
                 tree->phe_pos[static_cast<size_t>(it.node)] = static_cast<int32_t>(at);
                 for (int32_t t : nd.tok) h = pa::path_hash_push(h, t);
-                v.end[it.node] = h;
+                v.path[it.node] = {key, h, it.depth, v.start[it.node], v.len[it.node], it.parent};
             }
             const int32_t end_depth = it.depth + static_cast<int32_t>(nd.tok.size());
             tree->end_depth[static_cast<size_t>(it.node)] = end_depth;
@@ -889,6 +875,13 @@ extern "C" int pa_tree_upload(pa_tree* tree, void* stream_) {
         }
     } catch (const std::bad_alloc&) {
         return pa::fail(PA_ENOMEM, "pa_tree_upload: out of host memory");
+    }
+    for (uint64_t i = 0; i < cap; ++i) {
+        pa::ChildEntry& ce = v.child[i];
+        if (ce.node < 0) continue;
+        ce.edge_start = v.start[ce.node];
+        ce.edge_len = v.len[ce.node];
+        ce.endhash = v.path[ce.node].endhash;
     }
 
     tree->uploaded = false;
@@ -910,13 +903,10 @@ extern "C" int pa_tree_upload(pa_tree* tree, void* stream_) {
     unsigned char* b = static_cast<unsigned char*>(d);
     tree->view.edge_tok = reinterpret_cast<const int32_t*>(b + f.o_tok);
     tree->view.edge_slot = reinterpret_cast<const int32_t*>(b + f.o_slot);
-    tree->view.node_start = reinterpret_cast<const int32_t*>(b + f.o_start);
-    tree->view.node_len = reinterpret_cast<const int32_t*>(b + f.o_len);
-    tree->view.ht_key = reinterpret_cast<const unsigned long long*>(b + f.o_key);
-    tree->view.ht_val = reinterpret_cast<const int32_t*>(b + f.o_val);
+    tree->view.child = reinterpret_cast<const pa::ChildEntry*>(b + f.o_child);
     tree->view.ht_mask = static_cast<uint32_t>(cap - 1);
-    tree->view.ph_entry = reinterpret_cast<const pa::PathEntry*>(b + f.o_phe);
-    tree->view.node_endhash = reinterpret_cast<const unsigned long long*>(b + f.o_end);
+    tree->view.path_slot = reinterpret_cast<const pa::PathSlot*>(b + f.o_pslot);
+    tree->view.path = reinterpret_cast<const pa::PathEntry*>(b + f.o_path);
     tree->view.ph_mask = static_cast<uint32_t>(cap - 1);
     tree->view.n_nodes = static_cast<int32_t>(nn);
     tree->view.n_tokens = static_cast<int32_t>(ntok);
