@@ -62,12 +62,10 @@ def algorithmic_work(wl, prefix_len):
 
 
 def workspace_traffic(wl, hdr):
-    """Bytes the launch moves through its workspace beyond the algorithmic ones: every part of a row tile whose key
-    range was split writes fp32 partial outputs and (maximum, sum) for its 128 rows and every KV head, and the merge
-    kernel reads them back (counted with all 128 rows of a tile in use).  hdr = (row tiles, items, tiles merged)."""
-    n_tiles, n_items, n_merge = hdr[:3]
-    split_items = n_items - (n_tiles - n_merge)
-    return 2 * split_items * wl.Hkv * 128 * (wl.D + 2) * 4
+    """Bytes the launch moves through its workspace beyond the algorithmic ones: rows that are computed in parts leave fp32
+    partial outputs and (maximum, sum) per part and KV head, and the merge kernel reads them back.  hdr = (row tiles, items,
+    pieces of the merge, -, rows of partial results)."""
+    return 2 * hdr[4] * wl.Hkv * (wl.D + 2) * 4
 
 
 def cpu_baseline(wl, budget_s=15.0):
@@ -296,7 +294,7 @@ def measure(name, steps, warmup, args, with_extras, kv_pool="bf16"):
     hdr = None
     if wl.dtype != "f32":
         pa.extend_status(ws)  # (raises if the work list of the launches above did not fit)
-        hdr = ws[:16].view(torch.int32).tolist()
+        hdr = ws[:20].view(torch.int32).tolist()
         # a few more steps with the clock probe in the kernel, kept out of the times above
         pa.profile_clock(ws, reset=True)
         pa.profile_enable(True, clock_probe=True)
@@ -331,7 +329,7 @@ def measure(name, steps, warmup, args, with_extras, kv_pool="bf16"):
             # traffic through the workspace (partial results of split row tiles, written by the attention kernel and
             # read back by the merge kernel): not part of algorithmic_bytes, shown beside it
             roofline["workspace_bytes"] = workspace_traffic(wl, hdr)
-            roofline["work_list"] = {"row_tiles": hdr[0], "items": hdr[1], "tiles_merged_from_parts": hdr[2]}
+            roofline["work_list"] = {"row_tiles": hdr[0], "items": hdr[1], "pieces_of_the_merge": hdr[2], "partial_rows": hdr[4]}
         if shader_mhz > 0 and wl.dtype != "f32":
             # the clock the kernel ran at (shader cycles against the 100 MHz constant counter, across the key loop of a
             # few workgroups), and the matrix peak at that clock: 2.5 PFLOP/s is quoted at 2,400 MHz

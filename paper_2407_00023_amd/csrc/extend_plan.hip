@@ -1,0 +1,682 @@
+// The planner of the bf16 extend attention: builds the work list of one launch on the device, from the lengths and slot
+// lists that the matcher left there.
+//
+// A row tile = up to 128 packed query rows (row = (extend token, query head of the group)) of one request, or rows of several
+// requests with a common prefix; a work item = a row tile x a contiguous part of its key range; one workgroup per (item, KV
+// head).  Workgroups cost about the same per key tile whatever the number of their rows, and the hardware starts them in
+// index order as slots fall free, so the list is built for an even finish: requests with the same prefix together, the
+// longest first, every tile cut into parts of about 1 / rounds of a slot's share of the whole work.  (Cutting the end of the
+// list finer still evens the finish further and was measured to gain nothing: while every slot is busy the chip is at its
+// power limit, and the extra parts cost a merge.)
+//
+// Kinds of tile.
+//   Whole: rows of one request over all its keys.
+//   Shared, whole prefix: the left-over rows of a request - those past its last full tile - cost a workgroup as much per key
+//     tile as a full tile, so where two or more requests share their whole prefix (at least kPackMinPrefix keys) their
+//     left-over rows are laid end to end and cut into tiles.  Such a tile walks the common prefix, every key of it visible to
+//     every row, and then the extend tokens of each request that has rows in it, one request's after the other's, visible to
+//     that request's rows only (and causally).  Its members are consecutive entries of the member table.
+//   Shared, common first part: requests may also share only the first part of their prefixes (a decode batch: a common system
+//     and tool prompt, then tokens of each request's own).  Those whose rows make less than one tile, and whose whole prefix
+//     nobody shares, are grouped by the deepest of a few fixed depths at which another such request has the same slot (slots
+//     name cached tokens: the same slot at a depth means the same tokens up to there); the group's common part is then
+//     measured, to a thirteenth of the distance to the next probe, against the group's first member.  Their rows are packed into tiles
+//     over the common keys, and again, request by request, into own-key tiles over the rest; the merge joins the two.
+//   Narrow: a tile of at most 32 rows, of any of these kinds.  Its workgroup splits the keys over its four waves.
+//
+// What bounds it: one workgroup's chain of dependent steps - two round trips to memory, about twelve barriers, for common
+// first parts one more round trip and six barriers - so equal keys are found through hash tables in LDS instead of all-pairs comparisons, a
+// scan costs one barrier, and small batches use four waves.  Kernel times against a planner that
+// compared all pairs in sixteen waves (us): 12 requests 14 -> 7, 64 requests 18 -> 10, 256 decode requests 51 -> 23.
+#include "extend_plan.h"
+
+namespace pa {
+
+constexpr int kWgSlots = 512;            // workgroups resident at once: two on each of the 256 compute units
+constexpr int kMinChunkTiles = 16;       // never split below this many key tiles (1,024 keys) per part (with 512 keys a decode
+                                         // batch's step took 3 % longer) ...
+constexpr int kMinChunkCommon = 8;       // ... unless the tile leaves partial results anyway ...
+constexpr int kMinChunkNarrow = 4;       // ... or is narrow: 64 keys for each of its waves
+constexpr int kItemOverhead = 4;         // fixed cost of a work item, in key tiles (its prologue and epilogue)
+constexpr int kMaxParts = 64;            // parts of one tile at most
+constexpr int kPackMax = 256;            // batches of up to this many requests are looked through for common prefixes
+constexpr int kSortMax = 1024;           // ... and up to this many are ordered
+constexpr int kPackMinPrefix = 512;      // prefixes, or first parts of them, are shared from this many keys on ...
+constexpr int kPackOwnCost = 2;          // ... and, whole ones, if the members' own keys, which a shared tile walks in the general
+                                         // tile for the few rows that see them, cost less than walking the prefix per member:
+                                         // this factor x their sum <= (members - 1) x the shared prefix
+constexpr int kProbes = 12;              // depths looked at for common first parts, and which
+__device__ __forceinline__ constexpr int probe_depth(int k) {
+    constexpr int in512[kProbes] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
+    return kPackMinPrefix * in512[k];
+}
+
+static inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
+
+ExtendPlan make_extend_plan(int B, int64_t T, int64_t max_kv_len, int Hq, int Hkv, int D, int rounds, size_t limit) {
+    ExtendPlan p{};
+    const int G = Hq / Hkv;
+    const int64_t rows = T * G;
+    p.rounds = rounds;
+    p.slots = kWgSlots / Hkv > 0 ? kWgSlots / Hkv : 1;
+    p.pack = B <= kPackMax;
+    p.tiles_cap = static_cast<int>((rows + kTileRows - 1) / kTileRows + B);  // (packing only lowers the number of row tiles)
+    p.chunk_rows = 256 / (D / 4);
+    // The number of parts of a tile is at most its cost over the target cost of an item + 3/4, so the sum of (parts - 1) over
+    // the tiles stays below whole cost / target = slots * rounds; and no part is shorter than the minimum.
+    const int64_t by_rule = static_cast<int64_t>(p.slots) * rounds + 1;
+    // (the key range of a shared tile holds the own keys of every member: of up to kTileRows requests)
+    const int64_t longest = p.pack ? max_kv_len * (B < kTileRows ? (B > 0 ? B : 1) : kTileRows) : max_kv_len;
+    const int64_t per_tile = (longest / kKT) / kMinChunkNarrow > 1 ? (longest / kKT) / kMinChunkNarrow : 1;
+    p.tile_parts = static_cast<int>(per_tile < kMaxParts ? per_tile : kMaxParts);
+    for (p.first_part = p.pack && B > 1; ; p.first_part = 0) {
+        // (rows of requests grouped by a common first part: fewer than a tile each; once per shared tile, once per own-key tile)
+        const int64_t fp_rows = !p.first_part ? 0 : rows < int64_t{B} * (kTileRows - 1) ? rows : int64_t{B} * (kTileRows - 1);
+        p.own_cap = static_cast<int>(p.first_part ? fp_rows / kNarrowRows + B : 0);
+        const int64_t by_size = (static_cast<int64_t>(p.tiles_cap) + p.own_cap) * p.tile_parts;
+        const int64_t more = by_rule < by_size ? by_rule : by_size;
+        p.items_cap = static_cast<int>(p.tiles_cap + p.own_cap + more);
+        const int64_t split_parts = 2 * by_rule < by_size ? 2 * by_rule : by_size;
+        p.prows_cap = static_cast<int>(split_parts * kTileRows + 2 * fp_rows);
+        p.chunks_cap = static_cast<int>((split_parts / 2 + 1) * (kTileRows / p.chunk_rows) + fp_rows / p.chunk_rows + 2 * p.own_cap);
+        p.off_tile = 256;
+        p.off_member = p.off_tile + up256(sizeof(int2) * (static_cast<size_t>(p.tiles_cap) + p.own_cap));
+        p.off_item = p.off_member + up256(p.pack ? sizeof(int4) * 2 * (B > 0 ? B : 1) : 0);
+        p.off_chunk = p.off_item + up256(sizeof(int4) * 3 * p.items_cap);
+        p.off_part_o = p.off_chunk + up256(sizeof(int4) * 3 * p.chunks_cap);
+        const size_t prows = static_cast<size_t>(p.prows_cap) * Hkv;
+        p.off_part_ml = p.off_part_o + up256(prows * D * sizeof(float));
+        p.total = p.off_part_ml + up256(prows * 2 * sizeof(float));
+        if (!p.first_part || limit == 0 || p.total <= limit) break;
+    }
+    return p;
+}
+
+PlanTables plan_tables(const ExtendPlan& p, void* workspace) {
+    unsigned char* ws = static_cast<unsigned char*>(workspace);
+    return {reinterpret_cast<int32_t*>(ws), reinterpret_cast<int2*>(ws + p.off_tile), reinterpret_cast<int4*>(ws + p.off_member),
+            reinterpret_cast<int4*>(ws + p.off_item), reinterpret_cast<int4*>(ws + p.off_chunk), reinterpret_cast<float*>(ws + p.off_part_o),
+            reinterpret_cast<float*>(ws + p.off_part_ml)};
+}
+
+struct PlanArgs {
+    const int32_t *prefix_len, *ext_len, *ext_offsets, *slot_offsets, *slot_idx;
+    int32_t* hdr;
+    int2* tile;
+    int4 *member, *item, *chunk;
+    int B, G, tiles_cap, own_cap, items_cap, prows_cap, chunks_cap, slot_items, pack, first_part, tile_parts, chunk_rows;
+};
+
+// All of a kernel's arguments asked for at its start: where they are looked at for the first time later on, each cache line of
+// them is another round trip to host memory.
+__device__ __forceinline__ void touch_args(const PlanArgs& a) {
+    asm volatile("" ::"s"(a.prefix_len), "s"(a.hdr), "s"(a.item), "s"(a.chunk), "s"(a.tile_parts), "s"(a.chunk_rows));
+}
+
+// Inclusive prefix sum over the wave, by the cross-lane moves of the vector ALU (rows of 16 lanes, then row to row).
+__device__ __forceinline__ int wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
+// Exclusive prefix sums of N ints per thread over the workgroup, and their totals: a scan inside each wave, then the
+// totals of the waves.  s_w is used by this call only (one barrier).
+template <int NT, int N>
+__device__ __forceinline__ void block_scan(int (&v)[N], int (&total)[N], int (*s_w)[NT / 64]) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int x[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = wave_scan(v[i]);
+    if (lane == 63)
+#pragma unroll
+        for (int i = 0; i < N; ++i) s_w[i][w] = x[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        int before = 0, all = 0;
+#pragma unroll
+        for (int k = 0; k < NT / 64; ++k) {
+            const int c = s_w[i][k];
+            before += k < w ? c : 0;
+            all += c;
+        }
+        v[i] = x[i] - v[i] + before;
+        total[i] = all;
+    }
+}
+
+struct TileDesc {
+    int r, row0, kv_lo, kv_end;      // request (a shared tile: one that has the common keys), first packed row, keys
+    int rows_here, e_or_rows, P;     // rows; extend length or rows of the group; prefix length or common part
+    int member0, n_members;          // shared tiles: the entries of the member table whose rows meet the tile
+    // own-key tiles: the shared tile of their group's first rows, their own first row counted from there, the group's rows
+    int common_tile, common_row, group_rows;
+    int e0, slot_off;
+    bool partial_only;               // a shared tile over a common first part: leaves partial results for the own-key tiles to join
+    bool own;
+};
+
+// The second half of every planner: costs, parts, items and pieces of the merge of tiles [0, n_all), of which n_rows are row
+// tiles.  describe(t) says what tile t is.
+template <int NT, class Describe>
+__device__ __forceinline__ void emit_items(const PlanArgs& a, int n_rows, int n_all, bool over, Describe describe) {
+    __shared__ int s_cost[NT / 64];
+    __shared__ int s_sum[3][NT / 64];
+    const int tid = threadIdx.x;
+    // thread i owns tiles [i * per, (i + 1) * per); where there are fewer tiles than threads, S threads (a power of two, up to
+    // 16, neighbours in a wave) share one and write its records in turn.  What a thread's first tile is (often its only one)
+    // is worked out once
+    const int per = (n_all + NT - 1) / NT;
+    int S = 1;
+    while (S < 16 && 2 * S * n_all <= NT) S *= 2;
+    const int sub = tid & (S - 1);
+    const int t_lo = min(n_all, S > 1 ? tid / S : tid * per), t_hi = min(n_all, t_lo + per);
+    const TileDesc d_first = t_lo < t_hi ? describe(t_lo) : TileDesc{};
+    auto tile_desc = [&](int t) { return t == t_lo ? d_first : describe(t); };
+    auto key_tiles = [](const TileDesc& d) { return (d.kv_end - d.kv_lo + kKT - 1) / kKT; };
+    auto narrow = [](const TileDesc& d) { return d.rows_here <= kNarrowRows; };
+    // (a narrow tile's waves do four blocks of 32 keys in the time of one)
+    auto cost_of = [&](const TileDesc& d) { return (narrow(d) ? (key_tiles(d) + 1) / 2 : key_tiles(d)) + kItemOverhead; };
+    int cost = 0;
+    for (int t = t_lo; t < t_hi; ++t) cost += sub == 0 ? cost_of(tile_desc(t)) : 0;
+    cost = wave_scan(cost);
+    if ((tid & 63) == 63) s_cost[tid >> 6] = cost;
+    __syncthreads();
+    int W = 0;
+#pragma unroll
+    for (int k = 0; k < NT / 64; ++k) W += s_cost[k];
+    // parts of a tile: its cost over the target cost of an item, rounded up from a quarter past a whole number (an item
+    // of 1.5 targets at the end of the list is a tail of its own)
+    const float target = fmaxf(static_cast<float>(W) / static_cast<float>(a.slot_items), 1.f);
+    auto parts_of = [&](const TileDesc& d) {
+        const int n = static_cast<int>(static_cast<float>(cost_of(d)) / target + 0.75f);
+        const int shortest = narrow(d) ? kMinChunkNarrow : d.partial_only ? kMinChunkCommon : kMinChunkTiles;
+        return max(min(min(n, key_tiles(d) / shortest), a.tile_parts), 1);
+    };
+    // pieces of the merge of a tile: up to chunk_rows rows each; those of an own-key tile inside one shared tile
+    auto next_piece = [&](const TileDesc& d, int row) {
+        int n = min(a.chunk_rows, d.rows_here - row);
+        if (d.own) n = min(n, kTileRows - (d.common_row + row) % kTileRows);
+        return n;
+    };
+    auto chunks_of = [&](const TileDesc& d, int n) {
+        if (d.partial_only || (n == 1 && !d.own)) return 0;
+        if (!d.own) return (d.rows_here + a.chunk_rows - 1) / a.chunk_rows;
+        int c = 0;
+        for (int row = 0; row < d.rows_here; row += next_piece(d, row)) ++c;
+        return c;
+    };
+    int v[3] = {0, 0, 0}, total[3];  // items, rows of partial results, pieces of the merge
+    for (int t = t_lo; t < t_hi; ++t) {
+        const TileDesc d = tile_desc(t);
+        const int n = parts_of(d);
+        v[0] += n;
+        v[1] += n > 1 || d.partial_only || d.own ? n * d.rows_here : 0;
+        v[2] += chunks_of(d, n);
+    }
+    if (sub > 0) v[0] = v[1] = v[2] = 0;
+    block_scan<NT, 3>(v, total, s_sum);
+    if (S > 1)  // (to the other threads of the tile)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) v[i] = __shfl(v[i], (tid & 63) - sub);
+    // The capacities follow from the host's T and max_kv_len: a batch on the device that is larger than they say does
+    // not fit.  Nothing is computed then (an empty list: no output row is written) and hdr[3] says so, which
+    // pa_extend_status reports.
+    const bool overflow = over || total[0] > a.items_cap || total[1] > a.prows_cap || total[2] > a.chunks_cap;
+    if (tid == 0) {
+        a.hdr[0] = overflow ? 0 : n_rows;
+        a.hdr[1] = overflow ? 0 : total[0];
+        a.hdr[2] = overflow ? 0 : total[2];
+        a.hdr[3] = overflow;
+        a.hdr[4] = overflow ? 0 : total[1];
+    }
+    if (overflow) return;
+    if (n_all > n_rows) {  // (own-key tiles look up the parts of their shared tile)
+        int prow = v[1];
+        for (int t = t_lo; t < t_hi; ++t) {
+            const TileDesc d = tile_desc(t);
+            const int n = parts_of(d);
+            if (d.partial_only && sub == 0) a.tile[t] = make_int2(n, prow);
+            prow += n > 1 || d.partial_only || d.own ? n * d.rows_here : 0;
+        }
+        __syncthreads();
+    }
+    for (int t = t_lo; t < t_hi; ++t) {
+        const TileDesc d = tile_desc(t);
+        const int K = key_tiles(d), n = parts_of(d);
+        const bool partial = n > 1 || d.partial_only || d.own;
+        for (int j = sub; j < n; j += S) {
+            // (K < 2^24 key tiles and n <= 64 parts: the products fit 32 bits)
+            const int lo = d.kv_lo + static_cast<int>(static_cast<unsigned>(K) * static_cast<unsigned>(j) / static_cast<unsigned>(n)) * kKT;
+            const int hi = min(d.kv_end, d.kv_lo + static_cast<int>(static_cast<unsigned>(K) * static_cast<unsigned>(j + 1) / static_cast<unsigned>(n)) * kKT);
+            int4* rec = a.item + 3 * static_cast<size_t>(v[0] + j);
+            rec[0] = make_int4(d.r, d.row0, lo, hi);
+            rec[1] = make_int4(partial ? v[1] + j * d.rows_here : -1, d.P, d.e_or_rows, d.e0);
+            rec[2] = make_int4(d.slot_off, narrow(d) ? 1 : 0, d.member0, d.n_members);
+        }
+        if (chunks_of(d, n) > 0) {
+            auto write = [&](int c, int row, int len, int n_common, int4 c2) {
+                int4* rec = a.chunk + 3 * static_cast<size_t>(v[2] + c);
+                rec[0] = make_int4(n, v[1], d.rows_here, row | len << 16);
+                rec[1] = make_int4(d.n_members == 0 ? d.e0 : d.member0, d.row0, d.n_members, n_common);
+                rec[2] = c2;
+            };
+            if (!d.own) {
+                for (int c = sub; c * a.chunk_rows < d.rows_here; c += S)
+                    write(c, c * a.chunk_rows, min(a.chunk_rows, d.rows_here - c * a.chunk_rows), 0, make_int4(0, 0, 0, 0));
+            } else if (sub == 0) {
+                for (int row = 0, c = 0, len; row < d.rows_here; row += len, ++c) {
+                    len = next_piece(d, row);
+                    const int at = d.common_row + row, k = at / kTileRows;
+                    const int2 ct = a.tile[d.common_tile + k];
+                    write(c, row, len, ct.x, make_int4(ct.y, min(kTileRows, d.group_rows - k * kTileRows), at % kTileRows, 0));
+                }
+            }
+        }
+        v[2] += chunks_of(d, n);
+        v[0] += n;
+        v[1] += partial ? n * d.rows_here : 0;
+    }
+}
+
+// Batches of up to MAXB requests.  MAXB = kPackMax: with the search for common prefixes; kSortMax: ordered only.
+template <int MAXB, int NT>
+__global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
+    constexpr bool kPack = MAXB <= kPackMax;
+    constexpr int HT = (kPack ? 4 : 2) * MAXB;              // hash table of whole prefixes
+    constexpr int PT = kPack ? 4096 : 1;      // ... of (probe depth, slot)
+    static_assert(!kPack || PT >= kProbes * MAXB + 1, "the table of probes is never full");
+    constexpr int NG = kPack ? 2 * MAXB : MAXB;  // groups: [0, MAXB) by whole prefix, [MAXB, 2 MAXB) by common first part
+    __shared__ int s_P[MAXB], s_E[MAXB], s_e0[MAXB], s_so[MAXB];
+    __shared__ int4 s_id[MAXB];               // prefix length, last, first and middle slot of it
+    __shared__ int s_ht[HT], s_hlead[HT], s_hcnt[HT];  // a request with the prefix (-1: none), the first one, how many
+    __shared__ int s_pt[PT], s_pc[PT];        // a pair (request, probe) (-1: none), later the first request that chose it;
+                                              // how many requests, and how many chose it << 16
+    __shared__ int s_pslot[kPack ? (kProbes + 2) * MAXB : 1];  // slots at the probes; later, of leaders, at the places compared
+    __shared__ int s_cutg[kPack ? MAXB : 1];  // per leader: at how many of these places its group agrees
+    __shared__ int s_cut[MAXB];               // per request: the same; its whole prefix otherwise
+    __shared__ int s_gid[MAXB];
+    __shared__ int s_gkey[NG];                // per group: the most keys of any of its requests
+    __shared__ int s_gn[NG], s_gL[NG], s_gown[NG];         // packable members, their rows, their extend tokens
+    __shared__ int s_gR[NG], s_gm[NG], s_go[NG], s_gt[NG]; // what the groups before it hold: rows, members, tokens; its first tile
+    __shared__ unsigned long long s_sk[MAXB];
+    __shared__ int s_order[MAXB];             // position in the list -> request
+    __shared__ int s_first[MAXB], s_ofirst[MAXB];  // per position: its first row tile and own-key tile
+    __shared__ int4 s_req[MAXB];              // ... its request, its group, the shared tiles in front of its own ones, and the
+                                              // first of its packed rows among the group's (-1: not packed)
+    __shared__ int s_mR[MAXB], s_mO[MAXB], s_mE[MAXB];     // per member: that; extend tokens of the members before it; its own
+    __shared__ int s_any;
+    __shared__ int s_scan[5][NT / 64];
+    const int tid = threadIdx.x, B = a.B, G = a.G, mt = kTileRows;
+    touch_args(a);
+    const bool first_part = kPack && a.first_part;
+    const int32_t* const slot_idx = a.slot_idx;
+    // ---- lengths, the slots that name a prefix, the probes ----
+    const bool on = tid < B;
+    int P = 0, E = 0, e0 = 0, so = 0;
+    if (on) {
+        P = a.prefix_len[tid];
+        E = a.ext_len[tid];
+        e0 = a.ext_offsets[tid];
+        so = a.slot_offsets[tid];
+    }
+    const int pmask = [&] {  // (a table of about sixteen entries per request, cleared below)
+        int n = 64;
+        while (n < 16 * B && n < PT) n <<= 1;
+        return n - 1;
+    }();
+    for (int i = tid; i < HT; i += NT) s_ht[i] = -1, s_hlead[i] = 0x7fffffff, s_hcnt[i] = 0;
+    for (int i = tid; i < NG; i += NT) s_gkey[i] = 0, s_gn[i] = 0, s_gL[i] = 0, s_gown[i] = 0;
+    if (first_part)
+        for (int i = tid; i <= pmask; i += NT) s_pt[i] = -1, s_pc[i] = 0;
+    if (tid == 0) s_any = 0;
+    const int rows = on ? max(E, 0) * G : 0, full = rows / mt, left = rows - full * mt;
+    const bool small = on && first_part && rows > 0 && rows < mt && P >= kPackMinPrefix;
+    if (on) {
+        s_P[tid] = P;
+        s_E[tid] = E;
+        s_e0[tid] = e0;
+        s_so[tid] = so;
+        s_cut[tid] = P;
+        if (kPack) s_cutg[tid] = 0x7fffffff;
+        const int32_t* list = slot_idx + so;
+        int4 id = make_int4(P, -1 - tid, 0, 0);
+        if (P > 0) id = make_int4(P, list[P - 1], list[0], list[P / 2]);
+        if (kPack && small)
+#pragma unroll
+            for (int k = 0; k < kProbes; ++k) s_pslot[(kProbes + 2) * tid + k] = probe_depth(k) <= P ? list[probe_depth(k) - 1] : -1;
+        s_id[tid] = id;
+    }
+    __syncthreads();
+    // ---- requests share their whole prefix if it has the same length and the same slots.  Slot lists that name the tokens of
+    // one prefix tree are equal as soon as their last slots are; the length, the first and the middle slot are compared as
+    // well, so that lists of other origin that merely end in the same slot stay apart ----
+    int hslot = 0;
+    if (rows > 0) {
+        const int4 id = s_id[tid];
+        hslot = hash_key((static_cast<unsigned long long>(static_cast<uint32_t>(id.x)) << 32) | static_cast<uint32_t>(id.y)) & (HT - 1);
+        for (int step = 0; step < HT; ++step) {
+            const int old = atomicCAS(&s_ht[hslot], -1, tid);
+            if (old < 0 || old == tid) break;
+            const int4 o = s_id[old];
+            if (o.x == id.x && o.y == id.y && o.z == id.z && o.w == id.w) break;
+            hslot = (hslot + 1) & (HT - 1);
+        }
+        atomicMin(&s_hlead[hslot], tid);
+        atomicAdd(&s_hcnt[hslot], 1);
+    }
+    __syncthreads();
+    int gid = tid;
+    if (rows > 0) gid = s_hlead[hslot];
+    if constexpr (kPack) {
+        const bool cand = small && s_hcnt[hslot] == 1;
+        if (cand) s_any = 1;
+        if (first_part) __syncthreads();
+        if (first_part && s_any) {
+            // ---- common first parts: the deepest probe at which another candidate has the same slot ----
+            // (the first look into the table goes out for all probes together; few need another)
+            int at[kProbes], old[kProbes], theirs[kProbes];
+            auto key_at = [&](int k) { return hash_key((static_cast<unsigned long long>(k) << 32) | static_cast<uint32_t>(s_pslot[(kProbes + 2) * tid + k])) & pmask; };
+#pragma unroll
+            for (int k = 0; k < kProbes; ++k) {
+                at[k] = cand && probe_depth(k) <= P ? key_at(k) : -1;
+                old[k] = at[k] >= 0 ? atomicCAS(&s_pt[max(at[k], 0)], -1, (1 << 16) | (tid * kProbes + k)) : -1;
+            }
+            auto slot_of = [&](int pair) { return s_pslot[(kProbes + 2) * (pair / kProbes) + pair % kProbes]; };
+#pragma unroll
+            for (int k = 0; k < kProbes; ++k) theirs[k] = old[k] >= 0 ? slot_of(old[k] & 0xFFFF) : 0;
+#pragma unroll
+            for (int k = 0; k < kProbes; ++k) {
+                if (at[k] < 0) continue;
+                const int slot = s_pslot[(kProbes + 2) * tid + k];
+                for (int step = 0; step <= pmask && old[k] >= 0; ++step) {
+                    const int who = old[k] & 0xFFFF;
+                    if (who % kProbes == k && (step == 0 ? theirs[k] : slot_of(who)) == slot) break;
+                    at[k] = (at[k] + 1) & pmask;
+                    old[k] = atomicCAS(&s_pt[at[k]], -1, (1 << 16) | (tid * kProbes + k));
+                }
+                atomicAdd(&s_pc[at[k]], 1);
+            }
+            __syncthreads();
+            int chosen = -1, depth = 0, next = 0x7fffffff;
+            if (cand)
+#pragma unroll
+                for (int k = 0; k < kProbes; ++k)
+                    if (at[k] >= 0 && (s_pc[at[k]] & 0xFFFF) >= 2) {
+                        chosen = at[k];
+                        depth = probe_depth(k);
+                        next = k + 1 < kProbes ? probe_depth(k + 1 < kProbes ? k + 1 : k) : 0x7fffffff;
+                    }
+            __syncthreads();
+            // the group: the candidates that chose this probe; its first member leads
+            if (chosen >= 0) {
+                atomicMin(&s_pt[chosen], tid);
+                atomicAdd(&s_pc[chosen], 1 << 16);
+            }
+            __syncthreads();
+            const bool grouped = chosen >= 0 && (s_pc[chosen] >> 16) >= 2;
+            const int lead = grouped ? s_pt[chosen] : tid;
+            // The slot lists agree up to the probe.  Beyond it, up to the next probe or the end of the leader's prefix, kProbes
+            // places are compared with the leader's list; what all members agree on is common (the tokens between the last
+            // place they agree at and the first they do not, a thirteenth of the interval, are each member's own).  (Lists of
+            // one prefix tree agree on everything before a place where they agree; for lists of other origin two more places
+            // and the first slot are compared, and a request that differs there stays on its own.)
+            const int pl = grouped ? s_P[lead] : 0, span = min(pl, next) - depth;
+            auto place = [&](int j) { return depth + static_cast<int>(static_cast<int64_t>(span) * (j + 1) / (kProbes + 1)); };
+            int mine[kProbes + 2];
+            if (grouped) {
+                const int32_t* x = slot_idx + so;
+#pragma unroll
+                for (int j = 0; j < kProbes; ++j) mine[j] = place(j) < min(P, pl) ? x[place(j)] : -2;
+                mine[kProbes] = x[depth / 3];
+                mine[kProbes + 1] = x[2 * (depth / 3)];
+                if (lead == tid)
+#pragma unroll
+                    for (int j = 0; j < kProbes + 2; ++j) s_pslot[(kProbes + 2) * tid + j] = mine[j];
+            }
+            __syncthreads();
+            bool agree = false;
+            if (grouped) {
+                const int* y = s_pslot + (kProbes + 2) * lead;
+                int same = 0;
+#pragma unroll
+                for (int j = kProbes - 1; j >= 0; --j) same = mine[j] == y[j] && mine[j] != -2 ? same + 1 : 0;  // (from place 0 on)
+                agree = mine[kProbes] == y[kProbes] && mine[kProbes + 1] == y[kProbes + 1] && s_id[tid].z == s_id[lead].z;
+                if (agree) atomicMin(&s_cutg[lead], same);
+            }
+            __syncthreads();
+            if (agree) {
+                const int same = s_cutg[lead];
+                gid = MAXB + lead;
+                s_cut[tid] = same > 0 ? place(same - 1) + 1 : depth;
+            }
+        }
+    }
+    // ---- what the groups hold ----
+    const bool fp = kPack && gid >= MAXB;  // grouped by a common first part
+    const int keys = rows > 0 ? P + E : 0;
+    if (on) {
+        s_gid[tid] = gid;
+        atomicMax(&s_gkey[gid], keys);
+        if (kPack && a.pack && left > 0 && (fp || P >= kPackMinPrefix)) {
+            atomicAdd(&s_gn[gid], 1);
+            atomicAdd(&s_gL[gid], left);
+            atomicAdd(&s_gown[gid], fp ? 0 : E);
+        }
+    }
+    __syncthreads();
+    // ---- order: groups with the most keys first, inside a group the request with the most keys first ----
+    if (on) {
+        constexpr unsigned kTop = (1u << 22) - 1;
+        const unsigned gk = min(kTop, static_cast<unsigned>(s_gkey[gid] + 63) >> 6), mine = min(kTop, static_cast<unsigned>(keys + 63) >> 6);
+        s_sk[tid] = (static_cast<unsigned long long>(kTop - gk) << 42) | (static_cast<unsigned long long>(gid) << 32) |
+                    (static_cast<unsigned long long>(kTop - mine) << 10) | static_cast<unsigned>(tid);
+    }
+    static_assert(NG <= 1024 && MAXB <= 1024, "the fields of the sort key");
+    __syncthreads();
+    {
+        // tpr threads per request (a power of two, neighbours in a wave), each over its share of the others
+        int tpr = 1;
+        while (tpr < 16 && 2 * tpr * B <= NT) tpr *= 2;
+        const int q = tid / tpr, first = tid & (tpr - 1);
+        const unsigned long long mine = s_sk[min(q, B - 1)];
+        int rank = 0;
+#pragma unroll 8
+        for (int i = first; i < B; i += tpr) rank += s_sk[i] < mine;
+        for (int off = 1; off < tpr; off <<= 1) rank += __shfl_xor(rank, off);
+        if (q < B && first == 0) s_order[rank] = q;
+        __syncthreads();
+    }
+    // ---- one thread per position of the list: tiles, packed rows, members ----
+    bool over;
+    int n_rows, n_own;
+    {
+        int r = 0, g = 0, pE = 0, pfull = 0, pleft = 0;
+        bool packed = false, pfp = false, head = false;
+        if (on) {
+            r = s_order[tid];
+            g = s_gid[r];
+            pE = s_E[r];
+            const int prow = max(pE, 0) * G;
+            pfull = prow / mt;
+            pleft = prow - pfull * mt;
+            pfp = kPack && g >= MAXB;
+            head = tid == 0 || s_gid[s_order[tid - 1]] != g;
+            // (requests with long extends behind a short common prefix stay on their own)
+            packed = kPack && s_gn[g] >= 2 && (pfp || static_cast<int64_t>(kPackOwnCost) * s_gown[g] <= static_cast<int64_t>(s_gn[g] - 1) * s_P[r]);
+        }
+        const int nshared = head && packed ? (s_gL[g] + mt - 1) / mt : 0;
+        packed = packed && pleft > 0;
+        int v[5] = {packed ? pleft : 0, packed ? 1 : 0, packed && !pfp ? pE : 0, nshared + pfull + (pleft > 0 && !packed ? 1 : 0),
+                    packed && pfp ? (pleft + kNarrowRows - 1) / kNarrowRows : 0};
+        int total[5];
+        block_scan<NT, 5>(v, total, s_scan);
+        if (head) {
+            s_gR[g] = v[0];
+            s_gm[g] = v[1];
+            s_go[g] = v[2];
+            s_gt[g] = v[3];
+            s_gL[g] = nshared > 0 ? s_gL[g] : 0;  // (0 from here on: not packed)
+        }
+        if (on) {
+            s_first[tid] = v[3];
+            s_ofirst[tid] = v[4];
+        }
+        __syncthreads();
+        if (on) s_req[tid] = make_int4(r, g, nshared, packed ? v[0] - s_gR[g] : -1);
+        if (packed) {
+            a.member[2 * v[1]] = make_int4(v[0] - s_gR[g], s_e0[r], pfull * mt, pE);
+            a.member[2 * v[1] + 1] = make_int4(v[2] - s_go[g], 0, 0, 0);
+            s_mR[v[1]] = v[0] - s_gR[g];
+            s_mO[v[1]] = v[2] - s_go[g];
+            s_mE[v[1]] = pfp ? 0 : pE;
+        }
+        n_rows = total[3];
+        n_own = total[4];
+        over = n_rows > a.tiles_cap || n_own > a.own_cap;
+    }
+    __syncthreads();
+    if (over) n_rows = n_own = 0;
+    // the last position whose first tile is <= t
+    auto position = [&](const int* first, int t) {
+        int lo = 0, hi = B;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (first[mid] <= t) lo = mid; else hi = mid;
+        }
+        return lo;
+    };
+    auto describe = [&](int t) {
+        TileDesc d{};
+        const bool own = t >= n_rows;
+        const int pos = own ? position(s_ofirst, t - n_rows) : position(s_first, t);
+        const int4 rq = s_req[pos];
+        const int r = rq.x, g = rq.y;
+        const int nrow = s_E[r] * G, full_r = nrow / mt;
+        int j = own ? t - n_rows - s_ofirst[pos] : t - s_first[pos];
+        d.r = r;
+        d.P = s_P[r];
+        d.e0 = s_e0[r];
+        d.slot_off = s_so[r];
+        if (own) {  // rows of one request over the keys behind its group's common part
+            d.own = true;
+            d.row0 = j * kNarrowRows;
+            d.rows_here = min(kNarrowRows, nrow - d.row0);
+            d.e_or_rows = s_E[r];
+            d.kv_lo = s_cut[r];
+            d.kv_end = d.P + (d.row0 + d.rows_here - 1) / G + 1;
+            d.common_tile = s_gt[g];
+            d.common_row = rq.w + d.row0;
+            d.group_rows = s_gL[g];
+            return d;
+        }
+        const int nshared = kPack ? rq.z : 0;
+        if (j < nshared) {  // a shared tile of the group this position heads
+            const int m0 = s_gm[g], nm = s_gn[g], L = s_gL[g];
+            d.row0 = j * mt;
+            d.rows_here = min(mt, L - d.row0);
+            d.e_or_rows = L;
+            // the members whose rows meet the tile: the one holding its first row ... the one holding its last
+            auto member_of = [&](int row) {
+                int lo = 0, hi = nm;
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (s_mR[m0 + mid] <= row) lo = mid; else hi = mid;
+                }
+                return m0 + lo;
+            };
+            const int ma = member_of(d.row0), mb = member_of(d.row0 + d.rows_here - 1);
+            d.member0 = ma;
+            d.n_members = mb - ma + 1;
+            d.P = s_cut[r];
+            d.kv_end = d.P + s_mO[mb] + s_mE[mb] - s_mO[ma];
+            d.partial_only = kPack && g >= MAXB;
+            return d;
+        }
+        j -= nshared;
+        d.e_or_rows = s_E[r];
+        // the request's last rows - the most keys - first: its left-over rows, if they were not packed, then the
+        // full tiles from the last one down
+        const int left_r = nrow - full_r * mt;
+        if (left_r > 0 && rq.w < 0) {
+            if (j == 0) {
+                d.row0 = full_r * mt;
+                d.rows_here = left_r;
+                d.kv_end = d.P + (nrow - 1) / G + 1;
+                return d;
+            }
+            --j;
+        }
+        d.row0 = (full_r - 1 - j) * mt;
+        d.rows_here = mt;
+        d.kv_end = d.P + (d.row0 + mt - 1) / G + 1;
+        return d;
+    };
+    emit_items<NT>(a, n_rows, n_rows + n_own, over, describe);
+}
+
+// Batches of more than kSortMax requests: in the order given, tables in global memory.
+template <int NT>
+__global__ __launch_bounds__(NT) void extend_plan_large_kernel(PlanArgs a) {
+    __shared__ int s_scan[2][1][NT / 64];
+    touch_args(a);
+    const int tid = threadIdx.x, G = a.G, mt = kTileRows;
+    int n_rows = 0;
+    for (int base = 0, round = 0; base < a.B; base += NT, ++round) {
+        const int r = base + tid;
+        int cnt = 0;
+        if (r < a.B) {
+            const int e = a.ext_len[r];
+            cnt = e > 0 ? (e * G + mt - 1) / mt : 0;
+        }
+        int v[1] = {cnt}, total[1];
+        block_scan<NT, 1>(v, total, s_scan[round & 1]);
+        for (int j = 0; j < cnt; ++j)  // a request's last rows - the most keys - first
+            if (n_rows + v[0] + j < a.tiles_cap) a.tile[n_rows + v[0] + j] = make_int2(r, (cnt - 1 - j) * mt);
+        n_rows += total[0];
+    }
+    __syncthreads();
+    const bool over = n_rows > a.tiles_cap;
+    if (over) n_rows = 0;
+    auto describe = [&](int t) {
+        TileDesc d{};
+        const int2 tt = a.tile[t];
+        d.r = tt.x;
+        d.row0 = tt.y;
+        d.P = a.prefix_len[d.r];
+        d.e_or_rows = a.ext_len[d.r];
+        d.e0 = a.ext_offsets[d.r];
+        d.slot_off = a.slot_offsets[d.r];
+        d.rows_here = min(mt, d.e_or_rows * G - d.row0);
+        d.kv_end = d.P + (d.row0 + d.rows_here - 1) / G + 1;
+        return d;
+    };
+    emit_items<NT>(a, n_rows, n_rows, over, describe);
+}
+
+int launch_extend_plan(const ExtendPlan& p, const PlanTables& t, const int32_t* prefix_len, const int32_t* ext_len, const int32_t* ext_offsets,
+                       const int32_t* slot_offsets, const int32_t* slot_idx, int B, int G, hipStream_t stream) {
+    const PlanArgs a{prefix_len, ext_len, ext_offsets, slot_offsets, slot_idx, t.hdr, t.tile, t.member, t.item, t.chunk, B, G, p.tiles_cap,
+                     p.own_cap, p.items_cap, p.prows_cap, p.chunks_cap, p.slots * p.rounds, p.pack, p.first_part, p.tile_parts, p.chunk_rows};
+    ProfScope prof(kProfPlan, stream);
+    // (few requests and tiles: four waves meet at a barrier sooner than sixteen)
+    const int most = p.tiles_cap + p.own_cap;
+    if (B <= kPackMax && most <= 512)
+        hipLaunchKernelGGL((extend_plan_kernel<kPackMax, 256>), dim3(1), dim3(256), 0, stream, a);
+    else if (B <= kPackMax && most <= 1024)
+        hipLaunchKernelGGL((extend_plan_kernel<kPackMax, 512>), dim3(1), dim3(512), 0, stream, a);
+    else if (B <= kPackMax)
+        hipLaunchKernelGGL((extend_plan_kernel<kPackMax, 1024>), dim3(1), dim3(1024), 0, stream, a);
+    else if (B <= kSortMax)
+        hipLaunchKernelGGL((extend_plan_kernel<kSortMax, 1024>), dim3(1), dim3(1024), 0, stream, a);
+    else
+        hipLaunchKernelGGL((extend_plan_large_kernel<1024>), dim3(1), dim3(1024), 0, stream, a);
+    return PA_OK;
+}
+
+}  // namespace pa

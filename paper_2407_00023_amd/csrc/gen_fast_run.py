@@ -492,9 +492,8 @@ __device__ __forceinline__ void {name}(int mode, f32x16& acc0, f32x16& acc1, f32
 '''
 
 
-HEADER = '''// GENERATED by gen_fast_run.py - do not edit.  Tiles of extend_bf16_kernel<128, 4, 1> (a wave loads four 1 KB blocks of
-// a K or V tile) and extend_bf16_kernel<128, 8, 1> (_w8: two blocks) as gfx950 assembly with fixed registers; the
-// generator describes the schedule.  One statement per kernel holds every kind of tile, so that the compiler meets one
+HEADER = '''// GENERATED by gen_fast_run.py - do not edit.  Tiles of extend_bf16_kernel<128> (a wave loads four 1 KB blocks of
+// a K or V tile) as gfx950 assembly with fixed registers; the generator describes the schedule.  One statement per kernel holds every kind of tile, so that the compiler meets one
 // set of register constraints; the mode operand chooses:
 //   1  a run of tiles, the NEXT tile of each wholly in the prefix (its rows come from the pool through slot ids)
 //   2  a run of tiles, the next tile wholly in the extend tokens
@@ -525,7 +524,7 @@ HEADER = '''// GENERATED by gen_fast_run.py - do not edit.  Tiles of extend_bf16
 
 def main():
     here = os.path.dirname(os.path.abspath(__file__))
-    text = (HEADER + emit("fast_tiles_d128", 4) + emit("fast_tiles_d128_w8", 2) +
+    text = (HEADER + emit("fast_tiles_d128", 4) +
             emit("fast_tiles_d128_kv8", 4, ["pool8", "ext", "plain", "masked"], no_barrier=("plain", "masked")))
     path = os.path.join(here, "fast_run_d128.inc")
     old = open(path).read() if os.path.exists(path) else None
