@@ -28,8 +28,8 @@
 //
 // Two kinds of tile.  The general tile (general_block below) takes any mix of pool and extend rows, masks and
 // ragged ends, and moves the running maximum; it runs for the first tile of a workgroup, where prefix and extend
-// tokens meet, and on the causal diagonal.  Runs of consecutive tiles that need no mask (D = 128) execute as one
-// assembly statement each (fast_run_d128.inc, written by gen_fast_run.py) with the running maximum frozen.
+// tokens meet, and on the causal diagonal.  Runs of consecutive tiles that need no mask execute as one
+// assembly statement each (fast_run.inc, written by gen_fast_run.py) with the running maximum frozen.
 #include <hip/hip_bf16.h>
 
 #include <atomic>
@@ -55,7 +55,7 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 // fast_run_pool_d128 / fast_run_ext_d128: runs of steady-state tiles as assembly with fixed registers
-#include "fast_run_d128.inc"
+#include "fast_run.inc"
 
 constexpr int kStages = 2;               // LDS ring: one tile being read, one being filled
 constexpr float kRescaleThreshold = 8.f; // log2 units: the running maximum may lag the true one by this much
@@ -153,7 +153,7 @@ constexpr int kLdsTail = kLdsMl + 4 * kNarrowRows * 8;
 // KV8: the pool holds one-byte codes and row exponents (fp8_rows.h) instead of bfloat16; its rows are decoded into the
 // bfloat16 tiles in LDS, and everything from there on is the same arithmetic.
 template <int D, bool KV8>
-__global__ __launch_bounds__(256, D == 64 ? 4 : 2) void extend_bf16_kernel(
+__global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_kernel(
     const __hip_bfloat16* __restrict__ q_ext, const __hip_bfloat16* __restrict__ k_ext,
     const __hip_bfloat16* __restrict__ v_ext, const __hip_bfloat16* __restrict__ pool, const signed char* __restrict__ pool_exp,
     const int32_t* __restrict__ slot_idx, int Hq, int Hkv, int page_size, int page_shift, unsigned page_magic,
@@ -170,6 +170,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void extend_bf16_kernel(
     constexpr int STAGEB = 2 * TILEB;        // one ring slot: K tile, V tile
     constexpr int RPB = 1024 / ROWB;         // rows per 1 KB block (what one wave-wide 16-byte load fills)
     constexpr int UPW = kKT / RPB / NW;      // blocks per wave, tile and tensor
+    constexpr bool kAsm = D == 128 || !KV8;  // there are assembly tiles for this kernel
     static_assert(UPW >= 1, "tile too small for this many waves");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [kStages][K tile | V tile]
 
@@ -569,7 +570,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void extend_bf16_kernel(
     // 0: the tile at p0 takes the general code; 1 / 2: the hand-scheduled one, the next tile lying wholly in the
     // prefix / wholly in the extend tokens (its rows clamp to the last valid key).  Uniform over the wave.
     auto tile_kind = [&](int p0) __attribute__((always_inline)) -> int {
-        if (!(fast_ok && D == 128 && (smem_addr & 255u) == 0)) return 0;
+        if (!(fast_ok && kAsm && (smem_addr & 255u) == 0)) return 0;
         if (!(wave_on && p0 <= P + wave_i_last && p0 + kKT <= blk_vis_min)) return 0;
         const int first = min(p0 + kKT, kv_hi - 1), last = min(p0 + 2 * kKT - 1, kv_hi - 1);
         // (after the common keys of a shared tile come several requests' keys: never one run of extend tokens)
@@ -769,27 +770,30 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void extend_bf16_kernel(
         ring ^= 1;
         p0 += kKT;
     };
-    // Tiles in assembly (D = 128; one statement, see fast_run_d128.inc).  A run: consecutive tiles that need no mask
+    // Tiles in assembly (one statement, see fast_run.inc).  A run: consecutive tiles that need no mask
     // and whose successors lie wholly in the prefix (mode 1, or 3 for pools of 4 GB and more) or wholly in the extend
     // tokens (2); it issues its tiles' loads itself.  A single tile: arithmetic only, with the keys a row must not see
     // hidden if there are any (5, else 4), the next tile's loads issued from here by the general code - for the tiles
     // that no run takes because of what their successor is (prefix and extend rows mixed) or because they touch the
     // causal diagonal; not in shared tiles (a second visibility bound).  Neither before the running maximum exists.
     auto single_tile_ok = [&](int p0) __attribute__((always_inline)) -> bool {
-        return (fast_ok || KV8) && D == 128 && (smem_addr & 255u) == 0 && !shared && wave_on && p0 <= P + wave_i_last;
+        return (fast_ok || KV8) && kAsm && (smem_addr & 255u) == 0 && !shared && wave_on && p0 <= P + wave_i_last;
     };
     // The assembly tiles want a running maximum to start from, and any lower bound of the true one will do as long as it
     // is not 2^40 short (then the tile is handed to the general code, as always): the largest score of the first 32 keys,
     // where every row of the wave sees all of them.  The first tile then runs in assembly like the others (its first
     // key block is multiplied twice) instead of in the general code, which establishes the maximum otherwise.
-    if constexpr (D == 128) {
+    if constexpr (kAsm) {
         // (also in shared tiles: the keys of the common prefix are visible to every row)
         if ((fast_ok || KV8) && (smem_addr & 255u) == 0 && wave_on && kv_lo <= P + wave_i_last && kv_lo + 32 <= blk_vis_min && kv_lo + 32 <= kv_hi) {
             const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             bf16x8 kf[KS];
 #pragma unroll
             for (int s = 0; s < KS; ++s) asm volatile("ds_read_b128 %0, %1" : "=v"(kf[s]) : "v"(k_rd[s]));
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]), "+v"(kf[4]), "+v"(kf[5]), "+v"(kf[6]), "+v"(kf[7]));
+            if constexpr (KS == 8)
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]), "+v"(kf[4]), "+v"(kf[5]), "+v"(kf[6]), "+v"(kf[7]));
+            else
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]));
             f32x16 sacc = zero16;
 #pragma unroll
             for (int s = 0; s < KS; ++s) sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qreg[s], sacc, 0, 0, 0);
@@ -811,7 +815,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void extend_bf16_kernel(
             mode = kind == 1 ? (KV8 ? 6 : fast_ok == 2 ? 3 : 1) : kind == 2 ? 2 : single_tile_ok(p0) ? (p0 + kKT > blk_vis_min ? 5 : 4) : 0;
         }
         if (mode != 0) {
-            if constexpr (D == 128) {
+            if constexpr (kAsm) {
                 // Against the running maximum as it stands: scores never move it in there (a row's probabilities may
                 // reach 2^40 instead), the output accumulators are touched by MFMAs only.
                 int p_end = p0 + kKT;
@@ -826,14 +830,12 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void extend_bf16_kernel(
                 }
                 const int p_start = p0, ring_start = ring;
                 int st = 0;
-                const bf16x16 q01 = __builtin_shufflevector(qreg[0], qreg[1], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
-                const bf16x16 q23 = __builtin_shufflevector(qreg[2], qreg[3], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
-                const bf16x16 q45 = __builtin_shufflevector(qreg[4], qreg[5], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
-                const bf16x16 q67 = __builtin_shufflevector(qreg[6], qreg[7], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
-                const bf16x32 q_lo = __builtin_shufflevector(q01, q23, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18,
-                                                             19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31);
-                const bf16x32 q_hi = __builtin_shufflevector(q45, q67, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18,
-                                                             19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31);
+                auto quad = [&](int k) __attribute__((always_inline)) {  // the query fragments k .. k + 3 in a row
+                    const bf16x16 a = __builtin_shufflevector(qreg[k], qreg[k + 1], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+                    const bf16x16 b = __builtin_shufflevector(qreg[k + 2], qreg[k + 3], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+                    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18, 19, 20, 21, 22, 23, 24,
+                                                   25, 26, 27, 28, 29, 30, 31);
+                };
                 // wave-uniform values, said so to the compiler (they go to scalar registers)
                 auto uni = [](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(x); };
                 auto uni_ptr = [&](const void* q) __attribute__((always_inline)) {
@@ -859,13 +861,17 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void extend_bf16_kernel(
                 const void* base_v = mode == 2 ? static_cast<const void*>(vx_g) : mode == 6 ? static_cast<const void*>(pool8_g + v_off8) : static_cast<const void*>(pool_g + v_off32);
                 const int lim = vis_end - p0 - 4 * hh;
                 if constexpr (KV8)  // (single tiles only; they end with this wave's loads landed and leave the barrier to the caller)
-                    fast_tiles_d128_kv8(uni(mode), oacc[0], oacc[1], oacc[2], oacc[3], q_lo, q_hi, l_run, -m_run, sl_next,
+                    fast_tiles_d128_kv8(uni(mode), oacc[0], oacc[1], oacc[2], oacc[3], quad(0), quad(4), l_run, -m_run, sl_next,
                                         k_rd[0], v_rd[0][0], ld_koff0, ld_voff0, row_in_tile, p0, ring, st, p_end, uni_ptr(slots),
                                         uni_ptr(base_k), uni_ptr(base_v), lim, c, c2, uni(static_cast<int>(smem_addr) + EX_OFF + wave * EXPB));
-                else
-                    fast_tiles_d128(uni(mode), oacc[0], oacc[1], oacc[2], oacc[3], q_lo, q_hi, l_run, -m_run, sl_next,
+                else if constexpr (D == 128)
+                    fast_tiles_d128(uni(mode), oacc[0], oacc[1], oacc[2], oacc[3], quad(0), quad(4), l_run, -m_run, sl_next,
                                     k_rd[0], v_rd[0][0], ld_koff0, ld_voff0, row_in_tile, p0, ring, st, p_end, uni_ptr(slots),
                                     uni_ptr(base_k), uni_ptr(base_v), lim, c, c2);
+                else
+                    fast_tiles_d64(uni(mode), oacc[0], oacc[1], quad(0), l_run, -m_run, sl_next,
+                                   k_rd[0], v_rd[0][0], ld_koff0, ld_voff0, row_in_tile, p0, ring, st, p_end, uni_ptr(slots),
+                                   uni_ptr(base_k), uni_ptr(base_v), lim, c, c2);
                 if constexpr (KV8) {
                     if (mode == 6 && st != 0) raw_mask = (1 << UPW) - 1;  // left inside a tile: the next one's rows are still codes
                     if (st == 0 && mode != 6 && mode >= 4) {

@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
-"""Writes fast_run_d128.inc: the tiles of the bf16 extend-attention kernel as gfx950 assembly.
+"""Writes fast_run.inc: the tiles of the bf16 extend-attention kernel as gfx950 assembly.
 
-One inline-assembly statement per kernel instance holds every kind of tile, for head dimension 128 and 32 packed query
+One inline-assembly statement per kernel instance holds every kind of tile, for head dimension 128 or 64 and 32 packed query
 rows per wave, with every register chosen here.  (Left to the compiler's register allocator the 64 output accumulators
 are split around the phases of a tile and copied every tile, and spill reloads inside the loop serialise the
 global -> LDS loads behind them; and several statements, each with its fixed registers, made the compiler spill
@@ -9,7 +9,7 @@ everything it held around them.)  A mode operand picks the kind: runs of consecu
 next tile's loads themselves (its rows in the pool through slot ids, 32-bit or 64-bit addresses, as codes of the fp8
 pool, or in the extend tokens), and single tiles, plain or with keys hidden from rows, whose loads the caller issues.
 
-A tile is 32 slots of one MFMA each; what follows an MFMA in the stream runs in its shadow:
+A tile is 32 slots (16 at head dimension 64) of one MFMA each; what follows an MFMA in the stream runs in its shadow:
     phase A  S0 = K(block 0) Q^T     | addresses + issue of the next tile's global -> LDS loads
     phase B  S1 = K(block 1) Q^T     | probabilities 2^(c S0 - m), their sum; slot ids of the tile after next
     (leave with status 1 if a lane's sum exceeds the limit: block 0 outgrew the running maximum m)
@@ -31,29 +31,46 @@ between tiles.
 Run:  python gen_fast_run.py  (the build does)."""
 import os
 
-KS, NB = 8, 4            # k-slices of QK^T, head-dim blocks of O^T
-ROWB, TILEB, STAGEB = 256, 16384, 32768
-UPW, RPB = 4, 4          # 1 KB load blocks per wave and tensor, rows per block
-
 NFR = 8                  # fragment buffers (K and V^T fragments share them: the two kinds are read in different phases)
 PD = 5                   # LDS fragments in flight ahead of their MFMA
 PAIRWAIT, DEFER_SUM, M0_FIRST, FAST_SLOTS, SETTLE = True, True, True, True, False   # (switches for experiments)
 
-# ---- vector registers (everything from v44 up belongs to the assembly) ----
-ACC = [192 + 16 * b for b in range(NB)]
-Q = [160 + 4 * s for s in range(KS)]
-SC0, SC1 = 144, 128
-PB0, PB1 = 120, 112
-FR = [80 + 4 * i for i in range(NFR)]
-KRD = [72 + s for s in range(8)]
-VRD = [64 + i for i in range(8)]   # index b * 2 + h2
-SLN = [60, 61, 62, 63]
-L, NEGM, KOFF0, VOFF0, ROWI, KRD0, VRD0 = 59, 58, 57, 56, 55, 54, 53
-T = [46, 47, 48, 49, 50, 51, 52]
-LSUM, ROWOFF = 45, 44
-LIM0, LIM1, NEGINF = T[0], T[1], T[6]   # masked single tiles (they issue no loads: the T registers are free)
-MASKS = [72, 74]                        # ... and two scalar register pairs for their comparisons
-FIRST_V = 44
+
+def shape(D):
+    """Sizes and vector registers for one head dimension.  D = 128 fills 256 registers (two waves on a SIMD), D = 64 keeps to
+    168 (three): half the arithmetic per tile, so more of the time goes to the exponentials of the wave itself, and a third
+    wave fills it."""
+    global KS, NB, ROWB, TILEB, STAGEB, UPW, RPB, NFR
+    global ACC, Q, SC0, SC1, PB0, PB1, FR, KRD, VRD, SLN, L, NEGM, KOFF0, VOFF0, ROWI, KRD0, VRD0, T, LSUM, ROWOFF, LIM0, LIM1, NEGINF, FIRST_V
+    KS, NB = D // 16, D // 32           # k-slices of QK^T, head-dim blocks of O^T
+    ROWB, TILEB, STAGEB = 2 * D, 128 * D, 256 * D
+    UPW, RPB = D // 32, 512 // D        # 1 KB load blocks per wave and tensor, rows per block
+    NFR = 8 if D == 128 else 6
+    # everything from FIRST_V up belongs to the assembly
+    top = 256 if D == 128 else 168
+
+    def take(n):
+        nonlocal top
+        top -= n
+        return top
+    ACC = [take(16) for _ in range(NB)][::-1]
+    Q = [take(4) for _ in range(KS)][::-1]
+    SC0, SC1 = take(16), take(16)
+    PB0, PB1 = take(8), take(8)
+    FR = [take(4) for _ in range(NFR)][::-1]
+    KRD = [take(1) for _ in range(KS)][::-1]
+    VRD = [take(1) for _ in range(2 * NB)][::-1]   # index b * 2 + h2
+    SLN = [take(1) for _ in range(UPW)][::-1]
+    L, NEGM, KOFF0, VOFF0, ROWI, KRD0, VRD0 = [take(1) for _ in range(7)]
+    if (top - 7) % 2:
+        take(1)                         # (pairs of T hold 64-bit addresses)
+    T = [take(1) for _ in range(7)][::-1]
+    LSUM, ROWOFF = take(1), take(1)
+    LIM0, LIM1, NEGINF = T[0], T[1], T[6]   # masked single tiles (they issue no loads: the T registers are free)
+    FIRST_V = top
+
+
+MASKS = [72, 74]                        # two scalar register pairs for the comparisons of masked single tiles
 # ---- scalar registers ----
 P0, RING, STATUS, PEND = 40, 41, 42, 43
 SLOTS, BASE_K, BASE_V = 44, 46, 48     # 64-bit pairs: slot ids; K rows (pool or k_ext); V rows (pool + K->V distance, or v_ext)
@@ -116,20 +133,20 @@ def tile(st, kind, ring, uid, upw):
     ext, wide, raw8 = kind == "ext", kind == "pool64", kind == "pool8"
     noload, masked = kind in ("plain", "masked"), kind == "masked"   # (single tiles: the kernel issues the next tile's loads itself)
     here, there = ring * STAGEB, (ring ^ 1) * STAGEB
-    last = {}   # fragment number (0..15 K, 16..31 V) -> id of its last LDS read
+    NK = 2 * KS   # K fragments of a tile (and V^T fragments: 2 * 2 * NB, the same)
+    last = {}   # fragment number (0 .. NK - 1 K, NK .. V) -> id of its last LDS read
 
     def read_frag(f):
-        if f >= 32:
+        if f >= 2 * NK:
             return
         buf = FR[f % NFR]
-        if f < 16:   # K fragment: key block f // 8, k-slice f % 8
-            blk, sl = divmod(f, 8)
+        if f < NK:   # K fragment: key block f // KS, k-slice f % KS
+            blk, sl = divmod(f, KS)
             off = here + blk * 32 * ROWB
             o = f" offset:{off}" if off else ""
             last[f] = st.lds_read(f"ds_read_b128 {v(buf, 4)}, {v(KRD[sl])}{o}")
-        else:        # V^T fragment: key block g // 8, 16-key group (g % 8) // 4, head-dim block g % 4
-            g = f - 16
-            blk, j = divmod(g, 8)
+        else:        # V^T fragment: key block, 16-key group, head-dim block
+            blk, j = divmod(f - NK, 2 * NB)
             cs, b = divmod(j, NB)
             off = here + blk * 32 * ROWB + cs * 16 * ROWB
             o = f" offset:{off}" if off else ""
@@ -173,7 +190,7 @@ def tile(st, kind, ring, uid, upw):
                 e(f"v_med3_i32 {v(T[0])}, {v(SLN[u])}, 0, {s(C_NSLOT1)}")
                 e(f"v_lshrrev_b32 {v(T[1])}, {s(C_SHIFT)}, {v(T[0])}")
                 e(f"v_and_b32 {v(T[0])}, {s(C_MASK)}, {v(T[0])}")
-                e(f"v_lshlrev_b32 {v(T[0])}, 8, {v(T[0])}")
+                e(f"v_lshlrev_b32 {v(T[0])}, {ROWB.bit_length() - 1}, {v(T[0])}")
                 e(f"v_mad_u32_u24 {v(ROWOFF)}, {v(T[1])}, {s(C_PSTRIDE)}, {v(T[0])}")
             x = [0, 64, s(C_128), s(C_192)][u]
             if wide:
@@ -189,7 +206,7 @@ def tile(st, kind, ring, uid, upw):
                 e(f"v_xad_u32 {v(T[4])}, {v(VOFF0)}, {16 * u}, {v(T[4])}")
                 addr, base = T[4], BASE_V
             else:
-                e(f"v_xad_u32 {v(T[3])}, {v(VOFF0)}, {16 * u}, {v(ROWOFF)}")
+                e(f"v_xad_u32 {v(T[3])}, {v(VOFF0)}, {(16 if ROWB == 256 else 32) * u}, {v(ROWOFF)}")
                 addr, base = T[3], BASE_V
         if not M0_FIRST:
             e(f"s_add_u32 m0, {s(C_LDSW)}, {m0}" if m0 else f"s_mov_b32 m0, {s(C_LDSW)}")
@@ -347,6 +364,7 @@ def tile(st, kind, ring, uid, upw):
         elif sl < 2 * upw and not noload:
             load_piece(sl // 2, sl % 2)
     # ---- phase B: S1 = K(block 1) Q^T | slot ids of the tile after next, probabilities of block 0 ----
+    per = 8 // KS   # pieces of probabilities per MFMA
     e(f"v_mov_b32 {v(LSUM)}, 0")
     for sl in range(KS):
         f = KS + sl
@@ -364,31 +382,34 @@ def tile(st, kind, ring, uid, upw):
         if sl == 0 and SETTLE:
             e("s_nop 7")
             e("s_nop 3")
-        exp_piece(SC0, PB0, sl, LIM0)
-    end_of_sums(2 * KS - 1)
+        for k in range(per):
+            exp_piece(SC0, PB0, per * sl + k, LIM0)
+    end_of_sums(NK - 1)
     e(f"v_cmp_lt_u32 vcc, {LIMIT}, {v(LSUM)}")
     e(f"s_cbranch_vccnz Lover1{st.kind_end}")
     e(f"v_add_f32 {v(L)}, {v(L)}, {v(LSUM)}")
     e(f"v_mov_b32 {v(LSUM)}, 0")
     # ---- phase C: O += V(block 0) P0 | probabilities of block 1 (its scores were last written thirteen issue slots ago) ----
-    for j in range(8):
-        f = 16 + j
+    NV = 2 * NB   # V^T fragments per key block
+    for j in range(NV):
+        f = NK + j
         wait_pair(f)
         cs, b = divmod(j, NB)
         mfma(v(ACC[b], 16), v(FR[f % NFR], 4), v(PB0 + 4 * cs, 4), v(ACC[b], 16))
-        if j < 7:
+        if j < NV - 1:
             read_frag(f + PD)
         if j == 0 and SETTLE:
             e("s_nop 7")
             e("s_nop 3")
-        exp_piece(SC1, PB1, j, LIM1)
-    end_of_sums(23)
+        for k in range(per):
+            exp_piece(SC1, PB1, per * j + k, LIM1)
+    end_of_sums(NK + NV - 1)
     e(f"v_cmp_lt_u32 vcc, {LIMIT}, {v(LSUM)}")
     e(f"s_cbranch_vccnz Lover2{st.kind_end}")
     e(f"v_add_f32 {v(L)}, {v(L)}, {v(LSUM)}")
     # ---- phase D: O += V(block 1) P1 ----
-    for j in range(8):
-        f = 24 + j
+    for j in range(NV):
+        f = NK + NV + j
         wait_pair(f)
         cs, b = divmod(j, NB)
         mfma(v(ACC[b], 16), v(FR[f % NFR], 4), v(PB1 + 4 * cs, 4), v(ACC[b], 16))
@@ -418,16 +439,16 @@ def gen(upw, kinds=KINDS, no_barrier=()):
     e = st.emit
     end = "%="
     # ---- entry: LDS read addresses in ring slot 0 (the operands give those of the slot that holds the tile at P0) ----
-    e(f"s_lshl_b32 {s(S_T[0])}, {s(RING)}, 15")
+    e(f"s_lshl_b32 {s(S_T[0])}, {s(RING)}, {STAGEB.bit_length() - 1}")
     e(f"v_subrev_u32 {v(KRD[0])}, {s(S_T[0])}, {v(KRD0)}")
     e(f"v_subrev_u32 {v(VRD[0])}, {s(S_T[0])}, {v(VRD0)}")
-    for k in range(1, 8):
+    for k in range(1, KS):
         e(f"v_xor_b32 {v(KRD[k])}, {32 * k}, {v(KRD[0])}")
     for b in range(1, NB):
         e(f"v_xor_b32 {v(VRD[2 * b])}, {64 * b}, {v(VRD[0])}")
     for b in range(NB):
         e(f"v_xor_b32 {v(VRD[2 * b + 1])}, 32, {v(VRD[2 * b])}")
-        e(f"v_add_u32 {v(VRD[2 * b + 1])}, 0x800, {v(VRD[2 * b + 1])}")
+        e(f"v_add_u32 {v(VRD[2 * b + 1])}, {8 * ROWB:#x}, {v(VRD[2 * b + 1])}")
     e(f"s_mov_b32 {s(STATUS)}, 0")
     for kind in kinds[1:]:
         e(f"s_cmp_eq_u32 {s(MODE)}, {KINDS.index(kind) + 1}")
@@ -464,36 +485,42 @@ def gen(upw, kinds=KINDS, no_barrier=()):
     return st.lines
 
 
-def emit(name, upw, kinds=KINDS[:5], no_barrier=()):
-    lines = gen(upw, kinds, no_barrier)
+def emit(name, D, kinds=KINDS[:5], no_barrier=()):
+    shape(D)
+    lines = gen(UPW, kinds, no_barrier)
     kv8 = "pool8" in kinds
     body = "\n".join(f'        "{ln}\\n\\t"' for ln in lines)
-    clob = ([f"v{i}" for i in range(FIRST_V, 53) if i != LIM0] + [f"v{i}" for i in range(64, 160)] + [f"s{i}" for i in S_T] +
+    free = set(range(FIRST_V, min(ACC))) - set(SLN) - {L, NEGM, KOFF0, VOFF0, ROWI, KRD0, VRD0, LIM0} - set(range(min(Q), max(Q) + 4))
+    clob = ([f"v{i}" for i in sorted(free)] + [f"s{i}" for i in S_T] +
             [f"s{i}" for i in range(MASKS[0], MASKS[1] + 2)] + ["vcc", "scc", "memory"] + (["exec"] if kv8 else []))
     clobbers = ", ".join(f'"{c}"' for c in clob)
-    sln = ", ".join(f'"+{{v{SLN[u]}}}"(sl_next[{u}])' for u in range(upw))
+    sln = ", ".join(f'"+{{v{SLN[u]}}}"(sl_next[{u}])' for u in range(UPW))
+    accs = ", ".join(f"f32x16& acc{b}" for b in range(NB))
+    qs = ["q_lo", "q_hi"][:KS // 4]
+    acc_ops = ", ".join(f'"+{{v[{ACC[b]}:{ACC[b] + 15}]}}"(acc{b})' for b in range(NB))
+    q_ops = ", ".join(f'"{{v[{Q[4 * k]}:{Q[4 * k] + 15}]}}"({q})' for k, q in enumerate(qs))
     return f'''
-// a wave loads {upw} blocks of a tile
-__device__ __forceinline__ void {name}(int mode, f32x16& acc0, f32x16& acc1, f32x16& acc2, f32x16& acc3, const bf16x32& q_lo,
-                                       const bf16x32& q_hi, float& l_run, float neg_m, int32_t (&sl_next)[{upw}],
+// head dimension {D}: a wave loads {UPW} blocks of a tile
+__device__ __forceinline__ void {name}(int mode, {accs}, {", ".join(f"const bf16x32& {q}" for q in qs)},
+                                       float& l_run, float neg_m, int32_t (&sl_next)[{UPW}],
                                        unsigned k_rd0, unsigned v_rd0, unsigned ld_koff0, unsigned ld_voff0, int row_in_tile,
                                        int& p0, int& ring, int& status, int p_end, const void* slots, const void* base_k,
                                        const void* base_v, int lim, const i32x8& c, const i32x4& c2{", unsigned exp_stage" if kv8 else ""}) {{
     asm volatile(
 {body}
-        : "+{{v[192:207]}}"(acc0), "+{{v[208:223]}}"(acc1), "+{{v[224:239]}}"(acc2), "+{{v[240:255]}}"(acc3), "+{{v59}}"(l_run),
+        : {acc_ops}, "+{{v{L}}}"(l_run),
           {sln}, "+{{s40}}"(p0),
           "+{{s41}}"(ring), "={{s42}}"(status), "+{{v{LIM0}}}"(lim)
-        : "{{v[160:175]}}"(q_lo), "{{v[176:191]}}"(q_hi), "{{v58}}"(neg_m), "{{v54}}"(k_rd0), "{{v53}}"(v_rd0), "{{v57}}"(ld_koff0),
-          "{{v56}}"(ld_voff0), "{{v55}}"(row_in_tile), "{{s43}}"(p_end), "{{s[44:45]}}"(slots), "{{s[46:47]}}"(base_k),
+        : {q_ops}, "{{v{NEGM}}}"(neg_m), "{{v{KRD0}}}"(k_rd0), "{{v{VRD0}}}"(v_rd0), "{{v{KOFF0}}}"(ld_koff0),
+          "{{v{VOFF0}}}"(ld_voff0), "{{v{ROWI}}}"(row_in_tile), "{{s43}}"(p_end), "{{s[44:45]}}"(slots), "{{s[46:47]}}"(base_k),
           "{{s[48:49]}}"(base_v), "{{s[52:59]}}"(c), "{{s[60:63]}}"(c2), "{{s{MODE}}}"(mode){f', "{{s{EXST}}}"(exp_stage)' if kv8 else ""}
         : {clobbers});
 }}
 '''
 
 
-HEADER = '''// GENERATED by gen_fast_run.py - do not edit.  Tiles of extend_bf16_kernel<128> (a wave loads four 1 KB blocks of
-// a K or V tile) as gfx950 assembly with fixed registers; the generator describes the schedule.  One statement per kernel holds every kind of tile, so that the compiler meets one
+HEADER = '''// GENERATED by gen_fast_run.py - do not edit.  Tiles of extend_bf16_kernel as gfx950 assembly with fixed registers; the
+// generator describes the schedule.  One statement per kernel holds every kind of tile, so that the compiler meets one
 // set of register constraints; the mode operand chooses:
 //   1  a run of tiles, the NEXT tile of each wholly in the prefix (its rows come from the pool through slot ids)
 //   2  a run of tiles, the next tile wholly in the extend tokens
@@ -524,9 +551,10 @@ HEADER = '''// GENERATED by gen_fast_run.py - do not edit.  Tiles of extend_bf16
 
 def main():
     here = os.path.dirname(os.path.abspath(__file__))
-    text = (HEADER + emit("fast_tiles_d128", 4) +
-            emit("fast_tiles_d128_kv8", 4, ["pool8", "ext", "plain", "masked"], no_barrier=("plain", "masked")))
-    path = os.path.join(here, "fast_run_d128.inc")
+    text = (HEADER + emit("fast_tiles_d128", 128) +
+            emit("fast_tiles_d128_kv8", 128, ["pool8", "ext", "plain", "masked"], no_barrier=("plain", "masked")) +
+            emit("fast_tiles_d64", 64, ["pool", "ext", "plain", "masked"]))
+    path = os.path.join(here, "fast_run.inc")
     old = open(path).read() if os.path.exists(path) else None
     if old != text:
         open(path, "w").write(text)
