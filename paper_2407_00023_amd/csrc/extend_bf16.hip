@@ -145,6 +145,28 @@ __device__ __forceinline__ unsigned lds_address(const void* p) {
     return static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const unsigned char*)(p)));
 }
 
+// The K fragments of a block of 32 keys, all asked for before the first product, so that their LDS round trips overlap
+// instead of following one another (the compiler, short of registers, reads one fragment at a time into the same four
+// registers).  The wait stands in the same statement: no register of a read in flight is ever the compiler's to use.
+template <int KS>
+__device__ __forceinline__ void read_k_block(bf16x8 (&kf)[KS], const unsigned (&at)[KS], unsigned off) {
+    static_assert(KS == 8 || KS == 4, "head dimension 128 or 64");
+    if constexpr (KS == 8)
+        asm volatile(
+            "ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+            "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\ts_waitcnt lgkmcnt(0)"
+            : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3]), "=&v"(kf[4]), "=&v"(kf[5]), "=&v"(kf[6]), "=&v"(kf[7])
+            : "v"(at[0] + off), "v"(at[1] + off), "v"(at[2] + off), "v"(at[3] + off), "v"(at[4] + off), "v"(at[5] + off),
+              "v"(at[6] + off), "v"(at[7] + off)
+            : "memory");
+    else
+        asm volatile(
+            "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+            : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3])
+            : "v"(at[0] + off), "v"(at[1] + off), "v"(at[2] + off), "v"(at[3] + off)
+            : "memory");
+}
+
 // LDS behind the K/V ring: the table of a shared tile's members (two ints each, one int more), two ints per wave, and, from
 // kLdsMl on, what the waves of a narrow tile leave for one another.
 constexpr int kLdsMl = ((2 * kTileRows + 1 + 2 * 4) * 4 + 15) & ~15;
@@ -469,18 +491,9 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         const unsigned off = static_cast<unsigned>(mb) * (32 * ROWB);
         const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         f32x16 sacc;
-        // S^T = K Q^T: all fragments of the block are asked for before
-        // the first product, so that their LDS round trips overlap instead of following one another.
-        // (Written as assembly: the compiler, short of registers, otherwise reads one fragment at a time into the same four
-        // registers, eight LDS round trips in a row.  Nothing else of this wave's is in flight on the LDS counter here:
-        // the compiler's own LDS reads are awaited before they are used, and one wait for all eight follows.)
+        // S^T = K Q^T
         bf16x8 kf[KS];
-#pragma unroll
-        for (int s = 0; s < KS; ++s) asm volatile("ds_read_b128 %0, %1" : "=v"(kf[s]) : "v"(k_rd[s] + off));
-        if constexpr (KS == 8)
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]), "+v"(kf[4]), "+v"(kf[5]), "+v"(kf[6]), "+v"(kf[7]));
-        else
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]));
+        read_k_block<KS>(kf, k_rd, off);
 #pragma unroll
         for (int s = 0; s < KS; ++s) sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qreg[s], s == 0 ? zero16 : sacc, 0, 0, 0);
         const int pb0 = p0 + 32 * mb;
@@ -788,12 +801,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         if ((fast_ok || KV8) && (smem_addr & 255u) == 0 && wave_on && kv_lo <= P + wave_i_last && kv_lo + 32 <= blk_vis_min && kv_lo + 32 <= kv_hi) {
             const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             bf16x8 kf[KS];
-#pragma unroll
-            for (int s = 0; s < KS; ++s) asm volatile("ds_read_b128 %0, %1" : "=v"(kf[s]) : "v"(k_rd[s]));
-            if constexpr (KS == 8)
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]), "+v"(kf[4]), "+v"(kf[5]), "+v"(kf[6]), "+v"(kf[7]));
-            else
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]));
+            read_k_block<KS>(kf, k_rd, 0);
             f32x16 sacc = zero16;
 #pragma unroll
             for (int s = 0; s < KS; ++s) sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qreg[s], sacc, 0, 0, 0);
