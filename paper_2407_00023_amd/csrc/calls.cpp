@@ -84,6 +84,12 @@ bool stream_of(PyObject* o, void** out) {
     return !PyErr_Occurred();
 }
 
+// The interpreter's lock is given up while the library launches (other threads run on while a launch waits for a full queue).
+struct WithoutGil {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~WithoutGil() { PyEval_RestoreThread(state); }
+};
+
 PyObject* raise_code(int rc, const char* where) {
     PyObject* e = PyObject_CallFunction(g_error_class, "is", rc, where);
     if (e) {
@@ -163,9 +169,13 @@ PyObject* match_prefixes(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyO
     }
     void* stream = nullptr;
     if (!stream_of(a[5], &stream)) return nullptr;
-    const int rc = pa_match_prefixes(tree, static_cast<const int32_t*>(tokens->const_data_ptr()),
-                                     static_cast<const int32_t*>(offsets->const_data_ptr()), static_cast<int>(B),
-                                     static_cast<int32_t*>(len->data_ptr()), static_cast<int32_t*>(slots->data_ptr()), stream);
+    int rc = PA_OK;
+    {
+        const WithoutGil released;
+        rc = pa_match_prefixes(tree, static_cast<const int32_t*>(tokens->const_data_ptr()),
+                               static_cast<const int32_t*>(offsets->const_data_ptr()), static_cast<int>(B),
+                               static_cast<int32_t*>(len->data_ptr()), static_cast<int32_t*>(slots->data_ptr()), stream);
+    }
     if (rc != PA_OK) return raise_code(rc, "pa_match_prefixes");
     PyObject* l = a[3] ? Py_NewRef(a[3]) : THPVariable_Wrap(made_len);
     PyObject* s = a[4] ? Py_NewRef(a[4]) : THPVariable_Wrap(made_slots);
@@ -238,10 +248,14 @@ PyObject* extend_attention(PyObject*, PyObject* const* args, Py_ssize_t nargs, P
     void* stream = nullptr;
     if (!stream_of(a[15], &stream)) return nullptr;
     auto i32 = [&](int i) { return static_cast<const int32_t*>(t[i]->const_data_ptr()); };
-    const int rc = pa_extend_attention(q.const_data_ptr(), k.const_data_ptr(), v.const_data_ptr(), pool.const_data_ptr(), i32(4),
-                                       i32(5), i32(6), i32(7), i32(8), static_cast<int>(B), T, max_kv_len, Hq, Hkv, D,
-                                       static_cast<int>(page_size), num_slots, dtype, static_cast<float>(scale),
-                                       out->data_ptr(), ws->data_ptr(), ws->nbytes(), stream);
+    int rc = PA_OK;
+    {
+        const WithoutGil released;
+        rc = pa_extend_attention(q.const_data_ptr(), k.const_data_ptr(), v.const_data_ptr(), pool.const_data_ptr(), i32(4),
+                                 i32(5), i32(6), i32(7), i32(8), static_cast<int>(B), T, max_kv_len, Hq, Hkv, D,
+                                 static_cast<int>(page_size), num_slots, dtype, static_cast<float>(scale),
+                                 out->data_ptr(), ws->data_ptr(), ws->nbytes(), stream);
+    }
     if (rc != PA_OK) return raise_code(rc, "pa_extend_attention");
     return a[13] ? Py_NewRef(a[13]) : THPVariable_Wrap(made_out);
     CALLS_CATCH
@@ -273,8 +287,12 @@ PyObject* append_kv(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObject
     if (!pool_large_enough(pool, num_slots, Hkv, D, dtype, page_size)) return nullptr;
     void* stream = nullptr;
     if (!stream_of(a[6], &stream)) return nullptr;
-    const int rc = pa_append_kv(pool.data_ptr(), static_cast<const int32_t*>(slots.const_data_ptr()), k.const_data_ptr(),
-                                v.const_data_ptr(), k.size(0), Hkv, D, static_cast<int>(page_size), num_slots, dtype, stream);
+    int rc = PA_OK;
+    {
+        const WithoutGil released;
+        rc = pa_append_kv(pool.data_ptr(), static_cast<const int32_t*>(slots.const_data_ptr()), k.const_data_ptr(),
+                          v.const_data_ptr(), k.size(0), Hkv, D, static_cast<int>(page_size), num_slots, dtype, stream);
+    }
     if (rc != PA_OK) return raise_code(rc, "pa_append_kv");
     Py_RETURN_NONE;
     CALLS_CATCH
