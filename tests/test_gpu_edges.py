@@ -1,0 +1,202 @@
+"""Parity at the edges of the kernels' tiles, walks and dispatch rules, against the CPU oracle.
+
+Bars: prefix lengths and slots bit-exact; extend attention within max-abs 1e-4 (fp32 sums of at most some hundred values of
+order one) and 2e-2 (bf16 probabilities and results: half a unit in the last place is 2^-9 of a value, values of up to 5)."""
+import threading
+
+import numpy as np
+import pytest
+import torch
+
+from harness import out_to_f64, to_torch
+from paper_2407_00023_amd import workloads as W
+
+TOL = {"f32": 1e-4, "bf16": 2e-2, "bf16_kv8": 2e-2}
+
+
+@pytest.fixture(scope="module")
+def pa(gpu_device):
+    from paper_2407_00023_amd import binding
+    return binding
+
+
+def _path(rng, edges, vocab=1000):
+    """A cached trunk cut into nodes with these edge lengths, by a sequence that leaves it at every cut."""
+    trunk = rng.integers(0, vocab, sum(edges)).astype(np.int32)
+    cached = [(trunk, np.arange(len(trunk), dtype=np.int32))]
+    for i, c in enumerate(np.cumsum(edges)[:-1]):
+        cached.append((np.append(trunk[:c], (trunk[c] + 1) % vocab).astype(np.int32),
+                       np.append(np.arange(c), 100000 + i).astype(np.int32)))
+    return trunk, cached
+
+
+# B = 3: several workgroups a request; 300: one.  Paths around the walk's limits: 4 nodes whatever their length, 16 while they
+# hold 128 tokens on average; swept by one workgroup up to 4,096 tokens, by several beyond
+@pytest.mark.gpu
+@pytest.mark.parametrize("B", [3, 300])
+@pytest.mark.parametrize("edges", [[1], [1, 1, 1], [1, 1, 1, 1], [2, 1, 3, 1, 5], [127] * 5, [128] * 5, [128] * 15, [128] * 16,
+                                   [200] * 17, [1023, 1, 1, 1021], [4096], [4097], [3000, 1500, 700], [2048] * 6, [1, 1, 1, 1, 9000],
+                                   [700] * 4 + [3] * 500],
+                         ids=lambda e: f"{len(e)}x{e[0]}")
+def test_match_at_the_limits_of_walk_sweep_and_window(pa, gpu_device, edges, B):
+    import oracle
+    rng = np.random.default_rng(len(edges) + edges[0])
+    trunk, cached = _path(rng, edges)
+    n, cuts = len(trunk), np.cumsum(edges)
+    prompts = [np.zeros(0, np.int32), trunk, np.append(trunk, np.int32(7))]
+    # ends and mismatches at the first and last token of edges, and around multiples of a wave, a sweep and a window
+    at = {0, 1, n // 2, n - 1} | {int(c) + d for c in (cuts[0], cuts[-1] - edges[-1], cuts[len(cuts) // 2]) for d in (-1, 0, 1)}
+    at |= {k + d for k in (64, 512, 1024, 2048, 4096) for d in (-1, 0)}
+    for c in sorted(x for x in at if 0 <= x < n):
+        wrong = trunk.copy()
+        wrong[c] = (wrong[c] + 500) % 1000
+        prompts += [trunk[:c], wrong]
+    prompts = (prompts * B)[:B] if B > len(prompts) else prompts
+    if B == 3:
+        assert len(prompts) <= 64
+    toks = np.concatenate(prompts).astype(np.int32)
+    off = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
+    pl_ref, si_ref = oracle.match_prefixes(cached, toks, off)
+    tree = pa.Tree()
+    for c in cached:
+        tree.insert(*c)
+    tree.upload()
+    print(f"[case] match path {edges[:4]}... B {len(prompts)}", flush=True)
+    pl, si = pa.match_prefixes(tree, torch.from_numpy(toks).to(gpu_device), torch.from_numpy(off).to(gpu_device))
+    pl, si = pl.cpu().numpy(), si.cpu().numpy()
+    np.testing.assert_array_equal(pl, pl_ref)
+    for r in range(len(prompts)):
+        np.testing.assert_array_equal(si[off[r]:off[r] + pl_ref[r]], si_ref[off[r]:off[r] + pl_ref[r]])
+
+
+def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0):
+    """Largest error against the oracle for requests with P[r] cached tokens, the first `common` of them the same for all."""
+    import oracle
+    rng = np.random.default_rng(seed)
+    P, E = np.asarray(P, np.int32), np.asarray(E, np.int32)
+    B, el = len(P), "f32" if dtype == "f32" else "bf16"
+    npages = -(-common // page) + sum(-(-int(p - common) // page) for p in P)
+    nslots = (npages + 3) * page
+    order, cur = rng.permutation(npages + 3), 0
+
+    def take(n):
+        nonlocal cur
+        k = -(-n // page)
+        pages, cur = order[cur:cur + k], cur + k
+        return (pages[:, None] * page + np.arange(page)).reshape(-1)[:n].astype(np.int32)
+
+    head = take(common)
+    slots = [np.concatenate([head, take(int(p) - common)]) for p in P]
+    off = np.concatenate([[0], np.cumsum(P + E)]).astype(np.int32)
+    eo = np.concatenate([[0], np.cumsum(E)]).astype(np.int32)
+    si = np.full(off[-1], -1, np.int32)
+    for r in range(B):
+        si[off[r]:off[r] + P[r]] = slots[r]
+    backed = np.unique(np.concatenate(slots))
+    ss = np.random.SeedSequence(seed + 17).spawn(5)
+    mk = lambda s, n, h: W._normal(s, n * h * D, el).reshape(n, h, D)
+    T = int(eo[-1])
+    q, k, v, pk, pv = mk(ss[0], T, Hq), mk(ss[1], T, Hkv), mk(ss[2], T, Hkv), mk(ss[3], len(backed), Hkv), mk(ss[4], len(backed), Hkv)
+    tdt, kv8 = (torch.float32 if dtype == "f32" else torch.bfloat16), dtype == "bf16_kv8"
+    kw = dict(page_size=page, num_slots=nslots, kv8=kv8)
+    pool = torch.zeros(pa.kv_pool_bytes(nslots, Hkv, D, tdt, page, kv8), dtype=torch.uint8, device=dev)
+    tt = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    pa.append_kv(pool, tt(backed), to_torch(pk, el, dev), to_torch(pv, el, dev), **kw)
+    print(f"[case] extend {dtype} P {P[:6]} E {E[:6]} Hq {Hq} Hkv {Hkv} D {D} page {page} common {common}", flush=True)
+    ws = torch.zeros(pa.extend_workspace_bytes(B, T, int((P + E).max()), Hq, Hkv, D, tdt), dtype=torch.uint8, device=dev)
+    out = pa.extend_attention(to_torch(q, el, dev), to_torch(k, el, dev), to_torch(v, el, dev), pool, tt(si), tt(off), tt(P), tt(E),
+                              tt(eo), D ** -0.5, max_kv_len=int((P + E).max()), workspace=ws, **kw)
+    torch.cuda.synchronize()
+    if dtype != "f32":
+        assert ws[12:16].view(torch.int32).item() == 0  # (the work list fitted)
+    opk, opv = oracle.new_pool(nslots, Hkv, D, dtype)
+    oracle.append_kv(opk, opv, backed, pk, pv, dtype)
+    ref = oracle.extend_attention(q, k, v, opk, opv, si, off, P, E, eo, D ** -0.5, dtype)
+    return np.abs(out_to_f64(out) - ref).max()
+
+
+# lanes of a key (D / 4), keys of a round (four each), heads of a KV head
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hq,Hkv,D", [(4, 2, 64), (1, 1, 64), (8, 1, 64), (6, 2, 128), (3, 1, 128), (16, 2, 128)])
+def test_f32_extend_around_its_key_rounds(pa, gpu_device, Hq, Hkv, D):
+    err = _extend(pa, gpu_device, "f32", [0, 1, 3, 4, 5, 7, 8, 15, 16, 17, 31, 33, 63, 65, 97], [1, 1, 2, 1, 3, 9, 1, 2, 1, 5, 1, 4, 1, 17, 1],
+                  Hq, Hkv, D, 1)
+    assert err <= TOL["f32"], err
+
+
+# rows around the 32 of a narrow tile and the 128 of a wide one, keys around a block of 32 and a round of the four waves
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_kv8"])
+@pytest.mark.parametrize("D,page", [(128, 16), (64, 1), (64, 64)])
+@pytest.mark.parametrize("E,G", [(1, 1), (31, 1), (33, 1), (8, 4), (9, 4), (4, 8), (16, 8), (17, 8)])
+def test_extend_around_the_narrow_and_wide_tile(pa, gpu_device, dtype, D, page, E, G):
+    P = [0, 1, 31, 32, 33, 63, 64, 127, 128, 129, 300, 1100]
+    assert _extend(pa, gpu_device, dtype, P, [E] * len(P), 2 * G, 2, D, page) <= TOL[dtype]
+
+
+# runs of tiles in assembly for heads of 64: ends of the prefix and of the new tokens around whole tiles, extends past the
+# diagonal of several row tiles, key ranges cut into parts
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_kv8"])
+@pytest.mark.parametrize("page", [1, 16, 24])
+@pytest.mark.parametrize("P,E", [([0], [513]), ([64, 63, 65], [129, 200, 64]), ([640, 127], [70, 300]), ([2100], [40])])
+def test_extend_heads_of_64_around_whole_tiles(pa, gpu_device, dtype, page, P, E):
+    assert _extend(pa, gpu_device, dtype, P, E, 8, 2, 64, page) <= TOL[dtype]
+
+
+# common first parts that end around the planner's probes (512, 1,024, 1,536) and between them; own keys from none to tiles
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("common", [511, 512, 513, 700, 1023, 1024, 1025, 1537])
+@pytest.mark.parametrize("own", [1, 3, 65])
+def test_extend_common_first_parts_around_the_probes(pa, gpu_device, D, common, own):
+    P = [common + own * (r % 3) + r // 3 for r in range(9)]
+    assert _extend(pa, gpu_device, "bf16", P, [1 + r % 2 for r in range(9)], 8, 2, D, 16, common=common) <= TOL["bf16"]
+
+
+# the largest batches of each planner (256: with sharing, 1,024: ordered, beyond: as given) and the smallest that are beyond
+@pytest.mark.gpu
+@pytest.mark.parametrize("B", [1, 2, 63, 64, 255, 256, 257, 1024, 1025])
+def test_extend_batch_sizes_around_the_planners(pa, gpu_device, B):
+    P = [600 + r % 7 for r in range(B)]
+    assert _extend(pa, gpu_device, "bf16", P, [1 + r % 2 for r in range(B)], 4, 1, 64, 16, common=600) <= TOL["bf16"]
+
+
+@pytest.mark.gpu
+def test_hot_path_calls_from_several_threads(pa, gpu_device):
+    """Threads with a stream each make the three calls at once, on tensors of their own."""
+    errs, lock = [], threading.Lock()
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for k in range(3):
+                e = _extend(pa, gpu_device, "bf16", [600 + i, 40], [1 + k, 70], 8, 2, 128, 16, seed=10 * i + k)
+                with lock:
+                    errs.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert len(errs) == 12 and max(errs) <= TOL["bf16"], errs
+
+
+def test_hot_path_calls_refuse_what_is_no_device_tensor():
+    """Checks that need no GPU: wrong kinds of arguments are refused before anything reaches the device."""
+    from paper_2407_00023_amd import binding
+    i32 = torch.zeros(2, dtype=torch.int32)
+    x = torch.zeros(1, 2, 64)
+    tree = binding.Tree()
+    with pytest.raises(TypeError):
+        binding.match_prefixes(tree, i32, i32)                       # tensors of the host
+    with pytest.raises(TypeError):
+        binding.match_prefixes(tree, i32)                            # an argument missing
+    with pytest.raises(TypeError):
+        binding.match_prefixes(tree, i32, i32, nonsense=1)
+    with pytest.raises(TypeError):
+        binding.append_kv(x, i32[:1], x, x, page_size=1, num_slots=1)
+    with pytest.raises(TypeError):
+        binding.append_kv(x, i32[:1], x, x, num_slots=1)             # page_size is required
+    with pytest.raises(TypeError):
+        binding.extend_attention(x, x, x, x, i32, i32, i32, i32, i32, 1.0, page_size=1, num_slots=1, max_kv_len=1)
