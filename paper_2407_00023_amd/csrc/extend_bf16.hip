@@ -27,9 +27,10 @@
 // row-major V tile with the transposing LDS read of gfx950.
 //
 // Two kinds of tile.  The general tile (general_block below) takes any mix of pool and extend rows, masks and
-// ragged ends, and moves the running maximum; it runs for the first tile of a workgroup, where prefix and extend
-// tokens meet, and on the causal diagonal.  Runs of consecutive tiles that need no mask execute as one
-// assembly statement each (fast_run.inc, written by gen_fast_run.py) with the running maximum frozen.
+// ragged ends, and moves the running maximum; it runs where nothing else applies (heads of 64 on the fp8 pool, pages
+// that are no power of two, the extend tokens in shared tiles, a tile that outgrew the frozen maximum, a first tile too short
+// to seed one).  The rest executes in one assembly statement (fast_run.inc, written by gen_fast_run.py) with the running
+// maximum frozen: runs of consecutive unmasked tiles, and single tiles, plain or on the causal diagonal.
 #include <hip/hip_bf16.h>
 
 #include <atomic>
@@ -54,7 +55,7 @@ typedef __bf16 bf16x32 __attribute__((ext_vector_type(32)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-// fast_run_pool_d128 / fast_run_ext_d128: runs of steady-state tiles as assembly with fixed registers
+// the tiles as assembly with fixed registers, for heads of 128 and of 64
 #include "fast_run.inc"
 
 constexpr int kStages = 2;               // LDS ring: one tile being read, one being filled
@@ -485,8 +486,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
 
     // ---- One block of 32 keys of the current tile, general: masks, any running maximum.  Kept small in registers
     // (one score block alive, no overlap of its phases inside the wave; the other wave of the SIMD fills the gaps):
-    // it runs for the first tile, the tile where prefix and extend tokens meet, the tiles on the causal diagonal, and
-    // wherever the hand-scheduled tile does not apply.  mb = 0 / 1: first / second block of the tile.
+    // it runs wherever the assembly tiles do not apply.  mb = 0 / 1: first / second block of the tile.
     auto general_block = [&](int p0, int mb, bool need_mask) __attribute__((always_inline)) {
         const unsigned off = static_cast<unsigned>(mb) * (32 * ROWB);
         const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
