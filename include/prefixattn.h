@@ -257,10 +257,13 @@ int pa_history_gpu_load(pa_history* h, int32_t gpu, int64_t now, double* L, doub
 size_t pa_kv_pool_bytes(int64_t num_slots, int Hkv, int D, int dtype, int page_size);
 
 /* Bytes of device workspace pa_extend_attention needs for any batch with at most B
- * requests, T extend tokens in total and prefix_len[r] + ext_len[r] <= max_kv_len.
- * It holds the work list of the launch and the partial results of row tiles whose key range is
- * split over several workgroups; with bf16 at serving sizes the bound on the latter dominates
- * (about 135 MB for 8 KV heads of 128: 2 x 2 parts per workgroup slot, each 128 rows of fp32).
+ * requests, T extend tokens in total and prefix_len[r] + ext_len[r] <= max_kv_len: it never falls
+ * when one of the three grows, so one workspace sized for the largest batch serves all smaller ones.
+ * It holds the work list of the launch and the partial results (fp32 rows) of what is computed in
+ * parts: rows of tiles whose key range is split over several workgroups (bf16, 8 KV heads of 128:
+ * up to 137 MB) and, twice, rows of requests of few new tokens that may share the first part of their
+ * prefixes (8.3 KB per row of a KV head there, at most 256 requests).  A workspace below this size
+ * that has room for the former is accepted too: such rows are then not shared.
  * Returns 0 for invalid arguments. */
 size_t pa_extend_workspace_bytes(int B, int64_t T, int64_t max_kv_len, int Hq, int Hkv, int D, int dtype);
 

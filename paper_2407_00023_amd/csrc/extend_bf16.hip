@@ -1101,8 +1101,13 @@ extern "C" int pa_extend_status(const void* workspace, void* stream) {
     return PA_OK;
 }
 
+// What the largest plan of up to B requests takes: a plan of more requests than the planner looks through for common prefixes
+// can be smaller than one of fewer, and a workspace is good for both.
 size_t pa_extend_workspace_bytes_bf16(int B, int64_t T, int64_t max_kv_len, int Hq, int Hkv, int D) {
-    return pa::make_extend_plan(B, T, max_kv_len, Hq, Hkv, D, pa::kRounds, 0).total;
+    const size_t all = pa::make_extend_plan(B, T, max_kv_len, Hq, Hkv, D, pa::kRounds, 0).total;
+    if (B <= pa::kPackMax) return all;
+    const size_t packed = pa::make_extend_plan(pa::kPackMax, T, max_kv_len, Hq, Hkv, D, pa::kRounds, 0).total;
+    return packed > all ? packed : all;
 }
 
 // The work of a bf16 call once its plan and its workspace are settled.
@@ -1138,9 +1143,11 @@ int pa_extend_attention_bf16(const void* q_ext, const void* k_ext, const void* v
                              void* workspace, size_t workspace_bytes, hipStream_t stream) {
     using namespace pa;
     if (const int rc = check_bf16_args(scale, num_slots, page_size, Hkv, D)) return rc;
-    const ExtendPlan p = make_extend_plan(B, T, max_kv_len, Hq, Hkv, D, kRounds, 0);  // (sized for shared row tiles whether or not they are on)
+    // (sized for shared row tiles whether or not they are on; a smaller workspace that does for a plan without grouping by
+    // common first parts gets that one)
+    const ExtendPlan p = make_extend_plan(B, T, max_kv_len, Hq, Hkv, D, kRounds, workspace_bytes);
     if (workspace_bytes < p.total || workspace == nullptr)
-        return fail(PA_ENOMEM, "pa_extend_attention: workspace of %zu bytes given, %zu needed", workspace_bytes, p.total);
+        return fail(PA_ENOMEM, "pa_extend_attention: workspace of %zu bytes given, at least %zu needed", workspace_bytes, p.total);
     PA_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & 255u) == 0, "pa_extend_attention: workspace must be 256-byte aligned");
     return run_extend_bf16(p, q_ext, k_ext, v_ext, kv_pool, slot_idx, slot_offsets, prefix_len, ext_len, ext_offsets, B, T, Hq,
                            Hkv, D, page_size, num_slots, kv8, scale, out, workspace, stream);

@@ -9,6 +9,7 @@ namespace pa {
 constexpr int kKT = 64;          // key tokens per tile
 constexpr int kTileRows = 128;   // packed query rows of a wide row tile (four waves, 32 rows each, every wave all keys)
 constexpr int kNarrowRows = 32;  // ... of a narrow one (four waves, the same rows each, every wave a quarter of the keys)
+constexpr int kPackMax = 256;    // batches of up to this many requests are looked through for common prefixes
 
 struct ExtendPlan {
     int tiles_cap;   // upper bound on the number of row tiles

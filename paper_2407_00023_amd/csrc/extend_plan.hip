@@ -39,7 +39,6 @@ constexpr int kMinChunkCommon = 8;       // ... unless the tile leaves partial r
 constexpr int kMinChunkNarrow = 4;       // ... or is narrow: 64 keys for each of its waves
 constexpr int kItemOverhead = 4;         // fixed cost of a work item, in key tiles (its prologue and epilogue)
 constexpr int kMaxParts = 64;            // parts of one tile at most
-constexpr int kPackMax = 256;            // batches of up to this many requests are looked through for common prefixes
 constexpr int kSortMax = 1024;           // ... and up to this many are ordered
 constexpr int kPackMinPrefix = 512;      // prefixes, or first parts of them, are shared from this many keys on ...
 constexpr int kPackOwnCost = 2;          // ... and, whole ones, if the members' own keys, which a shared tile walks in the general
@@ -77,16 +76,23 @@ ExtendPlan make_extend_plan(int B, int64_t T, int64_t max_kv_len, int Hq, int Hk
         const int64_t more = by_rule < by_size ? by_rule : by_size;
         p.items_cap = static_cast<int>(p.tiles_cap + p.own_cap + more);
         const int64_t split_parts = 2 * by_rule < by_size ? 2 * by_rule : by_size;
-        p.prows_cap = static_cast<int>(split_parts * kTileRows + 2 * fp_rows);
+        // Rows of partial results, the smallest of three bounds: every part of a split tile full (n <= 2 (n - 1) for n >= 2
+        // parts) and the rows of common first parts twice; each row once, those of common first parts twice, and 128 rows
+        // more for every part beyond a tile's first; each of these rows in as many parts as a tile may have.
+        const int64_t once = rows + fp_rows;
+        int64_t prows = split_parts * kTileRows + 2 * fp_rows;
+        prows = by_rule * kTileRows + once < prows ? by_rule * kTileRows + once : prows;
+        prows = p.tile_parts * once < prows ? p.tile_parts * once : prows;
+        p.prows_cap = static_cast<int>(prows);
         p.chunks_cap = static_cast<int>((split_parts / 2 + 1) * (kTileRows / p.chunk_rows) + fp_rows / p.chunk_rows + 2 * p.own_cap);
         p.off_tile = 256;
         p.off_member = p.off_tile + up256(sizeof(int2) * (static_cast<size_t>(p.tiles_cap) + p.own_cap));
         p.off_item = p.off_member + up256(p.pack ? sizeof(int4) * 2 * (B > 0 ? B : 1) : 0);
         p.off_chunk = p.off_item + up256(sizeof(int4) * 3 * p.items_cap);
         p.off_part_o = p.off_chunk + up256(sizeof(int4) * 3 * p.chunks_cap);
-        const size_t prows = static_cast<size_t>(p.prows_cap) * Hkv;
-        p.off_part_ml = p.off_part_o + up256(prows * D * sizeof(float));
-        p.total = p.off_part_ml + up256(prows * 2 * sizeof(float));
+        const size_t head_rows = static_cast<size_t>(p.prows_cap) * Hkv;
+        p.off_part_ml = p.off_part_o + up256(head_rows * D * sizeof(float));
+        p.total = p.off_part_ml + up256(head_rows * 2 * sizeof(float));
         if (!p.first_part || limit == 0 || p.total <= limit) break;
     }
     return p;

@@ -125,3 +125,31 @@ def lib_ws(lib, B, T, kv, Hq, Hkv, D, dtype):
     lib.pa_extend_workspace_bytes.restype = C.c_size_t
     lib.pa_extend_workspace_bytes.argtypes = [C.c_int, C.c_int64, C.c_int64, C.c_int, C.c_int, C.c_int, C.c_int]
     return lib.pa_extend_workspace_bytes(B, T, kv, Hq, Hkv, D, dtype)
+
+
+def _extend_rc(lib, B, T, kv, Hq, Hkv, D, ws_bytes):
+    """pa_extend_attention's answer to host sizes alone.  The workspace pointer is misaligned, which is looked at after the
+    sizes: -2 = too small, -1 = large enough (and refused for its alignment, before anything touches a device)."""
+    vp, i, i64 = C.c_void_p, C.c_int, C.c_int64
+    lib.pa_extend_attention.argtypes = [vp] * 9 + [i, i64, i64, i, i, i, i, i64, i, C.c_float, vp, vp, C.c_size_t, vp]
+    p = [4096 * k for k in range(1, 12)]
+    return lib.pa_extend_attention(*p[:9], B, T, kv, Hq, Hkv, D, 16, 65536, 1, 1.0, p[9], p[10] + 16, ws_bytes, None)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (64, 8, 64), (8, 1, 128), (4, 4, 64)])
+def test_a_workspace_is_good_for_every_smaller_batch(pa, Hq, Hkv, D):
+    """The size grows with the number of requests, tokens and keys, also across 256 requests, where batches are no longer
+    looked through for common prefixes; a workspace sized for a batch is accepted for any smaller one."""
+    lib = C.CDLL(pa.LIB_PATH)
+    Bs = [1, 2, 64, 255, 256, 257, 300, 1024, 1025]
+    for per, kv in [(1, 64), (1, 2048), (8, 600), (64, 600), (300, 8192)]:
+        size = {B: lib_ws(lib, B, 300 * per, kv, Hq, Hkv, D, 1) for B in Bs}
+        assert [size[B] for B in Bs] == sorted(size.values())
+        for B in Bs[1:]:
+            have = lib_ws(lib, B, B * per, kv, Hq, Hkv, D, 1)
+            assert have <= lib_ws(lib, B, B * per + 1, kv, Hq, Hkv, D, 1) and have <= lib_ws(lib, B, B * per, kv + 64, Hq, Hkv, D, 1)
+            for b in [x for x in Bs if x <= B]:
+                assert _extend_rc(lib, b, b * per, kv, Hq, Hkv, D, have) == -1, (B, b, per, kv)
+    # no room for the partial results of common first parts: the plan does without them; no room for any plan: refused
+    assert _extend_rc(lib, 256, 256, 4096, Hq, Hkv, D, lib_ws(lib, 256, 256, 4096, Hq, Hkv, D, 1) - 1) == -1
+    assert _extend_rc(lib, 256, 256, 4096, Hq, Hkv, D, 4096) == -2
