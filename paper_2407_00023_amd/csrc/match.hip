@@ -91,8 +91,9 @@ constexpr int kSplitSweep = 4096; // a walked path longer than this is compared 
 // names, and where the walk would stand after it.  The workgroup that finishes last (a counter per request) joins the
 // summaries in order - a window's chain is accepted if it begins exactly where the walk stands and names the walk's node as
 // parent: the same exact link as inside a window - and walks on alone from where the chain of accepted windows ends.  Nobody
-// waits for anybody.  Slot ids that a window writes before it is accepted are those of nodes whose whole path hashes like
-// the prompt, confirmed token by token along their edges; the last workgroup's own writes come after all of them.
+// waits for anybody.  Slot ids that a window writes before it is accepted are those of a chain of linked nodes, confirmed
+// token by token, behind a first node whose path hashes like the prompt; where that node proves to be none of the path, the
+// last workgroup writes what the chain has written, and all that lies behind it, again: its writes come after all others.
 constexpr int kMaxW = 16;        // workgroups per request at most; a longer path's rest is walked by the last one
 constexpr int kMultiMaxB = 256;  // batches of up to this many requests take this form
 constexpr int kMultiWgs = 1024;  // ... with up to this many workgroups (four on a compute unit)
@@ -167,8 +168,9 @@ __global__ __launch_bounds__(kT, kMulti ? 4 : 8) void match_prefixes_kernel(Devi
     auto put_slot = [&](int32_t p, int32_t v, bool through) __attribute__((always_inline)) {
         // Slot ids written by a lone window go straight through to memory (stores of device scope leave no dirty line in
         // this XCD's L2), so that waiting for them to be acknowledged is all it takes for the last workgroup's own writes to
-        // come after them; a fence of device scope would write the whole L2 back and costs 100 us and more here.  (What the
-        // walk from the root writes is exact whenever it is written and needs no such care.)
+        // come after them; a fence of device scope would write the whole L2 back and costs 100 us and more here.  (The walk
+        // from the root writes the slots of nodes that are linked to it, up to where they differ from the prompt: final
+        // ones, or past the end of the match.)
         if (kMulti && through) __hip_atomic_store(out_slots + p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         else out_slots[p] = v;
     };
@@ -520,13 +522,16 @@ __global__ __launch_bounds__(kT, kMulti ? 4 : 8) void match_prefixes_kernel(Devi
             if (lane == 0) s_red2[red_round & 1][wave] = brk;
         }
         lds_barrier();
-        // ---- D. every position against the edge of its node; slots of what an edge covers ----
+        // ---- D. every position against the edge of its node; slots of what the chain holds.  (Not before it is known how far
+        // the chain goes: the edge of a node nominated by a colliding hash may reach over positions of other windows, whose
+        // workgroups write the right slots meanwhile.) ----
         const int32_t lim_end = min(kWinP, n - w0);
         int32_t bad = INT32_MAX;
         int32_t head = -1;  // first nominated position
+        int32_t sl[kPos];
+        unsigned in = 0;
         {
-            int32_t et[kPos], pt[kPos], sl[kPos];
-            unsigned in = 0;
+            int32_t et[kPos], pt[kPos];
 #pragma unroll
             for (int i = 0; i < kPos; ++i) {
                 const int rel = i * kT + tid;
@@ -541,13 +546,8 @@ __global__ __launch_bounds__(kT, kMulti ? 4 : 8) void match_prefixes_kernel(Devi
                 pt[i] = prompt[w0 + min(rel, lim_end - 1)];
             }
 #pragma unroll
-            for (int i = 0; i < kPos; ++i) {
-                const int rel = i * kT + tid;
-                if (in >> i & 1) {
-                    put_slot(w0 + rel, sl[i], role == 2);
-                    if (et[i] != pt[i]) bad = min(bad, rel);
-                }
-            }
+            for (int i = 0; i < kPos; ++i)
+                if ((in >> i & 1) && et[i] != pt[i]) bad = min(bad, i * kT + tid);
         }
         const int round = red_round & 1;
         bad = wg_min(bad);
@@ -556,6 +556,9 @@ __global__ __launch_bounds__(kT, kMulti ? 4 : 8) void match_prefixes_kernel(Devi
         for (int v = 0; v < kWaves; ++v) brk = min(brk, s_red2[round][v]);
         // ---- E. where the walk stands after this window (the same in every thread) ----
         const int32_t end = min(min(bad, brk), lim_end);
+#pragma unroll
+        for (int i = 0; i < kPos; ++i)
+            if ((in >> i & 1) && i * kT + tid < end) put_slot(w0 + i * kT + tid, sl[i], role == 2);
         if (role == 2) {
             // the first nominated position: the first whose last nomination is itself (every thread looks at its share)
             int32_t f = INT32_MAX;
@@ -635,13 +638,16 @@ __global__ __launch_bounds__(kT, kMulti ? 4 : 8) void match_prefixes_kernel(Devi
             last_es = field(ww, 5);
             last_start = field(ww, 6);
         };
-        // A window that is no part of the walk may still have written slot ids below the walk's position: only a chain
-        // that begins with a node nominated by a colliding hash does (no node of the path begins inside an edge).  What
-        // it wrote there is put right from the edge the walk took.
+        // A window that is no part of the walk may still have written slot ids, from its first nominated position on: only a
+        // chain that begins with a node nominated by a colliding hash does (no node of the path begins inside an edge).  What
+        // it wrote below the walk's position is put right from the edge the walk took; what it wrote beyond may lie over a
+        // later window's slots, so no later window is accepted then and the walk goes on by itself, writing all of them.
+        bool stray = false;
         auto repair = [&](int ww) __attribute__((always_inline)) {
-            const int32_t fp = field(ww, 0), ep = field(ww, 2);
-            if (fp >= 0 && fp < pos)
-                for (int32_t k = max(fp, last_start) + tid; k < min(ep, pos); k += kT) out_slots[k] = t.edge_slot[last_es + (k - last_start)];
+            const int32_t fp = field(ww, 0);
+            stray |= fp >= 0;
+            if (fp >= 0)
+                for (int32_t k = max(fp, last_start) + tid; k < pos; k += kT) out_slots[k] = t.edge_slot[last_es + (k - last_start)];
         };
         accept(0);
         int wlast = 0;  // the last window (counted from the one where the first walk stood) whose chain is part of the walk
@@ -650,7 +656,7 @@ __global__ __launch_bounds__(kT, kMulti ? 4 : 8) void match_prefixes_kernel(Devi
             const int ww = max(0, min(pos / kWinP - win0, n_wg));
             for (int x = wlast + 1; x < ww; ++x) repair(x);  // (windows that lie inside the last edge)
             if (ww >= n_wg || ww == wlast) break;
-            if (!done && pos < n && field(ww, 0) == pos && field(ww, 1) == cur && field(ww, 2) > pos) {
+            if (!stray && !done && pos < n && field(ww, 0) == pos && field(ww, 1) == cur && field(ww, 2) > pos) {
                 accept(ww);  // the walk's next node begins this window's chain
                 wlast = ww;
                 continue;

@@ -30,10 +30,11 @@ def _path(rng, edges, vocab=1000):
     return trunk, cached
 
 
-# B = 3: several workgroups a request; 300: one.  Paths around the walk's limits: 4 nodes whatever their length, 16 while they
-# hold 128 tokens on average; swept by one workgroup up to 4,096 tokens, by several beyond
+# None: as many requests as there are prompts below (5 to 49), 16 workgroups each; 65: 15, 256: 4, 257 and 300: one.  Paths around
+# the walk's limits: 4 nodes whatever their length, 16 while they hold 128 tokens on average; swept by one workgroup up to 4,096
+# tokens, by several beyond; in the end windows, more of them than workgroups
 @pytest.mark.gpu
-@pytest.mark.parametrize("B", [3, 300])
+@pytest.mark.parametrize("B", [None, 65, 256, 257, 300])
 @pytest.mark.parametrize("edges", [[1], [1, 1, 1], [1, 1, 1, 1], [2, 1, 3, 1, 5], [127] * 5, [128] * 5, [128] * 15, [128] * 16,
                                    [200] * 17, [1023, 1, 1, 1021], [4096], [4097], [3000, 1500, 700], [2048] * 6, [1, 1, 1, 1, 9000],
                                    [700] * 4 + [3] * 500],
@@ -51,9 +52,7 @@ def test_match_at_the_limits_of_walk_sweep_and_window(pa, gpu_device, edges, B):
         wrong = trunk.copy()
         wrong[c] = (wrong[c] + 500) % 1000
         prompts += [trunk[:c], wrong]
-    prompts = (prompts * B)[:B] if B > len(prompts) else prompts
-    if B == 3:
-        assert len(prompts) <= 64
+    prompts = (prompts * 60)[:B] if B else prompts
     toks = np.concatenate(prompts).astype(np.int32)
     off = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
     pl_ref, si_ref = oracle.match_prefixes(cached, toks, off)
@@ -67,6 +66,80 @@ def test_match_at_the_limits_of_walk_sweep_and_window(pa, gpu_device, edges, B):
     np.testing.assert_array_equal(pl, pl_ref)
     for r in range(len(prompts)):
         np.testing.assert_array_equal(si[off[r]:off[r] + pl_ref[r]], si_ref[off[r]:off[r] + pl_ref[r]])
+
+
+def _same_hash_blocks(n=128):
+    """Two blocks of n tokens whose path hashes are equal behind any common beginning: a Thue-Morse sequence of two token ids and
+    its complement.  The hashes differ by (difference of the ids) x prod_i (base^(2^i) - 1), a multiple of 2^64 for n = 128
+    and ids 2^29 apart; checked here with the library's base."""
+    import os
+    import re
+    src = open(os.path.join(os.path.dirname(W.__file__), "csrc", "common.h")).read()
+    base = int(re.search(r"kPathHashBase = (0x[0-9A-Fa-f]+)", src).group(1), 16)
+    tm = np.array([bin(i).count("1") & 1 for i in range(n)], np.int32)
+    x, y = (tm << 29).astype(np.int32), ((1 - tm) << 29).astype(np.int32)
+    h = [0, 0]
+    for k, block in enumerate((x, y)):
+        for t in block:
+            h[k] = (h[k] * base + int(t) + 1) % 2 ** 64
+    assert h[0] == h[1]
+    return x, y
+
+
+def _insert_cuts(cached, seq, cuts, slot0):
+    """seq cut into nodes at `cuts`, by sequences that leave it there."""
+    cached.append((seq, np.arange(slot0, slot0 + len(seq), dtype=np.int32)))
+    for c in cuts:
+        cached.append((np.append(seq[:c], np.int32(5000 + len(cached))), np.append(np.arange(slot0, slot0 + c), 10 ** 6 + len(cached)).astype(np.int32)))
+
+
+# Two paths with the same hash at some depth.  "same depth": a node begins there on both, a long edge on one, short ones on the
+# other, cut just past the end of the first window, so that the long edge, where it hides the other node in the index, reaches
+# over the next window's nodes.  "inside an edge": on one path the depth lies inside an edge of some windows' length, behind
+# which short edges go on, and the other's node reaches past that edge's end.
+@pytest.mark.gpu
+@pytest.mark.parametrize("B", [2, 65, 256, 257])
+@pytest.mark.parametrize("kind", ["same depth", "inside an edge"])
+@pytest.mark.parametrize("swap", [False, True])
+def test_match_on_paths_with_colliding_hashes(pa, gpu_device, kind, swap, B):
+    import oracle
+    rng = np.random.default_rng(5)
+    x, y = _same_hash_blocks()
+    if swap:
+        x, y = y, x
+    edges = [200] * 4 + [3] * 3 + [12]   # the walk stops at 809, short of the blocks
+    head, tail = rng.integers(0, 4000, sum(edges)).astype(np.int32), rng.integers(0, 4000, 7000).astype(np.int32)
+    at = len(head) + len(x)
+    long_path, cut_path = np.concatenate([head, x, tail]), np.concatenate([head, y, tail])
+    cached = []
+    if kind == "same depth":
+        _insert_cuts(cached, long_path, list(np.cumsum(edges)) + [at], 0)
+        _insert_cuts(cached, cut_path, [at] + list(range(1030, 4000, 50)), 20000)
+    else:
+        _insert_cuts(cached, long_path, list(np.cumsum(edges)) + [at + 300], 0)
+        _insert_cuts(cached, cut_path, list(range(at + 2500, at + 5500, 50)), 20000)
+    prompts = [cut_path, long_path]
+    for cut in (at - 1, at, at + 1, 1024, 1030, 1031, 2048, at + 2499, at + 2500, at + 2600, 4096):
+        for path in (cut_path, long_path):
+            wrong = path.copy()
+            wrong[cut] = 4999
+            prompts += [path[:cut], wrong]
+    prompts = (prompts * 8)[:B]
+    toks = np.concatenate(prompts).astype(np.int32)
+    off = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
+    pl_ref, si_ref = oracle.match_prefixes(cached, toks, off)
+    tree = pa.Tree()
+    for c in cached:
+        tree.insert(*c)
+    tree.upload()
+    print(f"[case] colliding hashes, {kind}, swapped {swap}, B {B}", flush=True)
+    t, o = torch.from_numpy(toks).to(gpu_device), torch.from_numpy(off).to(gpu_device)
+    for _ in range(4):
+        pl, si = pa.match_prefixes(tree, t, o)
+        pl, si = pl.cpu().numpy(), si.cpu().numpy()
+        np.testing.assert_array_equal(pl, pl_ref)
+        for r in range(len(prompts)):
+            np.testing.assert_array_equal(si[off[r]:off[r] + pl_ref[r]], si_ref[off[r]:off[r] + pl_ref[r]])
 
 
 def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0):
