@@ -283,11 +283,14 @@ size_t pa_extend_workspace_bytes(int B, int64_t T, int64_t max_kv_len, int Hq, i
  *                                j for j < prefix_len[r]; entries past that are
  *                                unspecified (never read by pa_extend_attention).
  * The tree must have been uploaded after its last insert (else PA_ESTATE).  B = 0 is a
- * no-op.  Read-only on the tree: concurrent matches on different streams are safe.  (For
- * batches of up to 64 requests, on a tree whose edges hold at most 4,096 tokens on average,
- * a prompt longer than 4,096 tokens is matched by several workgroups, which meet in one of
- * 64 small buffers of the library's own, taken in turn: more than 64 such calls in flight
- * at once on one device are not supported.) */
+ * no-op.  Read-only on the tree: concurrent matches on different streams are safe.  Batches of
+ * up to 256 requests are matched by several workgroups per request, which meet in buffers of the
+ * library's own: each stream has its own ones, and so has each call captured into a HIP graph, so
+ * that a replay may overlap any other call.  Limits: matches in flight at once on more than 64
+ * streams of one device are not supported; the first 128 captured calls of a process on a device
+ * get such buffers, later ones run without (one workgroup per request: slower for long prompts in
+ * trees of many short edges).  The first call on a device looks the buffers' address up; make it
+ * outside any stream capture. */
 int pa_match_prefixes(const pa_tree* tree, const int32_t* tokens, const int32_t* offsets, int B,
                       int32_t* prefix_len, int32_t* slot_idx, void* stream);
 

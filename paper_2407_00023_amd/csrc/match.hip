@@ -14,7 +14,6 @@
 // workgroups of 1,024 threads that compared every edge before they looked for the next one: 4,096 prompts of 2,650 tokens
 // over four edges of 512 each 150 -> 24 us; 64 prompts over three or four edges 18 -> 9; a path of 541 nodes (32 prompts of
 // 8,483 tokens) 41 -> 23; one long edge of 16,384 tokens (16 prompts) 24 -> 13; the smallest call 13 -> 5.
-#include <atomic>
 #include <mutex>
 
 #include "common.h"
@@ -97,7 +96,8 @@ constexpr int kSplitSweep = 4096; // a walked path longer than this is compared 
 constexpr int kMaxW = 16;        // workgroups per request at most; a longer path's rest is walked by the last one
 constexpr int kMultiMaxB = 256;  // batches of up to this many requests take this form
 constexpr int kMultiWgs = 1024;  // ... with up to this many workgroups (four on a compute unit)
-constexpr int kScratchSets = 64; // calls in flight at once on a device that may use it
+constexpr int kStreamSets = 128;   // sets of summaries and counters for calls on streams, two to a stream ...
+constexpr int kGraphSets = 128;    // ... and for captured calls, one each
 struct MatchSummary {
     int32_t f_pos, f_parent;     // position of the first node of the chain (-1: none), the parent it names
     int32_t exit_pos, exit_cur;  // matched length and current node after the chain
@@ -678,28 +678,58 @@ __global__ __launch_bounds__(kT, kMulti ? 4 : 8) void match_prefixes_kernel(Devi
 }  // namespace pa
 
 // Summaries and counters of the multi-workgroup form: part of the library's code object (each GPU holds its own copy;
-// in host code the array's name is only a handle for hipGetSymbolAddress).  A call takes the next of kScratchSets sets,
-// so that calls in flight at once on different streams do not meet in one (more than kScratchSets of them could).
-static __device__ pa::MatchScratch g_match_scratch[pa::kScratchSets];
+// in host code the array's name is only a handle for hipGetSymbolAddress).  No two calls that can be in flight at once may
+// meet in one set.  Calls on one stream follow one another, so a stream has sets of its own (two in turn: a new stream may be
+// given the handle of one just destroyed), those of the stream that has not matched for longest going to a new one.  A
+// captured call keeps its set for good, since its graph may be replayed at any time beside any other call (two replays of one
+// captured call would meet in its output as well); where no such set is left, it takes the form without shared state.
+static __device__ pa::MatchScratch g_match_scratch[pa::kStreamSets + pa::kGraphSets];
 
 namespace {
 constexpr int kMaxDevices = 64;
+struct DeviceSets {
+    pa::MatchScratch* base = nullptr;
+    struct { const void* stream; uint64_t used; unsigned calls; } of[pa::kStreamSets / 2] = {};  // (used = 0: free)
+    uint64_t clock = 0;
+    int captured = 0;
+};
 std::mutex g_ms_mu;
-pa::MatchScratch* g_ms_ptr[kMaxDevices] = {};
-std::atomic<unsigned> g_ms_next{0};
+DeviceSets g_ms[kMaxDevices];
 
-int match_scratch_of_current_device(pa::MatchScratch** out) {
+// The set for a call on `stream` of the current device; *out = nullptr: none.
+int match_scratch_for(hipStream_t stream, pa::MatchScratch** out) {
+    *out = nullptr;
     int dev = -1;
     PA_HIP(hipGetDevice(&dev));
     PA_REQUIRE(dev >= 0 && dev < kMaxDevices, "pa_match_prefixes: device ordinal %d not supported", dev);
+    const void* key = stream == hipStreamLegacy ? nullptr : static_cast<const void*>(stream);
+    static thread_local char this_thread;
+    if (stream == hipStreamPerThread) key = &this_thread;  // (one handle, a stream for every thread)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (key != nullptr) PA_HIP(hipStreamIsCapturing(stream, &capture));  // (the default stream cannot be captured)
     std::lock_guard<std::mutex> lk(g_ms_mu);
-    if (g_ms_ptr[dev] == nullptr) {
+    DeviceSets& d = g_ms[dev];
+    if (d.base == nullptr) {
         void* ptr = nullptr;
         PA_HIP(hipGetSymbolAddress(&ptr, HIP_SYMBOL(g_match_scratch)));
         PA_REQUIRE(ptr != nullptr, "pa_match_prefixes: no address for the library's scratch array");
-        g_ms_ptr[dev] = static_cast<pa::MatchScratch*>(ptr);
+        d.base = static_cast<pa::MatchScratch*>(ptr);
     }
-    *out = g_ms_ptr[dev];
+    if (capture != hipStreamCaptureStatusNone) {
+        if (d.captured < pa::kGraphSets) *out = d.base + pa::kStreamSets + d.captured++;
+        return PA_OK;
+    }
+    int at = 0;
+    for (int i = 0; i < pa::kStreamSets / 2; ++i) {
+        if (d.of[i].used != 0 && d.of[i].stream == key) {
+            at = i;
+            break;
+        }
+        if (d.of[i].used < d.of[at].used) at = i;
+    }
+    d.of[at].stream = key;
+    d.of[at].used = ++d.clock;
+    *out = d.base + 2 * at + (d.of[at].calls++ & 1);
     return PA_OK;
 }
 }  // namespace
@@ -715,15 +745,11 @@ extern "C" int pa_match_prefixes(const pa_tree* tree, const int32_t* tokens, con
     // tokens / slot_idx may be NULL only if every prompt is empty (offsets[B] == 0), which the host cannot see
     // Up to kMultiMaxB requests: several workgroups per request, four on a compute unit in all.  Larger batches fill the chip
     // with one workgroup per request, eight on a unit (windows of 512 positions and no copy of the prompt in LDS).
-    const bool multi = B <= pa::kMultiMaxB;
     pa::MatchScratch* scratch = nullptr;
-    if (multi) {
-        if ((rc = match_scratch_of_current_device(&scratch)) != PA_OK) return rc;
-        scratch += g_ms_next.fetch_add(1) % pa::kScratchSets;
-    }
+    if (B <= pa::kMultiMaxB && (rc = match_scratch_for(static_cast<hipStream_t>(stream), &scratch)) != PA_OK) return rc;
     {
         pa::ProfScope prof(pa::kProfMatch, static_cast<hipStream_t>(stream));
-        if (multi) {
+        if (scratch != nullptr) {
             const int per = pa::kMultiWgs / B < pa::kMaxW ? pa::kMultiWgs / B : pa::kMaxW;
             hipLaunchKernelGGL((pa::match_prefixes_kernel<256, 4, true>), dim3(B * per), dim3(256), 0, static_cast<hipStream_t>(stream),
                                *view, tokens, offsets, prefix_len, slot_idx, B, scratch);

@@ -142,6 +142,72 @@ def test_match_on_paths_with_colliding_hashes(pa, gpu_device, kind, swap, B):
             np.testing.assert_array_equal(si[off[r]:off[r] + pl_ref[r]], si_ref[off[r]:off[r] + pl_ref[r]])
 
 
+@pytest.mark.gpu
+def test_captured_matches_beside_eager_ones(pa, gpu_device):
+    """Graphs with a match of several workgroups per request, replayed while other matches run on other streams; then a graph
+    with more captured calls than the library keeps buffers for.  Every replay is compared, with eager work in between."""
+    import oracle
+    rng = np.random.default_rng(11)
+    trunk, cached = _path(rng, [700] * 4 + [3] * 500)
+    tree = pa.Tree()
+    for c in cached:
+        tree.insert(*c)
+    tree.upload()
+
+    def batch(B, seed):
+        cuts = np.random.default_rng(seed).integers(0, len(trunk), B)
+        prompts = [np.append(trunk[:c], np.int32(2000)) for c in cuts]
+        toks, off = np.concatenate(prompts).astype(np.int32), np.concatenate([[0], np.cumsum(cuts + 1)]).astype(np.int32)
+        pl, si = oracle.match_prefixes(cached, toks, off)
+        assert np.array_equal(pl, cuts)
+        b = dict(t=torch.from_numpy(toks).to(gpu_device), o=torch.from_numpy(off).to(gpu_device), want=(pl, si), off=off)
+        b["len"], b["slot"] = torch.full((B,), -1, dtype=torch.int32, device=gpu_device), torch.full_like(b["t"], -1)
+        return b
+
+    def check(b, pl, si):
+        pl, si, off = pl.cpu().numpy(), si.cpu().numpy(), b["off"]
+        np.testing.assert_array_equal(pl, b["want"][0])
+        for r in range(len(pl)):
+            np.testing.assert_array_equal(si[off[r]:off[r] + pl[r]], b["want"][1][off[r]:off[r] + pl[r]])
+
+    run = lambda b: pa.match_prefixes(tree, b["t"], b["o"], b["len"], b["slot"])
+    batches = [batch(B, B) for B in (40, 128, 200, 256)]
+    streams = [torch.cuda.Stream() for _ in batches]
+    for b in batches:
+        run(b)
+    torch.cuda.synchronize()
+    graphs = []
+    for b in batches[:2]:
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            run(b)
+    for k in range(10):
+        print(f"[case] captured matches beside eager ones, round {k}", flush=True)
+        for b in batches:
+            b["len"].fill_(-1), b["slot"].fill_(-1)
+        torch.cuda.synchronize()
+        for i, b in enumerate(batches):
+            with torch.cuda.stream(streams[i]):
+                for _ in range(1 if i < 2 else 40):
+                    graphs[i].replay() if i < 2 else run(b)
+        torch.cuda.synchronize()
+        for b in batches:
+            check(b, b["len"], b["slot"])
+    small, many = batch(3, 1), 130
+    pls = torch.full((many, 3), -1, dtype=torch.int32, device=gpu_device)
+    sis = torch.full((many, len(small["t"])), -1, dtype=torch.int32, device=gpu_device)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for k in range(many):
+            pa.match_prefixes(tree, small["t"], small["o"], pls[k], sis[k])
+    for _ in range(3):
+        pls.fill_(-1), sis.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        for k in range(many):
+            check(small, pls[k], sis[k])
+
+
 def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0):
     """Largest error against the oracle for requests with P[r] cached tokens, the first `common` of them the same for all."""
     import oracle
