@@ -30,11 +30,12 @@ def _path(rng, edges, vocab=1000):
     return trunk, cached
 
 
-# None: as many requests as there are prompts below (5 to 49), 16 workgroups each; 65: 15, 256: 4, 257 and 300: one.  Paths around
+# None: as many requests as there are prompts below (5 to 49), 16 workgroups each; 65: 15, 256: 4; 257, 300: one, windows of 1,024
+# positions; 1025: of 512.  Paths around
 # the walk's limits: 4 nodes whatever their length, 16 while they hold 128 tokens on average; swept by one workgroup up to 4,096
 # tokens, by several beyond; in the end windows, more of them than workgroups
 @pytest.mark.gpu
-@pytest.mark.parametrize("B", [None, 65, 256, 257, 300])
+@pytest.mark.parametrize("B", [None, 65, 256, 257, 300, 1025])
 @pytest.mark.parametrize("edges", [[1], [1, 1, 1], [1, 1, 1, 1], [2, 1, 3, 1, 5], [127] * 5, [128] * 5, [128] * 15, [128] * 16,
                                    [200] * 17, [1023, 1, 1, 1021], [4096], [4097], [3000, 1500, 700], [2048] * 6, [1, 1, 1, 1, 9000],
                                    [700] * 4 + [3] * 500],
@@ -52,7 +53,7 @@ def test_match_at_the_limits_of_walk_sweep_and_window(pa, gpu_device, edges, B):
         wrong = trunk.copy()
         wrong[c] = (wrong[c] + 500) % 1000
         prompts += [trunk[:c], wrong]
-    prompts = (prompts * 60)[:B] if B else prompts
+    prompts = (prompts * 210)[:B] if B else prompts
     toks = np.concatenate(prompts).astype(np.int32)
     off = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
     pl_ref, si_ref = oracle.match_prefixes(cached, toks, off)
@@ -98,7 +99,7 @@ def _insert_cuts(cached, seq, cuts, slot0):
 # over the next window's nodes.  "inside an edge": on one path the depth lies inside an edge of some windows' length, behind
 # which short edges go on, and the other's node reaches past that edge's end.
 @pytest.mark.gpu
-@pytest.mark.parametrize("B", [2, 65, 256, 257])
+@pytest.mark.parametrize("B", [2, 65, 256, 257, 1025])
 @pytest.mark.parametrize("kind", ["same depth", "inside an edge"])
 @pytest.mark.parametrize("swap", [False, True])
 def test_match_on_paths_with_colliding_hashes(pa, gpu_device, kind, swap, B):
@@ -124,7 +125,7 @@ def test_match_on_paths_with_colliding_hashes(pa, gpu_device, kind, swap, B):
             wrong = path.copy()
             wrong[cut] = 4999
             prompts += [path[:cut], wrong]
-    prompts = (prompts * 8)[:B]
+    prompts = (prompts * 24)[:B]
     toks = np.concatenate(prompts).astype(np.int32)
     off = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
     pl_ref, si_ref = oracle.match_prefixes(cached, toks, off)
