@@ -261,8 +261,9 @@ size_t pa_kv_pool_bytes(int64_t num_slots, int Hkv, int D, int dtype, int page_s
  * when one of the three grows, so one workspace sized for the largest batch serves all smaller ones.
  * It holds the work list of the launch and the partial results (fp32 rows) of what is computed in
  * parts: rows of tiles whose key range is split over several workgroups (bf16, 8 KV heads of 128:
- * up to 137 MB) and, twice, rows of requests of few new tokens that may share the first part of their
- * prefixes (8.3 KB per row of a KV head there, at most 256 requests).  A workspace below this size
+ * up to 137 MB) and, for batches of up to 256 requests, twice the rows of requests of few new tokens,
+ * which may share the first part of their prefixes (520 bytes per query head of a token and time
+ * there, at most 48 query heads of tokens per request and KV head).  A workspace below this size
  * that has room for the former is accepted too: such rows are then not shared.
  * Returns 0 for invalid arguments. */
 size_t pa_extend_workspace_bytes(int B, int64_t T, int64_t max_kv_len, int Hq, int Hkv, int D, int dtype);

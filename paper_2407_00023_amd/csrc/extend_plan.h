@@ -20,7 +20,7 @@ struct ExtendPlan {
     int slots;       // workgroup slots per KV head
     int rounds;      // work items aimed at per workgroup slot
     int pack;        // 1: rows of requests with a common prefix may be packed
-    int first_part;  // 1: also where they have only the first part of it in common
+    int first_part;  // ... of requests of up to this many rows also where they have only the first part of it in common (0: not)
     int tile_parts;  // parts of one tile at most
     int chunk_rows;  // rows per piece of the merge
     size_t off_tile, off_member, off_item, off_chunk, off_part_o, off_part_ml, total;

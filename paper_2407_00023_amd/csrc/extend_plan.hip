@@ -17,8 +17,8 @@
 //     every row, and then the extend tokens of each request that has rows in it, one request's after the other's, visible to
 //     that request's rows only (and causally).  Its members are consecutive entries of the member table.
 //   Shared, common first part: requests may also share only the first part of their prefixes (a decode batch: a common system
-//     and tool prompt, then tokens of each request's own).  Those whose rows make less than one tile, and whose whole prefix
-//     nobody shares, are grouped by the deepest of a few fixed depths at which another such request has the same slot (slots
+//     and tool prompt, then tokens of each request's own).  Those of few rows (first_part_rows), whose whole prefix nobody
+//     shares, are grouped by the deepest of a few fixed depths at which another such request has the same slot (slots
 //     name cached tokens: the same slot at a depth means the same tokens up to there); the group's common part is then
 //     measured, to a thirteenth of the distance to the next probe, against the group's first member.  Their rows are packed into tiles
 //     over the common keys, and again, request by request, into own-key tiles over the rest; the merge joins the two.
@@ -44,6 +44,14 @@ constexpr int kPackMinPrefix = 512;      // prefixes, or first parts of them, ar
 constexpr int kPackOwnCost = 2;          // ... and, whole ones, if the members' own keys, which a shared tile walks in the general
                                          // tile for the few rows that see them, cost less than walking the prefix per member:
                                          // this factor x their sum <= (members - 1) x the shared prefix
+// Rows of a request at most that are shared over a common first part, and the keys it has to have for a request of more rows
+// than a narrow tile.  Every 32 of these rows walk the request's own keys in a tile of their own and leave fp32 partial results
+// twice, while they save the less of the common keys' tiles the more they are.  Measured (us, shared | not; 256 requests, 2,000
+// common and 300 own keys): heads of 128, 8 rows 117 | 234, 32 rows 195 | 237, 48 rows 288 | 301, 64 rows 339 | 304, 96 rows
+// 472 | 339; heads of 64, 48 rows 175 | 239, 64 rows 193 | 236, 80 rows 257 | 227; with 600 common keys, heads of 128, 8 rows
+// 85 | 103, 48 rows 207 | 141.
+static inline int first_part_rows(int D) { return D == 128 ? 48 : 64; }
+constexpr int kPackWidePrefix = 1024;
 constexpr int kProbes = 12;              // depths looked at for common first parts, and which
 __device__ __forceinline__ constexpr int probe_depth(int k) {
     constexpr int in512[kProbes] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
@@ -68,9 +76,9 @@ ExtendPlan make_extend_plan(int B, int64_t T, int64_t max_kv_len, int Hq, int Hk
     const int64_t longest = p.pack ? max_kv_len * (B < kTileRows ? (B > 0 ? B : 1) : kTileRows) : max_kv_len;
     const int64_t per_tile = (longest / kKT) / kMinChunkNarrow > 1 ? (longest / kKT) / kMinChunkNarrow : 1;
     p.tile_parts = static_cast<int>(per_tile < kMaxParts ? per_tile : kMaxParts);
-    for (p.first_part = p.pack && B > 1; ; p.first_part = 0) {
-        // (rows of requests grouped by a common first part: fewer than a tile each; once per shared tile, once per own-key tile)
-        const int64_t fp_rows = !p.first_part ? 0 : rows < int64_t{B} * (kTileRows - 1) ? rows : int64_t{B} * (kTileRows - 1);
+    for (p.first_part = p.pack && B > 1 ? first_part_rows(D) : 0; ; p.first_part = 0) {
+        // (rows of requests grouped by a common first part: once per shared tile, once per own-key tile)
+        const int64_t fp_rows = rows < int64_t{B} * p.first_part ? rows : int64_t{B} * p.first_part;
         p.own_cap = static_cast<int>(p.first_part ? fp_rows / kNarrowRows + B : 0);
         const int64_t by_size = (static_cast<int64_t>(p.tiles_cap) + p.own_cap) * p.tile_parts;
         const int64_t more = by_rule < by_size ? by_rule : by_size;
@@ -342,7 +350,7 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
         for (int i = tid; i <= pmask; i += NT) s_pt[i] = -1, s_pc[i] = 0;
     if (tid == 0) s_any = 0;
     const int rows = on ? max(E, 0) * G : 0, full = rows / mt, left = rows - full * mt;
-    const bool small = on && first_part && rows > 0 && rows < mt && P >= kPackMinPrefix;
+    const bool small = on && first_part && rows > 0 && rows <= a.first_part && P >= kPackMinPrefix;
     if (on) {
         s_P[tid] = P;
         s_E[tid] = E;
@@ -390,7 +398,7 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
             auto key_at = [&](int k) { return hash_key((static_cast<unsigned long long>(k) << 32) | static_cast<uint32_t>(s_pslot[(kProbes + 2) * tid + k])) & pmask; };
 #pragma unroll
             for (int k = 0; k < kProbes; ++k) {
-                at[k] = cand && probe_depth(k) <= P ? key_at(k) : -1;
+                at[k] = cand && probe_depth(k) <= P && (rows <= kNarrowRows || probe_depth(k) >= kPackWidePrefix) ? key_at(k) : -1;
                 old[k] = at[k] >= 0 ? atomicCAS(&s_pt[max(at[k], 0)], -1, (1 << 16) | (tid * kProbes + k)) : -1;
             }
             auto slot_of = [&](int pair) { return s_pslot[(kProbes + 2) * (pair / kProbes) + pair % kProbes]; };

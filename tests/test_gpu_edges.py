@@ -209,8 +209,9 @@ def test_captured_matches_beside_eager_ones(pa, gpu_device):
             check(small, pls[k], sis[k])
 
 
-def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0):
-    """Largest error against the oracle for requests with P[r] cached tokens, the first `common` of them the same for all."""
+def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None):
+    """Largest error against the oracle for requests with P[r] cached tokens, the first `common` of them the same for all.
+    tiles: how many row tiles the work list has to hold."""
     import oracle
     rng = np.random.default_rng(seed)
     P, E = np.asarray(P, np.int32), np.asarray(E, np.int32)
@@ -249,6 +250,7 @@ def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0):
     torch.cuda.synchronize()
     if dtype != "f32":
         assert ws[12:16].view(torch.int32).item() == 0  # (the work list fitted)
+        assert tiles is None or ws[:4].view(torch.int32).item() == tiles
     opk, opv = oracle.new_pool(nslots, Hkv, D, dtype)
     oracle.append_kv(opk, opv, backed, pk, pv, dtype)
     ref = oracle.extend_attention(q, k, v, opk, opv, si, off, P, E, eo, D ** -0.5, dtype)
@@ -292,6 +294,16 @@ def test_extend_heads_of_64_around_whole_tiles(pa, gpu_device, dtype, page, P, E
 def test_extend_common_first_parts_around_the_probes(pa, gpu_device, D, common, own):
     P = [common + own * (r % 3) + r // 3 for r in range(9)]
     assert _extend(pa, gpu_device, "bf16", P, [1 + r % 2 for r in range(9)], 8, 2, D, 16, common=common) <= TOL["bf16"]
+
+
+# rows of a request up to which a common first part is shared: 48 (heads of 128) or 64, behind fewer than 1,024 common keys 32;
+# eight requests share tiles of 128 rows, or have one each
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,common,E,tiles", [(128, 1100, 12, 3), (128, 1100, 13, 8), (64, 1100, 16, 4), (64, 1100, 17, 8), (128, 700, 8, 2),
+                                              (128, 700, 9, 8), (128, 1024, 9, 3), (128, 1023, 9, 8), (128, 1100, 24, 8)])
+def test_extend_rows_that_share_a_first_part(pa, gpu_device, D, common, E, tiles):
+    P = [common + 70 + r for r in range(8)]
+    assert _extend(pa, gpu_device, "bf16", P, [E] * 8, 8, 2, D, 16, common=common, tiles=tiles) <= TOL["bf16"]
 
 
 # the largest batches of each planner (256: with sharing, 1,024: ordered, beyond: as given) and the smallest that are beyond

@@ -65,3 +65,30 @@ def test_static_scratch_entry_point_matches_the_one_with_a_workspace(gpu_device)
             torch.cuda.synchronize()
             assert rc == -2 and b"bytes" in pa._lib.pa_last_error()
             assert bool((mark == 5.0).all())
+
+
+@pytest.mark.parametrize("E", [1, 8])
+def test_static_scratch_on_decode_batches(gpu_device, E):
+    """256 requests behind a common first part, 64 query heads over 8.  With one new token each the plan with shared first parts
+    fits the library's buffer; with eight it does not, and the rows are not shared.  Against the call with a workspace, whose
+    parity with the oracle other tests cover: two bf16 results, each within half a unit in the last place of the same value."""
+    from paper_2407_00023_amd import binding as pa
+    B, P, common, Hq, Hkv, D, page, nslots = 256, 700, 640, 64, 8, 128, 16, 32768
+    gen = torch.Generator(device=gpu_device).manual_seed(E)
+    mk = lambda n, h: torch.randn(n, h, D, generator=gen, dtype=torch.bfloat16, device=gpu_device)
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=gpu_device)
+    pool = torch.zeros(pa.kv_pool_bytes(nslots, Hkv, D, torch.bfloat16, page), dtype=torch.uint8, device=gpu_device)
+    kw = dict(page_size=page, num_slots=nslots)
+    pa.append_kv(pool, torch.arange(nslots, dtype=torch.int32, device=gpu_device), mk(nslots, Hkv), mk(nslots, Hkv), **kw)
+    slots = torch.full((B, P + E), -1, dtype=torch.int32)
+    for r in range(B):
+        slots[r, :common] = torch.arange(common)
+        slots[r, common:P] = torch.arange(common + r * (P - common), common + (r + 1) * (P - common))
+    q, k, v = mk(B * E, Hq), mk(B * E, Hkv), mk(B * E, Hkv)
+    args = (q, k, v, pool, slots.to(gpu_device).view(-1), i32(range(0, B * (P + E) + 1, P + E)), i32([P] * B), i32([E] * B),
+            i32(range(0, B * E + 1, E)), D ** -0.5)
+    print(f"[case] static scratch, decode batch of {B} x {E}", flush=True)
+    ref = pa.extend_attention(*args, max_kv_len=P + E, **kw)
+    out = pa.extend_attention_static(*args, max_kv_len=P + E, out=torch.empty_like(q), **kw)
+    torch.cuda.synchronize()
+    assert float((out.double() - ref.double()).abs().max()) <= TOL["bf16"]
