@@ -108,6 +108,12 @@ __global__ __launch_bounds__(256) void extend_f32_kernel(
                 for (int off = 1; off < kLanes; off <<= 1) d += __shfl_xor(d, off);
                 s[u] = j0 + u * kGroups + group < nvis ? d : -INFINITY;
             }
+            // (a key past the end has probability 0, which must not meet an infinity of the row it repeats; here and not at the
+            // loads, so that the scores do not wait for the V rows)
+            if (x == 0 && j0 + kGroups * kUnroll > nvis)
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u)
+                    if (j0 + u * kGroups + group >= nvis) v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
             float mx = m[x];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) mx = fmaxf(mx, s[u]);

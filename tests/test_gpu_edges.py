@@ -266,6 +266,33 @@ def test_f32_extend_around_its_key_rounds(pa, gpu_device, Hq, Hkv, D):
     assert err <= TOL["f32"], err
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("P,E", [(0, 1), (3, 1), (3, 5), (17, 2), (64, 3), (97, 30)])
+def test_f32_extend_with_an_infinite_value(pa, gpu_device, D, P, E):
+    """An infinity in a V row that is visible to a row makes that element of the row infinite, not NaN, wherever the row stands
+    among the keys; rows that do not see it are untouched."""
+    nslots, Hq, Hkv = 128, 4, 2
+    gen = torch.Generator(device=gpu_device).manual_seed(P + E)
+    mk = lambda n, h: torch.randn(n, h, D, generator=gen, device=gpu_device)
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=gpu_device)
+    q, k, v, pk, pv = mk(E, Hq), mk(E, Hkv), mk(E, Hkv), mk(nslots, Hkv), mk(nslots, Hkv)
+    kw = dict(page_size=1, num_slots=nslots)
+    for at in sorted({P + E - 1, P + E // 2, max(P - 1, 0)}):  # the key whose V row holds it
+        vv, pvv = v.clone(), pv.clone()
+        (pvv[at] if at < P else vv[at - P])[1, 5] = float("inf")
+        pool = torch.zeros(pa.kv_pool_bytes(nslots, Hkv, D, torch.float32, 1), dtype=torch.uint8, device=gpu_device)
+        pa.append_kv(pool, i32(range(nslots)), pk, pvv, **kw)
+        out = pa.extend_attention(q, k, vv, pool, i32(range(P + E)), i32([0, P + E]), i32([P]), i32([E]), i32([0, E]), D ** -0.5,
+                                  max_kv_len=P + E, **kw).cpu().double()
+        K, V = torch.cat([pk[:P], k]).cpu().double(), torch.cat([pvv[:P], vv]).cpu().double()
+        for i in range(E):
+            for h in range(Hq):
+                n = P + i + 1
+                p = torch.softmax(K[:n, h // 2] @ q[i, h].cpu().double() * D ** -0.5, 0)
+                torch.testing.assert_close(out[i, h], p @ V[:n, h // 2], atol=TOL["f32"], rtol=0)
+
+
 # rows around the 32 of a narrow tile and the 128 of a wide one, keys around a block of 32 and a round of the four waves
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["bf16", "bf16_kv8"])
