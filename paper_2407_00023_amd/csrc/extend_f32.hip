@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void extend_f32_kernel(
     const int i = static_cast<int>(t - e0);
     const int P = prefix_len[r];
     const int32_t* __restrict__ slots = slot_idx + slot_offsets[r];
-    if (i >= ext_len[r]) return;  // inconsistent offsets: produce nothing rather than read out of range
+    if (i < 0 || i >= ext_len[r]) return;  // inconsistent offsets: produce nothing rather than read out of range
     const int nvis = P + i + 1;
     const unsigned last_slot = static_cast<unsigned>(min(num_slots, int64_t{INT32_MAX})) - 1u;
 

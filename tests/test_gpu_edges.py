@@ -293,6 +293,32 @@ def test_f32_extend_with_an_infinite_value(pa, gpu_device, D, P, E):
                 torch.testing.assert_close(out[i, h], p @ V[:n, h // 2], atol=TOL["f32"], rtol=0)
 
 
+# a token's request is found by comparisons of all offsets at once up to 256 requests, by a search beyond; requests without new
+# tokens among them, first and last
+@pytest.mark.gpu
+@pytest.mark.parametrize("B", [64, 65, 255, 256, 257, 400])
+def test_f32_extend_finds_the_request_of_a_token(pa, gpu_device, B):
+    E = [(r % 3) if r % 50 else 0 for r in range(B)]
+    E[-2:] = [2, B % 2]
+    assert _extend(pa, gpu_device, "f32", [r % 5 for r in range(B)], E, 2, 1, 64, 1) <= TOL["f32"]
+
+
+@pytest.mark.gpu
+def test_f32_extend_leaves_rows_of_no_request_alone(pa, gpu_device):
+    """Offsets that do not begin at 0: the rows before the first request's get no output, its own do."""
+    D, gen = 64, torch.Generator(device=gpu_device).manual_seed(1)
+    mk = lambda n, h: torch.randn(n, h, D, generator=gen, device=gpu_device)
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=gpu_device)
+    q, k, v = mk(5, 2), mk(5, 1), mk(5, 1)
+    pool = torch.zeros(pa.kv_pool_bytes(8, 1, D, torch.float32, 1), dtype=torch.uint8, device=gpu_device)
+    out = torch.full_like(q, 7.0)
+    pa.extend_attention(q, k, v, pool, i32([-1] * 2), i32([0, 2]), i32([0]), i32([2]), i32([3, 5]), D ** -0.5, max_kv_len=2,
+                        page_size=1, num_slots=8, out=out)
+    out = out.cpu()
+    assert bool((out[:3] == 7.0).all())
+    torch.testing.assert_close(out[3], v[3].expand(2, D).cpu(), atol=TOL["f32"], rtol=0)
+
+
 # rows around the 32 of a narrow tile and the 128 of a wide one, keys around a block of 32 and a round of the four waves
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["bf16", "bf16_kv8"])
