@@ -84,6 +84,27 @@ bool stream_of(PyObject* o, void** out) {
     return !PyErr_Occurred();
 }
 
+// While one is alive, tensors are allocated for the call's stream instead of torch's current one: the caching allocator hands a
+// block that is free on a stream to that stream's next tensors, and the kernels that use it are on the call's.  A tensor that is
+// given to the caller is also marked as used on the current stream, where the caller will read it.
+struct AllocateOn {
+    const c10::hip::HIPStream before;
+    bool other = false;
+    AllocateOn(void* stream, const at::Tensor& like) : before(c10::hip::getCurrentHIPStream(like.device().index())) {
+        hipStream_t s = static_cast<hipStream_t>(stream);
+        if (s == hipStreamLegacy) s = nullptr;  // (two names of the default stream)
+        other = before.stream() != s;
+        if (other) c10::hip::setCurrentHIPStream(c10::hip::getStreamFromExternal(s, like.device().index()));
+    }
+    ~AllocateOn() { if (other) c10::hip::setCurrentHIPStream(before); }
+    at::Tensor given(at::Tensor t) const {
+        if (other) t.record_stream(c10::Stream(c10::Stream::UNSAFE, t.device(), before.id()));
+        return t;
+    }
+    AllocateOn(const AllocateOn&) = delete;
+    AllocateOn& operator=(const AllocateOn&) = delete;
+};
+
 // The interpreter's lock is given up while the library launches (other threads run on while a launch waits for a full queue).
 struct WithoutGil {
     PyThreadState* const state = PyEval_SaveThread();
@@ -155,20 +176,23 @@ PyObject* match_prefixes(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyO
     const at::Tensor *tokens = tensor_of(a[1], "tokens"), *offsets = tokens ? tensor_of(a[2], "offsets") : nullptr;
     if (!offsets || !device_int32(*tokens, "tokens") || !device_int32(*offsets, "offsets")) return nullptr;
     const int64_t B = offsets->numel() - 1;
+    void* stream = nullptr;
+    if (!stream_of(a[5], &stream)) return nullptr;
     at::Tensor made_len, made_slots;
     const at::Tensor *len = nullptr, *slots = nullptr;
+    if (!a[3] || !a[4]) {
+        const AllocateOn streams(stream, *tokens);
+        if (!a[3]) len = &(made_len = streams.given(at::empty({B}, tokens->options())));
+        if (!a[4]) slots = &(made_slots = streams.given(at::empty_like(*tokens)));
+    }
     if (a[3]) len = tensor_of(a[3], "prefix_len");
-    else len = &(made_len = at::empty({B}, tokens->options()));
     if (!len) return nullptr;
     if (a[4]) slots = tensor_of(a[4], "slot_idx");
-    else slots = &(made_slots = at::empty_like(*tokens));
     if (!slots || !device_int32(*len, "prefix_len") || !device_int32(*slots, "slot_idx")) return nullptr;
     if (len->numel() < B || slots->numel() < tokens->numel()) {
         PyErr_SetString(PyExc_ValueError, "output tensors too small");
         return nullptr;
     }
-    void* stream = nullptr;
-    if (!stream_of(a[5], &stream)) return nullptr;
     int rc = PA_OK;
     {
         const WithoutGil released;
@@ -224,6 +248,8 @@ PyObject* extend_attention(PyObject*, PyObject* const* args, Py_ssize_t nargs, P
     long long page_size = 0, num_slots = 0, max_kv_len = 0;
     if (!int_of(a[10], &page_size) || !int_of(a[11], &num_slots) || !int_of(a[12], &max_kv_len)) return nullptr;
     if (!pool_large_enough(pool, num_slots, Hkv, D, dtype, page_size)) return nullptr;
+    void* stream = nullptr;
+    if (!stream_of(a[15], &stream)) return nullptr;
     at::Tensor made_out, made_ws;
     const at::Tensor *out = nullptr, *ws = nullptr;
     if (a[13]) {
@@ -232,21 +258,18 @@ PyObject* extend_attention(PyObject*, PyObject* const* args, Py_ssize_t nargs, P
             PyErr_SetString(PyExc_ValueError, "bad out tensor");
             return nullptr;
         }
-    } else {
-        out = &(made_out = at::empty_like(q));
     }
     const size_t need = pa_extend_workspace_bytes(static_cast<int>(B), T, max_kv_len, Hq, Hkv, D, dtype);
     if (need == 0) {
         PyErr_SetString(PyExc_ValueError, "pa_extend_workspace_bytes: invalid arguments");
         return nullptr;
     }
-    if (a[14]) {
-        if (!(ws = tensor_of(a[14], "workspace"))) return nullptr;
-    } else {
-        ws = &(made_ws = at::empty({static_cast<int64_t>(need)}, q.options().dtype(at::kByte)));
+    if (a[14] && !(ws = tensor_of(a[14], "workspace"))) return nullptr;
+    if (!out || !ws) {
+        const AllocateOn streams(stream, q);
+        if (!out) out = &(made_out = streams.given(at::empty_like(q)));
+        if (!ws) ws = &(made_ws = at::empty({static_cast<int64_t>(need)}, q.options().dtype(at::kByte)));
     }
-    void* stream = nullptr;
-    if (!stream_of(a[15], &stream)) return nullptr;
     auto i32 = [&](int i) { return static_cast<const int32_t*>(t[i]->const_data_ptr()); };
     int rc = PA_OK;
     {

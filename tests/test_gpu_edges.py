@@ -387,6 +387,49 @@ def test_hot_path_calls_from_several_threads(pa, gpu_device):
     assert len(errs) == 12 and max(errs) <= TOL["bf16"], errs
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("how", ["stream object", "raw handle"])
+def test_tensors_made_by_a_call_belong_to_its_stream(pa, gpu_device, how):
+    """What the calls allocate themselves is used by kernels on the stream they are given, and freed by the host while these still
+    wait: it has to come from that stream's share of the allocator, also where another stream is torch's current one."""
+    import gc
+    side = torch.cuda.Stream()
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=gpu_device)
+    tree = pa.Tree()
+    tree.insert(np.arange(600, dtype=np.int32), np.arange(600, dtype=np.int32))
+    tree.upload()
+    gen = torch.Generator(device=gpu_device).manual_seed(2)
+    mk = lambda n, h: torch.randn(n, h, 128, generator=gen, dtype=torch.bfloat16, device=gpu_device)
+    kw = dict(page_size=1, num_slots=600)
+    pool = torch.zeros(pa.kv_pool_bytes(600, 2, 128, torch.bfloat16, 1), dtype=torch.uint8, device=gpu_device)
+    pa.append_kv(pool, i32(range(600)), mk(600, 2), mk(600, 2), **kw)
+    toks, off = i32(list(range(600)) + [7000] * 64), i32([0, 664])
+    q, k, v, e, eo = mk(64, 8), mk(64, 2), mk(64, 2), i32([64]), i32([0, 64])
+
+    def step(stream):
+        pl, si = pa.match_prefixes(tree, toks, off, stream=stream)
+        return pl, si, pa.extend_attention(q, k, v, pool, si, off, pl, e, eo, 128 ** -0.5, max_kv_len=664, stream=stream, **kw)
+
+    want = [t.clone() for t in step(None)]
+    gc.collect()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    sizes = lambda: {s["stream"]: sum(x["total_size"] for x in torch.cuda.memory_snapshot() if x["stream"] == s["stream"])
+                     for s in torch.cuda.memory_snapshot()}
+    before = sizes()
+    side.wait_stream(torch.cuda.current_stream())
+    print(f"[case] tensors made for a side stream, {how}", flush=True)
+    got = step(side if how == "stream object" else side.cuda_stream)
+    torch.cuda.current_stream().wait_stream(side)
+    after = sizes()
+    assert after.get(0, 0) == before.get(0, 0) and after[side.cuda_stream] > before.get(side.cuda_stream, 0)
+    for t in got:
+        assert any(s["stream"] == side.cuda_stream and s["address"] <= t.data_ptr() < s["address"] + s["total_size"]
+                   for s in torch.cuda.memory_snapshot())
+    assert torch.cuda.current_stream().cuda_stream == 0
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1][:600], want[1][:600]) and torch.equal(got[2], want[2])
+
+
 def test_hot_path_calls_refuse_what_is_no_device_tensor():
     """Checks that need no GPU: wrong kinds of arguments are refused before anything reaches the device."""
     from paper_2407_00023_amd import binding
