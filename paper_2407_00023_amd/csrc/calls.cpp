@@ -121,6 +121,10 @@ PyObject* raise_code(int rc, const char* where) {
 }
 
 bool int_of(PyObject* o, long long* out) {
+    if (!o) {
+        PyErr_SetString(PyExc_TypeError, "page_size, num_slots and max_kv_len must be integers");
+        return false;
+    }
     *out = PyLong_AsLongLong(o);
     return !(*out == -1 && PyErr_Occurred());
 }
@@ -241,6 +245,10 @@ PyObject* extend_attention(PyObject*, PyObject* const* args, Py_ssize_t nargs, P
     const int64_t B = t[6]->numel();
     if (t[5]->numel() != B + 1 || t[8]->numel() != B + 1 || t[7]->numel() != B) {
         PyErr_SetString(PyExc_ValueError, "per-request arrays disagree on B");
+        return nullptr;
+    }
+    if (!a[9]) {
+        PyErr_SetString(PyExc_TypeError, "scale must be a number");
         return nullptr;
     }
     const double scale = PyFloat_AsDouble(a[9]);

@@ -388,6 +388,24 @@ def test_hot_path_calls_from_several_threads(pa, gpu_device):
 
 
 @pytest.mark.gpu
+def test_hot_path_calls_refuse_none_for_a_number(pa, gpu_device):
+    """A TypeError, raised before anything is launched."""
+    slots = torch.zeros(1, dtype=torch.int32, device=gpu_device)
+    x, pool = torch.zeros(1, 1, 64, device=gpu_device), torch.zeros(4096, device=gpu_device)
+    ok = dict(page_size=1, num_slots=1, max_kv_len=1)
+    for name in ok:
+        bad = dict(ok, **{name: None})
+        with pytest.raises(TypeError):
+            pa.extend_attention(x, x, x, pool, slots, slots.expand(2).contiguous(), slots, slots, slots.expand(2).contiguous(), 1.0, **bad)
+        bad.pop("max_kv_len")
+        if name != "max_kv_len":
+            with pytest.raises(TypeError):
+                pa.append_kv(pool, slots, x, x, **bad)
+    with pytest.raises(TypeError):
+        pa.extend_attention(x, x, x, pool, slots, slots.expand(2).contiguous(), slots, slots, slots.expand(2).contiguous(), None, **ok)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("how", ["stream object", "raw handle"])
 def test_tensors_made_by_a_call_belong_to_its_stream(pa, gpu_device, how):
     """What the calls allocate themselves is used by kernels on the stream they are given, and freed by the host while these still
