@@ -335,8 +335,9 @@ int pa_extend_attention(const void* q_ext, const void* k_ext, const void* v_ext,
  * arguments (minus workspace and workspace_bytes), its work list and partial results kept in a buffer of
  * PA_STATIC_SCRATCH_BYTES that is part of the library's code object (every GPU the library runs on holds its copy from
  * the first use until the process ends).  The call allocates nothing and frees nothing.  To fit that buffer the
- * launch aims at one work item per workgroup slot instead of three, so long key ranges are cut into fewer parts
- * (results agree with pa_extend_attention within the tolerance of the dtype, bit for bit where no row tile is split);
+ * launch aims at one work item per workgroup slot instead of two, so long key ranges are cut into fewer parts
+ * (results agree with pa_extend_attention within the tolerance of the dtype, bit for bit where no row tile is split),
+ * and where partial results of shared first parts of prefixes would not fit, those rows are not shared;
  * a batch whose plan still does not fit is refused with PA_ENOMEM and a message that names both sizes, and nothing
  * is launched.  All calls on one GPU share that GPU's buffer: calls that overlap in time on one GPU - on different
  * streams or from different threads - race, and the caller must order them.  Nothing in the buffer has to be zero

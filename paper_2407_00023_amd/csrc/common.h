@@ -68,8 +68,6 @@ struct DeviceTree {
     const int32_t* edge_slot;
     const ChildEntry* child;
     uint32_t ht_mask;
-    int32_t n_nodes;
-    int32_t n_tokens;  // edge tokens of all nodes together (as of the upload)
     // Second index, by position: a node is also reachable through the hash of the whole token path from
     // the root up to and including the FIRST token of its edge, together with the depth of that token.
     // A prompt can therefore look up every node boundary on its path at once from its own prefix hashes.
@@ -118,7 +116,7 @@ __host__ __device__ inline int64_t pool_row(int64_t slot, int which, int g, int 
 // Per-kernel event timing (profile.cpp).  A ProfScope around a launch records a start/stop event
 // pair on the stream while profiling is switched on, and does nothing otherwise.
 // Byte offset, in the workspace of pa_extend_attention, of the two 64-bit counters of the clock probe (the header
-// of the workspace is 256 bytes; the first 12 hold the work-list counts).
+// of the workspace is 256 bytes; the first 20 hold the work-list counts).
 constexpr size_t kClockProbeOffset = 128;
 bool prof_clock_enabled();
 

@@ -27,16 +27,15 @@
 // row-major V tile with the transposing LDS read of gfx950.
 //
 // Two kinds of tile.  The general tile (general_block below) takes any mix of pool and extend rows, masks and
-// ragged ends, and moves the running maximum; it runs where nothing else applies (heads of 64 on the fp8 pool, pages
-// that are no power of two, the extend tokens in shared tiles, a tile that outgrew the frozen maximum, a first tile too short
-// to seed one).  The rest executes in one assembly statement (fast_run.inc, written by gen_fast_run.py) with the running
-// maximum frozen: runs of consecutive unmasked tiles, and single tiles, plain or on the causal diagonal.
+// ragged ends, and moves the running maximum; it runs where nothing else applies (heads of 64 on the fp8 pool or on
+// pools of 4 GB and more, pages that are no power of two, the extend tokens in shared tiles, a tile that outgrew the frozen
+// maximum, a first tile too short to seed one).  The rest executes in one assembly statement (fast_run.inc, written by
+// gen_fast_run.py) with the running maximum frozen: runs of consecutive unmasked tiles, and single tiles, plain or on the
+// causal diagonal.
 #include <hip/hip_bf16.h>
 
 #include <atomic>
-#include <cstdlib>
 #include <mutex>
-#include <type_traits>
 
 #include "extend_plan.h"
 #include "fp8_rows.h"

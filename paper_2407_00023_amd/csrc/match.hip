@@ -10,10 +10,11 @@
 // workgroup per window.
 //
 // What bounds it: the number of dependent round trips to memory and, in large batches, how many requests are in flight
-// on a compute unit.  Hence workgroups of 256 threads with 13 to 27 KB of LDS.  Measured on a 256-unit chip against
-// workgroups of 1,024 threads that compared every edge before they looked for the next one: 4,096 prompts of 2,650 tokens
-// over four edges of 512 each 150 -> 24 us; 64 prompts over three or four edges 18 -> 9; a path of 541 nodes (32 prompts of
-// 8,483 tokens) 41 -> 23; one long edge of 16,384 tokens (16 prompts) 24 -> 13; the smallest call 13 -> 5.
+// on a compute unit.  Hence workgroups of 256 threads with 10 (windows of 512 positions) to 19 KB of LDS.  Measured on a
+// 256-unit chip against workgroups of 1,024 threads that compared every edge before they looked for the next one: 4,096
+// prompts of 2,650 tokens over four edges of 512 each 150 -> 24 us; 64 prompts over three or four edges 18 -> 9; a path of
+// 541 nodes (32 prompts of 8,483 tokens) 41 -> 23; one long edge of 16,384 tokens (16 prompts) 24 -> 13; the smallest call
+// 13 -> 5.
 #include <mutex>
 
 #include "common.h"
@@ -82,23 +83,23 @@ constexpr int kSplitSweep = 4096; // a walked path longer than this is compared 
 
 // Several workgroups per request (batches of up to kMultiMaxB).  The hashes of a window depend on the prompt alone, so the
 // windows of a long path need not wait for one another.  All workgroups of a request make the same walk of kWalk nodes; if
-// the path ends there the first one compares it and the others leave (a long one is compared by several, 2,048 tokens each
-// or more; the last of them to finish takes the first mismatch).  Otherwise the windows lie at fixed places
-// [k * kWinP, (k + 1) * kWinP): workgroup 0 goes on walking as long as it begins a step inside the window where the walk
-// stands, workgroup w takes the w-th window after that one, from the first node nominated in it, its entry hash formed
-// from the prompt's tokens before the window - and leaves a summary: where its chain begins, the parent its first node
-// names, and where the walk would stand after it.  The workgroup that finishes last (a counter per request) joins the
-// summaries in order - a window's chain is accepted if it begins exactly where the walk stands and names the walk's node as
-// parent: the same exact link as inside a window - and walks on alone from where the chain of accepted windows ends.  Nobody
-// waits for anybody.  Slot ids that a window writes before it is accepted are those of a chain of linked nodes, confirmed
+// the path ends there the first one compares it and the others leave (one longer than kSplitSweep is compared by as many as
+// make the shares 2,048 tokens or fewer, if there are so many; the last of them to finish takes the first mismatch).
+// Otherwise the windows lie at fixed places [k * kWinP, (k + 1) * kWinP): workgroup 0 goes on walking as long as it begins a
+// step inside the window where the walk stands, workgroup w takes the w-th window after that one, from the first node
+// nominated in it, its entry hash formed from the prompt's tokens before the window - and leaves a summary: where its chain
+// begins, the parent its first node names, and where the walk would stand after it.  The workgroup that finishes last (a
+// counter per request) joins the summaries in order - a window's chain is accepted if it begins exactly where the walk stands
+// and names the walk's node as parent: the same exact link as inside a window - and walks on alone from where the chain of
+// accepted windows ends.  Nobody waits for anybody.  Slot ids that a window writes before it is accepted are those of a chain of linked nodes, confirmed
 // token by token, behind a first node whose path hashes like the prompt; where that node proves to be none of the path, the
 // last workgroup writes what the chain has written, and all that lies behind it, again: its writes come after all others.
 constexpr int kMaxW = 16;        // workgroups per request at most; a longer path's rest is walked by the last one
 constexpr int kMultiMaxB = 256;  // batches of up to this many requests take this form
 constexpr int kMultiWgs = 1024;  // ... with up to this many workgroups (four on a compute unit)
-constexpr int kWideMaxB = 1024;   // one workgroup per request: wide windows up to this many requests
-constexpr int kStreamSets = 128;   // sets of summaries and counters for calls on streams, two to a stream ...
-constexpr int kGraphSets = 128;    // ... and for captured calls, one each
+constexpr int kWideMaxB = 1024;  // one workgroup per request: wide windows up to this many requests
+constexpr int kStreamSets = 128; // sets of summaries and counters for calls on streams, two to a stream ...
+constexpr int kGraphSets = 128;  // ... and for captured calls, one each
 struct MatchSummary {
     int32_t f_pos, f_parent;     // position of the first node of the chain (-1: none), the parent it names
     int32_t exit_pos, exit_cur;  // matched length and current node after the chain
@@ -126,8 +127,8 @@ __global__ __launch_bounds__(kT, kPos == 4 ? 4 : 8) void match_prefixes_kernel(D
                                                             int32_t* __restrict__ slot_idx, int n_req, MatchScratch* scratch) {
     constexpr int kWinP = kT * kPos;
     constexpr int kWaves = kT / 64;
-    constexpr int kLogT = kT == 256 ? 8 : kT == 512 ? 9 : 10;
-    static_assert(kT == 1 << kLogT, "threads: 256, 512 or 1,024");
+    constexpr int kLogT = 8;
+    static_assert(kT == 1 << kLogT, "256 threads");
     // The first kStage tokens of the prompt during the walk; afterwards, per window position: {nominated node or -1, its
     // parent, its edge length, index of its first edge token}
     constexpr int kStage = 4 * kWinP;

@@ -782,8 +782,6 @@ extern "C" int pa_tree_upload(pa_tree* tree, void* stream_) {
             PA_HIP(hipEventRecord(tree->xfer_done[x], stream));
             tree->xfer_pending[x] = true;
         }
-        tree->view.n_nodes = static_cast<int32_t>(nn);
-        tree->view.n_tokens = static_cast<int32_t>(tree->n_tokens);
         tree->uploaded = true;
         ++tree->n_incremental_uploads;
         tree->last_upload_bytes = static_cast<int64_t>(bytes);
@@ -908,8 +906,6 @@ extern "C" int pa_tree_upload(pa_tree* tree, void* stream_) {
     tree->view.path_slot = reinterpret_cast<const pa::PathSlot*>(b + f.o_pslot);
     tree->view.path = reinterpret_cast<const pa::PathEntry*>(b + f.o_path);
     tree->view.ph_mask = static_cast<uint32_t>(cap - 1);
-    tree->view.n_nodes = static_cast<int32_t>(nn);
-    tree->view.n_tokens = static_cast<int32_t>(ntok);
     tree->uploaded = true;
     tree->mirror_ok = tree->incremental;
     tree->arena_end = cursor;

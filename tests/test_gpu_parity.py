@@ -96,8 +96,8 @@ def test_match_long_paths_of_mixed_edge_lengths(pa, gpu_device, seed, copies, tr
     """A trunk with branch points at spacings from 1 to thousands of tokens: the prompt's path runs through
     hundreds of nodes whose edges are short, medium and very long in turn, stops at node boundaries, inside
     edges of every class, at the trunk's end and inside side branches; bit-exact vs the oracle trie.
-    copies = 1: 64 prompts, several workgroups per prompt (a trunk of 40,000 tokens reaches past the windows that get a
-    workgroup of their own); 2: 128 prompts, one workgroup each; 5: 320 prompts, shorter windows."""
+    copies = 1: 64 prompts, 16 workgroups per prompt (a trunk of 40,000 tokens reaches past the windows that get a
+    workgroup of their own); 2: 128 prompts, 8 workgroups each (fewer than windows); 5: 320 prompts, one each."""
     import oracle
     rng = np.random.default_rng(100 + seed)
     vocab = 50000
@@ -149,9 +149,8 @@ def test_match_long_paths_of_mixed_edge_lengths(pa, gpu_device, seed, copies, tr
 
 @pytest.mark.parametrize("seed", [0, 1])
 def test_match_long_edges_in_a_tree_of_short_ones(pa, gpu_device, seed):
-    """Edges of 10,000 to 18,000 tokens, three or four matcher windows long, in a tree whose edges are short on
-    average - so that small batches get several workgroups per prompt (a tree of long edges only gets one) and the
-    walks cross whole windows inside one edge: prompts that end at and next to window boundaries, inside the long
+    """Edges of 10,000 to 18,000 tokens, ten to eighteen matcher windows long, in a tree whose edges are short on
+    average, matched by several workgroups per prompt whose walks cross whole windows inside one edge: prompts that end at and next to window boundaries, inside the long
     edges, at their ends and in the branches that leave them; bit-exact vs the oracle trie."""
     import oracle
     rng = np.random.default_rng(300 + seed)
@@ -662,7 +661,7 @@ def test_full_config_extend_every_element(pa, gpu_device, full_cache, name):
     agent_tree, whose oracle run would take a minute, every row of a quarter of the (request, head) pairs: all heads of
     the longest and shortest requests and of requests whose left-over rows are packed into shared tiles, the rest drawn
     at random.  The error is reported for rows in full 128-row tiles and for left-over rows apart (the latter are the
-    ones that shared tiles hold), next to what the work list says about tiles, items and merged tiles.  Plus a property
+    ones that shared tiles hold), next to what the work list says about tiles, items and pieces of the merge.  Plus a property
     that holds at any size: every output element lies inside the range of the visible V."""
     say(f"[case] full extend {name}")
     wl, g, o = _full(name, gpu_device, full_cache)
@@ -699,7 +698,7 @@ def test_full_config_extend_every_element(pa, gpu_device, full_cache, name):
     e_full = float(err_rows[~leftover].max()) if (~leftover).any() else 0.0
     e_left = float(err_rows[leftover].max()) if leftover.any() else 0.0
     say(f"  {covered}: max abs err {err_rows.max():.3e} (rows of full tiles {e_full:.3e}, left-over rows {e_left:.3e}); "
-        f"work list: {n_tiles} row tiles, {n_items} items, {n_merge} tiles merged from parts")
+        f"work list: {n_tiles} row tiles, {n_items} items, {n_merge} pieces of the merge")
     assert err_rows.max() <= TOL[wl.dtype]
     # softmax weights are a convex combination: |out| can never exceed the largest |V| in the inputs
     vmax = max(float(np.abs(W.bf16_bits_to_f32(wl.pool_v)).max()), float(np.abs(W.bf16_bits_to_f32(wl.v_ext)).max()))
@@ -786,7 +785,7 @@ def test_extend_packs_leftover_rows_of_requests_with_a_common_prefix(pa, gpu_dev
     groups = len(set(wl.notes["tool_of_request"].tolist()))
     rows = wl.ext_len.astype(np.int64) * (wl.Hq // wl.Hkv)
     unpacked = int(((rows + 127) // 128).sum())
-    say(f"  tiles {n_tiles} (one request at a time: {unpacked}), items {n_items}, merged tiles {n_merge}; {groups} prefix groups")
+    say(f"  tiles {n_tiles} (one request at a time: {unpacked}), items {n_items}, pieces of the merge {n_merge}; {groups} prefix groups")
     assert overflow == 0 and n_tiles < unpacked
     pl_ref, si_ref = o.match()
     assert_match_equal(wl, pl, si, pl_ref, si_ref)
@@ -822,7 +821,7 @@ def test_extend_shares_tiles_between_requests_with_a_common_first_part(pa, gpu_d
     out = g.extend(pl, si, workspace=ws)
     torch.cuda.synchronize()
     n_tiles, n_items, n_merge, overflow = ws[:16].view(torch.int32).tolist()
-    say(f"  {wl.B} requests, tiles {n_tiles}, items {n_items}, merged tiles {n_merge}")
+    say(f"  {wl.B} requests, tiles {n_tiles}, items {n_items}, pieces of the merge {n_merge}")
     assert overflow == 0 and n_tiles < wl.B
     pl_ref, si_ref = o.match()
     assert_match_equal(wl, pl, si, pl_ref, si_ref)
@@ -854,7 +853,7 @@ def test_extend_random_decode_batches_against_the_oracle(pa, gpu_device, seed):
     out = g.extend(pl, si, workspace=ws)
     torch.cuda.synchronize()
     n_tiles, n_items, n_merge, overflow = ws[:16].view(torch.int32).tolist()
-    say(f"  tiles {n_tiles}, items {n_items}, merged {n_merge}")
+    say(f"  tiles {n_tiles}, items {n_items}, pieces of the merge {n_merge}")
     assert overflow == 0
     pl_ref, si_ref = o.match()
     assert_match_equal(wl, pl, si, pl_ref, si_ref)
@@ -896,15 +895,15 @@ def test_extend_random_shapes_against_the_oracle(pa, gpu_device, seed):
     assert_match_equal(wl, pl, si, pl_ref, si_ref)
     ref = o.extend(pl_ref, si_ref)
     err = np.abs(out_to_f64(out) - ref).max()
-    say(f"  tiles {n_tiles}, items {n_items}, merged {n_merge}; max abs err {err:.3e}")
+    say(f"  tiles {n_tiles}, items {n_items}, pieces of the merge {n_merge}; max abs err {err:.3e}")
     assert err <= TOL[wl.dtype]
 
 
 @pytest.mark.parametrize("case", ["many_requests", "many_tiles", "pack_256", "no_pack_300"])
 def test_extend_work_list_beyond_the_small_table_sizes(pa, gpu_device, case):
-    """The kernel that plans a launch keeps its tables in LDS for up to 1,024 requests and 3,072 row tiles and in
-    global memory beyond (more than 1,024 requests also keep their given order), and packs left-over rows in batches
-    of up to 256 requests: shapes on either side of these limits against the oracle."""
+    """The kernel that plans a launch orders up to 1,024 requests, whatever the number of their row tiles (a thread then
+    owns several), keeps more in the order given with its tables in global memory, and packs left-over rows in batches of
+    up to 256 requests: shapes on either side of these limits against the oracle."""
     say(f"[case] work list {case}")
     if case == "many_requests":
         wl = W.tiny_fp32(seed=11, B=1100, prefix=96, ext_lo=1, ext_hi=5, n_distract=2, Hq=8, Hkv=2, D=64,

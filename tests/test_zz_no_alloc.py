@@ -46,7 +46,7 @@ def test_static_scratch_entry_point_matches_the_one_with_a_workspace(gpu_device)
         diff = float((out.double() - ref.double()).abs().max())
         same = torch.equal(out.view(torch.int16 if wl.dtype == "bf16" else torch.int32),
                            ref.view(torch.int16 if wl.dtype == "bf16" else torch.int32))
-        print(f"  tiles merged from parts by pa_extend_attention: {merged}; max abs difference {diff:.3e}, bit-equal {same}", flush=True)
+        print(f"  pieces of the merge in pa_extend_attention: {merged}; max abs difference {diff:.3e}, bit-equal {same}", flush=True)
         assert diff <= TOL[wl.dtype]
         if merged == 0:
             assert same
