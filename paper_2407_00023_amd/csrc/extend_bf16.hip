@@ -11,7 +11,8 @@
 // key axis in tiles of kKT = 64 tokens: prefix positions first, then the extend tokens
 // (the same loop; only the row address differs); where there are at most 32 rows, its waves share the keys
 // instead (narrow tiles).  A planning kernel (extend_plan.hip) builds the list of work items per launch - row tile x part of
-// its key range - from the lengths on the device; the parts of a split tile are merged by a third kernel.
+// its key range - from the lengths on the device; the parts of a split tile are merged by a third kernel.  Small batches go
+// without list and merge: a workgroup finds its item from the lengths, the last one of a tile joins its parts (kDirect).
 //
 // Data movement.  K and V tiles go from global memory straight into LDS (16 bytes per
 // lane, no register staging), one tile ahead of the arithmetic, into a ring of LDS
@@ -36,6 +37,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "extend_plan.h"
 #include "fp8_rows.h"
@@ -167,6 +169,81 @@ __device__ __forceinline__ void read_k_block(bf16x8 (&kf)[KS], const unsigned (&
             : "memory");
 }
 
+// A store of 16 bytes that goes through to memory: the workgroup that joins the parts of a tile may run on another XCD, whose
+// L2 does not see this one's.  (The s_nop: a vector-ALU write of the data registers must stay two slots away.)
+__device__ __forceinline__ void store_through_16(float* p, float4 v) {
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    const f32x4 x = {v.x, v.y, v.z, v.w};
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(x) : "memory");
+}
+__device__ __forceinline__ float2 load_through_8(const float* p) {
+    const unsigned long long x = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float2(__uint_as_float(static_cast<unsigned>(x)), __uint_as_float(static_cast<unsigned>(x >> 32)));
+}
+__device__ __forceinline__ void store_through_8(float* p, float2 v) {
+    const unsigned long long x = static_cast<unsigned long long>(__float_as_uint(v.x)) | static_cast<unsigned long long>(__float_as_uint(v.y)) << 32;
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// What a workgroup of a launch without a work list needs to find its item (parts = 0: there is a work list).
+struct DirectArgs {
+    const int32_t *prefix_len, *ext_len, *ext_offsets, *slot_offsets;
+    unsigned* counter;  // per tile and KV head: parts finished; back to 0 with the last one
+    int32_t* hdr;
+    int B, parts, tile_rows, tiles, stride;
+};
+
+struct NoArgs {};
+
+// The item of a workgroup of a launch without a work list, in the form of a record of the list: the parts of the first
+// request's tiles, then the second's, and so on.  (Every request cuts all of its tiles into the same number of parts, so that
+// the workgroups without an item are the last ones: scattered between the others, they left compute units empty while others
+// had two items.)  *n_parts = parts of the tile, *tile = its number.  false: there is no such item.  Wave-uniform.
+__device__ __forceinline__ bool direct_item(const DirectArgs& a, int item, int G, int Hkv, int4& rec0, int4& rec1, int4& rec2, int* n_parts, int* tile) {
+    const int lane = threadIdx.x & 63;
+    int P = 0, E = 0, e0 = 0, so = 0;
+    if (lane < a.B) {
+        P = a.prefix_len[lane];
+        E = a.ext_len[lane];
+        e0 = a.ext_offsets[lane];
+        so = a.slot_offsets[lane];
+    }
+    // (a length that cannot fit counts as one that just does not: the sums stay small)
+    const int rows = min(max(E, 0), a.stride / G + 1) * G;
+    const int shortest = a.tile_rows == kNarrowRows ? kMinChunkNarrow : rows * Hkv <= kDirectJoinRows ? kDirectMinChunkWide : 2 * kDirectMinChunkWide;
+    const int parts = max(1, min(a.parts, (P + E + kKT - 1) / kKT / shortest)), tiles = (rows + a.tile_rows - 1) / a.tile_rows;
+    const int tiles_incl = wave_scan(tiles), rows_incl = wave_scan(rows), items_incl = wave_scan(tiles * parts);
+    const int n_tiles = __builtin_amdgcn_readlane(tiles_incl, 63), n_rows = __builtin_amdgcn_readlane(rows_incl, 63);
+    const int n_items = __builtin_amdgcn_readlane(items_incl, 63);
+    const bool over = n_tiles > a.tiles || n_rows > a.stride;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.hdr[0] = over ? 0 : n_tiles;
+        a.hdr[1] = over ? 0 : n_items;
+        a.hdr[2] = 0;
+        a.hdr[3] = over;
+        a.hdr[4] = over || n_items == n_tiles ? 0 : n_rows * a.parts;  // (at most)
+    }
+    if (over || item >= n_items) return false;
+    const int r = __popcll(__ballot(items_incl <= item));  // (the items of the requests up to this one are all before it)
+    auto of = [&](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(x, r); };
+    const int n_req = of(parts), local = item - (of(items_incl) - of(tiles) * n_req), t = local / n_req, j = local - t * n_req;
+    const int rP = of(P), all = of(rows);
+    const int row0 = t * a.tile_rows, rows_here = min(a.tile_rows, all - row0);
+    const int end = rP + (row0 + rows_here - 1) / G + 1, K = (end + kKT - 1) / kKT;
+    const int n = min(n_req, K);
+    if (j >= n) return false;
+    // (K < 2^24 key tiles, n <= 16: the products fit 32 bits)
+    const int lo = static_cast<int>(static_cast<unsigned>(K) * static_cast<unsigned>(j) / static_cast<unsigned>(n)) * kKT;
+    const int hi = min(end, static_cast<int>(static_cast<unsigned>(K) * static_cast<unsigned>(j + 1) / static_cast<unsigned>(n)) * kKT);
+    const int first = of(rows_incl) - all + row0;  // this tile's first row among the partial rows of a part
+    rec0 = make_int4(first, row0, lo, hi);
+    rec1 = make_int4(n > 1 ? j * a.stride + first : -1, rP, of(E), of(e0));
+    rec2 = make_int4(of(so), rows_here <= kNarrowRows ? 1 : 0, 0, 0);
+    *n_parts = n;
+    *tile = of(tiles_incl) - of(tiles) + t;
+    return true;
+}
+
 // LDS behind the K/V ring: the table of a shared tile's members (two ints each, one int more), two ints per wave, and, from
 // kLdsMl on, what the waves of a narrow tile leave for one another.
 constexpr int kLdsMl = ((2 * kTileRows + 1 + 2 * 4) * 4 + 15) & ~15;
@@ -174,14 +251,15 @@ constexpr int kLdsTail = kLdsMl + 4 * kNarrowRows * 8;
 
 // KV8: the pool holds one-byte codes and row exponents (fp8_rows.h) instead of bfloat16; its rows are decoded into the
 // bfloat16 tiles in LDS, and everything from there on is the same arithmetic.
-template <int D, bool KV8>
+// kDirect: a launch without a work list (DirectArgs, direct_item); a kernel of its own, so that the other keeps its registers and code.
+template <int D, bool KV8, bool kDirect>
 __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_kernel(
     const __hip_bfloat16* __restrict__ q_ext, const __hip_bfloat16* __restrict__ k_ext,
     const __hip_bfloat16* __restrict__ v_ext, const __hip_bfloat16* __restrict__ pool, const signed char* __restrict__ pool_exp,
     const int32_t* __restrict__ slot_idx, int Hq, int Hkv, int page_size, int page_shift, unsigned page_magic,
     int page_mshift, int num_slots, int fast_ok, float scale_log2e, __hip_bfloat16* __restrict__ out, const int32_t* __restrict__ hdr,
     const int4* __restrict__ item_tab, const int4* __restrict__ member_tab, float* __restrict__ part_o,
-    float* __restrict__ part_ml, unsigned long long* __restrict__ clk) {
+    float* __restrict__ part_ml, unsigned long long* __restrict__ clk, std::conditional_t<kDirect, DirectArgs, NoArgs> direct) {
     constexpr int NW = 4;                    // waves
     constexpr int MT = kTileRows;            // packed query rows per wide row tile, 32 per wave
     constexpr int NB = D / 32;               // MFMA row blocks of the head dimension in O^T
@@ -200,9 +278,16 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     // dealt round-robin to the 8 XCDs) serves one head and keeps its shared prefixes in L2
     const int g = blockIdx.x % Hkv;
     const int item = blockIdx.x / Hkv;
-    if (item >= hdr[1]) return;
-    const int4 rec0 = item_tab[3 * static_cast<size_t>(item)], rec1 = item_tab[3 * static_cast<size_t>(item) + 1];
-    const int4 rec2 = item_tab[3 * static_cast<size_t>(item) + 2];
+    int4 rec0, rec1, rec2;
+    [[maybe_unused]] int n_join = 0, join_tile = 0;  // parts of the tile, and its number, if its workgroups join them themselves
+    if constexpr (kDirect) {
+        if (!direct_item(direct, item, Hq / Hkv, Hkv, rec0, rec1, rec2, &n_join, &join_tile)) return;
+    } else {
+        if (item >= hdr[1]) return;
+        rec0 = item_tab[3 * static_cast<size_t>(item)];
+        rec1 = item_tab[3 * static_cast<size_t>(item) + 1];
+        rec2 = item_tab[3 * static_cast<size_t>(item) + 2];
+    }
     const int slot_off = rec2.x;
     const int row0 = rec0.y, kv_lo = rec0.z, kv_hi = rec0.w;
     const int prow = rec1.x;  // first row of this item's partial result; -1: the item covers all keys and writes the output
@@ -210,7 +295,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     const int G = Hq / Hkv;
     // a shared tile: rows of n_members requests with this prefix, laid end to end; after the common keys come the members'
     // extend tokens, member after member (unless only the first part of their prefixes is common: the tile ends there)
-    const int member0 = __builtin_amdgcn_readfirstlane(rec2.z), n_members = __builtin_amdgcn_readfirstlane(rec2.w);
+    const int member0 = __builtin_amdgcn_readfirstlane(rec2.z), n_members = kDirect ? 0 : __builtin_amdgcn_readfirstlane(rec2.w);
     const bool narrow = __builtin_amdgcn_readfirstlane(rec2.y) != 0;
     const bool shared = n_members > 0;
     const int rows_total = shared ? rec1.z : rec1.z * G;
@@ -235,6 +320,12 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     int* const s_mx0 = s_mseg + (MT + 1);
     int* const s_wave_own = s_mx0 + MT;  // per wave: the key range that holds the extend tokens of its rows' members
     float2* const s_ml = reinterpret_cast<float2*>(smem + kStages * STAGEB + kLdsMl);  // narrow tiles: (maximum, sum) per wave and row
+    // (a launch without a work list has no members: what is needed to join the parts of the tile, read behind the key loop)
+    if (kDirect && tid == 0) {
+        s_mseg[0] = n_join;
+        s_mseg[2] = join_tile;
+        s_mseg[3] = rec0.x;
+    }
     if (shared) {
         if (tid < n_members) {  // (a member has at least one row in the tile: there are at most MT)
             const int4 mem = member_tab[2 * (member0 + tid)];
@@ -591,6 +682,99 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         return (first >= P && !shared && (!KV8 || (fast_ok & 1))) ? 2 : 0;
     };
 
+    // ---- a launch without a work list: the parts of a tile are joined by the workgroup that finishes last (a counter per tile
+    // and KV head).  Nobody waits for anybody; partial results are stored through to memory and awaited before the count, and
+    // read past this XCD's L2, which may hold what an earlier call left in the workspace.  All threads; prow >= 0. ----
+    [[maybe_unused]] auto join_parts = [&]() __attribute__((always_inline)) {
+        if constexpr (kDirect) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            const int n = s_mseg[0];
+            if (tid == 0) s_mseg[1] = atomicInc(direct.counter + s_mseg[2] * Hkv + g, n - 1) == static_cast<unsigned>(n - 1);
+            __syncthreads();
+            if (!s_mseg[1]) return;
+            const size_t base = static_cast<size_t>(s_mseg[3]) * Hkv + static_cast<size_t>(g) * rows_here;
+            const size_t step = static_cast<size_t>(direct.stride) * Hkv;
+            // what each part of a row counts for: 2^(its maximum - the row's), over the row's sum (the LDS ring is free by now)
+            constexpr int kW = kDirectWideParts * MT;
+            static_assert(kMaxDirectParts * kNarrowRows <= kW && 2 * kW * 4 <= kStages * STAGEB, "fits the ring");
+            float* const s_w = reinterpret_cast<float*>(smem);  // [part][row]: maximum, then weight
+            float* const s_l = s_w + kW;                        // ... sum
+            auto weigh = [&]() __attribute__((always_inline)) {
+                for (int x = tid; x < rows_here * n; x += 256) {
+                    const int s = x / rows_here;
+                    const float2 ml = load_through_8(part_ml + 2 * (base + (x - s * rows_here) + s * step));
+                    s_w[x] = ml.x;
+                    s_l[x] = ml.y;
+                }
+                __syncthreads();
+                if (tid < rows_here) {
+                    float m = -INFINITY, l = 0.f;
+                    for (int s = 0; s < n; ++s) m = fmaxf(m, s_w[s * rows_here + tid]);  // (some part has seen a key)
+                    for (int s = 0; s < n; ++s) {
+                        const float w = __builtin_amdgcn_exp2f(s_w[s * rows_here + tid] - m);
+                        s_w[s * rows_here + tid] = w;
+                        l += w * s_l[s * rows_here + tid];
+                    }
+                    const float inv = 1.f / l;
+                    for (int s = 0; s < n; ++s) s_w[s * rows_here + tid] *= inv;
+                }
+                __syncthreads();
+            };
+            constexpr int V4 = D / 4;   // 16-byte pieces per partial row: one thread per (row, piece)
+            const int n_x = rows_here * V4;
+            auto store_row = [&](int x, float4 acc) __attribute__((always_inline)) {
+                const int rr = row0 + x / V4;
+                reinterpret_cast<uint2*>(out + ((e0 + rr / G) * Hq + g * G + rr % G) * static_cast<int64_t>(D))[x % V4] =
+                    make_uint2(pack_bf16x2(acc.x, acc.y), pack_bf16x2(acc.z, acc.w));
+            };
+            // kX (row, piece) pairs of a thread and kS parts of each in flight
+            auto sum_parts = [&](auto k_x, auto k_s, int x0, int s0, float4* acc, auto before_use) __attribute__((always_inline)) {
+                constexpr int kX = decltype(k_x)::value, kS = decltype(k_s)::value;
+                float2 a[kX][kS], b[kX][kS];
+#pragma unroll
+                for (int k = 0; k < kX; ++k) {
+                    const int x = min(x0 + 256 * k, n_x - 1);
+#pragma unroll
+                    for (int u = 0; u < kS; ++u) {
+                        const float* from = part_o + (base + x / V4 + min(s0 + u, n - 1) * step) * D + 4 * (x % V4);
+                        a[k][u] = load_through_8(from);
+                        b[k][u] = load_through_8(from + 2);
+                    }
+                }
+                before_use();
+#pragma unroll
+                for (int k = 0; k < kX; ++k) {
+                    const int x = min(x0 + 256 * k, n_x - 1);
+#pragma unroll
+                    for (int u = 0; u < kS; ++u) {
+                        const float w = s0 + u < n ? s_w[min(s0 + u, n - 1) * rows_here + x / V4] : 0.f;
+                        acc[k].x += w * a[k][u].x; acc[k].y += w * a[k][u].y; acc[k].z += w * b[k][u].x; acc[k].w += w * b[k][u].y;
+                    }
+                }
+            };
+            const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (n_x <= 256) {
+                // (few rows: everything a thread sums is asked for at once, the maxima and sums behind it)
+                static_assert(kMaxDirectParts == 16, "in one go");
+                float4 acc[1] = {zero};
+                sum_parts(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{}, tid, 0, acc, weigh);
+                if (tid < n_x) store_row(tid, acc[0]);
+            } else {
+                constexpr int kX = 4, kS = 4;
+                weigh();
+                for (int x0 = tid; x0 < n_x; x0 += 256 * kX) {
+                    float4 acc[kX] = {zero, zero, zero, zero};
+                    for (int s0 = 0; s0 < n; s0 += kS)
+                        sum_parts(std::integral_constant<int, kX>{}, std::integral_constant<int, kS>{}, x0, s0, acc, [] {});
+#pragma unroll
+                    for (int k = 0; k < kX; ++k)
+                        if (x0 + 256 * k < n_x) store_row(x0 + 256 * k, acc[k]);
+                }
+            }
+        }
+    };
+
     // ---- narrow tiles: at most 32 rows, so that one wave's registers hold them all, and the four waves take the keys in
     // turn, 32 at a time, each through a quarter of the LDS ring of its own: no barrier until the end, where the four partial
     // results are joined.  What bounds them is memory (a few rows make little arithmetic): eight waves of a compute unit have
@@ -708,7 +892,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         const int jr = tid >> 3, sub = tid & 7;  // eight threads per row
         const int64_t out_row = __shfl(my_out, jr);
         __syncthreads();
-        if (jr >= rows_here) return;
+        if (jr < rows_here) {
         float2 ml[NW];
         float m = -INFINITY, l = 0.f;
 #pragma unroll
@@ -738,11 +922,19 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                 v.x = pack_bf16x2(acc.x * inv, acc.y * inv);
                 v.y = pack_bf16x2(acc.z * inv, acc.w * inv);
                 reinterpret_cast<uint2*>(out + out_row * D)[c] = v;
+            } else if constexpr (kDirect) {
+                store_through_16(part_o + part_row * D + 4 * c, acc);
             } else {
                 reinterpret_cast<float4*>(part_o + part_row * D)[c] = acc;
             }
         }
-        if (prow >= 0 && sub == 0) reinterpret_cast<float2*>(part_ml)[part_row] = make_float2(m, l);
+        if (prow >= 0 && sub == 0) {
+            if constexpr (kDirect) store_through_8(part_ml + 2 * part_row, make_float2(m, l));
+            else reinterpret_cast<float2*>(part_ml)[part_row] = make_float2(m, l);
+        }
+        }
+        if constexpr (kDirect)
+            if (prow >= 0) join_parts();
         return;
     }
 
@@ -904,8 +1096,9 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     }
     // ---- epilogue: lane holds, for block b and register i, head-dim element 32 b + 8 (i / 4) + 4 hh + i % 4 ----
     const float l_row = row_sum(l_run);
-    if (!row_ok) return;
-    if (prow < 0) {
+    if (!row_ok) {
+        // (no row of its own: helps to join the parts, below)
+    } else if (prow < 0) {
         const float inv = 1.f / l_row;
         __hip_bfloat16* orow = out + ((e0_row + qi) * Hq + qh) * static_cast<int64_t>(D);
 #pragma unroll
@@ -919,14 +1112,36 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
             }
     } else {
         const size_t part_row = static_cast<size_t>(prow) * Hkv + static_cast<size_t>(g) * rows_here + (wave * 32 + n);
-        float* po = part_o + part_row * D;
+        if constexpr (kDirect) {
+            // (through LDS, the pieces of a row XORed with its number as where narrow tiles join their waves: the stores that go
+            // through to memory then write whole lines; the ring is free, the last tile ended with a barrier)
+            float4* const mine = reinterpret_cast<float4*>(smem) + (wave * 32 + n) * (D / 4);
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+            for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-                *reinterpret_cast<float4*>(po + 32 * b + 8 * q4 + 4 * hh) = make_float4(
-                    oacc[b][4 * q4 + 0], oacc[b][4 * q4 + 1], oacc[b][4 * q4 + 2], oacc[b][4 * q4 + 3]);
-        if (hh == 0) reinterpret_cast<float2*>(part_ml)[part_row] = make_float2(m_run, l_row);
+                for (int q4 = 0; q4 < 4; ++q4)
+                    mine[(8 * b + 2 * q4 + hh) ^ (n & (D / 4 - 1))] = make_float4(oacc[b][4 * q4], oacc[b][4 * q4 + 1], oacc[b][4 * q4 + 2], oacc[b][4 * q4 + 3]);
+            if (hh == 0) store_through_8(part_ml + 2 * part_row, make_float2(m_run, l_row));
+        } else {
+            float* po = part_o + part_row * D;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    *reinterpret_cast<float4*>(po + 32 * b + 8 * q4 + 4 * hh) = make_float4(
+                        oacc[b][4 * q4 + 0], oacc[b][4 * q4 + 1], oacc[b][4 * q4 + 2], oacc[b][4 * q4 + 3]);
+            if (hh == 0) reinterpret_cast<float2*>(part_ml)[part_row] = make_float2(m_run, l_row);
+        }
+    }
+    if constexpr (kDirect) {
+        if (prow < 0) return;
+        __syncthreads();
+        float* const po = part_o + (static_cast<size_t>(prow) * Hkv + static_cast<size_t>(g) * rows_here) * D;
+        for (int x = tid; x < rows_here * (D / 4); x += 256) {
+            const int row = x / (D / 4), c = x % (D / 4);
+            store_through_16(po + 4 * static_cast<size_t>(x), reinterpret_cast<const float4*>(smem)[row * (D / 4) + (c ^ (row & 31 & (D / 4 - 1)))]);
+        }
+        join_parts();
     }
 }
 
@@ -1032,7 +1247,7 @@ static void page_divider(int d, int* shift, unsigned* magic, int* mshift) {
 template <int D, bool KV8>
 static int launch_extend(const ExtendPlan& p, const PlanTables& t, const void* q_ext, const void* k_ext, const void* v_ext,
                          const void* kv_pool, const int32_t* slot_idx, int Hq, int Hkv, int page_size, int64_t num_slots, int64_t T_total,
-                         float scale_log2e, void* out, unsigned long long* clk, hipStream_t stream) {
+                         float scale_log2e, void* out, unsigned long long* clk, const DirectArgs& direct, hipStream_t stream) {
     // the K/V ring and what lies behind it (fp8 pool: rounded up to 256 bytes, then one 32-bit word per lane, load block of a
     // wave and tensor for the row exponents)
     constexpr size_t lds_plain = static_cast<size_t>(kStages) * 2 * kKT * D * 2 + kLdsTail;
@@ -1040,7 +1255,7 @@ static int launch_extend(const ExtendPlan& p, const PlanTables& t, const void* q
     int page_shift = -1, page_mshift = 0;
     unsigned page_magic = 0;
     page_divider(page_size, &page_shift, &page_magic, &page_mshift);
-    const dim3 grid(static_cast<unsigned>(p.items_cap) * Hkv);
+    const dim3 grid(static_cast<unsigned>(direct.parts > 0 ? direct.tiles * direct.parts : p.items_cap) * Hkv);
     // The hand-scheduled tiles multiply in 24 bits and take a power-of-two page size.  They address pool rows by
     // 32-bit byte offsets where the pool is below 4 GB (1); by row numbers in units of 256 bytes, the byte address
     // formed in 64 bits, where it is larger (2: D = 128, a pool base aligned to 256 bytes, up to 64 GB).  The extend
@@ -1061,15 +1276,19 @@ static int launch_extend(const ExtendPlan& p, const PlanTables& t, const void* q
     const int fast_ok = KV8 ? (ext_ok ? 1 : 0) | (pool8_ok ? 2 : 0) : ok32 ? 1 : ok64 ? 2 : 0;
     // (fp8 pool: the row exponents lie behind the codes)
     const signed char* pool_exp = KV8 ? static_cast<const signed char*>(kv_pool) + static_cast<size_t>(num_slots) * 2u * Hkv * D : nullptr;
-    {
+    const auto launch = [&](auto kernel, auto args) {
         ProfScope prof(kProfExtend, stream);
-        hipLaunchKernelGGL((extend_bf16_kernel<D, KV8>), grid, dim3(256), lds_bytes, stream,
+        hipLaunchKernelGGL(kernel, grid, dim3(256), lds_bytes, stream,
                            static_cast<const __hip_bfloat16*>(q_ext), static_cast<const __hip_bfloat16*>(k_ext),
                            static_cast<const __hip_bfloat16*>(v_ext), static_cast<const __hip_bfloat16*>(kv_pool), pool_exp, slot_idx,
                            Hq, Hkv, page_size, page_shift, page_magic, page_mshift, static_cast<int>(num_slots), fast_ok,
-                           scale_log2e, static_cast<__hip_bfloat16*>(out), t.hdr, t.item, t.member, t.part_o, t.part_ml, clk);
-    }
-    {  // whether any tile was split is known on the device only: otherwise the blocks leave at once
+                           scale_log2e, static_cast<__hip_bfloat16*>(out), t.hdr, t.item, t.member, t.part_o, t.part_ml, clk, args);
+    };
+    if (direct.parts > 0) {
+        launch(extend_bf16_kernel<D, KV8, true>, direct);
+    } else {
+        launch(extend_bf16_kernel<D, KV8, false>, NoArgs{});
+        // whether any tile was split is known on the device only: otherwise the merge's blocks leave at once
         ProfScope prof(kProfMerge, stream);
         const int64_t most = static_cast<int64_t>(p.chunks_cap) * Hkv;
         hipLaunchKernelGGL((extend_merge_kernel<D>), dim3(static_cast<unsigned>(most < 2048 ? most : 2048)), dim3(256), 0, stream,
@@ -1079,6 +1298,9 @@ static int launch_extend(const ExtendPlan& p, const PlanTables& t, const void* q
 }
 
 }  // namespace pa
+
+// Counters of launches without a work list, per call in flight: part of the code object, zero when it is loaded and after every launch.
+static __device__ unsigned g_join_counters[pa::kCallSets][pa::kDirectSlots];
 
 // Process-wide switch: 0 = every request gets row tiles of its own (no grouping by equal slots).
 static std::atomic<int> g_row_sharing{1};
@@ -1120,9 +1342,18 @@ static int run_extend_bf16(pa::ExtendPlan p, const void* q_ext, const void* k_ex
     // with the clock probe on, a few workgroups also add their cycle counts to two counters in the header
     unsigned long long* clk = prof_clock_enabled() ? reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(workspace) + kClockProbeOffset) : nullptr;
     const float scale_log2e = scale * 1.4426950408889634f;
-    launch_extend_plan(p, t, prefix_len, ext_len, ext_offsets, slot_offsets, slot_idx, B, Hq / Hkv, stream);
+    DirectArgs direct{prefix_len, ext_len, ext_offsets, slot_offsets, nullptr, t.hdr, B, p.direct_parts, p.direct_tile_rows, p.direct_tiles,
+                      p.direct_stride};
+    if (direct.parts > 0) {
+        void* base = nullptr;
+        int set = -1;
+        if (const int rc = call_set_for(kSetsExtend, "pa_extend_attention", g_join_counters, stream, &base, &set)) return rc;
+        if (set < 0) direct.parts = 0;  // (more captured calls than sets: with a work list)
+        else direct.counter = static_cast<unsigned*>(base) + static_cast<size_t>(set) * kDirectSlots;
+    }
+    if (direct.parts == 0) launch_extend_plan(p, t, prefix_len, ext_len, ext_offsets, slot_offsets, slot_idx, B, Hq / Hkv, stream);
     const auto launch = D == 64 ? (kv8 ? launch_extend<64, true> : launch_extend<64, false>) : (kv8 ? launch_extend<128, true> : launch_extend<128, false>);
-    launch(p, t, q_ext, k_ext, v_ext, kv_pool, slot_idx, Hq, Hkv, page_size, num_slots, T, scale_log2e, out, clk, stream);
+    launch(p, t, q_ext, k_ext, v_ext, kv_pool, slot_idx, Hq, Hkv, page_size, num_slots, T, scale_log2e, out, clk, direct, stream);
     PA_HIP(hipGetLastError());
     return PA_OK;
 }

@@ -23,6 +23,11 @@ struct ExtendPlan {
     int first_part;  // ... of requests of up to this many rows also where they have only the first part of it in common (0: not)
     int tile_parts;  // parts of one tile at most
     int chunk_rows;  // rows per piece of the merge
+    // small batches: no work list is built, every workgroup finds its own item (see make_direct in extend_plan.hip)
+    int direct_parts;      // parts of a tile at most; 0: a work list
+    int direct_tile_rows;  // rows of a tile
+    int direct_tiles;      // upper bound on the number of tiles
+    int direct_stride;     // rows of partial results of one part of all tiles, per KV head
     size_t off_tile, off_member, off_item, off_chunk, off_part_o, off_part_ml, total;
 };
 
@@ -33,9 +38,29 @@ constexpr int kRounds = 2;        // the plan aims at about this many work items
                                   // results and their merge - with 1.5 its last round ran thin; the rest did not care)
 constexpr int kRoundsStatic = 1;  // ... with the library's own scratch buffer as workspace (fewer partial results)
 
+constexpr int kMinChunkNarrow = 4;      // a part of a narrow tile has at least this many key tiles: 64 keys for each of its waves
+constexpr int kDirectMinChunkWide = 8;  // ... of a wide one in a launch without a work list, or twice as many where the rows of a
+constexpr int kDirectJoinRows = 2048;   // request, in all KV heads, are more than this: the partial results are stored through to
+                                        // memory and read again (100 to 300 new tokens behind 2,200 keys, 8 KV heads, 46.7 us, with
+                                        // parts of 8 50.8; 20 to 60 new tokens 36.3, with parts of 16 43.4)
+constexpr int kMaxDirectParts = 16;     // parts of a tile at most in such a launch ...
+constexpr int kDirectWideParts = 4;     // ... and of a wide one
+constexpr int kDirectSlots = 512;  // counters of the tiles of a direct launch (tile x KV head), per call
+
+// Inclusive prefix sum over the wave, by the cross-lane moves of the vector ALU (rows of 16 lanes, then row to row).
+__device__ __forceinline__ int wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
 // Workspace: a header of 256 bytes - hdr[0] = row tiles, hdr[1] = work items, hdr[2] = pieces of the merge, hdr[3] = 1 if
-// the batch on the device does not fit the plan (nothing is computed then), hdr[4] = rows of partial results, per KV head - and
-// tables of int4:
+// the batch on the device does not fit the plan (nothing is computed then), hdr[4] = rows of partial results, per KV head (without a
+// work list: at most that many) - and tables of int4:
 //   member[2 m]     = (first row among its group's packed rows, first extend token, first packed row of the request,
 //                      extend length)
 //   member[2 m + 1] = (extend tokens of the group's members before it, 0, 0, 0)

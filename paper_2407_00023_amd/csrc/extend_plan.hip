@@ -35,8 +35,7 @@ namespace pa {
 constexpr int kWgSlots = 512;            // workgroups resident at once: two on each of the 256 compute units
 constexpr int kMinChunkTiles = 16;       // never split below this many key tiles (1,024 keys) per part (with 512 keys a decode
                                          // batch's step took 3 % longer) ...
-constexpr int kMinChunkCommon = 8;       // ... unless the tile leaves partial results anyway ...
-constexpr int kMinChunkNarrow = 4;       // ... or is narrow: 64 keys for each of its waves
+constexpr int kMinChunkCommon = 8;       // ... unless the tile leaves partial results anyway (or is narrow: kMinChunkNarrow)
 constexpr int kItemOverhead = 4;         // fixed cost of a work item, in key tiles (its prologue and epilogue)
 constexpr int kMaxParts = 64;            // parts of one tile at most
 constexpr int kSortMax = 1024;           // ... and up to this many are ordered
@@ -56,6 +55,41 @@ constexpr int kProbes = 12;              // depths looked at for common first pa
 __device__ __forceinline__ constexpr int probe_depth(int k) {
     constexpr int in512[kProbes] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
     return kPackMinPrefix * in512[k];
+}
+
+// Small batches need no work list: where all tiles together fill the chip once at most, a workgroup can find its item - the
+// part w % parts of tile w / parts, the tiles counted request by request - from the lengths alone, and the workgroup that
+// finishes a tile last joins its parts.  That saves the launches of the planner and of the merge (13 and 5 us of the 42 of a
+// step of four decode requests) and gives up what the planner knows: rows of different requests never share a tile, so a common
+// prefix is read once per request instead of once (from the L2s, which hold it).  Measured, steps in us, list | direct: decode
+// behind 1,800 common keys and up to 3,000 own ones, 1 request 30.1 | 23.7, 4 39.1 | 28.0, 6 44.6 | 31.6; 20 to 60 new tokens
+// behind 2,200 keys, 1 42.6 | 36.3, 4 50.4 | 38.3; 100 to 300 new tokens behind 1,000 keys, 2 69.0 | 36.2, 4 79.8 | 37.8; behind
+// 2,200 keys, 1 48.5 | 47.9.  Hence the limits:
+constexpr int kDirectMaxB = 6;             // more requests have more to share
+constexpr int kDirectFewRows = 16;         // rows per request on average: up to this many in narrow tiles; more, but too few not to
+                                           // be shared over a common first part (first_part_rows): with a work list
+constexpr int kDirectKeyTilesNarrow = 16;  // key tiles per workgroup slot, at the longest lengths the host was told ...
+constexpr int kDirectKeyTilesWide = 10;    // ... (20 to 60 new tokens of 6 requests behind 3,400 keys, 11 a slot: 55.1 | 58.7)
+// and no more than kDirectWideParts parts of a tile of 128 rows where a list would make more: one workgroup joins them, 64 KB a part.
+static void make_direct(ExtendPlan& p, int B, int64_t rows, int64_t max_kv_len, int Hkv, int D) {
+    p.direct_parts = 0;
+    if (B < 1 || B > kDirectMaxB) return;
+    const bool few = rows <= int64_t{kDirectFewRows} * B;
+    if (!few && rows <= int64_t{first_part_rows(D)} * B) return;
+    const int tile_rows = few ? kNarrowRows : kTileRows;
+    const int64_t tiles = rows / tile_rows + B, key_tiles = (max_kv_len + kKT - 1) / kKT, per_tile = p.slots / tiles;
+    if (per_tile < 1 || tiles * Hkv > kDirectSlots || tiles * key_tiles > int64_t{p.slots} * (few ? kDirectKeyTilesNarrow : kDirectKeyTilesWide)) return;
+    const auto least = [](int64_t a, int64_t b) { return a < b ? a : b; };
+    if (!few && least(per_tile, key_tiles / kMinChunkTiles) > kDirectWideParts) return;
+    // (wide tiles: one workgroup on a compute unit; a second one there slows the first by what it does itself)
+    int64_t parts = least(least(few ? per_tile : per_tile / 2, key_tiles / (few ? kMinChunkNarrow : kDirectMinChunkWide)), few ? kMaxDirectParts : kDirectWideParts);
+    parts = least(parts, p.tile_parts);
+    if (parts < 1) parts = 1;
+    if (p.prows_cap / parts < rows) return;
+    p.direct_parts = static_cast<int>(parts);
+    p.direct_tile_rows = tile_rows;
+    p.direct_tiles = static_cast<int>(tiles);
+    p.direct_stride = static_cast<int>(p.prows_cap / parts);
 }
 
 static inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -103,6 +137,7 @@ ExtendPlan make_extend_plan(int B, int64_t T, int64_t max_kv_len, int Hq, int Hk
         p.total = p.off_part_ml + up256(head_rows * 2 * sizeof(float));
         if (!p.first_part || limit == 0 || p.total <= limit) break;
     }
+    make_direct(p, B, rows, max_kv_len, Hkv, D);
     return p;
 }
 
@@ -125,17 +160,6 @@ struct PlanArgs {
 // them is another round trip to host memory.
 __device__ __forceinline__ void touch_args(const PlanArgs& a) {
     asm volatile("" ::"s"(a.prefix_len), "s"(a.hdr), "s"(a.item), "s"(a.chunk), "s"(a.tile_parts), "s"(a.chunk_rows));
-}
-
-// Inclusive prefix sum over the wave, by the cross-lane moves of the vector ALU (rows of 16 lanes, then row to row).
-__device__ __forceinline__ int wave_scan(int x) {
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
-    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
-    return x;
 }
 
 // Exclusive prefix sums of N ints per thread over the workgroup, and their totals: a scan inside each wave, then the

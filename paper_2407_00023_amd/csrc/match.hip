@@ -15,8 +15,6 @@
 // prompts of 2,650 tokens over four edges of 512 each 150 -> 24 us; 64 prompts over three or four edges 18 -> 9; a path of
 // 541 nodes (32 prompts of 8,483 tokens) 41 -> 23; one long edge of 16,384 tokens (16 prompts) 24 -> 13; the smallest call
 // 13 -> 5.
-#include <mutex>
-
 #include "common.h"
 
 namespace pa {
@@ -98,8 +96,6 @@ constexpr int kMaxW = 16;        // workgroups per request at most; a longer pat
 constexpr int kMultiMaxB = 256;  // batches of up to this many requests take this form
 constexpr int kMultiWgs = 1024;  // ... with up to this many workgroups (four on a compute unit)
 constexpr int kWideMaxB = 1024;  // one workgroup per request: wide windows up to this many requests
-constexpr int kStreamSets = 128; // sets of summaries and counters for calls on streams, two to a stream ...
-constexpr int kGraphSets = 128;  // ... and for captured calls, one each
 struct MatchSummary {
     int32_t f_pos, f_parent;     // position of the first node of the chain (-1: none), the parent it names
     int32_t exit_pos, exit_cur;  // matched length and current node after the chain
@@ -680,61 +676,8 @@ __global__ __launch_bounds__(kT, kPos == 4 ? 4 : 8) void match_prefixes_kernel(D
 }  // namespace pa
 
 // Summaries and counters of the multi-workgroup form: part of the library's code object (each GPU holds its own copy;
-// in host code the array's name is only a handle for hipGetSymbolAddress).  No two calls that can be in flight at once may
-// meet in one set.  Calls on one stream follow one another, so a stream has sets of its own (two in turn: a new stream may be
-// given the handle of one just destroyed), those of the stream that has not matched for longest going to a new one.  A
-// captured call keeps its set for good, since its graph may be replayed at any time beside any other call (two replays of one
-// captured call would meet in its output as well); where no such set is left, it takes the form without shared state.
-static __device__ pa::MatchScratch g_match_scratch[pa::kStreamSets + pa::kGraphSets];
-
-namespace {
-constexpr int kMaxDevices = 64;
-struct DeviceSets {
-    pa::MatchScratch* base = nullptr;
-    struct { const void* stream; uint64_t used; unsigned calls; } of[pa::kStreamSets / 2] = {};  // (used = 0: free)
-    uint64_t clock = 0;
-    int captured = 0;
-};
-std::mutex g_ms_mu;
-DeviceSets g_ms[kMaxDevices];
-
-// The set for a call on `stream` of the current device; *out = nullptr: none.
-int match_scratch_for(hipStream_t stream, pa::MatchScratch** out) {
-    *out = nullptr;
-    int dev = -1;
-    PA_HIP(hipGetDevice(&dev));
-    PA_REQUIRE(dev >= 0 && dev < kMaxDevices, "pa_match_prefixes: device ordinal %d not supported", dev);
-    const void* key = stream == hipStreamLegacy ? nullptr : static_cast<const void*>(stream);
-    static thread_local char this_thread;
-    if (stream == hipStreamPerThread) key = &this_thread;  // (one handle, a stream for every thread)
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (key != nullptr) PA_HIP(hipStreamIsCapturing(stream, &capture));  // (the default stream cannot be captured)
-    std::lock_guard<std::mutex> lk(g_ms_mu);
-    DeviceSets& d = g_ms[dev];
-    if (d.base == nullptr) {
-        void* ptr = nullptr;
-        PA_HIP(hipGetSymbolAddress(&ptr, HIP_SYMBOL(g_match_scratch)));
-        PA_REQUIRE(ptr != nullptr, "pa_match_prefixes: no address for the library's scratch array");
-        d.base = static_cast<pa::MatchScratch*>(ptr);
-    }
-    if (capture != hipStreamCaptureStatusNone) {
-        if (d.captured < pa::kGraphSets) *out = d.base + pa::kStreamSets + d.captured++;
-        return PA_OK;
-    }
-    int at = 0;
-    for (int i = 0; i < pa::kStreamSets / 2; ++i) {
-        if (d.of[i].used != 0 && d.of[i].stream == key) {
-            at = i;
-            break;
-        }
-        if (d.of[i].used < d.of[at].used) at = i;
-    }
-    d.of[at].stream = key;
-    d.of[at].used = ++d.clock;
-    *out = d.base + 2 * at + (d.of[at].calls++ & 1);
-    return PA_OK;
-}
-}  // namespace
+// in host code the array's name is only a handle for hipGetSymbolAddress).
+static __device__ pa::MatchScratch g_match_scratch[pa::kCallSets];
 
 extern "C" int pa_match_prefixes(const pa_tree* tree, const int32_t* tokens, const int32_t* offsets, int B,
                                  int32_t* prefix_len, int32_t* slot_idx, void* stream) {
@@ -750,7 +693,13 @@ extern "C" int pa_match_prefixes(const pa_tree* tree, const int32_t* tokens, con
     // beyond that of 512, eight on a unit.  Measured (us, 1,024 | 512): 257 requests with paths of 250 nodes in 2,100 tokens
     // 19.3 | 25.8, of 540 in 8,448 51 | 60; 1,024 of these 81 | 87; short paths the same.
     pa::MatchScratch* scratch = nullptr;
-    if (B <= pa::kMultiMaxB && (rc = match_scratch_for(static_cast<hipStream_t>(stream), &scratch)) != PA_OK) return rc;
+    if (B <= pa::kMultiMaxB) {
+        void* base = nullptr;
+        int set = -1;
+        rc = pa::call_set_for(pa::kSetsMatch, "pa_match_prefixes", HIP_SYMBOL(g_match_scratch), static_cast<hipStream_t>(stream), &base, &set);
+        if (rc != PA_OK) return rc;
+        if (set >= 0) scratch = static_cast<pa::MatchScratch*>(base) + set;
+    }
     {
         pa::ProfScope prof(pa::kProfMatch, static_cast<hipStream_t>(stream));
         if (scratch != nullptr) {

@@ -466,3 +466,70 @@ def test_hot_path_calls_refuse_what_is_no_device_tensor():
         binding.append_kv(x, i32[:1], x, x, num_slots=1)             # page_size is required
     with pytest.raises(TypeError):
         binding.extend_attention(x, x, x, x, i32, i32, i32, i32, i32, 1.0, page_size=1, num_slots=1, max_kv_len=1)
+
+
+# launches without a work list: up to 6 requests of up to 16 rows each on average (narrow tiles) or of more than 48 (64 with
+# heads of 64; tiles of 128 rows), tiles cut from 256 (narrow) and 512 or 1,024 keys on, up to 16 and 4 parts
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,P,E,Hq,Hkv,D,page", [
+    ("bf16", [0], [1], 4, 1, 128, 16), ("bf16", [511], [1], 8, 2, 128, 16), ("bf16", [512], [4], 8, 2, 128, 1),
+    ("bf16", [255, 4095, 4096, 0, 7, 5000], [1] * 6, 8, 2, 128, 16), ("bf16", [300] * 7, [1] * 7, 8, 2, 128, 16),
+    ("bf16", [900, 0, 3000], [0, 11, 1], 8, 2, 64, 48), ("bf16", [700, 20], [1, 23], 32, 8, 64, 16),
+    ("bf16", [0], [13], 8, 2, 128, 16), ("bf16", [1023 - 40, 1024 - 40], [40, 40], 8, 2, 128, 16),
+    ("bf16", [2100, 5], [33, 64], 8, 1, 128, 16), ("bf16", [2400, 600, 0], [300, 97, 1], 16, 8, 64, 1),
+    ("bf16", [0, 0, 100], [400, 0, 250], 8, 2, 128, 64), ("bf16", [1100] * 6, [40] * 6, 8, 2, 128, 24),
+    ("bf16_kv8", [700, 1500], [1, 2], 8, 2, 128, 16), ("bf16_kv8", [1400, 9], [70, 33], 8, 2, 64, 16),
+    ("bf16_kv8", [1400, 9], [70, 33], 8, 2, 128, 16)])
+def test_extend_of_small_batches(pa, gpu_device, dtype, P, E, Hq, Hkv, D, page):
+    assert _extend(pa, gpu_device, dtype, P, E, Hq, Hkv, D, page) <= TOL["bf16"]
+
+
+@pytest.mark.gpu
+def test_small_batches_on_streams_and_in_graphs(pa, gpu_device):
+    """Small batches cut into parts that their workgroups join through counters of the library's, on four streams at once, in
+    more captured calls than the library keeps counters for, and on replays beside eager calls: every result equals the eager one
+    bit for bit, but for captured calls beyond the counters, which build a work list: within the tolerance."""
+    rng = np.random.default_rng(3)
+    Hq, Hkv, D, page, nslots = 8, 2, 128, 16, 8192
+    pool = torch.randn(pa.kv_pool_bytes(nslots, Hkv, D, torch.bfloat16, page) // 2, device=gpu_device).to(torch.bfloat16).view(torch.uint8)
+    tt = lambda a: torch.from_numpy(np.asarray(a, np.int32)).to(gpu_device)
+
+    def batch(P, E):
+        off, eo = np.concatenate([[0], np.cumsum(np.add(P, E))]), np.concatenate([[0], np.cumsum(E)])
+        x = lambda h: torch.randn(int(eo[-1]), h, D, device=gpu_device).to(torch.bfloat16)
+        b = dict(a=[x(Hq), x(Hkv), x(Hkv), pool, tt(rng.permutation(nslots)[:off[-1]]), tt(off), tt(P), tt(E), tt(eo), D ** -0.5])
+        kv = int(np.add(P, E).max())
+        b["kw"] = dict(page_size=page, num_slots=nslots, max_kv_len=kv, out=torch.empty_like(b["a"][0]), workspace=torch.zeros(
+            pa.extend_workspace_bytes(len(P), int(eo[-1]), kv, Hq, Hkv, D, torch.bfloat16), dtype=torch.uint8, device=gpu_device))
+        b["want"] = pa.extend_attention(*b["a"], **b["kw"]).clone()
+        return b
+
+    batches = [batch([1500, 700], [1, 3]), batch([2000], [90]), batch([900, 10, 2500], [1, 1, 2]), batch([1200, 1100], [40, 30])]
+    streams = [torch.cuda.Stream() for _ in batches]
+    torch.cuda.synchronize()
+    graph, n = torch.cuda.CUDAGraph(), 40
+    outs = [[torch.empty_like(b["want"]) for b in batches] for _ in range(n)]
+    with torch.cuda.graph(graph):
+        for k in range(n):
+            for b, o in zip(batches, outs[k]):
+                pa.extend_attention(*b["a"], **dict(b["kw"], out=o))
+    for k in range(4):
+        print(f"[case] small batches on streams and in graphs, round {k}", flush=True)
+        for o in outs:
+            for x in o:
+                x.zero_()
+        for b in batches:
+            b["kw"]["out"].zero_()
+        torch.cuda.synchronize()
+        for b, s in zip(batches, streams):
+            with torch.cuda.stream(s):
+                for _ in range(20):
+                    pa.extend_attention(*b["a"], **b["kw"])
+        torch.cuda.synchronize()
+        for b in batches:
+            assert torch.equal(b["kw"]["out"], b["want"])
+        graph.replay()
+        torch.cuda.synchronize()
+        for i, o in enumerate(outs):
+            for b, x in zip(batches, o):
+                assert torch.equal(x, b["want"]) if i < 8 else (x.float() - b["want"].float()).abs().max() <= TOL["bf16"]
