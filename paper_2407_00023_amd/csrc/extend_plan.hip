@@ -27,8 +27,12 @@
 // What bounds it: one workgroup's chain of dependent steps - two round trips to memory, about twelve barriers, for common
 // first parts one more round trip and six barriers - so equal keys are found through hash tables in LDS instead of all-pairs comparisons, a
 // scan costs one barrier, and small batches use four waves.  Kernel times against a planner that
-// compared all pairs in sixteen waves (us): 12 requests 14 -> 7, 64 requests 18 -> 10, 256 decode requests 51 -> 23.
+// compared all pairs in sixteen waves (us): 12 requests 14 -> 7, 64 requests 18 -> 10, 256 decode requests 51 -> 21.  Counted in
+// cycles, 256 decode requests: lengths and slots from memory 8,400, whole prefixes 3,200, probes 6,000, places compared 12,000 (3,000
+// of them for 8 requests: one compute unit fetches 14 lines per request), order 4,300, tiles and items 15,000.
 #include "extend_plan.h"
+
+#include <type_traits>
 
 namespace pa {
 
@@ -148,6 +152,13 @@ PlanTables plan_tables(const ExtendPlan& p, void* workspace) {
             reinterpret_cast<float*>(ws + p.off_part_ml)};
 }
 
+// Where a pair (place, slot) is looked for in a table in LDS of a power of two of entries.  (One multiplication: the 64-bit mix
+// that the tree's tables use costs this kernel, which forms twelve of them per request, 2,500 cycles.)
+__device__ __forceinline__ unsigned lds_hash(unsigned place, unsigned slot) {
+    const unsigned x = (slot ^ (place << 24) ^ (place >> 8)) * 0x9E3779B1u;
+    return x ^ (x >> 15);
+}
+
 struct PlanArgs {
     const int32_t *prefix_len, *ext_len, *ext_offsets, *slot_offsets, *slot_idx;
     int32_t* hdr;
@@ -200,9 +211,9 @@ struct TileDesc {
 };
 
 // The second half of every planner: costs, parts, items and pieces of the merge of tiles [0, n_all), of which n_rows are row
-// tiles.  describe(t) says what tile t is.
+// tiles.  describe(t) says what tile t is; tile_tab: room for what own-key tiles look up of their shared tile.
 template <int NT, class Describe>
-__device__ __forceinline__ void emit_items(const PlanArgs& a, int n_rows, int n_all, bool over, Describe describe) {
+__device__ __forceinline__ void emit_items(const PlanArgs& a, int n_rows, int n_all, bool over, int2* tile_tab, Describe describe) {
     __shared__ int s_cost[NT / 64];
     __shared__ int s_sum[3][NT / 64];
     const int tid = threadIdx.x;
@@ -279,7 +290,7 @@ __device__ __forceinline__ void emit_items(const PlanArgs& a, int n_rows, int n_
         for (int t = t_lo; t < t_hi; ++t) {
             const TileDesc d = tile_desc(t);
             const int n = parts_of(d);
-            if (d.partial_only && sub == 0) a.tile[t] = make_int2(n, prow);
+            if (d.partial_only && sub == 0) tile_tab[t] = make_int2(n, prow);
             prow += n > 1 || d.partial_only || d.own ? n * d.rows_here : 0;
         }
         __syncthreads();
@@ -311,7 +322,7 @@ __device__ __forceinline__ void emit_items(const PlanArgs& a, int n_rows, int n_
                 for (int row = 0, c = 0, len; row < d.rows_here; row += len, ++c) {
                     len = next_piece(d, row);
                     const int at = d.common_row + row, k = at / kTileRows;
-                    const int2 ct = a.tile[d.common_tile + k];
+                    const int2 ct = tile_tab[d.common_tile + k];
                     write(c, row, len, ct.x, make_int4(ct.y, min(kTileRows, d.group_rows - k * kTileRows), at % kTileRows, 0));
                 }
             }
@@ -333,7 +344,7 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
     __shared__ int s_P[MAXB], s_E[MAXB], s_e0[MAXB], s_so[MAXB];
     __shared__ int4 s_id[MAXB];               // prefix length, last, first and middle slot of it
     __shared__ int s_ht[HT], s_hlead[HT], s_hcnt[HT];  // a request with the prefix (-1: none), the first one, how many
-    __shared__ int s_pt[PT], s_pc[PT];        // a pair (request, probe) (-1: none), later the first request that chose it;
+    __shared__ __attribute__((aligned(16))) int s_pt[PT], s_pc[PT];  // a pair (request, probe) (-1: none), later the first request that chose it;
                                               // how many requests, and how many chose it << 16
     __shared__ int s_pslot[kPack ? (kProbes + 2) * MAXB : 1];  // slots at the probes; later, of leaders, at the places compared
     __shared__ int s_cutg[kPack ? MAXB : 1];  // per leader: at how many of these places its group agrees
@@ -342,7 +353,8 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
     __shared__ int s_gkey[NG];                // per group: the most keys of any of its requests
     __shared__ int s_gn[NG], s_gL[NG], s_gown[NG];         // packable members, their rows, their extend tokens
     __shared__ int s_gR[NG], s_gm[NG], s_go[NG], s_gt[NG]; // what the groups before it hold: rows, members, tokens; its first tile
-    __shared__ unsigned long long s_sk[MAXB];
+    using SortKey = std::conditional_t<kPack, unsigned, unsigned long long>;
+    __shared__ __attribute__((aligned(16))) SortKey s_sk[MAXB];
     __shared__ int s_order[MAXB];             // position in the list -> request
     __shared__ int s_first[MAXB], s_ofirst[MAXB];  // per position: its first row tile and own-key tile
     __shared__ int4 s_req[MAXB];              // ... its request, its group, the shared tiles in front of its own ones, and the
@@ -375,6 +387,9 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
     if (tid == 0) s_any = 0;
     const int rows = on ? max(E, 0) * G : 0, full = rows / mt, left = rows - full * mt;
     const bool small = on && first_part && rows > 0 && rows <= a.first_part && P >= kPackMinPrefix;
+    [[maybe_unused]] int probe[kProbes];  // this request's slots at the probes (-1: none)
+#pragma unroll
+    for (int k = 0; k < kProbes; ++k) probe[k] = -1;
     if (on) {
         s_P[tid] = P;
         s_E[tid] = E;
@@ -385,9 +400,15 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
         const int32_t* list = slot_idx + so;
         int4 id = make_int4(P, -1 - tid, 0, 0);
         if (P > 0) id = make_int4(P, list[P - 1], list[0], list[P / 2]);
-        if (kPack && small)
+        if constexpr (kPack) {
+            if (small) {
 #pragma unroll
-            for (int k = 0; k < kProbes; ++k) s_pslot[(kProbes + 2) * tid + k] = probe_depth(k) <= P ? list[probe_depth(k) - 1] : -1;
+                for (int k = 0; k < kProbes; ++k)
+                    if (probe_depth(k) <= P) probe[k] = list[probe_depth(k) - 1];
+#pragma unroll
+                for (int k = 0; k < kProbes; ++k) s_pslot[(kProbes + 2) * tid + k] = probe[k];
+            }
+        }
         s_id[tid] = id;
     }
     __syncthreads();
@@ -397,7 +418,7 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
     int hslot = 0;
     if (rows > 0) {
         const int4 id = s_id[tid];
-        hslot = hash_key((static_cast<unsigned long long>(static_cast<uint32_t>(id.x)) << 32) | static_cast<uint32_t>(id.y)) & (HT - 1);
+        hslot = lds_hash(static_cast<unsigned>(id.x), static_cast<unsigned>(id.y)) & (HT - 1);
         for (int step = 0; step < HT; ++step) {
             const int old = atomicCAS(&s_ht[hslot], -1, tid);
             if (old < 0 || old == tid) break;
@@ -417,39 +438,61 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
         if (first_part) __syncthreads();
         if (first_part && s_any) {
             // ---- common first parts: the deepest probe at which another candidate has the same slot ----
-            // (the first look into the table goes out for all probes together; few need another)
-            int at[kProbes], old[kProbes], theirs[kProbes];
-            auto key_at = [&](int k) { return hash_key((static_cast<unsigned long long>(k) << 32) | static_cast<uint32_t>(s_pslot[(kProbes + 2) * tid + k])) & pmask; };
+            // (The first look into the table goes out for all probes together; few need another.)
+            // (Of the lanes of a wave that have the same slot as its first one - a system prompt common to the batch - only that
+            // one goes to the table, and counts for all: 256 atomic operations on one entry follow one another.)
+            int at[kProbes], old[kProbes], theirs[kProbes], first_lane[kProbes];
+            unsigned with_first = 0;  // bit k: same slot at probe k as the wave's first lane with one
+            const int lane = tid & 63;
 #pragma unroll
             for (int k = 0; k < kProbes; ++k) {
-                at[k] = cand && probe_depth(k) <= P && (rows <= kNarrowRows || probe_depth(k) >= kPackWidePrefix) ? key_at(k) : -1;
-                old[k] = at[k] >= 0 ? atomicCAS(&s_pt[max(at[k], 0)], -1, (1 << 16) | (tid * kProbes + k)) : -1;
+                const bool has = cand && probe_depth(k) <= P && (rows <= kNarrowRows || probe_depth(k) >= kPackWidePrefix);
+                const unsigned long long any = __ballot(has);
+                at[k] = old[k] = -1;
+                first_lane[k] = -1;
+                if (any) {
+                    const int slot = has ? probe[k] : -1;
+                    first_lane[k] = __ffsll(any) - 1;
+                    const bool same = has && slot == __builtin_amdgcn_readlane(slot, first_lane[k]);
+                    with_first |= same ? 1u << k : 0u;
+                    if (has && (!same || lane == first_lane[k])) {
+                        at[k] = lds_hash(static_cast<unsigned>(k), static_cast<unsigned>(slot)) & pmask;
+                        old[k] = atomicCAS(&s_pt[at[k]], -1, (1 << 16) | (tid * kProbes + k));
+                    }
+                }
             }
             auto slot_of = [&](int pair) { return s_pslot[(kProbes + 2) * (pair / kProbes) + pair % kProbes]; };
 #pragma unroll
             for (int k = 0; k < kProbes; ++k) theirs[k] = old[k] >= 0 ? slot_of(old[k] & 0xFFFF) : 0;
 #pragma unroll
             for (int k = 0; k < kProbes; ++k) {
-                if (at[k] < 0) continue;
-                const int slot = s_pslot[(kProbes + 2) * tid + k];
-                for (int step = 0; step <= pmask && old[k] >= 0; ++step) {
-                    const int who = old[k] & 0xFFFF;
-                    if (who % kProbes == k && (step == 0 ? theirs[k] : slot_of(who)) == slot) break;
-                    at[k] = (at[k] + 1) & pmask;
-                    old[k] = atomicCAS(&s_pt[at[k]], -1, (1 << 16) | (tid * kProbes + k));
+                if (first_lane[k] < 0) continue;
+                const unsigned long long sharers = __ballot(with_first >> k & 1);
+                if (at[k] >= 0) {
+                    const int slot = probe[k];
+                    for (int step = 0; step <= pmask && old[k] >= 0; ++step) {
+                        const int who = old[k] & 0xFFFF;
+                        if (who % kProbes == k && (step == 0 ? theirs[k] : slot_of(who)) == slot) break;
+                        at[k] = (at[k] + 1) & pmask;
+                        old[k] = atomicCAS(&s_pt[at[k]], -1, (1 << 16) | (tid * kProbes + k));
+                    }
+                    atomicAdd(&s_pc[at[k]], lane == first_lane[k] ? __popcll(sharers) : 1);
                 }
-                atomicAdd(&s_pc[at[k]], 1);
+                const int theirs_at = __builtin_amdgcn_readlane(at[k], first_lane[k]);
+                if (with_first >> k & 1) at[k] = theirs_at;
             }
             __syncthreads();
             int chosen = -1, depth = 0, next = 0x7fffffff;
-            if (cand)
+            int with[kProbes];
 #pragma unroll
-                for (int k = 0; k < kProbes; ++k)
-                    if (at[k] >= 0 && (s_pc[at[k]] & 0xFFFF) >= 2) {
-                        chosen = at[k];
-                        depth = probe_depth(k);
-                        next = k + 1 < kProbes ? probe_depth(k + 1 < kProbes ? k + 1 : k) : 0x7fffffff;
-                    }
+            for (int k = 0; k < kProbes; ++k) with[k] = s_pc[max(at[k], 0)] & 0xFFFF;
+#pragma unroll
+            for (int k = 0; k < kProbes; ++k)
+                if (at[k] >= 0 && with[k] >= 2) {
+                    chosen = at[k];
+                    depth = probe_depth(k);
+                    next = k + 1 < kProbes ? probe_depth(k + 1 < kProbes ? k + 1 : k) : 0x7fffffff;
+                }
             __syncthreads();
             // the group: the candidates that chose this probe; its first member leads
             if (chosen >= 0) {
@@ -464,8 +507,8 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
             // place they agree at and the first they do not, a thirteenth of the interval, are each member's own).  (Lists of
             // one prefix tree agree on everything before a place where they agree; for lists of other origin two more places
             // and the first slot are compared, and a request that differs there stays on its own.)
-            const int pl = grouped ? s_P[lead] : 0, span = min(pl, next) - depth;
-            auto place = [&](int j) { return depth + static_cast<int>(static_cast<int64_t>(span) * (j + 1) / (kProbes + 1)); };
+            const int pl = grouped ? s_P[lead] : 0, stride = static_cast<int>(static_cast<unsigned>(max(min(pl, next) - depth, 0)) / (kProbes + 1));
+            auto place = [&](int j) { return depth + stride * (j + 1); };
             int mine[kProbes + 2];
             if (grouped) {
                 const int32_t* x = slot_idx + so;
@@ -508,8 +551,22 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
         }
     }
     __syncthreads();
-    // ---- order: groups with the most keys first, inside a group the request with the most keys first ----
-    if (on) {
+    // ---- order: groups with the most keys first, inside a group the request with the most keys first.  In batches of up to
+    // kPackMax in a sort key of 32 bits, all different (the comparison of every request with every other is what this costs,
+    // and one of 64 bits takes three times as long): the group's most keys, in tiles, on a scale of 16 steps per doubling; the
+    // group; the request's keys as a fraction of the group's most; its number ----
+    if constexpr (kPack) {
+        static_assert(NG <= 512 && MAXB <= 256, "nine bits and eight");
+        if (on) {
+            constexpr unsigned kTop = (1u << 20) - 1;
+            const unsigned most = max(1u, min(kTop, static_cast<unsigned>(s_gkey[gid] + 63) >> 6)), mine = min(most, static_cast<unsigned>(max(keys, 0) + 63) >> 6);
+            const unsigned e = max(0, 27 - static_cast<int>(__clz(static_cast<int>(most))));  // (below 16 + 16 x 16 = 272: the last step is open)
+            const unsigned gk = min(255u, (e << 4) + (most >> e));
+            const unsigned part = static_cast<unsigned>(127.f * __builtin_amdgcn_rcpf(static_cast<float>(most)) * static_cast<float>(mine));
+            s_sk[tid] = ((255u - gk) << 24) | (static_cast<unsigned>(gid) << 15) | ((127u - min(127u, part)) << 8) | static_cast<unsigned>(tid);
+        }
+        for (int i = B + tid; i < ((B + 3) & ~3); i += NT) s_sk[i] = 0xFFFFFFFFu;
+    } else if (on) {
         constexpr unsigned kTop = (1u << 22) - 1;
         const unsigned gk = min(kTop, static_cast<unsigned>(s_gkey[gid] + 63) >> 6), mine = min(kTop, static_cast<unsigned>(keys + 63) >> 6);
         s_sk[tid] = (static_cast<unsigned long long>(kTop - gk) << 42) | (static_cast<unsigned long long>(gid) << 32) |
@@ -518,18 +575,31 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
     static_assert(NG <= 1024 && MAXB <= 1024, "the fields of the sort key");
     __syncthreads();
     {
-        // tpr threads per request (a power of two, neighbours in a wave), each over its share of the others
+        // tpr threads per request (a power of two, neighbours in a wave), each over its share of the others, four at a time
         int tpr = 1;
         while (tpr < 16 && 2 * tpr * B <= NT) tpr *= 2;
         const int q = tid / tpr, first = tid & (tpr - 1);
-        const unsigned long long mine = s_sk[min(q, B - 1)];
+        const SortKey mine = s_sk[min(q, B - 1)];
         int rank = 0;
+        if constexpr (kPack) {
 #pragma unroll 8
-        for (int i = first; i < B; i += tpr) rank += s_sk[i] < mine;
+            for (int i = 4 * first; i < B; i += 4 * tpr) {
+                const uint4 k = *reinterpret_cast<const uint4*>(&s_sk[i]);
+                rank += (k.x < mine) + (k.y < mine) + (k.z < mine) + (k.w < mine);
+            }
+        } else {
+#pragma unroll 8
+            for (int i = first; i < B; i += tpr) rank += s_sk[i] < mine;
+        }
         for (int off = 1; off < tpr; off <<= 1) rank += __shfl_xor(rank, off);
         if (q < B && first == 0) s_order[rank] = q;
         __syncthreads();
     }
+    // (the tables of the probes are free by now)
+    constexpr int kTileTab = kPack ? PT / 2 : 0;
+    int2* const s_tpart = reinterpret_cast<int2*>(s_pt);       // per row tile: what own-key tiles look up of their shared one
+    short* const s_tpos = reinterpret_cast<short*>(s_pc);      // per tile: its position in the list
+    short* const s_tmem = s_tpos + kTileTab;                   // per shared tile: its first member
     // ---- one thread per position of the list: tiles, packed rows, members ----
     bool over;
     int n_rows, n_own;
@@ -553,7 +623,9 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
         int v[5] = {packed ? pleft : 0, packed ? 1 : 0, packed && !pfp ? pE : 0, nshared + pfull + (pleft > 0 && !packed ? 1 : 0),
                     packed && pfp ? (pleft + kNarrowRows - 1) / kNarrowRows : 0};
         int total[5];
+        const int n_mine = v[3], n_mine_own = v[4];
         block_scan<NT, 5>(v, total, s_scan);
+        const int first_mine = v[3], first_own = v[4];
         if (head) {
             s_gR[g] = v[0];
             s_gm[g] = v[1];
@@ -567,6 +639,15 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
         }
         __syncthreads();
         if (on) s_req[tid] = make_int4(r, g, nshared, packed ? v[0] - s_gR[g] : -1);
+        if constexpr (kPack) {
+            // which position a tile belongs to, and the first member of a shared one, where the tables hold all tiles
+            if (total[3] + total[4] <= kTileTab) {
+                for (int i = 0; i < n_mine; ++i) s_tpos[first_mine + i] = static_cast<short>(tid);
+                for (int i = 0; i < n_mine_own; ++i) s_tpos[total[3] + first_own + i] = static_cast<short>(tid);
+                const int R0 = packed ? v[0] - s_gR[g] : 0, k = (R0 + mt - 1) / mt;
+                if (packed && k * mt < R0 + pleft) s_tmem[s_gt[g] + k] = static_cast<short>(v[1]);
+            }
+        }
         if (packed) {
             a.member[2 * v[1]] = make_int4(v[0] - s_gR[g], s_e0[r], pfull * mt, pE);
             a.member[2 * v[1] + 1] = make_int4(v[2] - s_go[g], 0, 0, 0);
@@ -580,8 +661,10 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
     }
     __syncthreads();
     if (over) n_rows = n_own = 0;
+    const bool tabled = kPack && n_rows + n_own <= kTileTab;
     // the last position whose first tile is <= t
     auto position = [&](const int* first, int t) {
+        if (tabled) return static_cast<int>(s_tpos[first == s_ofirst ? n_rows + t : t]);
         int lo = 0, hi = B;
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
@@ -628,7 +711,16 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
                 }
                 return m0 + lo;
             };
-            const int ma = member_of(d.row0), mb = member_of(d.row0 + d.rows_here - 1);
+            int ma, mb;
+            if (tabled) {
+                ma = s_tmem[t];
+                const bool last = d.row0 + mt >= L;  // (the next tile's first member may have rows in this one)
+                mb = last ? m0 + nm - 1 : s_tmem[t + 1];
+                if (!last && s_mR[mb] >= d.row0 + mt) --mb;
+            } else {
+                ma = member_of(d.row0);
+                mb = member_of(d.row0 + d.rows_here - 1);
+            }
             d.member0 = ma;
             d.n_members = mb - ma + 1;
             d.P = s_cut[r];
@@ -655,7 +747,7 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
         d.kv_end = d.P + (d.row0 + mt - 1) / G + 1;
         return d;
     };
-    emit_items<NT>(a, n_rows, n_rows + n_own, over, describe);
+    emit_items<NT>(a, n_rows, n_rows + n_own, over, tabled ? s_tpart : a.tile, describe);
 }
 
 // Batches of more than kSortMax requests: in the order given, tables in global memory.
@@ -694,7 +786,7 @@ __global__ __launch_bounds__(NT) void extend_plan_large_kernel(PlanArgs a) {
         d.kv_end = d.P + (d.row0 + d.rows_here - 1) / G + 1;
         return d;
     };
-    emit_items<NT>(a, n_rows, n_rows, over, describe);
+    emit_items<NT>(a, n_rows, n_rows, over, a.tile, describe);
 }
 
 int launch_extend_plan(const ExtendPlan& p, const PlanTables& t, const int32_t* prefix_len, const int32_t* ext_len, const int32_t* ext_offsets,
