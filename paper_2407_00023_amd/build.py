@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libprefixattn.so")
 CALLS = os.path.join(HERE, "_calls.so")
-SOURCES = ["tree.cpp", "sched.cpp", "profile.cpp", "call_sets.cpp", "match.hip", "kvpool.hip", "extend.cpp", "extend_f32.hip", "extend_plan.hip", "extend_bf16.hip", "calib.hip"]
+SOURCES = ["tree.cpp", "sched.cpp", "profile.cpp", "call_sets.cpp", "tree_changes.hip", "match.hip", "kvpool.hip", "extend.cpp", "extend_f32.hip", "extend_plan.hip", "extend_bf16.hip", "calib.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 code generation
          "-Wall", "-Wno-unused-function"]

@@ -79,6 +79,16 @@ struct DeviceTree {
     uint32_t ph_mask;
 };
 
+// A piece of the changes to a DeviceTree (tree_changes.hip): where its words go, counted from the start of the mirror in words
+// of 32 bits.  The words of piece i lie at i * kChangeWords of the transfer buffer.
+constexpr int kChangeWords = 256;
+struct __attribute__((aligned(16))) ChangePiece {
+    uint64_t to;
+    uint32_t words, pad;
+};
+// piece, words: device addresses of pinned host memory.
+int launch_apply_changes(const ChangePiece* piece, const uint32_t* words, int n, void* mirror, hipStream_t stream);
+
 constexpr unsigned long long kEmptyKey = ~0ull;
 constexpr unsigned long long kDeletedKey = ~0ull - 1;  // child table: an entry that was removed (never a real key)
 

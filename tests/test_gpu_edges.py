@@ -533,3 +533,32 @@ def test_small_batches_on_streams_and_in_graphs(pa, gpu_device):
         for i, o in enumerate(outs):
             for b, x in zip(batches, o):
                 assert torch.equal(x, b["want"]) if i < 8 else (x.float() - b["want"].float()).abs().max() <= TOL["bf16"]
+
+
+# changes of a tree go to the device in pieces of 256 words, runs of more than 16,384 words by copies of their own
+@pytest.mark.gpu
+def test_upload_of_changes_at_the_edges_of_pieces_and_long_runs(pa, gpu_device):
+    """After every insertion and upload the matcher finds the whole new sequence with its slots, the one before it and the first."""
+    rng = np.random.default_rng(7)
+    tree = pa.Tree()
+    tree.insert(*(lambda n: (rng.integers(0, 1000, n).astype(np.int32), np.arange(n, dtype=np.int32)))(60000))
+    tree.upload()
+    cached, base = [], 100000
+    for k, n in enumerate([1, 255, 256, 257, 511, 513, 16383, 16384, 16385, 300, 20000, 2]):
+        toks = rng.integers(0, 1000, n).astype(np.int32)
+        toks[0] = 2000 + k
+        cached.append((toks, np.arange(base, base + n, dtype=np.int32)))
+        base += n
+        tree.insert(*cached[-1])
+        tree.upload()
+        print(f"[case] upload of a run of {n} tokens", flush=True)
+        ask = [cached[-1], cached[max(0, k - 1)], cached[0]]
+        off = np.concatenate([[0], np.cumsum([len(t) + 1 for t, _ in ask])]).astype(np.int32)
+        prompt = np.concatenate([np.append(t, np.int32(5000)) for t, _ in ask])
+        pl, si = pa.match_prefixes(tree, torch.from_numpy(prompt).to(gpu_device), torch.from_numpy(off).to(gpu_device))
+        pl, si = pl.cpu().numpy(), si.cpu().numpy()
+        for r, (t, s) in enumerate(ask):
+            assert pl[r] == len(t)
+            np.testing.assert_array_equal(si[off[r]:off[r] + pl[r]], s)
+    full, partial, _ = tree.upload_stats()
+    assert partial >= 10
