@@ -17,7 +17,8 @@ struct ExtendPlan {
     int items_cap;   // ... on the number of work items (tile x part of its key range)
     int prows_cap;   // ... on the number of rows of partial results, per KV head
     int chunks_cap;  // ... on the number of pieces of the merge
-    int slots;       // workgroup slots per KV head
+    int slots;       // workgroup slots per KV head, two on a compute unit
+    int resident;    // workgroups per KV head that are resident at once (heads of 64: three on a compute unit)
     int rounds;      // work items aimed at per workgroup slot
     int pack;        // 1: rows of requests with a common prefix may be packed
     int first_part;  // ... of requests of up to this many rows also where they have only the first part of it in common (0: not)

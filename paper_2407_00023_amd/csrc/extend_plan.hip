@@ -41,6 +41,8 @@ constexpr int kMinChunkTiles = 16;       // never split below this many key tile
                                          // batch's step took 3 % longer) ...
 constexpr int kMinChunkCommon = 8;       // ... unless the tile leaves partial results anyway (or is narrow: kMinChunkNarrow)
 constexpr int kItemOverhead = 4;         // fixed cost of a work item, in key tiles (its prologue and epilogue)
+constexpr int kItemFixed = 6;            // ... as the time of a workgroup goes: 9 us, a key tile 1.6
+constexpr int kMergeCost = 4;            // what partial results cost a launch, in key tiles
 constexpr int kMaxParts = 64;            // parts of one tile at most
 constexpr int kSortMax = 1024;           // ... and up to this many are ordered
 constexpr int kPackMinPrefix = 512;      // prefixes, or first parts of them, are shared from this many keys on ...
@@ -104,6 +106,7 @@ ExtendPlan make_extend_plan(int B, int64_t T, int64_t max_kv_len, int Hq, int Hk
     const int64_t rows = T * G;
     p.rounds = rounds;
     p.slots = kWgSlots / Hkv > 0 ? kWgSlots / Hkv : 1;
+    p.resident = D == 128 ? p.slots : p.slots + p.slots / 2;
     p.pack = B <= kPackMax;
     p.tiles_cap = static_cast<int>((rows + kTileRows - 1) / kTileRows + B);  // (packing only lowers the number of row tiles)
     p.chunk_rows = 256 / (D / 4);
@@ -164,13 +167,24 @@ struct PlanArgs {
     int32_t* hdr;
     int2* tile;
     int4 *member, *item, *chunk;
-    int B, G, tiles_cap, own_cap, items_cap, prows_cap, chunks_cap, slot_items, pack, first_part, tile_parts, chunk_rows;
+    int B, G, tiles_cap, own_cap, items_cap, prows_cap, chunks_cap, resident, slot_items, pack, first_part, tile_parts, chunk_rows;
 };
 
 // All of a kernel's arguments asked for at its start: where they are looked at for the first time later on, each cache line of
 // them is another round trip to host memory.
 __device__ __forceinline__ void touch_args(const PlanArgs& a) {
     asm volatile("" ::"s"(a.prefix_len), "s"(a.hdr), "s"(a.item), "s"(a.chunk), "s"(a.tile_parts), "s"(a.chunk_rows));
+}
+
+// The largest of the wave's values, none negative, in its last lane; by the same moves as wave_scan.
+__device__ __forceinline__ int wave_max(int x) {
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+    return x;
 }
 
 // Exclusive prefix sums of N ints per thread over the workgroup, and their totals: a scan inside each wave, then the
@@ -214,7 +228,7 @@ struct TileDesc {
 // tiles.  describe(t) says what tile t is; tile_tab: room for what own-key tiles look up of their shared tile.
 template <int NT, class Describe>
 __device__ __forceinline__ void emit_items(const PlanArgs& a, int n_rows, int n_all, bool over, int2* tile_tab, Describe describe) {
-    __shared__ int s_cost[NT / 64];
+    __shared__ int s_cost[2][NT / 64];
     __shared__ int s_sum[3][NT / 64];
     const int tid = threadIdx.x;
     // thread i owns tiles [i * per, (i + 1) * per); where there are fewer tiles than threads, S threads (a power of two, up to
@@ -231,18 +245,31 @@ __device__ __forceinline__ void emit_items(const PlanArgs& a, int n_rows, int n_
     auto narrow = [](const TileDesc& d) { return d.rows_here <= kNarrowRows; };
     // (a narrow tile's waves do four blocks of 32 keys in the time of one)
     auto cost_of = [&](const TileDesc& d) { return (narrow(d) ? (key_tiles(d) + 1) / 2 : key_tiles(d)) + kItemOverhead; };
-    int cost = 0;
-    for (int t = t_lo; t < t_hi; ++t) cost += sub == 0 ? cost_of(tile_desc(t)) : 0;
+    int cost = 0, longest = 0;
+    for (int t = t_lo; t < t_hi; ++t) {
+        const int c = cost_of(tile_desc(t));
+        cost += sub == 0 ? c : 0;
+        longest = max(longest, c);
+    }
     cost = wave_scan(cost);
-    if ((tid & 63) == 63) s_cost[tid >> 6] = cost;
+    longest = wave_max(longest);
+    if ((tid & 63) == 63) {
+        s_cost[0][tid >> 6] = cost;
+        s_cost[1][tid >> 6] = longest;
+    }
     __syncthreads();
     int W = 0;
 #pragma unroll
-    for (int k = 0; k < NT / 64; ++k) W += s_cost[k];
+    for (int k = 0; k < NT / 64; ++k) {
+        W += s_cost[0][k];
+        longest = max(longest, s_cost[1][k]);
+    }
     // parts of a tile: its cost over the target cost of an item, rounded up from a quarter past a whole number (an item
     // of 1.5 targets at the end of the list is a tail of its own)
     const float target = fmaxf(static_cast<float>(W) / static_cast<float>(a.slot_items), 1.f);
+    bool whole = false;  // no tile is cut (decided below)
     auto parts_of = [&](const TileDesc& d) {
+        if (whole) return 1;
         const int n = static_cast<int>(static_cast<float>(cost_of(d)) / target + 0.75f);
         const int shortest = narrow(d) ? kMinChunkNarrow : d.partial_only ? kMinChunkCommon : kMinChunkTiles;
         return max(min(min(n, key_tiles(d) / shortest), a.tile_parts), 1);
@@ -273,6 +300,29 @@ __device__ __forceinline__ void emit_items(const PlanArgs& a, int n_rows, int n_
     if (S > 1)  // (to the other threads of the tile)
 #pragma unroll
         for (int i = 0; i < 3; ++i) v[i] = __shfl(v[i], (tid & 63) - sub);
+    // ---- cut or not: where the tiles as they are fill the slots about once or twice, cutting them can make one round of
+    // workgroups more than it shortens them.  Compared in key tiles: whole rounds of workgroups of the average cost, a last
+    // round that leaves half of the slots empty at two thirds of that (a workgroup alone on its compute unit is faster), the
+    // fixed cost of an item, and what the partial results cost.  Steps in us, always cut | by this rule: 16 requests of 50 to 150
+    // new tokens behind 2,200 keys (50 tiles for 64 slots) 124.6 | 112.0, 24 160.9 | 149.2; 32 on 2 KV heads 128.2 | 114.9. ----
+    if (n_all == n_rows && total[0] > n_all) {
+        const float inv_slots = __builtin_amdgcn_rcpf(static_cast<float>(a.resident));
+        const float keys_cost = static_cast<float>(W - n_all * kItemOverhead);  // without the items' fixed cost
+        auto finish = [&](int items) {
+            const float n = static_cast<float>(items), rounds = n * inv_slots, whole_rounds = floorf(rounds + 0.001f), rest = rounds - whole_rounds;
+            const float one = keys_cost * __builtin_amdgcn_rcpf(n) + static_cast<float>(kItemFixed);
+            return one * (whole_rounds + (rest < 0.001f ? 0.f : rest < 0.501f ? 0.65f : 1.f));
+        };
+        const float cut = finish(total[0]) + static_cast<float>(kMergeCost);
+        const float uncut = fmaxf(finish(n_all), (2 * n_all <= a.resident ? 0.65f : 1.f) * static_cast<float>(longest - kItemOverhead + kItemFixed));
+        if (uncut < cut) {
+            whole = true;
+            v[0] = t_lo;
+            v[1] = v[2] = 0;
+            total[0] = n_all;
+            total[1] = total[2] = 0;
+        }
+    }
     // The capacities follow from the host's T and max_kv_len: a batch on the device that is larger than they say does
     // not fit.  Nothing is computed then (an empty list: no output row is written) and hdr[3] says so, which
     // pa_extend_status reports.
@@ -553,17 +603,18 @@ __global__ __launch_bounds__(NT) void extend_plan_kernel(PlanArgs a) {
     __syncthreads();
     // ---- order: groups with the most keys first, inside a group the request with the most keys first.  In batches of up to
     // kPackMax in a sort key of 32 bits, all different (the comparison of every request with every other is what this costs,
-    // and one of 64 bits takes three times as long): the group's most keys, in tiles, on a scale of 16 steps per doubling; the
-    // group; the request's keys as a fraction of the group's most; its number ----
+    // and one of 64 bits takes three times as long): the group's most keys, in tiles, on a scale of 64 steps per doubling (16 of
+    // them: 64 requests on 16 tools 302.5 -> 306.4 us); the group's leader, which heads no other; the request's keys as a
+    // fraction of the group's most; its number ----
     if constexpr (kPack) {
-        static_assert(NG <= 512 && MAXB <= 256, "nine bits and eight");
+        static_assert(MAXB <= 256, "eight bits");
         if (on) {
             constexpr unsigned kTop = (1u << 20) - 1;
             const unsigned most = max(1u, min(kTop, static_cast<unsigned>(s_gkey[gid] + 63) >> 6)), mine = min(most, static_cast<unsigned>(max(keys, 0) + 63) >> 6);
-            const unsigned e = max(0, 27 - static_cast<int>(__clz(static_cast<int>(most))));  // (below 16 + 16 x 16 = 272: the last step is open)
-            const unsigned gk = min(255u, (e << 4) + (most >> e));
-            const unsigned part = static_cast<unsigned>(127.f * __builtin_amdgcn_rcpf(static_cast<float>(most)) * static_cast<float>(mine));
-            s_sk[tid] = ((255u - gk) << 24) | (static_cast<unsigned>(gid) << 15) | ((127u - min(127u, part)) << 8) | static_cast<unsigned>(tid);
+            const unsigned e = max(0, 25 - static_cast<int>(__clz(static_cast<int>(most))));
+            const unsigned gk = (e << 6) + (most >> e);  // (below 15 x 64)
+            const unsigned part = static_cast<unsigned>(63.f * __builtin_amdgcn_rcpf(static_cast<float>(most)) * static_cast<float>(mine));
+            s_sk[tid] = ((1023u - gk) << 22) | (static_cast<unsigned>(gid & 255) << 14) | ((63u - min(63u, part)) << 8) | static_cast<unsigned>(tid);
         }
         for (int i = B + tid; i < ((B + 3) & ~3); i += NT) s_sk[i] = 0xFFFFFFFFu;
     } else if (on) {
@@ -792,7 +843,7 @@ __global__ __launch_bounds__(NT) void extend_plan_large_kernel(PlanArgs a) {
 int launch_extend_plan(const ExtendPlan& p, const PlanTables& t, const int32_t* prefix_len, const int32_t* ext_len, const int32_t* ext_offsets,
                        const int32_t* slot_offsets, const int32_t* slot_idx, int B, int G, hipStream_t stream) {
     const PlanArgs a{prefix_len, ext_len, ext_offsets, slot_offsets, slot_idx, t.hdr, t.tile, t.member, t.item, t.chunk, B, G, p.tiles_cap,
-                     p.own_cap, p.items_cap, p.prows_cap, p.chunks_cap, p.slots * p.rounds, p.pack, p.first_part, p.tile_parts, p.chunk_rows};
+                     p.own_cap, p.items_cap, p.prows_cap, p.chunks_cap, p.resident, p.slots * p.rounds, p.pack, p.first_part, p.tile_parts, p.chunk_rows};
     ProfScope prof(kProfPlan, stream);
     // (few requests and tiles: four waves meet at a barrier sooner than sixteen)
     const int most = p.tiles_cap + p.own_cap;

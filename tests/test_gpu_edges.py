@@ -562,3 +562,10 @@ def test_upload_of_changes_at_the_edges_of_pieces_and_long_runs(pa, gpu_device):
             np.testing.assert_array_equal(si[off[r]:off[r] + pl[r]], s)
     full, partial, _ = tree.upload_stats()
     assert partial >= 10
+
+
+# 16 workgroup slots per KV head and tiles of 35 key tiles: 4 tiles are cut in two, 16 are one round as they are, 17 are cut again
+@pytest.mark.gpu
+@pytest.mark.parametrize("B", [4, 16, 17])
+def test_extend_cuts_tiles_or_not_around_a_round_of_workgroups(pa, gpu_device, B):
+    assert _extend(pa, gpu_device, "bf16", [2100 + r % 3 for r in range(B)], [128 - r % 2 for r in range(B)], 32, 32, 128, 16, common=300) <= TOL["bf16"]
