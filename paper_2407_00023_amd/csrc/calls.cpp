@@ -1,4 +1,4 @@
-// Python module _calls: the three calls of the hot path, taking torch tensors.
+// Python module _calls: the three calls of the hot path and the admission of a request, taking torch tensors.
 //
 // Argument marshalling only, in native code because a step of a small batch (a few requests being decoded) takes the
 // GPU some tens of microseconds: through ctypes the three calls cost the host 38 us (checks, pointer objects, 3 us per
@@ -10,6 +10,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstring>
+#include <vector>
 
 #include "../../include/prefixattn.h"
 
@@ -160,23 +161,29 @@ bool pool_large_enough(const at::Tensor& pool, long long num_slots, int Hkv, int
         return nullptr;                                   \
     }
 
+// The tree of a Python Tree object; false with an exception set if it is none.
+bool tree_of(PyObject* o, pa_tree** out) {
+    PyObject* holder = o ? PyObject_GetAttrString(o, "_h") : nullptr;  // (ctypes.c_void_p of the tree)
+    if (!holder) {
+        if (!o) PyErr_SetString(PyExc_TypeError, "tree must be a Tree");
+        return false;
+    }
+    PyObject* value = holder == Py_None ? Py_NewRef(holder) : PyObject_GetAttrString(holder, "value");
+    Py_DECREF(holder);
+    if (!value) return false;
+    *out = value == Py_None ? nullptr : static_cast<pa_tree*>(PyLong_AsVoidPtr(value));
+    Py_DECREF(value);
+    return !PyErr_Occurred();
+}
+
 // match_prefixes(tree, tokens, offsets, prefix_len=None, slot_idx=None, stream=None); `tree` is the handle's address here
 PyObject* match_prefixes(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObject* kwnames) {
     static const char* const names[] = {"tree", "tokens", "offsets", "prefix_len", "slot_idx", "stream"};
     PyObject* a[6];
     if (!parse_args("match_prefixes", names, 6, 3, args, nargs, kwnames, a)) return nullptr;
     CALLS_TRY
-    PyObject* holder = a[0] ? PyObject_GetAttrString(a[0], "_h") : nullptr;  // (ctypes.c_void_p of the tree)
-    if (!holder) {
-        if (!a[0]) PyErr_SetString(PyExc_TypeError, "tree must be a Tree");
-        return nullptr;
-    }
-    PyObject* value = holder == Py_None ? Py_NewRef(holder) : PyObject_GetAttrString(holder, "value");
-    Py_DECREF(holder);
-    if (!value) return nullptr;
-    const pa_tree* tree = value == Py_None ? nullptr : static_cast<const pa_tree*>(PyLong_AsVoidPtr(value));
-    Py_DECREF(value);
-    if (PyErr_Occurred()) return nullptr;
+    pa_tree* tree = nullptr;
+    if (!tree_of(a[0], &tree)) return nullptr;
     const at::Tensor *tokens = tensor_of(a[1], "tokens"), *offsets = tokens ? tensor_of(a[2], "offsets") : nullptr;
     if (!offsets || !device_int32(*tokens, "tokens") || !device_int32(*offsets, "offsets")) return nullptr;
     const int64_t B = offsets->numel() - 1;
@@ -329,6 +336,41 @@ PyObject* append_kv(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObject
     CALLS_CATCH
 }
 
+// tree_admit(tree, tokens, now) -> (n_cached, new_slots, handle), or None where tokens is no contiguous int32 vector in host
+// memory (the caller converts it).  Native because a serving loop makes this call once per request: marshalled through ctypes
+// and torch it took 6.4 us for 2 us of work.
+PyObject* tree_admit(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+    if (nargs != 3) {
+        PyErr_SetString(PyExc_TypeError, "tree_admit() takes 3 arguments");
+        return nullptr;
+    }
+    CALLS_TRY
+    if (!THPVariable_Check(args[1])) Py_RETURN_NONE;
+    const at::Tensor& tokens = THPVariable_Unpack(args[1]);
+    if (tokens.scalar_type() != at::kInt || !tokens.is_cpu() || tokens.dim() != 1 || !tokens.is_contiguous() || tokens.numel() > INT32_MAX) Py_RETURN_NONE;
+    if (!PyLong_Check(args[2])) {
+        PyErr_SetString(PyExc_TypeError, "now must be an integer");
+        return nullptr;
+    }
+    const int64_t now = static_cast<int64_t>(PyLong_AsUnsignedLongLongMask(args[2]));
+    pa_tree* tree = nullptr;
+    if (PyErr_Occurred() || !tree_of(args[0], &tree)) return nullptr;
+    const int32_t n = static_cast<int32_t>(tokens.numel());
+    int32_t cached = 0;
+    int64_t handle = 0;
+    std::vector<int32_t> slots(static_cast<size_t>(n) + 1);
+    int rc = PA_OK;
+    {
+        const WithoutGil released;
+        rc = pa_tree_admit(tree, static_cast<const int32_t*>(tokens.const_data_ptr()), n, now, slots.data(), &cached, &handle);
+    }
+    if (rc != PA_OK) return raise_code(rc, "pa_tree_admit");
+    at::Tensor fresh = at::empty({n - cached}, tokens.options());
+    if (n > cached) std::memcpy(fresh.mutable_data_ptr(), slots.data() + cached, sizeof(int32_t) * static_cast<size_t>(n - cached));
+    return Py_BuildValue("iNL", static_cast<int>(cached), THPVariable_Wrap(std::move(fresh)), static_cast<long long>(handle));
+    CALLS_CATCH
+}
+
 // setup(PrefixAttnError): the exception class that error codes are raised as
 PyObject* setup(PyObject*, PyObject* cls) {
     Py_INCREF(cls);
@@ -348,6 +390,8 @@ PyMethodDef g_methods[] = {
     {"append_kv", PA_FAST(append_kv),
      "append_kv($module, /, kv_pool, new_slots, k_ext, v_ext, *, page_size, num_slots, stream=None, kv8=False)\n--\n\n"
      "pool[new_slots[t]] = (k_ext[t], v_ext[t]).  Asynchronous on the stream."},
+    {"tree_admit", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(tree_admit)), METH_FASTCALL,
+     "tree_admit($module, tree, tokens, now, /)\n--\n\n-> (n_cached, new_slots, handle), or None if tokens has to be converted first."},
     {"setup", setup, METH_O, "setup($module, error_class, /)\n--\n\nThe exception class error codes are raised as."},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_calls", "The hot-path calls of libprefixattn on torch tensors.", -1, g_methods,

@@ -129,6 +129,15 @@ static int32_t new_node(pa_tree* t) {
     return static_cast<int32_t>(t->nodes.size() - 1);
 }
 
+// How many leading tokens of a and b, both of length n >= 1, are the same; the first is known to be.  (Sixteen at a time: a prompt
+// is compared with some thousand cached tokens per admission.)
+static int32_t common_run(const int32_t* a, const int32_t* b, int32_t n) {
+    int32_t k = 1;
+    while (k + 16 <= n && std::memcmp(a + k, b + k, 16 * sizeof(int32_t)) == 0) k += 16;
+    while (k < n && a[k] == b[k]) ++k;
+    return k;
+}
+
 // Splits node c after its first k edge tokens (0 < k < length).  The TAIL keeps the id c - whoever holds c as the
 // deepest node of a path still does - and a new node takes the head, between c and its old parent; both halves
 // carry the pins and the access time.  Returns the head.
@@ -329,8 +338,7 @@ extern "C" int pa_tree_insert(pa_tree* tree, const int32_t* tokens, const int32_
             int32_t c = it->second;
             const int32_t elen = static_cast<int32_t>(nodes[c].tok.size());
             const int32_t lim = std::min(elen, n - pos);
-            int32_t k = 1;  // first token equal by construction of the child map
-            while (k < lim && nodes[c].tok[k] == tokens[pos + k]) ++k;
+            const int32_t k = pa::common_run(nodes[c].tok.data(), tokens + pos, lim);  // (first token equal by construction of the child map)
             if (k < elen) {
                 if (pos + k == n) { pos = n; break; }  // the sequence ends inside this edge: nothing new to store
                 cur = pa::split_node(tree, c, k);
@@ -409,8 +417,7 @@ extern "C" int pa_tree_admit(pa_tree* tree, const int32_t* tokens, int32_t n, in
             const int32_t c = it->second;
             const int32_t elen = static_cast<int32_t>(nodes[c].tok.size());
             const int32_t lim = std::min(elen, n - pos);
-            int32_t k = 1;
-            while (k < lim && nodes[c].tok[k] == tokens[pos + k]) ++k;
+            const int32_t k = pa::common_run(nodes[c].tok.data(), tokens + pos, lim);
             if (k < elen) {
                 cur = pa::split_node(tree, c, k);
                 pa::mirror_split(tree, c, cur, k);
@@ -558,8 +565,7 @@ static void keep_for_prompt(const pa_tree* tree, const int32_t* tokens, int32_t 
         const int32_t c = it->second;
         const int32_t elen = static_cast<int32_t>(nodes[c].tok.size());
         const int32_t lim = std::min(elen, n - pos);
-        int32_t k = 1;
-        while (k < lim && nodes[c].tok[k] == tokens[pos + k]) ++k;
+        const int32_t k = common_run(nodes[c].tok.data(), tokens + pos, lim);
         keep.emplace(c, k);
         pos += k;
         if (k < elen) break;
