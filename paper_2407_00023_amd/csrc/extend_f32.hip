@@ -52,12 +52,27 @@ __global__ __launch_bounds__(256) void extend_f32_kernel(
     const int G = Hq / Hkv, g = blockIdx.y;
     const int h0 = g * G + blockIdx.z * kHeads, n_heads = min(kHeads, (g + 1) * G - h0);
 
-    const int r = request_of(ext_offsets, B, t);
-    const int64_t e0 = ext_offsets[r];
+    // the token's request and what there is to know of it; up to 64 requests: all of it asked for together, a request per lane
+    int64_t e0;
+    int P, E, slot_off;
+    if (B <= 64) {
+        const int lane = threadIdx.x & 63, k = min(lane, B - 1);
+        const int o = ext_offsets[k], p = prefix_len[k], e = ext_len[k], so = slot_offsets[k];
+        const int r = __popcll(__ballot(lane >= 1 && lane < B && o <= t));
+        e0 = __builtin_amdgcn_readlane(o, r);
+        P = __builtin_amdgcn_readlane(p, r);
+        E = __builtin_amdgcn_readlane(e, r);
+        slot_off = __builtin_amdgcn_readlane(so, r);
+    } else {
+        const int r = request_of(ext_offsets, B, t);
+        e0 = ext_offsets[r];
+        P = prefix_len[r];
+        E = ext_len[r];
+        slot_off = slot_offsets[r];
+    }
     const int i = static_cast<int>(t - e0);
-    const int P = prefix_len[r];
-    const int32_t* __restrict__ slots = slot_idx + slot_offsets[r];
-    if (i < 0 || i >= ext_len[r]) return;  // inconsistent offsets: produce nothing rather than read out of range
+    const int32_t* __restrict__ slots = slot_idx + slot_off;
+    if (i < 0 || i >= E) return;  // inconsistent offsets: produce nothing rather than read out of range
     const int nvis = P + i + 1;
     const unsigned last_slot = static_cast<unsigned>(min(num_slots, int64_t{INT32_MAX})) - 1u;
 
