@@ -1344,6 +1344,7 @@ static int run_extend_bf16(pa::ExtendPlan p, const void* q_ext, const void* k_ex
     const float scale_log2e = scale * 1.4426950408889634f;
     DirectArgs direct{prefix_len, ext_len, ext_offsets, slot_offsets, nullptr, t.hdr, B, p.direct_parts, p.direct_tile_rows, p.direct_tiles,
                       p.direct_stride};
+    if (kv8 && p.direct_key_tiles > kDirectKeyTilesFp8) direct.parts = 0;
     if (direct.parts > 0) {
         void* base = nullptr;
         int set = -1;

@@ -28,6 +28,7 @@ struct ExtendPlan {
     int direct_parts;      // parts of a tile at most; 0: a work list
     int direct_tile_rows;  // rows of a tile
     int direct_tiles;      // upper bound on the number of tiles
+    int direct_key_tiles;  // key tiles per workgroup slot
     int direct_stride;     // rows of partial results of one part of all tiles, per KV head
     size_t off_tile, off_member, off_item, off_chunk, off_part_o, off_part_ml, total;
 };
@@ -44,6 +45,9 @@ constexpr int kDirectMinChunkWide = 8;  // ... of a wide one in a launch without
 constexpr int kDirectJoinRows = 2048;   // request, in all KV heads, are more than this: the partial results are stored through to
                                         // memory and read again (100 to 300 new tokens behind 2,200 keys, 8 KV heads, 46.7 us, with
                                         // parts of 8 50.8; 20 to 60 new tokens 36.3, with parts of 16 43.4)
+constexpr int kDirectKeyTilesFp8 = 9;   // key tiles per workgroup slot that go without a work list where the pool is in fp8 (a narrow
+                                        // tile takes longer there: 12 decode requests, 8.5 a slot, 41.4 us with list | 39.5 without;
+                                        // 16, 11.8 a slot, 42.2 | 47.2)
 constexpr int kMaxDirectParts = 16;     // parts of a tile at most in such a launch ...
 constexpr int kDirectWideParts = 4;     // ... and of a wide one
 constexpr int kDirectSlots = 512;  // counters of the tiles of a direct launch (tile x KV head), per call

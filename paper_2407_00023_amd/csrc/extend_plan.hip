@@ -71,22 +71,27 @@ __device__ __forceinline__ constexpr int probe_depth(int k) {
 // behind 1,800 common keys and up to 3,000 own ones, 1 request 30.1 | 23.7, 4 39.1 | 28.0, 6 44.6 | 31.6; 20 to 60 new tokens
 // behind 2,200 keys, 1 42.6 | 36.3, 4 50.4 | 38.3; 100 to 300 new tokens behind 1,000 keys, 2 69.0 | 36.2, 4 79.8 | 37.8; behind
 // 2,200 keys, 1 48.5 | 47.9.  Hence the limits:
-constexpr int kDirectMaxB = 6;             // more requests have more to share
+constexpr int kDirectMaxB = 6;             // more requests have more to share ...
+constexpr int kDirectMaxBFew = 64;         // ... but in narrow tiles, where these fill the slots in kMaxDirectParts parts: decode behind
+                                           // 1,800 + 400 common and up to 350 own keys, 8 requests 36.1 | 28.0, 16 39.4 | 37.0; heads
+                                           // of 64 behind 900 and up to 900, 16 43.6 | 27.8; 1 to 6 new tokens, 8 requests 57.0 | 28.8
 constexpr int kDirectFewRows = 16;         // rows per request on average: up to this many in narrow tiles; more, but too few not to
                                            // be shared over a common first part (first_part_rows): with a work list
-constexpr int kDirectKeyTilesNarrow = 16;  // key tiles per workgroup slot, at the longest lengths the host was told ...
+constexpr int kDirectKeyTilesNarrow = 16;  // key tiles per workgroup slot, at the longest lengths the host was told (fp8 pool:
+                                           // kDirectKeyTilesFp8) ...
 constexpr int kDirectKeyTilesWide = 10;    // ... (20 to 60 new tokens of 6 requests behind 3,400 keys, 11 a slot: 55.1 | 58.7)
 // and no more than kDirectWideParts parts of a tile of 128 rows where a list would make more: one workgroup joins them, 64 KB a part.
 static void make_direct(ExtendPlan& p, int B, int64_t rows, int64_t max_kv_len, int Hkv, int D) {
     p.direct_parts = 0;
-    if (B < 1 || B > kDirectMaxB) return;
     const bool few = rows <= int64_t{kDirectFewRows} * B;
+    if (B < 1 || B > (few ? kDirectMaxBFew : kDirectMaxB)) return;
     if (!few && rows <= int64_t{first_part_rows(D)} * B) return;
     const int tile_rows = few ? kNarrowRows : kTileRows;
     const int64_t tiles = rows / tile_rows + B, key_tiles = (max_kv_len + kKT - 1) / kKT, per_tile = p.slots / tiles;
     if (per_tile < 1 || tiles * Hkv > kDirectSlots || tiles * key_tiles > int64_t{p.slots} * (few ? kDirectKeyTilesNarrow : kDirectKeyTilesWide)) return;
     const auto least = [](int64_t a, int64_t b) { return a < b ? a : b; };
     if (!few && least(per_tile, key_tiles / kMinChunkTiles) > kDirectWideParts) return;
+    if (B > kDirectMaxB && per_tile > kMaxDirectParts) return;
     // (wide tiles: one workgroup on a compute unit; a second one there slows the first by what it does itself)
     int64_t parts = least(least(few ? per_tile : per_tile / 2, key_tiles / (few ? kMinChunkNarrow : kDirectMinChunkWide)), few ? kMaxDirectParts : kDirectWideParts);
     parts = least(parts, p.tile_parts);
@@ -95,6 +100,7 @@ static void make_direct(ExtendPlan& p, int B, int64_t rows, int64_t max_kv_len, 
     p.direct_parts = static_cast<int>(parts);
     p.direct_tile_rows = tile_rows;
     p.direct_tiles = static_cast<int>(tiles);
+    p.direct_key_tiles = static_cast<int>((tiles * key_tiles + p.slots - 1) / p.slots);
     p.direct_stride = static_cast<int>(p.prows_cap / parts);
 }
 

@@ -468,8 +468,9 @@ def test_hot_path_calls_refuse_what_is_no_device_tensor():
         binding.extend_attention(x, x, x, x, i32, i32, i32, i32, i32, 1.0, page_size=1, num_slots=1, max_kv_len=1)
 
 
-# launches without a work list: up to 6 requests of up to 16 rows each on average (narrow tiles) or of more than 48 (64 with
-# heads of 64; tiles of 128 rows), tiles cut from 256 (narrow) and 512 or 1,024 keys on, up to 16 and 4 parts
+# launches without a work list: up to 6 requests of up to 16 rows each on average (narrow tiles; up to 64 where they fill the slots
+# in 16 parts) or of more than 48 (64 with heads of 64; tiles of 128 rows), tiles cut from 256 (narrow) and 512 or 1,024 keys on, up
+# to 16 and 4 parts
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,P,E,Hq,Hkv,D,page", [
     ("bf16", [0], [1], 4, 1, 128, 16), ("bf16", [511], [1], 8, 2, 128, 16), ("bf16", [512], [4], 8, 2, 128, 1),
@@ -478,6 +479,9 @@ def test_hot_path_calls_refuse_what_is_no_device_tensor():
     ("bf16", [0], [13], 8, 2, 128, 16), ("bf16", [1023 - 40, 1024 - 40], [40, 40], 8, 2, 128, 16),
     ("bf16", [2100, 5], [33, 64], 8, 1, 128, 16), ("bf16", [2400, 600, 0], [300, 97, 1], 16, 8, 64, 1),
     ("bf16", [0, 0, 100], [400, 0, 250], 8, 2, 128, 64), ("bf16", [1100] * 6, [40] * 6, 8, 2, 128, 24),
+    ("bf16", [300 + 7 * r for r in range(12)], [1 + r % 3 for r in range(12)], 16, 8, 128, 16),
+    ("bf16", [40 * r for r in range(40)], [1] * 40, 8, 8, 64, 16), ("bf16", [250] * 65, [1] * 65, 4, 4, 64, 16),
+    ("bf16_kv8", [90 * r for r in range(9)], [1] * 9, 32, 8, 128, 16), ("bf16_kv8", [2000] * 20, [1] * 20, 8, 8, 64, 16),
     ("bf16_kv8", [700, 1500], [1, 2], 8, 2, 128, 16), ("bf16_kv8", [1400, 9], [70, 33], 8, 2, 64, 16),
     ("bf16_kv8", [1400, 9], [70, 33], 8, 2, 128, 16)])
 def test_extend_of_small_batches(pa, gpu_device, dtype, P, E, Hq, Hkv, D, page):
