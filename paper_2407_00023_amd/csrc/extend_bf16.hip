@@ -226,7 +226,8 @@ __device__ __forceinline__ bool direct_item(const DirectArgs& a, int item, int G
     if (over || item >= n_items) return false;
     const int r = __popcll(__ballot(items_incl <= item));  // (the items of the requests up to this one are all before it)
     auto of = [&](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(x, r); };
-    const int n_req = of(parts), local = item - (of(items_incl) - of(tiles) * n_req), t = local / n_req, j = local - t * n_req;
+    // (a request's last rows, the most keys, first)
+    const int n_req = of(parts), local = item - (of(items_incl) - of(tiles) * n_req), at = local / n_req, j = local - at * n_req, t = of(tiles) - 1 - at;
     const int rP = of(P), all = of(rows);
     const int row0 = t * a.tile_rows, rows_here = min(a.tile_rows, all - row0);
     const int end = rP + (row0 + rows_here - 1) / G + 1, K = (end + kKT - 1) / kKT;
@@ -1344,7 +1345,7 @@ static int run_extend_bf16(pa::ExtendPlan p, const void* q_ext, const void* k_ex
     const float scale_log2e = scale * 1.4426950408889634f;
     DirectArgs direct{prefix_len, ext_len, ext_offsets, slot_offsets, nullptr, t.hdr, B, p.direct_parts, p.direct_tile_rows, p.direct_tiles,
                       p.direct_stride};
-    if (kv8 && p.direct_key_tiles > kDirectKeyTilesFp8) direct.parts = 0;
+    if (kv8 && p.direct_tile_rows == kNarrowRows && p.direct_key_tiles > kDirectKeyTilesFp8) direct.parts = 0;
     if (direct.parts > 0) {
         void* base = nullptr;
         int set = -1;

@@ -63,35 +63,45 @@ __device__ __forceinline__ constexpr int probe_depth(int k) {
     return kPackMinPrefix * in512[k];
 }
 
-// Small batches need no work list: where all tiles together fill the chip once at most, a workgroup can find its item - the
-// part w % parts of tile w / parts, the tiles counted request by request - from the lengths alone, and the workgroup that
-// finishes a tile last joins its parts.  That saves the launches of the planner and of the merge (13 and 5 us of the 42 of a
-// step of four decode requests) and gives up what the planner knows: rows of different requests never share a tile, so a common
-// prefix is read once per request instead of once (from the L2s, which hold it).  Measured, steps in us, list | direct: decode
-// behind 1,800 common keys and up to 3,000 own ones, 1 request 30.1 | 23.7, 4 39.1 | 28.0, 6 44.6 | 31.6; 20 to 60 new tokens
-// behind 2,200 keys, 1 42.6 | 36.3, 4 50.4 | 38.3; 100 to 300 new tokens behind 1,000 keys, 2 69.0 | 36.2, 4 79.8 | 37.8; behind
-// 2,200 keys, 1 48.5 | 47.9.  Hence the limits:
-constexpr int kDirectMaxB = 6;             // more requests have more to share ...
-constexpr int kDirectMaxBFew = 64;         // ... but in narrow tiles, where these fill the slots in kMaxDirectParts parts: decode behind
-                                           // 1,800 + 400 common and up to 350 own keys, 8 requests 36.1 | 28.0, 16 39.4 | 37.0; heads
-                                           // of 64 behind 900 and up to 900, 16 43.6 | 27.8; 1 to 6 new tokens, 8 requests 57.0 | 28.8
+// Batches whose tiles fill the chip a few times at most need no work list: a workgroup can find its item from the lengths alone - the
+// parts of the first request's tiles, then the second's, and so on - and the workgroup that finishes a tile last joins its parts.
+// That saves the launches of the planner and of the merge (13 and 5 us of the 42 of a step of four decode requests) and gives up
+// what the planner knows: rows of different requests never share a tile.  A common prefix is then read once per request (from the
+// L2s, which hold it), and left-over rows have tiles of their own; but a shared tile walks the own keys of all its members in the
+// general tile, 5 us per 64 keys, and with few rounds of workgroups the longest decides.  Measured, steps in us, list | direct:
+//   decode behind 1,800 + 400 common and up to 350 own keys, 8 requests 36.1 | 28.0, 16 39.4 | 37.0; 4 with up to 3,000 own ones
+//   39.1 | 28.0; heads of 64 behind 900 and up to 900, 16 requests 43.6 | 27.8; 1 to 6 new tokens, 8 requests 57.0 | 28.8
+//   50 to 150 new tokens behind 800 keys, 8 requests 58.9 | 32.5, 16 83.6 | 49, 32 114 | 83; behind 2,200 keys, 8 91.9 | 77, 16
+//   114 | 118 or, of other lengths, 135 | 122, 20 154 | 123; 20 to 60 new tokens of 32 110.7 | 82
+// Hence the limits:
+constexpr int kDirectMaxB = 64;            // one request per lane
 constexpr int kDirectFewRows = 16;         // rows per request on average: up to this many in narrow tiles; more, but too few not to
                                            // be shared over a common first part (first_part_rows): with a work list
-constexpr int kDirectKeyTilesNarrow = 16;  // key tiles per workgroup slot, at the longest lengths the host was told (fp8 pool:
-                                           // kDirectKeyTilesFp8) ...
-constexpr int kDirectKeyTilesWide = 10;    // ... (20 to 60 new tokens of 6 requests behind 3,400 keys, 11 a slot: 55.1 | 58.7)
+constexpr int kDirectKeyTilesNarrow = 16;  // narrow tiles: key tiles per workgroup slot, at the longest lengths the host was told (fp8
+                                           // pool: kDirectKeyTilesFp8)
+constexpr int kDirectKeyTilesWide = 24;    // the same for wide tiles, where a slot has half a tile at most
+constexpr int kDirectRounds = 3;           // wide tiles per slot at most ...
+constexpr int kDirectLongest = 48;         // ... of up to this many key tiles (longer ones want cutting: 20 requests behind 8,000 keys
+                                           // 168 | 208)
+constexpr int kDirectFewTiles = 6;         // batches of up to this many requests also where their tiles, in as many parts as there may be
+                                           // (kMaxDirectParts, kDirectWideParts), leave slots empty
 // and no more than kDirectWideParts parts of a tile of 128 rows where a list would make more: one workgroup joins them, 64 KB a part.
 static void make_direct(ExtendPlan& p, int B, int64_t rows, int64_t max_kv_len, int Hkv, int D) {
     p.direct_parts = 0;
+    if (B < 1 || B > kDirectMaxB) return;
     const bool few = rows <= int64_t{kDirectFewRows} * B;
-    if (B < 1 || B > (few ? kDirectMaxBFew : kDirectMaxB)) return;
     if (!few && rows <= int64_t{first_part_rows(D)} * B) return;
     const int tile_rows = few ? kNarrowRows : kTileRows;
     const int64_t tiles = rows / tile_rows + B, key_tiles = (max_kv_len + kKT - 1) / kKT, per_tile = p.slots / tiles;
-    if (per_tile < 1 || tiles * Hkv > kDirectSlots || tiles * key_tiles > int64_t{p.slots} * (few ? kDirectKeyTilesNarrow : kDirectKeyTilesWide)) return;
     const auto least = [](int64_t a, int64_t b) { return a < b ? a : b; };
-    if (!few && least(per_tile, key_tiles / kMinChunkTiles) > kDirectWideParts) return;
-    if (B > kDirectMaxB && per_tile > kMaxDirectParts) return;
+    if (few || per_tile >= 2) {
+        if (per_tile < 1 || tiles * Hkv > kDirectSlots) return;
+        if (tiles * key_tiles > int64_t{p.slots} * (few ? kDirectKeyTilesNarrow : kDirectKeyTilesWide)) return;
+        if (!few && least(per_tile, key_tiles / kMinChunkTiles) > kDirectWideParts) return;
+        if (B > kDirectFewTiles && (few ? per_tile > kMaxDirectParts : per_tile / 2 > kDirectWideParts)) return;
+    } else if (tiles > int64_t{p.slots} * kDirectRounds || key_tiles > kDirectLongest) {
+        return;
+    }
     // (wide tiles: one workgroup on a compute unit; a second one there slows the first by what it does itself)
     int64_t parts = least(least(few ? per_tile : per_tile / 2, key_tiles / (few ? kMinChunkNarrow : kDirectMinChunkWide)), few ? kMaxDirectParts : kDirectWideParts);
     parts = least(parts, p.tile_parts);
