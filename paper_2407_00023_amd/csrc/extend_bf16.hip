@@ -1346,7 +1346,7 @@ static int run_extend_bf16(pa::ExtendPlan p, const void* q_ext, const void* k_ex
     DirectArgs direct{prefix_len, ext_len, ext_offsets, slot_offsets, nullptr, t.hdr, B, p.direct_parts, p.direct_tile_rows, p.direct_tiles,
                       p.direct_stride};
     if (kv8 && p.direct_tile_rows == kNarrowRows && p.direct_key_tiles > kDirectKeyTilesFp8) direct.parts = 0;
-    if (direct.parts > 0) {
+    if (direct.parts > 1) {  // (the counters of tiles in parts)
         void* base = nullptr;
         int set = -1;
         if (const int rc = call_set_for(kSetsExtend, "pa_extend_attention", g_join_counters, stream, &base, &set)) return rc;
