@@ -73,6 +73,9 @@ __device__ __forceinline__ constexpr int probe_depth(int k) {
 //   39.1 | 28.0; heads of 64 behind 900 and up to 900, 16 requests 43.6 | 27.8; 1 to 6 new tokens, 8 requests 57.0 | 28.8
 //   50 to 150 new tokens behind 800 keys, 8 requests 58.9 | 32.5, 16 83.6 | 49, 32 114 | 83; behind 2,200 keys, 8 91.9 | 77, 16
 //   114 | 118 or, of other lengths, 135 | 122, 20 154 | 123; 20 to 60 new tokens of 32 110.7 | 82
+//   four rounds: 50 to 150 new tokens of 52 requests behind 800 keys 131 | 113, 73 to 219 of 44 behind 1,500 214 | 197, 184 to 552
+//   of 16 behind 100 94 | 88; heads of 64, 11 to 220 of 52 behind 800 129 | 99, but 152 to 457 of 22 behind 400, whose
+//   left-over rows nobody shares, 85 | 91, 403 to 492 of 16 behind 800 113 | 118; heads of 128, 200 to 1,200 of 12 118 | 120
 // Hence the limits:
 constexpr int kDirectMaxB = 64;            // one request per lane
 constexpr int kDirectFewRows = 16;         // rows per request on average: up to this many in narrow tiles; more, but too few not to
@@ -80,7 +83,9 @@ constexpr int kDirectFewRows = 16;         // rows per request on average: up to
 constexpr int kDirectKeyTilesNarrow = 16;  // narrow tiles: key tiles per workgroup slot, at the longest lengths the host was told (fp8
                                            // pool: kDirectKeyTilesFp8)
 constexpr int kDirectKeyTilesWide = 24;    // the same for wide tiles, where a slot has half a tile at most
-constexpr int kDirectRounds = 3;           // wide tiles per slot at most ...
+constexpr int kDirectRounds = 3;           // wide tiles per slot at most, or where requests have up to direct_short_rows on average, so
+constexpr int kDirectRoundsShort = 4;      // that what their left-over rows cost a list weighs more than what cutting would give, this many ...
+static inline int direct_short_rows(int D) { return D == 128 ? 1536 : 1024; }
 constexpr int kDirectLongest = 48;         // ... of up to this many key tiles (longer ones want cutting: 20 requests behind 8,000 keys
                                            // 168 | 208)
 constexpr int kDirectFewTiles = 6;         // batches of up to this many requests also where their tiles, in as many parts as there may be
@@ -99,7 +104,7 @@ static void make_direct(ExtendPlan& p, int B, int64_t rows, int64_t max_kv_len, 
         if (tiles * key_tiles > int64_t{p.slots} * (few ? kDirectKeyTilesNarrow : kDirectKeyTilesWide)) return;
         if (!few && least(per_tile, key_tiles / kMinChunkTiles) > kDirectWideParts) return;
         if (B > kDirectFewTiles && (few ? per_tile > kMaxDirectParts : per_tile / 2 > kDirectWideParts)) return;
-    } else if (tiles > int64_t{p.slots} * kDirectRounds || key_tiles > kDirectLongest) {
+    } else if (tiles > int64_t{p.slots} * (rows <= int64_t{direct_short_rows(D)} * B ? kDirectRoundsShort : kDirectRounds) || key_tiles > kDirectLongest) {
         return;
     }
     // (wide tiles: one workgroup on a compute unit; a second one there slows the first by what it does itself)

@@ -483,7 +483,10 @@ def test_hot_path_calls_refuse_what_is_no_device_tensor():
     ("bf16", [40 * r for r in range(40)], [1] * 40, 8, 8, 64, 16), ("bf16", [250] * 65, [1] * 65, 4, 4, 64, 16),
     ("bf16_kv8", [90 * r for r in range(9)], [1] * 9, 32, 8, 128, 16), ("bf16_kv8", [2000] * 20, [1] * 20, 8, 8, 64, 16),
     ("bf16_kv8", [700, 1500], [1, 2], 8, 2, 128, 16), ("bf16_kv8", [1400, 9], [70, 33], 8, 2, 64, 16),
-    ("bf16_kv8", [1400, 9], [70, 33], 8, 2, 128, 16)])
+    ("bf16_kv8", [1400, 9], [70, 33], 8, 2, 128, 16),
+    ("bf16", [30 * r for r in range(20)], [190 + 3 * r for r in range(20)], 32, 32, 128, 16),   # four tiles per slot: launched so,
+    ("bf16", [200, 0, 90, 64], [400, 390, 1, 130], 64, 64, 64, 16), ("bf16", [5, 0], [1600, 1600], 64, 64, 128, 16),
+    ("bf16", [100, 40], [1536, 1537], 64, 64, 128, 16), ("bf16", [9, 70, 0], [1024, 1000, 1048], 64, 64, 64, 16)])   # and a little beyond
 def test_extend_of_small_batches(pa, gpu_device, dtype, P, E, Hq, Hkv, D, page):
     assert _extend(pa, gpu_device, dtype, P, E, Hq, Hkv, D, page) <= TOL["bf16"]
 
