@@ -319,7 +319,10 @@ int pa_match_prefixes(const pa_tree* tree, const int32_t* tokens, const int32_t*
  * T, max_kv_len  HOST values: total extend tokens, and an upper bound on
  *                prefix_len[r] + ext_len[r] (used to size the launch; a request exceeding
  *                it is still computed correctly, only less efficiently)
- * workspace    at least pa_extend_workspace_bytes(B, T, max_kv_len, ...) bytes, 256-byte aligned
+ * workspace    at least pa_extend_workspace_bytes(B, T, max_kv_len, ...) bytes, 256-byte aligned.  What it holds beforehand does
+ *                not matter.  The call keeps nothing outside it: calls with workspaces of their own are independent of one
+ *                another on any number of streams and threads and in any number of captured graphs; calls that overlap
+ *                in time must not share one.
  * Requests with ext_len[r] = 0 produce no output rows.  Prefix slots must lie in
  * [0, num_slots); a slot outside is clamped into the pool (no fault, result for that
  * request unspecified).  out must not alias the inputs. */
@@ -341,7 +344,7 @@ int pa_extend_attention(const void* q_ext, const void* k_ext, const void* v_ext,
  * a batch whose plan still does not fit is refused with PA_ENOMEM and a message that names both sizes, and nothing
  * is launched.  All calls on one GPU share that GPU's buffer: calls that overlap in time on one GPU - on different
  * streams or from different threads - race, and the caller must order them.  Nothing in the buffer has to be zero
- * beforehand (each call writes every word it later reads).  The very first call on a device looks the buffer's
+ * beforehand.  The very first call on a device looks the buffer's
  * address up (hipGetSymbolAddress); make it once outside any stream capture.  PA_F32 needs no workspace and simply runs. */
 #define PA_STATIC_SCRATCH_BYTES (80u << 20)
 int pa_extend_attention_static(const void* q_ext, const void* k_ext, const void* v_ext, const void* kv_pool,

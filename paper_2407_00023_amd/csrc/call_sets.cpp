@@ -1,4 +1,4 @@
-// Which set of shared scratch memory a call may use (see common.h).
+// Which set of the matcher's shared scratch memory a call may use (see common.h).
 #include <mutex>
 
 #include "common.h"
@@ -13,10 +13,10 @@ struct DeviceSets {
     int captured = 0;
 };
 std::mutex g_mu;
-DeviceSets g_sets[kSetsUsers][kMaxDevices];
+DeviceSets g_sets[kMaxDevices];
 }  // namespace
 
-int call_set_for(CallSetUser user, const char* fn, const void* symbol, hipStream_t stream, void** base, int* set) {
+int call_set_for(const char* fn, const void* symbol, hipStream_t stream, void** base, int* set) {
     *set = -1;
     int dev = -1;
     PA_HIP(hipGetDevice(&dev));
@@ -27,7 +27,7 @@ int call_set_for(CallSetUser user, const char* fn, const void* symbol, hipStream
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (key != nullptr) PA_HIP(hipStreamIsCapturing(stream, &capture));  // (the default stream cannot be captured)
     std::lock_guard<std::mutex> lk(g_mu);
-    DeviceSets& d = g_sets[user][dev];
+    DeviceSets& d = g_sets[dev];
     if (d.base == nullptr) {
         void* ptr = nullptr;
         PA_HIP(hipGetSymbolAddress(&ptr, symbol));

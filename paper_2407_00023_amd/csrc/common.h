@@ -143,19 +143,18 @@ struct ProfScope {
     ProfScope& operator=(const ProfScope&) = delete;
 };
 
-// ---- scratch memory that workgroups of one launch share (counters, summaries): sets in an array of the code object ----
-// No two calls that can be in flight at once may meet in one set.  Calls on one stream follow one another, so a stream has
+// ---- scratch memory that the workgroups of one match share (counters, summaries): sets in an array of the code object ----
+// No two matches that can be in flight at once may meet in one set.  Matches on one stream follow one another, so a stream has
 // sets of its own (two in turn: a new stream may be given the handle of one just destroyed), those of the stream that has not
-// called for longest going to a new one.  A captured call keeps its set for good, since its graph may be replayed at any time
-// beside any other call (two replays of one captured call would meet in its output as well); where no such set is left, the
-// call takes a form without shared state.
+// matched for longest going to a new one: matches in flight at once on more than 64 streams are excluded by the interface.  A
+// captured call keeps its set for good, since its graph may be replayed at any time beside any other call (two replays of one
+// captured call would meet in its output as well); where no such set is left, it takes the form without shared state.
 constexpr int kStreamSets = 128;  // sets for calls on streams, two to a stream ...
 constexpr int kGraphSets = 128;   // ... and for captured calls, one each
 constexpr int kCallSets = kStreamSets + kGraphSets;
-enum CallSetUser { kSetsMatch = 0, kSetsExtend, kSetsUsers };
-// The set for a call of `user` on `stream` of the current device (`fn` names the entry point in messages); *set = -1: none.
+// The set for a call on `stream` of the current device (`fn` names the entry point in messages); *set = -1: none.
 // *base: the device address of the array, looked up once per device from `symbol`.
-int call_set_for(CallSetUser user, const char* fn, const void* symbol, hipStream_t stream, void** base, int* set);
+int call_set_for(const char* fn, const void* symbol, hipStream_t stream, void** base, int* set);
 
 }  // namespace pa
 

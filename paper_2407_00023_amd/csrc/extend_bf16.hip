@@ -35,7 +35,10 @@
 // causal diagonal.
 #include <hip/hip_bf16.h>
 
+#include <unistd.h>
+
 #include <atomic>
+#include <chrono>
 #include <mutex>
 #include <type_traits>
 
@@ -143,6 +146,10 @@ __device__ __forceinline__ void load_to_lds_16(const void* base, unsigned off, u
 __device__ __forceinline__ void load_to_lds_1(const void* g, unsigned lds_addr) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_ubyte %0, off" ::"v"(g), "s"(lds_addr) : "memory");
 }
+// Four bytes per lane, past the L2: lane l of the wave writes the 32-bit word at lds_addr + 4 l.
+__device__ __forceinline__ void load_to_lds_4(const void* g, unsigned lds_addr) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off sc1" ::"v"(g), "s"(lds_addr) : "memory");
+}
 __device__ __forceinline__ unsigned lds_address(const void* p) {
     return static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const unsigned char*)(p)));
 }
@@ -188,7 +195,7 @@ __device__ __forceinline__ void store_through_8(float* p, float2 v) {
 // What a workgroup of a launch without a work list needs to find its item (parts = 0: there is a work list).
 struct DirectArgs {
     const int32_t *prefix_len, *ext_len, *ext_offsets, *slot_offsets;
-    unsigned* counter;  // per tile and KV head: parts finished; back to 0 with the last one
+    unsigned long long *join, tag;  // a word in the workspace per tile and KV head, and this call's number in its upper 56 bits (join_parts)
     int32_t* hdr;
     int B, parts, tile_rows, tiles, stride;
 };
@@ -322,10 +329,15 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     int* const s_wave_own = s_mx0 + MT;  // per wave: the key range that holds the extend tokens of its rows' members
     float2* const s_ml = reinterpret_cast<float2*>(smem + kStages * STAGEB + kLdsMl);  // narrow tiles: (maximum, sum) per wave and row
     // (a launch without a work list has no members: what is needed to join the parts of the tile, read behind the key loop)
-    if (kDirect && tid == 0) {
-        s_mseg[0] = n_join;
-        s_mseg[2] = join_tile;
-        s_mseg[3] = rec0.x;
+    if constexpr (kDirect) {
+        if (tid == 0) {
+            s_mseg[0] = n_join;
+            s_mseg[2] = join_tile;
+            s_mseg[3] = rec0.x;
+        }
+        // (what the tile's word holds now, into s_mseg[4] and [5]: it flies during the key loop and takes no register)
+        if (n_join > 1 && tid < 2)
+            load_to_lds_4(reinterpret_cast<const unsigned*>(direct.join + join_tile * Hkv + g) + tid, __builtin_amdgcn_readfirstlane(lds_address(s_mseg + 4)));
     }
     if (shared) {
         if (tid < n_members) {  // (a member has at least one row in the tile: there are at most MT)
@@ -683,15 +695,41 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         return (first >= P && !shared && (!KV8 || (fast_ok & 1))) ? 2 : 0;
     };
 
-    // ---- a launch without a work list: the parts of a tile are joined by the workgroup that finishes last (a counter per tile
-    // and KV head).  Nobody waits for anybody; partial results are stored through to memory and awaited before the count, and
-    // read past this XCD's L2, which may hold what an earlier call left in the workspace.  All threads; prow >= 0. ----
+    // ---- a launch without a work list: the parts of a tile are joined by the workgroup that finishes last.  A word of the
+    // workspace per tile and KV head counts the parts that have finished.  It may hold anything beforehand: every part first
+    // sees to it that it holds this call's number and a count of 0 (claim_word; whoever comes first exchanges what was there
+    // for that, for the others the exchange fails), and the last one leaves 0, so that a captured call, whose number is the
+    // same in every replay, finds no count of its own.  The library keeps nothing outside the workspace, so calls with workspaces
+    // of their own never meet, whatever their streams, threads and graphs.  (Counters in arrays of the library's, a set per
+    // stream, were shared as soon as more streams called than there were sets.)  Nobody waits for anybody; partial results are stored
+    // through to memory and awaited before the count, and read past this XCD's L2, which may hold what an earlier call left
+    // there.  The word is asked for before the key loop and claimed ahead of the stores, so that its
+    // round trips hide behind them: a step of four decode requests takes 28.9 us with counters known to be 0, 29.2 so. ----
+    [[maybe_unused]] auto claim_word = [&]() __attribute__((always_inline)) {
+        if constexpr (kDirect) {
+            if (prow >= 0 && tid == 0) {
+                wait_vm_all();
+                const unsigned long long seen = static_cast<unsigned long long>(static_cast<unsigned>(s_mseg[5])) << 32 | static_cast<unsigned>(s_mseg[4]);
+                unsigned long long expected = seen;
+                if ((seen ^ direct.tag) >> 8 != 0)
+                    (void)__hip_atomic_compare_exchange_strong(direct.join + s_mseg[2] * Hkv + g, &expected, direct.tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    };
+    // All threads; prow >= 0.
     [[maybe_unused]] auto join_parts = [&]() __attribute__((always_inline)) {
         if constexpr (kDirect) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
             const int n = s_mseg[0];
-            if (tid == 0) s_mseg[1] = atomicInc(direct.counter + s_mseg[2] * Hkv + g, n - 1) == static_cast<unsigned>(n - 1);
+            if (tid == 0) {
+                unsigned long long* const word = direct.join + s_mseg[2] * Hkv + g;
+                const unsigned long long before = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const bool last = static_cast<int>(before & 255) == n - 1;
+                if (last) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s_mseg[1] = last;
+            }
             __syncthreads();
             if (!s_mseg[1]) return;
             const size_t base = static_cast<size_t>(s_mseg[3]) * Hkv + static_cast<size_t>(g) * rows_here;
@@ -876,6 +914,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
             if (p <= P + wave_i_last && !not_ours) general_block(p, 0, p + 32 > blk_vis_min);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (nothing still reads what the next loads overwrite)
         }
+        claim_word();
         // ---- join the waves: each leaves its sums in its quarter of the ring (16-byte pieces of a row XORed with the row's
         // number, so that the lanes of a store meet different banks) ----
         constexpr int V4 = D / 4;  // pieces per row
@@ -1095,6 +1134,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         atomicAdd(clk, static_cast<unsigned long long>(clock64() - clk_c0));
         atomicAdd(clk + 1, static_cast<unsigned long long>(wall_clock64() - clk_w0));
     }
+    claim_word();
     // ---- epilogue: lane holds, for block b and register i, head-dim element 32 b + 8 (i / 4) + 4 hh + i % 4 ----
     const float l_row = row_sum(l_run);
     if (!row_ok) {
@@ -1300,8 +1340,18 @@ static int launch_extend(const ExtendPlan& p, const PlanTables& t, const void* q
 
 }  // namespace pa
 
-// Counters of launches without a work list, per call in flight: part of the code object, zero when it is loaded and after every launch.
-static __device__ unsigned g_join_counters[pa::kCallSets][pa::kDirectSlots];
+// A number that no other call has, in the upper 56 bits (DirectArgs::tag): counted up from a start that differs from process to
+// process, since memory may come from another one's workspace.
+static unsigned long long next_call_tag() {
+    static std::atomic<unsigned long long> next{[] {
+        const int on_stack = 0;
+        unsigned long long x = static_cast<unsigned long long>(std::chrono::system_clock::now().time_since_epoch().count()) ^
+                               static_cast<unsigned long long>(std::chrono::steady_clock::now().time_since_epoch().count()) << 32 ^
+                               reinterpret_cast<uintptr_t>(&on_stack) << 16 ^ static_cast<unsigned long long>(getpid()) << 40;
+        return pa::path_mix(x, 0);
+    }()};
+    return next.fetch_add(1, std::memory_order_relaxed) << 8;
+}
 
 // Process-wide switch: 0 = every request gets row tiles of its own (no grouping by equal slots).
 static std::atomic<int> g_row_sharing{1};
@@ -1343,16 +1393,10 @@ static int run_extend_bf16(pa::ExtendPlan p, const void* q_ext, const void* k_ex
     // with the clock probe on, a few workgroups also add their cycle counts to two counters in the header
     unsigned long long* clk = prof_clock_enabled() ? reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(workspace) + kClockProbeOffset) : nullptr;
     const float scale_log2e = scale * 1.4426950408889634f;
-    DirectArgs direct{prefix_len, ext_len, ext_offsets, slot_offsets, nullptr, t.hdr, B, p.direct_parts, p.direct_tile_rows, p.direct_tiles,
+    DirectArgs direct{prefix_len, ext_len, ext_offsets, slot_offsets, reinterpret_cast<unsigned long long*>(t.tile), 0, t.hdr, B, p.direct_parts, p.direct_tile_rows, p.direct_tiles,
                       p.direct_stride};
     if (kv8 && p.direct_tile_rows == kNarrowRows && p.direct_key_tiles > kDirectKeyTilesFp8) direct.parts = 0;
-    if (direct.parts > 1) {  // (the counters of tiles in parts)
-        void* base = nullptr;
-        int set = -1;
-        if (const int rc = call_set_for(kSetsExtend, "pa_extend_attention", g_join_counters, stream, &base, &set)) return rc;
-        if (set < 0) direct.parts = 0;  // (more captured calls than sets: with a work list)
-        else direct.counter = static_cast<unsigned*>(base) + static_cast<size_t>(set) * kDirectSlots;
-    }
+    if (direct.parts > 1) direct.tag = next_call_tag();
     if (direct.parts == 0) launch_extend_plan(p, t, prefix_len, ext_len, ext_offsets, slot_offsets, slot_idx, B, Hq / Hkv, stream);
     const auto launch = D == 64 ? (kv8 ? launch_extend<64, true> : launch_extend<64, false>) : (kv8 ? launch_extend<128, true> : launch_extend<128, false>);
     launch(p, t, q_ext, k_ext, v_ext, kv_pool, slot_idx, Hq, Hkv, page_size, num_slots, T, scale_log2e, out, clk, direct, stream);

@@ -50,7 +50,6 @@ constexpr int kDirectKeyTilesFp8 = 9;   // key tiles per workgroup slot that go 
                                         // 16, 11.8 a slot, 42.2 | 47.2)
 constexpr int kMaxDirectParts = 16;     // parts of a tile at most in such a launch ...
 constexpr int kDirectWideParts = 4;     // ... and of a wide one
-constexpr int kDirectSlots = 512;  // counters of the tiles of a direct launch (tile x KV head), per call
 
 // Inclusive prefix sum over the wave, by the cross-lane moves of the vector ALU (rows of 16 lanes, then row to row).
 __device__ __forceinline__ int wave_scan(int x) {
@@ -65,7 +64,8 @@ __device__ __forceinline__ int wave_scan(int x) {
 
 // Workspace: a header of 256 bytes - hdr[0] = row tiles, hdr[1] = work items, hdr[2] = pieces of the merge, hdr[3] = 1 if
 // the batch on the device does not fit the plan (nothing is computed then), hdr[4] = rows of partial results, per KV head (without a
-// work list: at most that many) - and tables of int4:
+// work list: at most that many) - and, without a work list, a word of 64 bits per tile and KV head that counts the tile's finished
+// parts, from off_tile on, or the tables of the list, of int4:
 //   member[2 m]     = (first row among its group's packed rows, first extend token, first packed row of the request,
 //                      extend length)
 //   member[2 m + 1] = (extend tokens of the group's members before it, 0, 0, 0)

@@ -100,7 +100,7 @@ static void make_direct(ExtendPlan& p, int B, int64_t rows, int64_t max_kv_len, 
     const int64_t tiles = rows / tile_rows + B, key_tiles = (max_kv_len + kKT - 1) / kKT, per_tile = p.slots / tiles;
     const auto least = [](int64_t a, int64_t b) { return a < b ? a : b; };
     if (few || per_tile >= 2) {
-        if (per_tile < 1 || tiles * Hkv > kDirectSlots) return;
+        if (per_tile < 1) return;
         if (tiles * key_tiles > int64_t{p.slots} * (few ? kDirectKeyTilesNarrow : kDirectKeyTilesWide)) return;
         if (!few && least(per_tile, key_tiles / kMinChunkTiles) > kDirectWideParts) return;
         if (B > kDirectFewTiles && (few ? per_tile > kMaxDirectParts : per_tile / 2 > kDirectWideParts)) return;
@@ -112,6 +112,8 @@ static void make_direct(ExtendPlan& p, int B, int64_t rows, int64_t max_kv_len, 
     parts = least(parts, p.tile_parts);
     if (parts < 1) parts = 1;
     if (p.prows_cap / parts < rows) return;
+    // (the words that count a tile's parts lie where a list would: always enough room, see make_extend_plan)
+    if (parts > 1 && static_cast<size_t>(tiles) * Hkv * sizeof(unsigned long long) > p.off_part_o - p.off_tile) return;
     p.direct_parts = static_cast<int>(parts);
     p.direct_tile_rows = tile_rows;
     p.direct_tiles = static_cast<int>(tiles);

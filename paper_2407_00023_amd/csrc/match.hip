@@ -696,7 +696,7 @@ extern "C" int pa_match_prefixes(const pa_tree* tree, const int32_t* tokens, con
     if (B <= pa::kMultiMaxB) {
         void* base = nullptr;
         int set = -1;
-        rc = pa::call_set_for(pa::kSetsMatch, "pa_match_prefixes", HIP_SYMBOL(g_match_scratch), static_cast<hipStream_t>(stream), &base, &set);
+        rc = pa::call_set_for("pa_match_prefixes", HIP_SYMBOL(g_match_scratch), static_cast<hipStream_t>(stream), &base, &set);
         if (rc != PA_OK) return rc;
         if (set >= 0) scratch = static_cast<pa::MatchScratch*>(base) + set;
     }

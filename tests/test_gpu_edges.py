@@ -491,55 +491,116 @@ def test_extend_of_small_batches(pa, gpu_device, dtype, P, E, Hq, Hkv, D, page):
     assert _extend(pa, gpu_device, dtype, P, E, Hq, Hkv, D, page) <= TOL["bf16"]
 
 
-@pytest.mark.gpu
-def test_small_batches_on_streams_and_in_graphs(pa, gpu_device):
-    """Small batches cut into parts that their workgroups join through counters of the library's, on four streams at once, in
-    more captured calls than the library keeps counters for, and on replays beside eager calls: every result equals the eager one
-    bit for bit, but for captured calls beyond the counters, which build a work list: within the tolerance."""
+def _small_batches(pa, dev, sizes, Hq=8, Hkv=2, D=128, page=16, nslots=8192):
+    """Batches (P, E) of one pool, each as a function of (workspace, output, stream), with a maker of workspaces and the result
+    of a first call on a fresh one."""
     rng = np.random.default_rng(3)
-    Hq, Hkv, D, page, nslots = 8, 2, 128, 16, 8192
-    pool = torch.randn(pa.kv_pool_bytes(nslots, Hkv, D, torch.bfloat16, page) // 2, device=gpu_device).to(torch.bfloat16).view(torch.uint8)
-    tt = lambda a: torch.from_numpy(np.asarray(a, np.int32)).to(gpu_device)
+    pool = torch.randn(pa.kv_pool_bytes(nslots, Hkv, D, torch.bfloat16, page) // 2, device=dev).to(torch.bfloat16).view(torch.uint8)
+    tt = lambda a: torch.from_numpy(np.asarray(a, np.int32)).to(dev)
 
     def batch(P, E):
         off, eo = np.concatenate([[0], np.cumsum(np.add(P, E))]), np.concatenate([[0], np.cumsum(E)])
-        x = lambda h: torch.randn(int(eo[-1]), h, D, device=gpu_device).to(torch.bfloat16)
-        b = dict(a=[x(Hq), x(Hkv), x(Hkv), pool, tt(rng.permutation(nslots)[:off[-1]]), tt(off), tt(P), tt(E), tt(eo), D ** -0.5])
+        x = lambda h: torch.randn(int(eo[-1]), h, D, device=dev).to(torch.bfloat16)
+        a = [x(Hq), x(Hkv), x(Hkv), pool, tt(rng.permutation(nslots)[:off[-1]]), tt(off), tt(P), tt(E), tt(eo), D ** -0.5]
         kv = int(np.add(P, E).max())
-        b["kw"] = dict(page_size=page, num_slots=nslots, max_kv_len=kv, out=torch.empty_like(b["a"][0]), workspace=torch.zeros(
-            pa.extend_workspace_bytes(len(P), int(eo[-1]), kv, Hq, Hkv, D, torch.bfloat16), dtype=torch.uint8, device=gpu_device))
-        b["want"] = pa.extend_attention(*b["a"], **b["kw"]).clone()
+        nbytes = pa.extend_workspace_bytes(len(P), int(eo[-1]), kv, Hq, Hkv, D, torch.bfloat16)
+        b = dict(ws=lambda: torch.zeros(nbytes, dtype=torch.uint8, device=dev), out=lambda: torch.zeros_like(a[0]))
+        b["run"] = lambda ws, out, stream=None, more_keys=0: pa.extend_attention(
+            *a, page_size=page, num_slots=nslots, max_kv_len=kv + more_keys, out=out, workspace=ws, stream=stream)
+        b["want"] = b["run"](b["ws"](), b["out"]())
         return b
 
-    batches = [batch([1500, 700], [1, 3]), batch([2000], [90]), batch([900, 10, 2500], [1, 1, 2]), batch([1200, 1100], [40, 30])]
-    streams = [torch.cuda.Stream() for _ in batches]
+    made = [batch(*s) for s in sizes]
     torch.cuda.synchronize()
-    graph, n = torch.cuda.CUDAGraph(), 40
-    outs = [[torch.empty_like(b["want"]) for b in batches] for _ in range(n)]
+    return made
+
+
+_IN_PARTS = [([1500, 700], [1, 3]), ([2000], [90]), ([900, 10, 2500], [1, 1, 2]), ([1200, 1100], [40, 30])]
+
+
+@pytest.mark.gpu
+def test_small_batches_on_streams_and_in_graphs(pa, gpu_device):
+    """Small batches cut into parts that their workgroups join: eager calls queued on four streams while a graph of 160 captured
+    ones is replayed on a fifth, three times in a row.  Every single result equals the first call's bit for bit."""
+    batches = _small_batches(pa, gpu_device, _IN_PARTS)
+    streams, side, n, eager = [torch.cuda.Stream() for _ in batches], torch.cuda.Stream(), 40, 20
+    for b in batches:
+        b["eager_ws"], b["graph_ws"] = b["ws"](), b["ws"]()
+        b["eager"], b["graph"] = [b["out"]() for _ in range(eager)], [b["out"]() for _ in range(n)]
+    graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         for k in range(n):
-            for b, o in zip(batches, outs[k]):
-                pa.extend_attention(*b["a"], **dict(b["kw"], out=o))
-    for k in range(4):
+            for b in batches:
+                b["run"](b["graph_ws"], b["graph"][k])
+    for k in range(3):
         print(f"[case] small batches on streams and in graphs, round {k}", flush=True)
-        for o in outs:
-            for x in o:
-                x.zero_()
         for b in batches:
-            b["kw"]["out"].zero_()
+            for x in b["eager"] + b["graph"]:
+                x.zero_()
         torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            graph.replay()
         for b, s in zip(batches, streams):
             with torch.cuda.stream(s):
-                for _ in range(20):
-                    pa.extend_attention(*b["a"], **b["kw"])
+                for x in b["eager"]:
+                    b["run"](b["eager_ws"], x)
         torch.cuda.synchronize()
         for b in batches:
-            assert torch.equal(b["kw"]["out"], b["want"])
-        graph.replay()
-        torch.cuda.synchronize()
-        for i, o in enumerate(outs):
-            for b, x in zip(batches, o):
-                assert torch.equal(x, b["want"]) if i < 8 else (x.float() - b["want"].float()).abs().max() <= TOL["bf16"]
+            assert all(torch.equal(x, b["want"]) for x in b["eager"])
+            assert all(torch.equal(x, b["want"]) for x in b["graph"])
+
+
+@pytest.mark.gpu
+def test_small_batches_on_many_streams(pa, gpu_device):
+    """Calls with workspaces of their own do not depend on one another, on however many streams: 80 of them, batches whose tiles
+    have different numbers of parts, six calls queued on each, every result compared."""
+    import ctypes
+    hip = ctypes.CDLL("libamdhip64.so")
+    batches = _small_batches(pa, gpu_device, _IN_PARTS)
+    streams = []
+    for _ in range(80):
+        s = ctypes.c_void_p()
+        assert hip.hipStreamCreateWithFlags(ctypes.byref(s), 1) == 0  # (non-blocking)
+        streams.append(s.value)
+    per = [(batches[i % 4], batches[i % 4]["ws"](), [batches[i % 4]["out"]() for _ in range(6)]) for i in range(80)]
+    torch.cuda.synchronize()
+    print("[case] small batches on 80 streams", flush=True)
+    for k in range(6):
+        for s, (b, ws, outs) in zip(streams, per):
+            b["run"](ws, outs[k], s)
+    torch.cuda.synchronize()
+    for b, _, outs in per:
+        assert all(torch.equal(x, b["want"]) for x in outs)
+    for s in streams:
+        assert hip.hipStreamDestroy(ctypes.c_void_p(s)) == 0
+
+
+@pytest.mark.gpu
+def test_small_batches_whatever_the_workspace_holds(pa, gpu_device):
+    """The words that count a tile's finished parts may hold anything before a call: zeros, ones, random bits, the tables that a
+    call with a work list left there, what the same captured call left; bit for bit the same result."""
+    for b in _small_batches(pa, gpu_device, _IN_PARTS):
+        ws, out = b["ws"](), b["out"]()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            b["run"](ws, out)
+        large = torch.zeros(1 << 28, dtype=torch.uint8, device=gpu_device)
+        fills = {"zeros": lambda: ws.zero_(), "ones": lambda: ws.fill_(255), "ones at the bottom": lambda: ws.view(torch.int64).fill_(1),
+                 "random": lambda: ws.random_(0, 256), "as it is": lambda: None}
+        for name, fill in fills.items():
+            for call in ("eager", "replay", "replay", "eager"):
+                print(f"[case] small batches, workspace {name}, {call}", flush=True)
+                fill()
+                out.zero_()
+                graph.replay() if call == "replay" else b["run"](ws, out)
+                torch.cuda.synchronize()
+                assert torch.equal(out, b["want"])
+        for _ in range(2):  # (a call told of 1,000,000 keys more builds a list)
+            b["run"](large, out, more_keys=1000000)
+            assert (out.float() - b["want"].float()).abs().max() <= TOL["bf16"]
+            out.zero_()
+            b["run"](large, out)
+            assert torch.equal(out, b["want"])
 
 
 # changes of a tree go to the device in pieces of 256 words, runs of more than 16,384 words by copies of their own
