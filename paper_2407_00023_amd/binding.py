@@ -150,12 +150,18 @@ class Tree:
     def admit(self, tokens, now: int):
         """-> (n_cached, new_slots int32 tensor of the tokens that were not cached, handle)."""
         admitted = _calls.tree_admit(self, tokens, now)
-        if admitted is None:
-            t = torch.as_tensor(tokens, dtype=torch.int32).contiguous()
-            if t.is_cuda or t.dim() != 1:
-                raise TypeError("tokens must be a host int32 vector")
-            admitted = _calls.tree_admit(self, t, now)
-        return admitted
+        if admitted is not None:
+            return admitted
+        t = torch.as_tensor(tokens, dtype=torch.int32).contiguous()
+        if t.is_cuda or t.dim() != 1:
+            raise TypeError("tokens must be a host int32 vector")
+        admitted = _calls.tree_admit(self, t, now)
+        if admitted is not None:
+            return admitted
+        slots = torch.full_like(t, -1)
+        cached, handle = C.c_int32(0), _i64(0)
+        _check(_lib.pa_tree_admit(self._h, _ptr(t), t.numel(), now, _ptr(slots), C.byref(cached), C.byref(handle)), "pa_tree_admit")
+        return int(cached.value), slots[int(cached.value):].clone(), int(handle.value)
 
     def release(self, handle: int) -> None:
         _check(_lib.pa_tree_release(self._h, handle), "pa_tree_release")

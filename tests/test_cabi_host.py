@@ -153,3 +153,51 @@ def test_a_workspace_is_good_for_every_smaller_batch(pa, Hq, Hkv, D):
     # no room for the partial results of common first parts: the plan does without them; no room for any plan: refused
     assert _extend_rc(lib, 256, 256, 4096, Hq, Hkv, D, lib_ws(lib, 256, 256, 4096, Hq, Hkv, D, 1) - 1) == -1
     assert _extend_rc(lib, 256, 256, 4096, Hq, Hkv, D, 4096) == -2
+
+
+class _AsParameter:
+    _as_parameter_ = C.c_int64(5)
+
+
+class _Index:
+    def __index__(self):
+        return 5
+
+
+def _other_types():
+    import torch
+    tok = torch.arange(8, dtype=torch.int32)
+    nows = [5, True, 1 << 70, np.int64(5), np.int32(5), np.array(5), torch.tensor(5), C.c_int64(5), _AsParameter(), _Index()]
+    prompts = [tok, tok.tolist(), tok.numpy(), tok.long(), tok.float(), np.repeat(tok.numpy(), 2)[::2]]
+    return [(tok, now) for now in nows] + [(p, now) for p in prompts[1:] for now in (5, np.int64(5))]
+
+
+@pytest.mark.parametrize("tokens,now", _other_types())
+def test_admit_takes_every_type_that_stands_for_the_numbers(pa, tokens, now):
+    """What ctypes takes for a 64-bit number and torch for an int32 vector, each the same admission."""
+    tree = pa.Tree()
+    tree.attach_pool(64, 4)
+    n_cached, slots, handle = tree.admit(tokens, now)
+    assert n_cached == 0 and slots.tolist() == list(range(8)) and str(slots.dtype) == "torch.int32"
+    assert type(handle) is int and tree.stats() == (2, 8)
+    tree.release(handle)
+
+
+@pytest.mark.parametrize("kind", ["float now", "text now", "no now", "int32 object", "meta tokens", "matrix", "scalar", "empty", "pool full", "closed"])
+def test_admit_refuses_by_an_exception(pa, kind):
+    """A call that cannot be made raises; it neither returns None nor admits anything."""
+    import torch
+    tok = torch.arange(8, dtype=torch.int32)
+    args = {"float now": (tok, 5.0), "text now": (tok, "5"), "no now": (tok, None), "int32 object": (tok, C.c_int32(5)),
+            "meta tokens": (tok.to("meta"), 5), "matrix": (tok.view(2, 4), 5), "scalar": (tok[0], 5), "empty": (tok[:0], 5)}.get(kind, (tok, 5))
+    want = {"meta tokens": pa.PrefixAttnError, "empty": pa.PrefixAttnError, "pool full": pa.PrefixAttnError, "closed": pa.PrefixAttnError,
+            "matrix": TypeError, "scalar": TypeError}.get(kind, C.ArgumentError)
+    tree = pa.Tree()
+    tree.attach_pool(4 if kind == "pool full" else 64, 1)
+    before = tree.stats()
+    if kind == "closed":
+        tree.close()
+    with pytest.raises(want):
+        tree.admit(*args)
+    if kind != "closed":
+        assert tree.stats() == before
