@@ -726,6 +726,74 @@ static void release_device(pa_tree* t) {
     t->uploaded = false;
 }
 
+namespace pa {
+
+// Writes these runs (offset, end) of the mirror to the device.
+static int write_changes(pa_tree* tree, const std::vector<std::pair<size_t, size_t>>& runs, hipStream_t stream) {
+    // the runs are gathered into a transfer buffer (two take turns) and written from there
+    const int x = tree->xfer_next;
+    tree->xfer_next ^= 1;
+    if (tree->xfer_pending[x]) {  // the upload before the last one, long done as a rule
+        PA_HIP(hipEventSynchronize(tree->xfer_done[x]));
+        tree->xfer_pending[x] = false;
+    }
+    // Short runs go in pieces, all of them with one launch; a run of more than kLongRun is copied by itself (the copy
+    // engines' rate is worth a command of their own then).
+    constexpr size_t kLongRun = size_t(64) << 10, kPieceBytes = size_t(4) * kChangeWords;
+    size_t n_pieces = 0, long_bytes = 0;
+    for (const auto& run : runs) {
+        const size_t len = run.second - run.first;
+        if (len > kLongRun) long_bytes += len;
+        else n_pieces += (len + kPieceBytes - 1) / kPieceBytes;
+    }
+    const size_t o_words = (n_pieces * sizeof(ChangePiece) + 255) & ~size_t(255), o_long = o_words + n_pieces * kPieceBytes;
+    const size_t need = o_long + long_bytes;
+    if (tree->xfer_cap[x] < need) {
+        if (tree->h_xfer[x]) (void)hipHostFree(tree->h_xfer[x]);
+        tree->h_xfer[x] = nullptr;
+        tree->xfer_cap[x] = 0;
+        const size_t want = need * 2 > (size_t(64) << 10) ? need * 2 : (size_t(64) << 10);
+        if (hipHostMalloc(&tree->h_xfer[x], want, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+            (void)hipGetLastError();
+            tree->h_xfer[x] = nullptr;
+            return fail(PA_ENOMEM, "pa_tree_upload: %zu bytes of pinned host memory", want);
+        }
+        PA_HIP(hipHostGetDevicePointer(&tree->d_xfer[x], tree->h_xfer[x], 0));
+        tree->xfer_cap[x] = want;  // (only a buffer with both addresses is used)
+    }
+    if (!tree->xfer_done[x]) PA_HIP(hipEventCreateWithFlags(&tree->xfer_done[x], hipEventDisableTiming));
+    unsigned char* h = static_cast<unsigned char*>(tree->h_stage);
+    unsigned char* d = static_cast<unsigned char*>(tree->d_blob);
+    unsigned char* xb = static_cast<unsigned char*>(tree->h_xfer[x]);
+    ChangePiece* piece = reinterpret_cast<ChangePiece*>(xb);
+    size_t k = 0, at = o_long;
+    for (const auto& run : runs) {
+        const size_t len = run.second - run.first;
+        if (len > kLongRun) {
+            std::memcpy(xb + at, h + run.first, len);
+            PA_HIP(hipMemcpyAsync(d + run.first, xb + at, len, hipMemcpyHostToDevice, stream));
+            at += len;
+            continue;
+        }
+        for (size_t from = run.first; from < run.second; from += kPieceBytes, ++k) {
+            const size_t n = std::min(kPieceBytes, run.second - from);
+            piece[k] = {from / 4, static_cast<uint32_t>(n / 4), 0u};  // (every array of the mirror is made of 32-bit words)
+            std::memcpy(xb + o_words + k * kPieceBytes, h + from, n);
+        }
+    }
+    if (n_pieces) {
+        const unsigned char* dx = static_cast<const unsigned char*>(tree->d_xfer[x]);
+        const int rc = launch_apply_changes(reinterpret_cast<const ChangePiece*>(dx), reinterpret_cast<const uint32_t*>(dx + o_words),
+                                            static_cast<int>(n_pieces), d, stream);
+        if (rc != PA_OK) return rc;
+    }
+    PA_HIP(hipEventRecord(tree->xfer_done[x], stream));
+    tree->xfer_pending[x] = true;
+    return PA_OK;
+}
+
+}  // namespace pa
+
 extern "C" int pa_tree_upload(pa_tree* tree, void* stream_) {
     PA_REQUIRE(tree != nullptr, "pa_tree_upload: tree is NULL");
     hipStream_t stream = static_cast<hipStream_t>(stream_);
@@ -757,66 +825,13 @@ extern "C" int pa_tree_upload(pa_tree* tree, void* stream_) {
         }
         dirty.clear();
         if (bytes) {
-            // the runs are gathered into a transfer buffer (two take turns) and written from there
-            const int x = tree->xfer_next;
-            tree->xfer_next ^= 1;
-            if (tree->xfer_pending[x]) {  // the upload before the last one, long done as a rule
-                PA_HIP(hipEventSynchronize(tree->xfer_done[x]));
-                tree->xfer_pending[x] = false;
+            // (whatever fails from here on leaves changes unwritten: the next upload writes the whole mirror)
+            tree->mirror_ok = false;
+            if (const int rc = pa::write_changes(tree, runs, stream)) {
+                (void)hipStreamSynchronize(stream);  // (what was enqueued before may still read the transfer buffer)
+                return rc;
             }
-            // Short runs go in pieces, all of them with one launch; a run of more than kLongRun is copied by itself (the copy
-            // engines' rate is worth a command of their own then).
-            constexpr size_t kLongRun = size_t(64) << 10, kPieceBytes = size_t(4) * pa::kChangeWords;
-            size_t n_pieces = 0, long_bytes = 0;
-            for (const auto& run : runs) {
-                const size_t len = run.second - run.first;
-                if (len > kLongRun) long_bytes += len;
-                else n_pieces += (len + kPieceBytes - 1) / kPieceBytes;
-            }
-            const size_t o_words = (n_pieces * sizeof(pa::ChangePiece) + 255) & ~size_t(255), o_long = o_words + n_pieces * kPieceBytes;
-            const size_t need = o_long + long_bytes;
-            if (tree->xfer_cap[x] < need) {
-                if (tree->h_xfer[x]) (void)hipHostFree(tree->h_xfer[x]);
-                tree->h_xfer[x] = nullptr;
-                tree->xfer_cap[x] = 0;
-                const size_t want = need * 2 > (size_t(64) << 10) ? need * 2 : (size_t(64) << 10);
-                if (hipHostMalloc(&tree->h_xfer[x], want, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
-                    (void)hipGetLastError();
-                    tree->h_xfer[x] = nullptr;
-                    tree->mirror_ok = false;
-                    return pa::fail(PA_ENOMEM, "pa_tree_upload: %zu bytes of pinned host memory", want);
-                }
-                tree->xfer_cap[x] = want;
-                PA_HIP(hipHostGetDevicePointer(&tree->d_xfer[x], tree->h_xfer[x], 0));
-            }
-            if (!tree->xfer_done[x]) PA_HIP(hipEventCreateWithFlags(&tree->xfer_done[x], hipEventDisableTiming));
-            unsigned char* h = static_cast<unsigned char*>(tree->h_stage);
-            unsigned char* d = static_cast<unsigned char*>(tree->d_blob);
-            unsigned char* xb = static_cast<unsigned char*>(tree->h_xfer[x]);
-            pa::ChangePiece* piece = reinterpret_cast<pa::ChangePiece*>(xb);
-            size_t k = 0, at = o_long;
-            for (const auto& run : runs) {
-                const size_t len = run.second - run.first;
-                if (len > kLongRun) {
-                    std::memcpy(xb + at, h + run.first, len);
-                    PA_HIP(hipMemcpyAsync(d + run.first, xb + at, len, hipMemcpyHostToDevice, stream));
-                    at += len;
-                    continue;
-                }
-                for (size_t from = run.first; from < run.second; from += kPieceBytes, ++k) {
-                    const size_t n = std::min(kPieceBytes, run.second - from);
-                    piece[k] = {from / 4, static_cast<uint32_t>(n / 4), 0u};  // (every array of the mirror is made of 32-bit words)
-                    std::memcpy(xb + o_words + k * kPieceBytes, h + from, n);
-                }
-            }
-            if (n_pieces) {
-                const unsigned char* dx = static_cast<const unsigned char*>(tree->d_xfer[x]);
-                const int rc = pa::launch_apply_changes(reinterpret_cast<const pa::ChangePiece*>(dx), reinterpret_cast<const uint32_t*>(dx + o_words),
-                                                        static_cast<int>(n_pieces), d, stream);
-                if (rc != PA_OK) return rc;
-            }
-            PA_HIP(hipEventRecord(tree->xfer_done[x], stream));
-            tree->xfer_pending[x] = true;
+            tree->mirror_ok = true;
         }
         tree->uploaded = true;
         ++tree->n_incremental_uploads;
