@@ -722,7 +722,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         if constexpr (kDirect) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            const int n = s_mseg[0];
+            const int n = __builtin_amdgcn_readfirstlane(s_mseg[0]);
             if (tid == 0) {
                 unsigned long long* const word = direct.join + s_mseg[2] * Hkv + g;
                 const unsigned long long before = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -787,7 +787,8 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                     const int x = min(x0 + 256 * k, n_x - 1);
 #pragma unroll
                     for (int u = 0; u < kS; ++u) {
-                        const float w = s0 + u < n ? s_w[min(s0 + u, n - 1) * rows_here + x / V4] : 0.f;
+                        if (s0 + u >= n) continue;  // (the last part again: 0 times it is no 0 where it holds an infinity)
+                        const float w = s_w[(s0 + u) * rows_here + x / V4];
                         acc[k].x += w * a[k][u].x; acc[k].y += w * a[k][u].y; acc[k].z += w * b[k][u].x; acc[k].w += w * b[k][u].y;
                     }
                 }
@@ -1248,7 +1249,9 @@ __global__ __launch_bounds__(256) void extend_merge_kernel(int Hq, int Hkv, __hi
                 acc.x *= old; acc.y *= old; acc.z *= old; acc.w *= old;
 #pragma unroll
                 for (int u = 0; u < kAhead; ++u) {
-                    const float wgt = s0 + u >= n || ml[u].x == -INFINITY ? 0.f : exp2f(ml[u].x - m_new);
+                    const bool again = s0 + u >= n;  // (the last part once more: 0 times it would be no 0 where it holds an infinity)
+                    const float wgt = again || ml[u].x == -INFINITY ? 0.f : exp2f(ml[u].x - m_new);
+                    o[u].x = again ? 0.f : o[u].x; o[u].y = again ? 0.f : o[u].y; o[u].z = again ? 0.f : o[u].z; o[u].w = again ? 0.f : o[u].w;
                     l += wgt * ml[u].y;
                     acc.x += wgt * o[u].x; acc.y += wgt * o[u].y; acc.z += wgt * o[u].z; acc.w += wgt * o[u].w;
                 }

@@ -603,6 +603,39 @@ def test_small_batches_whatever_the_workspace_holds(pa, gpu_device):
             assert torch.equal(out, b["want"])
 
 
+# prefixes cut into 2 to 16 parts of narrow tiles and 2 to 4 of wide ones, with and without a work list; E new tokens of G rows
+@pytest.mark.gpu
+@pytest.mark.parametrize("kv_more", [0, 1000000])
+@pytest.mark.parametrize("P,E,G,D", [(2000, 1, 4, 128), (2000, 1, 4, 64), (700, 2, 8, 128), (1300, 11, 1, 128), (5000, 1, 1, 64), (1600, 90, 2, 128),
+                                     (2600, 70, 4, 64)])
+def test_extend_in_parts_with_an_infinite_value(pa, gpu_device, P, E, G, D, kv_more):
+    """An infinity in a V row of the prefix makes that element of every row infinite, not NaN, whichever part of the keys it lies in
+    and however many parts there are; the other elements are untouched.  (kv_more: told of as many keys more, a call builds a list.)"""
+    Hkv, nslots = 2, -(-P // 16) * 16
+    gen = torch.Generator(device=gpu_device).manual_seed(P + E)
+    mk = lambda n, h: torch.randn(n, h, D, generator=gen, device=gpu_device).to(torch.bfloat16)
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=gpu_device)
+    q, k, v, pk, pv = mk(E, G * Hkv), mk(E, Hkv), mk(E, Hkv), mk(nslots, Hkv), mk(nslots, Hkv)
+    kw, slots = dict(page_size=16, num_slots=nslots), torch.arange(nslots, dtype=torch.int32, device=gpu_device)
+
+    def run(pvv):
+        pool = torch.zeros(pa.kv_pool_bytes(nslots, Hkv, D, torch.bfloat16, 16), dtype=torch.uint8, device=gpu_device)
+        pa.append_kv(pool, slots, pk, pvv, **kw)
+        ws = torch.zeros(pa.extend_workspace_bytes(1, E, P + E + kv_more, G * Hkv, Hkv, D, torch.bfloat16), dtype=torch.uint8, device=gpu_device)
+        out = pa.extend_attention(q, k, v, pool, i32(list(range(P)) + [-1] * E), i32([0, P + E]), i32([P]), i32([E]), i32([0, E]), D ** -0.5,
+                                  max_kv_len=P + E + kv_more, workspace=ws, **kw)
+        return out.float().cpu()
+
+    plain = run(pv)
+    for at in (3, P // 2, P - 70, P - 1):
+        pvv = pv.clone()
+        pvv[at, 1, 5] = float("inf")
+        out = run(pvv)
+        assert (out[:, G:, 5] == float("inf")).all(), at
+        out[:, G:, 5] = plain[:, G:, 5]
+        assert torch.equal(out, plain), at
+
+
 # changes of a tree go to the device in pieces of 256 words, runs of more than 16,384 words by copies of their own
 @pytest.mark.gpu
 def test_upload_of_changes_at_the_edges_of_pieces_and_long_runs(pa, gpu_device):
