@@ -190,7 +190,7 @@ struct PlanArgs {
     int32_t* hdr;
     int2* tile;
     int4 *member, *item, *chunk;
-    int B, G, tiles_cap, own_cap, items_cap, prows_cap, chunks_cap, resident, slot_items, pack, first_part, tile_parts, chunk_rows;
+    int B, G, tiles_cap, own_cap, items_cap, prows_cap, chunks_cap, slots, resident, slot_items, pack, first_part, tile_parts, chunk_rows;
 };
 
 // All of a kernel's arguments asked for at its start: where they are looked at for the first time later on, each cache line of
@@ -328,7 +328,13 @@ __device__ __forceinline__ void emit_items(const PlanArgs& a, int n_rows, int n_
     // round that leaves half of the slots empty at two thirds of that (a workgroup alone on its compute unit is faster), the
     // fixed cost of an item, and what the partial results cost.  Steps in us, always cut | by this rule: 16 requests of 50 to 150
     // new tokens behind 2,200 keys (50 tiles for 64 slots) 124.6 | 112.0, 24 160.9 | 149.2; 32 on 2 KV heads 128.2 | 114.9. ----
-    if (n_all == n_rows && total[0] > n_all) {
+    // Narrow tiles are bound by memory, and with slots empty by the time a workgroup waits for it: they are cut as they were before,
+    // unless every round of them uncut is at least half full (us, cut | uncut; 8 KV heads: 16 decode requests with 4,000 keys each 68 | 85
+    // (4 KV heads, 32), 70 with 2,500 151 | 165, but 48 with 1,000 51 | 42, 64 56 | 48; 2 KV heads: 64 with 4,000 69 | 85, 100 with
+    // 2,500 62 | 69, but 160 with 1,000 53 | 44).
+    const int last_round = n_all % a.slots;
+    const bool may_stay = total[1] > kNarrowRows * total[0] || last_round == 0 || 2 * last_round >= a.slots;
+    if (n_all == n_rows && total[0] > n_all && may_stay) {
         const float inv_slots = __builtin_amdgcn_rcpf(static_cast<float>(a.resident));
         const float keys_cost = static_cast<float>(W - n_all * kItemOverhead);  // without the items' fixed cost
         auto finish = [&](int items) {
@@ -866,7 +872,7 @@ __global__ __launch_bounds__(NT) void extend_plan_large_kernel(PlanArgs a) {
 int launch_extend_plan(const ExtendPlan& p, const PlanTables& t, const int32_t* prefix_len, const int32_t* ext_len, const int32_t* ext_offsets,
                        const int32_t* slot_offsets, const int32_t* slot_idx, int B, int G, hipStream_t stream) {
     const PlanArgs a{prefix_len, ext_len, ext_offsets, slot_offsets, slot_idx, t.hdr, t.tile, t.member, t.item, t.chunk, B, G, p.tiles_cap,
-                     p.own_cap, p.items_cap, p.prows_cap, p.chunks_cap, p.resident, p.slots * p.rounds, p.pack, p.first_part, p.tile_parts, p.chunk_rows};
+                     p.own_cap, p.items_cap, p.prows_cap, p.chunks_cap, p.slots, p.resident, p.slots * p.rounds, p.pack, p.first_part, p.tile_parts, p.chunk_rows};
     ProfScope prof(kProfPlan, stream);
     // (few requests and tiles: four waves meet at a barrier sooner than sixteen)
     const int most = p.tiles_cap + p.own_cap;

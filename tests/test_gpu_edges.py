@@ -209,9 +209,10 @@ def test_captured_matches_beside_eager_ones(pa, gpu_device):
             check(small, pls[k], sis[k])
 
 
-def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None):
+def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None, kv_more=0, cut=None):
     """Largest error against the oracle for requests with P[r] cached tokens, the first `common` of them the same for all.
-    tiles: how many row tiles the work list has to hold."""
+    tiles: how many row tiles the work list has to hold; kv_more: how many more keys than it has the call is told of (1,000,000: it
+    builds a list whatever the batch); cut: whether any tile has to be cut into parts."""
     import oracle
     rng = np.random.default_rng(seed)
     P, E = np.asarray(P, np.int32), np.asarray(E, np.int32)
@@ -244,13 +245,15 @@ def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None
     tt = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
     pa.append_kv(pool, tt(backed), to_torch(pk, el, dev), to_torch(pv, el, dev), **kw)
     print(f"[case] extend {dtype} P {P[:6]} E {E[:6]} Hq {Hq} Hkv {Hkv} D {D} page {page} common {common}", flush=True)
-    ws = torch.zeros(pa.extend_workspace_bytes(B, T, int((P + E).max()), Hq, Hkv, D, tdt), dtype=torch.uint8, device=dev)
+    told = int((P + E).max()) + kv_more
+    ws = torch.zeros(pa.extend_workspace_bytes(B, T, told, Hq, Hkv, D, tdt), dtype=torch.uint8, device=dev)
     out = pa.extend_attention(to_torch(q, el, dev), to_torch(k, el, dev), to_torch(v, el, dev), pool, tt(si), tt(off), tt(P), tt(E),
-                              tt(eo), D ** -0.5, max_kv_len=int((P + E).max()), workspace=ws, **kw)
+                              tt(eo), D ** -0.5, max_kv_len=told, workspace=ws, **kw)
     torch.cuda.synchronize()
     if dtype != "f32":
         assert ws[12:16].view(torch.int32).item() == 0  # (the work list fitted)
         assert tiles is None or ws[:4].view(torch.int32).item() == tiles
+        assert cut is None or (ws[4:8].view(torch.int32).item() > ws[:4].view(torch.int32).item()) == cut
     opk, opv = oracle.new_pool(nslots, Hkv, D, dtype)
     oracle.append_kv(opk, opv, backed, pk, pv, dtype)
     ref = oracle.extend_attention(q, k, v, opk, opv, si, off, P, E, eo, D ** -0.5, dtype)
@@ -670,3 +673,12 @@ def test_upload_of_changes_at_the_edges_of_pieces_and_long_runs(pa, gpu_device):
 @pytest.mark.parametrize("B", [4, 16, 17])
 def test_extend_cuts_tiles_or_not_around_a_round_of_workgroups(pa, gpu_device, B):
     assert _extend(pa, gpu_device, "bf16", [2100 + r % 3 for r in range(B)], [128 - r % 2 for r in range(B)], 32, 32, 128, 16, common=300) <= TOL["bf16"]
+
+
+# narrow tiles in a list: uncut only where every round of workgroups is at least half full (8, 4 and 2 KV heads: 64, 128 and 256 slots)
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hkv,D,P,cut", [(12, 8, 128, 1000, True), (12, 8, 64, 1000, True), (32, 4, 64, 1000, True), (70, 2, 128, 1000, True),
+                                           (70, 8, 64, 520, True), (31, 8, 64, 600, True), (32, 8, 64, 600, False), (48, 8, 64, 600, False),
+                                           (64, 8, 64, 600, False), (7, 1, 128, 1000, True)])
+def test_extend_cuts_narrow_tiles_or_not(pa, gpu_device, B, Hkv, D, P, cut):
+    assert _extend(pa, gpu_device, "bf16", [P + r % 3 for r in range(B)], [1] * B, 4 * Hkv, Hkv, D, 16, kv_more=1000000, cut=cut) <= TOL["bf16"]
