@@ -229,6 +229,7 @@ __device__ __forceinline__ bool direct_item(const DirectArgs& a, int item, int G
         a.hdr[2] = 0;
         a.hdr[3] = over;
         a.hdr[4] = over || n_items == n_tiles ? 0 : n_rows * a.parts;  // (at most)
+        a.hdr[5] = a.parts;
     }
     if (over || item >= n_items) return false;
     const int r = __popcll(__ballot(items_incl <= item));  // (the items of the requests up to this one are all before it)
@@ -1398,7 +1399,9 @@ static int run_extend_bf16(pa::ExtendPlan p, const void* q_ext, const void* k_ex
     const float scale_log2e = scale * 1.4426950408889634f;
     DirectArgs direct{prefix_len, ext_len, ext_offsets, slot_offsets, reinterpret_cast<unsigned long long*>(t.tile), 0, t.hdr, B, p.direct_parts, p.direct_tile_rows, p.direct_tiles,
                       p.direct_stride};
-    if (kv8 && p.direct_tile_rows == kNarrowRows && p.direct_key_tiles > kDirectKeyTilesFp8) direct.parts = 0;
+    if (kv8 && p.direct_tile_rows == kNarrowRows &&
+        (p.direct_key_tiles > kDirectKeyTilesFp8 || p.direct_part_tiles > (p.direct_idle ? kDirectPartIdleFp8 : kDirectPartFp8)))
+        direct.parts = 0;
     if (direct.parts > 1) direct.tag = next_call_tag();
     if (direct.parts == 0) launch_extend_plan(p, t, prefix_len, ext_len, ext_offsets, slot_offsets, slot_idx, B, Hq / Hkv, stream);
     const auto launch = D == 64 ? (kv8 ? launch_extend<64, true> : launch_extend<64, false>) : (kv8 ? launch_extend<128, true> : launch_extend<128, false>);

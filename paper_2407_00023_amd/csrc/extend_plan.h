@@ -29,6 +29,8 @@ struct ExtendPlan {
     int direct_tile_rows;  // rows of a tile
     int direct_tiles;      // upper bound on the number of tiles
     int direct_key_tiles;  // key tiles per workgroup slot
+    int direct_part_tiles; // ... and of a part
+    bool direct_idle;      // the parts take less than an eighth of the slots
     int direct_stride;     // rows of partial results of one part of all tiles, per KV head
     size_t off_tile, off_member, off_item, off_chunk, off_part_o, off_part_ml, total;
 };
@@ -48,6 +50,9 @@ constexpr int kDirectJoinRows = 2048;   // request, in all KV heads, are more th
 constexpr int kDirectKeyTilesFp8 = 9;   // key tiles per workgroup slot that go without a work list where the pool is in fp8 (a narrow
                                         // tile takes longer there: 12 decode requests, 8.5 a slot, 41.4 us with list | 39.5 without;
                                         // 16, 11.8 a slot, 42.2 | 47.2)
+constexpr int kDirectPartFp8 = 20;      // ... and key tiles of a part (as kDirectPartNarrow and kDirectPartIdle for bf16 ones): one
+constexpr int kDirectPartIdleFp8 = 16;  // decode request, 8 KV heads, 20,000 keys 39.6 | 40.3, 32,000 44.2 | 57.3; 1 KV head, 16,000 33.5 | 34.2,
+                                        // 20,000 34.7 | 39.0
 constexpr int kMaxDirectParts = 16;     // parts of a tile at most in such a launch ...
 constexpr int kDirectWideParts = 4;     // ... and of a wide one
 
@@ -64,7 +69,7 @@ __device__ __forceinline__ int wave_scan(int x) {
 
 // Workspace: a header of 256 bytes - hdr[0] = row tiles, hdr[1] = work items, hdr[2] = pieces of the merge, hdr[3] = 1 if
 // the batch on the device does not fit the plan (nothing is computed then), hdr[4] = rows of partial results, per KV head (without a
-// work list: at most that many) - and, without a work list, a word of 64 bits per tile and KV head that counts the tile's finished
+// work list: at most that many), hdr[5] = parts of a tile at most without a work list, 0 with one - and, without a work list, a word of 64 bits per tile and KV head that counts the tile's finished
 // parts, from off_tile on, or the tables of the list, of int4:
 //   member[2 m]     = (first row among its group's packed rows, first extend token, first packed row of the request,
 //                      extend length)

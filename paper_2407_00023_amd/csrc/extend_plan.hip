@@ -88,6 +88,13 @@ constexpr int kDirectRoundsShort = 4;      // that what their left-over rows cos
 static inline int direct_short_rows(int D) { return D == 128 ? 1536 : 1024; }
 constexpr int kDirectLongest = 48;         // ... of up to this many key tiles (longer ones want cutting: 20 requests behind 8,000 keys
                                            // 168 | 208)
+constexpr int kDirectPartNarrow = 34;      // key tiles of a part at most, so that few long requests on few KV heads do not leave most of the
+constexpr int kDirectPartIdle = 20;        // chip empty: narrow tiles, and with less than an eighth of the slots taken (list | direct, cold in
+                                           // brackets; decode, 1 KV head, 1 request of 16,384 keys 31.6 | 24.1 (36 | 32), 32,768 35.1 | 36.6
+                                           // (42 | 51), 262,144 93 | 232; 4 requests of 32,768 46.9 | 39.6 (61 | 59), 65,536 57.8 | 68.6)
+constexpr int kDirectPartWide = 32;        // wide tiles, where one part more of each would still leave half of the slots empty (30 new tokens,
+                                           // 4 KV heads, 18 requests of 3,000 keys, uncut 48 | 54 (71 | 84), 5,600 62 | 87; 12 of 4,400, two
+                                           // parts, 44 | 54 (70 | 82), of 3,000 46.4 | 44.8)
 constexpr int kDirectFewTiles = 6;         // batches of up to this many requests also where their tiles, in as many parts as there may be
                                            // (kMaxDirectParts, kDirectWideParts), leave slots empty
 // and no more than kDirectWideParts parts of a tile of 128 rows where a list would make more: one workgroup joins them, 64 KB a part.
@@ -111,6 +118,14 @@ static void make_direct(ExtendPlan& p, int B, int64_t rows, int64_t max_kv_len, 
     int64_t parts = least(least(few ? per_tile : per_tile / 2, key_tiles / (few ? kMinChunkNarrow : kDirectMinChunkWide)), few ? kMaxDirectParts : kDirectWideParts);
     parts = least(parts, p.tile_parts);
     if (parts < 1) parts = 1;
+    const int64_t part_tiles = (key_tiles + parts - 1) / parts;
+    p.direct_idle = 8 * tiles * parts < p.slots;
+    if (few) {
+        if (part_tiles > (p.direct_idle ? kDirectPartIdle : kDirectPartNarrow)) return;
+    } else if (per_tile >= 2 && part_tiles > kDirectPartWide) {
+        const int64_t rows_each = int64_t{B} * kTileRows, likely = B * ((rows + rows_each - 1) / rows_each);  // tiles of requests of like length
+        if (2 * likely * (parts + 1) <= p.slots) return;
+    }
     if (p.prows_cap / parts < rows) return;
     // (the words that count a tile's parts lie where a list would: always enough room, see make_extend_plan)
     if (parts > 1 && static_cast<size_t>(tiles) * Hkv * sizeof(unsigned long long) > p.off_part_o - p.off_tile) return;
@@ -118,6 +133,7 @@ static void make_direct(ExtendPlan& p, int B, int64_t rows, int64_t max_kv_len, 
     p.direct_tile_rows = tile_rows;
     p.direct_tiles = static_cast<int>(tiles);
     p.direct_key_tiles = static_cast<int>((tiles * key_tiles + p.slots - 1) / p.slots);
+    p.direct_part_tiles = static_cast<int>(part_tiles);
     p.direct_stride = static_cast<int>(p.prows_cap / parts);
 }
 
@@ -362,6 +378,7 @@ __device__ __forceinline__ void emit_items(const PlanArgs& a, int n_rows, int n_
         a.hdr[2] = overflow ? 0 : total[2];
         a.hdr[3] = overflow;
         a.hdr[4] = overflow ? 0 : total[1];
+        a.hdr[5] = 0;
     }
     if (overflow) return;
     if (n_all > n_rows) {  // (own-key tiles look up the parts of their shared tile)

@@ -209,10 +209,10 @@ def test_captured_matches_beside_eager_ones(pa, gpu_device):
             check(small, pls[k], sis[k])
 
 
-def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None, kv_more=0, cut=None):
+def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None, kv_more=0, cut=None, direct=None):
     """Largest error against the oracle for requests with P[r] cached tokens, the first `common` of them the same for all.
     tiles: how many row tiles the work list has to hold; kv_more: how many more keys than it has the call is told of (1,000,000: it
-    builds a list whatever the batch); cut: whether any tile has to be cut into parts."""
+    builds a list whatever the batch); cut, direct: whether any tile has to be cut into parts, and the call to go without a list."""
     import oracle
     rng = np.random.default_rng(seed)
     P, E = np.asarray(P, np.int32), np.asarray(E, np.int32)
@@ -253,6 +253,7 @@ def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None
     if dtype != "f32":
         assert ws[12:16].view(torch.int32).item() == 0  # (the work list fitted)
         assert tiles is None or ws[:4].view(torch.int32).item() == tiles
+        assert direct is None or (ws[20:24].view(torch.int32).item() > 0) == direct
         assert cut is None or (ws[4:8].view(torch.int32).item() > ws[:4].view(torch.int32).item()) == cut
     opk, opv = oracle.new_pool(nslots, Hkv, D, dtype)
     oracle.append_kv(opk, opv, backed, pk, pv, dtype)
@@ -682,3 +683,18 @@ def test_extend_cuts_tiles_or_not_around_a_round_of_workgroups(pa, gpu_device, B
                                            (64, 8, 64, 600, False), (7, 1, 128, 1000, True)])
 def test_extend_cuts_narrow_tiles_or_not(pa, gpu_device, B, Hkv, D, P, cut):
     assert _extend(pa, gpu_device, "bf16", [P + r % 3 for r in range(B)], [1] * B, 4 * Hkv, Hkv, D, 16, kv_more=1000000, cut=cut) <= TOL["bf16"]
+
+
+# where a list would cut further than the 16 (narrow tiles) or 4 parts of a launch without one, up to which length of a part such
+# launches are made, in keys that the call is told of: 34 tiles of 64 keys (fp8 pool: 20), on an almost empty chip 20 (16), wide tiles 32
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,B,E,Hkv,G,D,told,direct", [
+    ("bf16", 1, 1, 1, 8, 128, 262144, False), ("bf16", 1, 1, 1, 8, 128, 20480, True), ("bf16", 1, 1, 1, 8, 128, 20481, False),
+    ("bf16", 1, 1, 8, 4, 64, 34816, True), ("bf16", 1, 1, 8, 4, 64, 34817, False), ("bf16", 2, 1, 2, 8, 128, 34816, True),
+    ("bf16", 2, 1, 2, 8, 128, 34817, False), ("bf16", 4, 2, 2, 8, 64, 65000, False), ("bf16_kv8", 1, 1, 1, 8, 128, 16384, True),
+    ("bf16_kv8", 1, 1, 1, 8, 128, 16385, False), ("bf16_kv8", 1, 1, 8, 4, 64, 20480, True), ("bf16_kv8", 1, 1, 8, 4, 64, 20481, False),
+    ("bf16", 18, 30, 4, 4, 128, 2048, True), ("bf16", 18, 30, 4, 4, 128, 2049, False), ("bf16", 12, 30, 4, 4, 128, 4096, True),
+    ("bf16", 12, 30, 4, 4, 128, 4097, False), ("bf16", 4, 100, 8, 4, 128, 5600, True)])
+def test_extend_of_long_requests_takes_a_list(pa, gpu_device, dtype, B, E, Hkv, G, D, told, direct):
+    assert _extend(pa, gpu_device, dtype, [40 + r for r in range(B)], [E] * B, G * Hkv, Hkv, D, 16, kv_more=told - (39 + B + E),
+                   direct=direct) <= TOL[dtype]
