@@ -335,6 +335,7 @@ def test_extend_around_the_narrow_and_wide_tile(pa, gpu_device, dtype, D, page, 
 
 # runs of tiles in assembly for heads of 64: ends of the prefix and of the new tokens around whole tiles, extends past the
 # diagonal of several row tiles, key ranges cut into parts
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["bf16", "bf16_kv8"])
 @pytest.mark.parametrize("page", [1, 16, 24])
@@ -364,6 +365,7 @@ def test_extend_rows_that_share_a_first_part(pa, gpu_device, D, common, E, tiles
 
 
 # the largest batches of each planner (256: with sharing, 1,024: ordered, beyond: as given) and the smallest that are beyond
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.gpu
 @pytest.mark.parametrize("B", [1, 2, 63, 64, 255, 256, 257, 1024, 1025])
 def test_extend_batch_sizes_around_the_planners(pa, gpu_device, B):
@@ -476,23 +478,23 @@ def test_hot_path_calls_refuse_what_is_no_device_tensor():
 # in 16 parts) or of more than 48 (64 with heads of 64; tiles of 128 rows), tiles cut from 256 (narrow) and 512 or 1,024 keys on, up
 # to 16 and 4 parts
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype,P,E,Hq,Hkv,D,page", [
-    ("bf16", [0], [1], 4, 1, 128, 16), ("bf16", [511], [1], 8, 2, 128, 16), ("bf16", [512], [4], 8, 2, 128, 1),
-    ("bf16", [255, 4095, 4096, 0, 7, 5000], [1] * 6, 8, 2, 128, 16), ("bf16", [300] * 7, [1] * 7, 8, 2, 128, 16),
-    ("bf16", [900, 0, 3000], [0, 11, 1], 8, 2, 64, 48), ("bf16", [700, 20], [1, 23], 32, 8, 64, 16),
-    ("bf16", [0], [13], 8, 2, 128, 16), ("bf16", [1023 - 40, 1024 - 40], [40, 40], 8, 2, 128, 16),
-    ("bf16", [2100, 5], [33, 64], 8, 1, 128, 16), ("bf16", [2400, 600, 0], [300, 97, 1], 16, 8, 64, 1),
-    ("bf16", [0, 0, 100], [400, 0, 250], 8, 2, 128, 64), ("bf16", [1100] * 6, [40] * 6, 8, 2, 128, 24),
-    ("bf16", [300 + 7 * r for r in range(12)], [1 + r % 3 for r in range(12)], 16, 8, 128, 16),
-    ("bf16", [40 * r for r in range(40)], [1] * 40, 8, 8, 64, 16), ("bf16", [250] * 65, [1] * 65, 4, 4, 64, 16),
-    ("bf16_kv8", [90 * r for r in range(9)], [1] * 9, 32, 8, 128, 16), ("bf16_kv8", [2000] * 20, [1] * 20, 8, 8, 64, 16),
-    ("bf16_kv8", [700, 1500], [1, 2], 8, 2, 128, 16), ("bf16_kv8", [1400, 9], [70, 33], 8, 2, 64, 16),
-    ("bf16_kv8", [1400, 9], [70, 33], 8, 2, 128, 16),
-    ("bf16", [30 * r for r in range(20)], [190 + 3 * r for r in range(20)], 32, 32, 128, 16),   # four tiles per slot: launched so,
-    ("bf16", [200, 0, 90, 64], [400, 390, 1, 130], 64, 64, 64, 16), ("bf16", [5, 0], [1600, 1600], 64, 64, 128, 16),
-    ("bf16", [100, 40], [1536, 1537], 64, 64, 128, 16), ("bf16", [9, 70, 0], [1024, 1000, 1048], 64, 64, 64, 16)])   # and a little beyond
-def test_extend_of_small_batches(pa, gpu_device, dtype, P, E, Hq, Hkv, D, page):
-    assert _extend(pa, gpu_device, dtype, P, E, Hq, Hkv, D, page) <= TOL["bf16"]
+@pytest.mark.parametrize("dtype,P,E,Hq,Hkv,D,page,direct", [
+    ("bf16", [0], [1], 4, 1, 128, 16, True), ("bf16", [511], [1], 8, 2, 128, 16, True), ("bf16", [512], [4], 8, 2, 128, 1, True),
+    ("bf16", [255, 4095, 4096, 0, 7, 5000], [1] * 6, 8, 2, 128, 16, True), ("bf16", [300] * 7, [1] * 7, 8, 2, 128, 16, False),
+    ("bf16", [900, 0, 3000], [0, 11, 1], 8, 2, 64, 48, True), ("bf16", [700, 20], [1, 23], 32, 8, 64, 16, False),
+    ("bf16", [0], [13], 8, 2, 128, 16, True), ("bf16", [1023 - 40, 1024 - 40], [40, 40], 8, 2, 128, 16, True),
+    ("bf16", [2100, 5], [33, 64], 8, 1, 128, 16, True), ("bf16", [2400, 600, 0], [300, 97, 1], 16, 8, 64, 1, True),
+    ("bf16", [0, 0, 100], [400, 0, 250], 8, 2, 128, 64, True), ("bf16", [1100] * 6, [40] * 6, 8, 2, 128, 24, True),
+    ("bf16", [300 + 7 * r for r in range(12)], [1 + r % 3 for r in range(12)], 16, 8, 128, 16, True),
+    ("bf16", [40 * r for r in range(40)], [1] * 40, 8, 8, 64, 16, False), ("bf16", [250] * 65, [1] * 65, 4, 4, 64, 16, False),
+    ("bf16_kv8", [90 * r for r in range(9)], [1] * 9, 32, 8, 128, 16, True), ("bf16_kv8", [2000] * 20, [1] * 20, 8, 8, 64, 16, False),
+    ("bf16_kv8", [700, 1500], [1, 2], 8, 2, 128, 16, True), ("bf16_kv8", [1400, 9], [70, 33], 8, 2, 64, 16, True),
+    ("bf16_kv8", [1400, 9], [70, 33], 8, 2, 128, 16, True),
+    ("bf16", [30 * r for r in range(20)], [190 + 3 * r for r in range(20)], 32, 32, 128, 16, True),   # four tiles per slot: launched so,
+    ("bf16", [200, 0, 90, 64], [400, 390, 1, 130], 64, 64, 64, 16, True), ("bf16", [5, 0], [1600, 1600], 64, 64, 128, 16, False),
+    ("bf16", [100, 40], [1536, 1537], 64, 64, 128, 16, False), ("bf16", [9, 70, 0], [1024, 1000, 1048], 64, 64, 64, 16, True)])   # and a little beyond
+def test_extend_of_small_batches(pa, gpu_device, dtype, P, E, Hq, Hkv, D, page, direct):
+    assert _extend(pa, gpu_device, dtype, P, E, Hq, Hkv, D, page, direct=direct) <= TOL["bf16"]
 
 
 def _small_batches(pa, dev, sizes, Hq=8, Hkv=2, D=128, page=16, nslots=8192):
@@ -673,7 +675,8 @@ def test_upload_of_changes_at_the_edges_of_pieces_and_long_runs(pa, gpu_device):
 @pytest.mark.gpu
 @pytest.mark.parametrize("B", [4, 16, 17])
 def test_extend_cuts_tiles_or_not_around_a_round_of_workgroups(pa, gpu_device, B):
-    assert _extend(pa, gpu_device, "bf16", [2100 + r % 3 for r in range(B)], [128 - r % 2 for r in range(B)], 32, 32, 128, 16, common=300) <= TOL["bf16"]
+    assert _extend(pa, gpu_device, "bf16", [2100 + r % 3 for r in range(B)], [128 - r % 2 for r in range(B)], 32, 32, 128, 16, common=300,
+                   kv_more=1000000, cut=B != 16) <= TOL["bf16"]
 
 
 # narrow tiles in a list: uncut only where every round of workgroups is at least half full (8, 4 and 2 KV heads: 64, 128 and 256 slots)

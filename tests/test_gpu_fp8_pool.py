@@ -100,6 +100,7 @@ def test_fp8_rows_stored_bit_exact(pa, gpu_device, Hkv, D, page, nslots):
 SMALL = ["tool_use", "long_doc_qa", "agent_tree", "video_qa", "programming", "tool_use_zipf", "decode"]
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("name", SMALL)
 @pytest.mark.parametrize("seed", [0, 1])
 def test_fp8_pool_small_config_whole_path(pa, gpu_device, name, seed):
@@ -123,6 +124,7 @@ def test_fp8_pool_small_config_whole_path(pa, gpu_device, name, seed):
     np.testing.assert_array_equal(gv.view(torch.int16).cpu().numpy(), o.pool_v[allslots].view(np.int16))
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("Hq,Hkv,D,page,p_hi,e_hi,B", [
     (8, 2, 128, 16, 700, 90, 6),      # several key tiles, ragged tails
     (4, 4, 64, 16, 300, 200, 4),      # D = 64
@@ -198,6 +200,7 @@ def test_fp8_pool_full_config_extend_every_element(pa, gpu_device, name):
     assert err <= TOL
 
 
+@pytest.mark.usefixtures("both_forms")
 def test_fp8_pool_beyond_4_gib(pa, gpu_device):
     """Codes of 4.8 GB: rows on both sides of the 4 GiB line.  The runs of assembly tiles address the codes by 32-bit
     offsets and stand back here; the other tiles, append and gather compute in 64 bits.  Every element, and the stored

@@ -260,6 +260,7 @@ def test_append_gather_round_trip_bit_exact(pa, gpu_device, dtype, Hkv, D, page,
 
 # ------------------------------------------------------------------------------------ whole path, small
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("name", SMALL)
 @pytest.mark.parametrize("seed", [0, 1])
 def test_small_config_whole_path(pa, gpu_device, name, seed):
@@ -316,6 +317,7 @@ def _random_case(rng, B, Hq, Hkv, D, p_hi, e_hi, dtype, page, nslots):
                 v=mk(ss[2], T, Hkv), pk=mk(ss[3], len(backed), Hkv), pv=mk(ss[4], len(backed), Hkv))
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("dtype,Hq,Hkv,D,page,p_hi,e_hi,B", [
     ("f32", 4, 2, 64, 1, 150, 40, 5),
     ("f32", 2, 1, 128, 4, 70, 20, 3),
@@ -354,6 +356,7 @@ def test_extend_random_shapes(pa, gpu_device, dtype, Hq, Hkv, D, page, p_hi, e_h
     assert err <= TOL[dtype]
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("direction", ["growing", "shrinking"])
 def test_extend_running_maximum_rescale(pa, gpu_device, direction):
     """Scores whose magnitude grows (or shrinks) along the key axis by far more than the lag the kernel allows its
@@ -395,6 +398,7 @@ def test_extend_running_maximum_rescale(pa, gpu_device, direction):
     assert np.isfinite(out_to_f64(out)).all() and err <= TOL["bf16"]
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("jump_at", [0.3, 0.6, 0.9])
 def test_extend_score_jump_leaves_the_steady_state_run(pa, gpu_device, jump_at):
     """Keys whose scores jump by far more than 2^40 (in probability) part of the way through the prefix or the
@@ -435,6 +439,7 @@ def test_extend_score_jump_leaves_the_steady_state_run(pa, gpu_device, jump_at):
     assert np.isfinite(out_to_f64(out)).all() and err <= TOL["bf16"]
 
 
+@pytest.mark.usefixtures("both_forms")
 def test_extend_slot_permutation_invariance(pa, gpu_device):
     """Moving the cached rows to other slots (and renaming slot_idx accordingly) must not change a single bit."""
     wl = W.small_variant("tool_use", 3)
@@ -453,6 +458,7 @@ def test_extend_slot_permutation_invariance(pa, gpu_device):
     assert torch.equal(out1.view(torch.int16), out2.view(torch.int16))
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("page", [12, 48])
 def test_whole_path_with_a_page_size_that_is_no_power_of_two(pa, gpu_device, page):
     """Tool-use-shaped batch on a pool of 12- or 48-token pages: tree, match, attention (whole tiles, shared tiles of
@@ -498,6 +504,7 @@ def _hand_built_lists(rng, kind, nslots, page):
     return lists
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("kind,sharing", [("unequal_length", True), ("differs_early", True),
                                           ("differs_between_probes", False), ("unequal_length", False)])
 def test_extend_slot_lists_that_do_not_come_from_one_tree(pa, gpu_device, kind, sharing):
@@ -545,14 +552,17 @@ def test_extend_slot_lists_that_do_not_come_from_one_tree(pa, gpu_device, kind, 
     assert err <= TOL["bf16"]
 
 
-def test_extend_reports_a_batch_larger_than_the_host_sizes(pa, gpu_device):
+@pytest.mark.parametrize("more_keys", [0, 1000000])
+def test_extend_reports_a_batch_larger_than_the_host_sizes(pa, gpu_device, more_keys):
     """pa_extend_attention sizes its launch from the host values T and max_kv_len.  Given a T smaller than what ext_len
     on the device adds up to, the work list does not fit: no output row is written, and pa_extend_status says so
-    (PA_EOVERFLOW); after a proper call on the same workspace it reports success again."""
+    (PA_EOVERFLOW); after a proper call on the same workspace it reports success again.  The batch goes without a work list, or,
+    told of 1,000,000 keys more, with one."""
     import ctypes as C
     wl = W.small_variant("agent_tree", 2)
     g = GpuSide(wl, gpu_device)
     pl, si = g.match()
+    g.max_kv_len += more_keys
     nbytes = pa.extend_workspace_bytes(wl.B, wl.T, g.max_kv_len, wl.Hq, wl.Hkv, wl.D, g.tdtype)
     ws = torch.zeros(nbytes, dtype=torch.uint8, device=gpu_device)
     out = torch.full_like(g.q, 7.0)
@@ -567,12 +577,15 @@ def test_extend_reports_a_batch_larger_than_the_host_sizes(pa, gpu_device):
     with pytest.raises(pa.PrefixAttnError) as e:
         pa.extend_status(ws)
     assert e.value.code == -5
+    assert (ws[20:24].view(torch.int32).item() > 0) == (more_keys == 0)
     assert bool((out == 7.0).all())  # nothing was written
     g.extend(pl, si, workspace=ws, out=out)
     pa.extend_status(ws)
+    assert (ws[20:24].view(torch.int32).item() > 0) == (more_keys == 0)
     assert torch.isfinite(out.float()).all() and not bool((out == 7.0).all())
 
 
+@pytest.mark.usefixtures("both_forms")
 def test_extend_pool_beyond_4_gib(pa, gpu_device):
     """A KV pool of 6.4 GB (1.5 M slots x 8 KV heads x 128 x bf16 x K and V): pool rows lie on either side of the 4 GiB line, so
     byte offsets no longer fit 32 bits - the assembly runs address rows in units of 256 bytes and form the address in
@@ -831,6 +844,7 @@ def test_extend_shares_tiles_between_requests_with_a_common_first_part(pa, gpu_d
     assert err <= TOL[wl.dtype]
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("seed", range(12))
 def test_extend_random_decode_batches_against_the_oracle(pa, gpu_device, seed):
     """Random batches of requests with prefix keys of their own behind a shared part: how long the shared levels are
@@ -863,6 +877,7 @@ def test_extend_random_decode_batches_against_the_oracle(pa, gpu_device, seed):
     assert err <= TOL[wl.dtype]
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("seed", range(24))
 def test_extend_random_shapes_against_the_oracle(pa, gpu_device, seed):
     """Small batches of random shape - head counts, head size, page size, number of requests, how many share a
@@ -934,6 +949,7 @@ def test_extend_work_list_beyond_the_small_table_sizes(pa, gpu_device, case):
     assert err <= TOL[wl.dtype]
 
 
+@pytest.mark.usefixtures("both_forms")
 def test_full_config_append_then_reuse(pa, gpu_device, full_cache):
     """After append_kv the new tokens are cached: re-running a request whose whole prompt is now the prefix
     of a longer one gives the same attention rows for the old positions (prefix reuse is lossless, Sec. 5)."""
@@ -964,6 +980,7 @@ def test_full_config_append_then_reuse(pa, gpu_device, full_cache):
     assert err <= TOL[wl.dtype]
 
 
+@pytest.mark.usefixtures("both_forms")
 def test_chunked_prefill_through_the_cache_loop(pa, gpu_device):
     """Chunked prefill (Sec. 3.3: long non-shared prompts are chunked): the extend part of every request is
     prefilled 48 tokens at a time, and between chunks the new KV is appended to the pool and the tokens are inserted
@@ -1112,6 +1129,7 @@ def test_uploads_that_copy_only_the_changes(pa, gpu_device, seed):
     assert evictions >= 3
 
 
+@pytest.mark.usefixtures("both_forms")
 def test_cache_loop_with_eviction(pa, gpu_device):
     """Rounds of upload -> match (GPU) -> admit (host: pages for the new tokens, pins) -> extend -> append, with
     releases and LRU evictions in between, so that pages are reused and pool rows overwritten.  Every round the
