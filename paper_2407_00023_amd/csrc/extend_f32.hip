@@ -52,7 +52,8 @@ __global__ __launch_bounds__(256) void extend_f32_kernel(
     const int G = Hq / Hkv, g = blockIdx.y;
     const int h0 = g * G + blockIdx.z * kHeads, n_heads = min(kHeads, (g + 1) * G - h0);
 
-    // the token's request and what there is to know of it; up to 64 requests: all of it asked for together, a request per lane
+    // the token's request and what there is to know of it; up to 64 requests: all of it asked for together, a request per lane (us, one
+    // after the other | together, 4 heads of 64: 4 requests, 95 tokens 6.52 | 6.27; 12, 433 tokens 21.0 | 20.7; 64, 994 tokens 17.6 | 16.8)
     int64_t e0;
     int P, E, slot_off;
     if (B <= 64) {

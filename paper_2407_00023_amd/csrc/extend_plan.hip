@@ -68,14 +68,19 @@ __device__ __forceinline__ constexpr int probe_depth(int k) {
 // That saves the launches of the planner and of the merge (13 and 5 us of the 42 of a step of four decode requests) and gives up
 // what the planner knows: rows of different requests never share a tile.  A common prefix is then read once per request (from the
 // L2s, which hold it), and left-over rows have tiles of their own; but a shared tile walks the own keys of all its members in the
-// general tile, 5 us per 64 keys, and with few rounds of workgroups the longest decides.  Measured, steps in us, list | direct:
-//   decode behind 1,800 + 400 common and up to 350 own keys, 8 requests 36.1 | 28.0, 16 39.4 | 37.0; 4 with up to 3,000 own ones
-//   39.1 | 28.0; heads of 64 behind 900 and up to 900, 16 requests 43.6 | 27.8; 1 to 6 new tokens, 8 requests 57.0 | 28.8
-//   50 to 150 new tokens behind 800 keys, 8 requests 58.9 | 32.5, 16 83.6 | 49, 32 114 | 83; behind 2,200 keys, 8 91.9 | 77, 16
-//   114 | 118 or, of other lengths, 135 | 122, 20 154 | 123; 20 to 60 new tokens of 32 110.7 | 82
-//   four rounds: 50 to 150 new tokens of 52 requests behind 800 keys 131 | 113, 73 to 219 of 44 behind 1,500 214 | 197, 184 to 552
-//   of 16 behind 100 94 | 88; heads of 64, 11 to 220 of 52 behind 800 129 | 99, but 152 to 457 of 22 behind 400, whose
-//   left-over rows nobody shares, 85 | 91, 403 to 492 of 16 behind 800 113 | 118; heads of 128, 200 to 1,200 of 12 118 | 120
+// general tile, 5 us per 64 keys, and with few rounds of workgroups the longest decides.  Measured (us, the call alone, 32 heads over 8
+// KV heads of 128 unless said otherwise, random lengths in the ranges given, list | direct, in brackets with 512 MB written in between, so that
+// nothing is in the caches):
+//   decode, 4 requests behind 1,800 common and 50 to 3,000 own keys 27.4 | 17.0 (34.9 | 24.0); behind 2,200 and up to 350 own ones 8
+//   27.4 | 17.7 (32.6 | 23.2), 16 33.3 | 25.2 (44.8 | 32.6); heads of 64 behind 900 and up to 900, 16 35.6 | 15.0 (49.1 | 21.6)
+//   50 to 150 new tokens behind 800 keys, 8 requests 63.6 | 34.7 (70.5 | 39.6), 16 71.9 | 38.3, 32 82.2 | 68.7, 52 114.6 | 109.1 (122.9 | 119.1)
+//   ... behind 2,200, 8 79.9 | 65.0 (87.0 | 69.4), 16 (five draws) 90 to 109 | 72 to 98; 18 to 22, about a
+//   round of workgroups, as the lengths fall: 26 draws 87 to 141 | 74 to 118, 1.09 times as fast in the mean (1.11), nine slower, by up to 20 %
+//   20 to 60 new tokens of 32 requests behind 2,200 keys 99.8 | 69.8 (106.8 | 75.0); 100 to 300 of 8 129.2 | 108.5 (138.9 | 115.4)
+//   three and four rounds: 73 to 219 new tokens of 40 requests behind 1,500 keys 201.9 | 187.5 (210.2 | 197.5), 25 to 478 of 24 behind
+//   800 150.1 | 138.0; heads of 64, 11 to 220 of 46 behind 800 87.8 | 83.5 (99.5 | 95.5), 152 to 457 of 16 behind 400 63.2 | 61.3, 403 to
+//   492 of 12 behind 800 82.1 | 79.5 (91.4 | 89.5)
+//   218 random batches of 1 to 72 requests, bf16 and fp8 pool, that go without a list: 1.52 times as fast (1.44)
 // Hence the limits:
 constexpr int kDirectMaxB = 64;            // one request per lane
 constexpr int kDirectFewRows = 16;         // rows per request on average: up to this many in narrow tiles; more, but too few not to
@@ -86,8 +91,8 @@ constexpr int kDirectKeyTilesWide = 24;    // the same for wide tiles, where a s
 constexpr int kDirectRounds = 3;           // wide tiles per slot at most, or where requests have up to direct_short_rows on average, so
 constexpr int kDirectRoundsShort = 4;      // that what their left-over rows cost a list weighs more than what cutting would give, this many ...
 static inline int direct_short_rows(int D) { return D == 128 ? 1536 : 1024; }
-constexpr int kDirectLongest = 48;         // ... of up to this many key tiles (longer ones want cutting: 20 requests behind 8,000 keys
-                                           // 168 | 208)
+constexpr int kDirectLongest = 48;         // ... of up to this many key tiles where a slot has more than half a tile (longer ones want
+                                           // cutting: 20 requests behind 8,000 keys 168 | 208)
 constexpr int kDirectPartNarrow = 34;      // key tiles of a part at most, so that few long requests on few KV heads do not leave most of the
 constexpr int kDirectPartIdle = 20;        // chip empty: narrow tiles, and with less than an eighth of the slots taken (list | direct, cold in
                                            // brackets; decode, 1 KV head, 1 request of 16,384 keys 31.6 | 24.1 (36 | 32), 32,768 35.1 | 36.6
@@ -95,8 +100,9 @@ constexpr int kDirectPartIdle = 20;        // chip empty: narrow tiles, and with
 constexpr int kDirectPartWide = 32;        // wide tiles, where one part more of each would still leave half of the slots empty (30 new tokens,
                                            // 4 KV heads, 18 requests of 3,000 keys, uncut 48 | 54 (71 | 84), 5,600 62 | 87; 12 of 4,400, two
                                            // parts, 44 | 54 (70 | 82), of 3,000 46.4 | 44.8)
-constexpr int kDirectFewTiles = 6;         // batches of up to this many requests also where their tiles, in as many parts as there may be
-                                           // (kMaxDirectParts, kDirectWideParts), leave slots empty
+constexpr int kDirectFewTiles = 6;         // batches of more requests only where a tile's share of the slots is no more than the parts there
+                                           // may be (kMaxDirectParts, kDirectWideParts); up to this many also beyond it (1 KV head, 5 of
+                                           // 4,000 keys 27.0 | 15.9, 6 of 12,000 36.5 | 22.0; more have not been measured without a list)
 // and no more than kDirectWideParts parts of a tile of 128 rows where a list would make more: one workgroup joins them, 64 KB a part.
 static void make_direct(ExtendPlan& p, int B, int64_t rows, int64_t max_kv_len, int Hkv, int D) {
     p.direct_parts = 0;
@@ -348,9 +354,11 @@ __device__ __forceinline__ void emit_items(const PlanArgs& a, int n_rows, int n_
     // unless every round of them uncut is at least half full (us, cut | uncut; 8 KV heads: 16 decode requests with 4,000 keys each 68 | 85
     // (4 KV heads, 32), 70 with 2,500 151 | 165, but 48 with 1,000 51 | 42, 64 56 | 48; 2 KV heads: 64 with 4,000 69 | 85, 100 with
     // 2,500 62 | 69, but 160 with 1,000 53 | 44).
-    const int last_round = n_all % a.slots;
-    const bool may_stay = total[1] > kNarrowRows * total[0] || last_round == 0 || 2 * last_round >= a.slots;
-    if (n_all == n_rows && total[0] > n_all && may_stay) {
+    auto may_stay = [&] {
+        const int last_round = n_all % a.slots;
+        return total[1] > kNarrowRows * total[0] || last_round == 0 || 2 * last_round >= a.slots;
+    };
+    if (n_all == n_rows && total[0] > n_all && may_stay()) {
         const float inv_slots = __builtin_amdgcn_rcpf(static_cast<float>(a.resident));
         const float keys_cost = static_cast<float>(W - n_all * kItemOverhead);  // without the items' fixed cost
         auto finish = [&](int items) {
