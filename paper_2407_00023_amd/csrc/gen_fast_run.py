@@ -19,9 +19,12 @@ A tile is 32 slots (16 at head dimension 64) of one MFMA each; what follows an M
     wait for this wave's loads (fp8 pool: turn the rows that landed into bfloat16), workgroup barrier, next tile
 
 Every instruction costs its wave an issue slot of about four cycles whatever unit executes it, so the schedule is
-written for few instructions: row sums deferred by one piece, one address for the four slot-id loads where the tile
+written for few instructions: one address for the four slot-id loads where the tile
 after next lies wholly in the prefix, M0 written ahead of the address arithmetic that then serves as its wait state,
-LDS reads awaited two fragments at a time by counting them (they return in order).  Wait states the hardware does not
+LDS reads awaited two fragments at a time by counting them (they return in order).  The row sums of a key block stand in
+a row behind its last conversion: a dot product waits for the matrix pipe to run dry and the pipe for the dot product, 16
+cycles each time one follows the other and 4 for each further dot product (a loop of one MFMA and one dot product 49 cycles,
+of an MFMA alone 32, with six other vector instructions 33; 8 MFMAs and 8 dot products 301).  Wait states the hardware does not
 interlock are written out, other work standing in them where there is any: the last MFMA of a score block and the
 first ALU read of it (eleven slots), a dot-product instruction and any other kind of ALU instruction that reads its
 result (three), a transcendental and a use of its result (one), a write of M0 and the load that uses it (one).  The
@@ -33,7 +36,7 @@ import os
 
 NFR = 8                  # fragment buffers (K and V^T fragments share them: the two kinds are read in different phases)
 PD = 5                   # LDS fragments in flight ahead of their MFMA
-PAIRWAIT, DEFER_SUM, M0_FIRST, FAST_SLOTS, SETTLE = True, True, True, True, False   # (switches for experiments)
+PAIRWAIT, M0_FIRST, FAST_SLOTS, SETTLE = True, True, True, False   # (switches for experiments)
 
 
 def shape(D):
@@ -281,45 +284,48 @@ def tile(st, kind, ring, uid, upw):
                 e(f"ds_write_b128 {v(T[6])}, {v(out, 4)} offset:{there + t * TILEB + u * 1024}")
         e("s_waitcnt lgkmcnt(0)")
 
-    pending = []   # probability pair whose row-sum contribution is still to be added: [register]
+    late = []      # probability pairs whose conversion is still to come: [(register, exponential, exponential)]
+    to_sum = []    # probability pairs of the block whose row sum is still to come
 
-    def flush_sum():
-        if pending:
-            e(f"v_dot2c_f32_bf16 {v(LSUM)}, {ONES}, {v(pending.pop())}")
+    def convert():
+        """Conversion of the oldest pair of exponentials (never the instruction after them: a transcendental and the use
+        of its result want one other instruction between them)."""
+        pb, t0, t1 = late.pop(0)
+        e(f"v_cvt_pk_bf16_f32 {v(pb)}, {v(t0)}, {v(t1)}")
+        to_sum.append(pb)
 
     def exp_piece(sc, pb, idx, lim=None):
-        """Probabilities of elements 2 idx, 2 idx + 1 of a score block.  The row-sum step of the piece before stands
-        between the exponentials and the first use of their results.  Masked tiles: register i of a lane holds the key
+        """Probabilities of elements 2 idx, 2 idx + 1 of a score block; the conversion of the piece before stands behind
+        their exponentials (two pairs of registers in turn).  Masked tiles: register i of a lane holds the key
         at offset 8 (i / 4) + i % 4 from the lane's first key of the block, visible if that is below the lane's limit;
         the exponent of a hidden key becomes -inf (two comparisons ahead of the two selections, so that their results
         have reached the scalar registers)."""
+        t0, t1 = (T[4], T[5]) if idx % 2 == 0 else (T[2], T[3])
         if masked:
             for k, i in enumerate((2 * idx, 2 * idx + 1)):
                 e(f"v_cmp_gt_i32 {s(MASKS[k], 2)}, {v(lim)}, {8 * (i // 4) + i % 4}")
-        e(f"v_fma_f32 {v(T[4])}, {v(sc + 2 * idx)}, {s(C_SCALE)}, {v(NEGM)}")
-        e(f"v_fma_f32 {v(T[5])}, {v(sc + 2 * idx + 1)}, {s(C_SCALE)}, {v(NEGM)}")
+        e(f"v_fma_f32 {v(t0)}, {v(sc + 2 * idx)}, {s(C_SCALE)}, {v(NEGM)}")
+        e(f"v_fma_f32 {v(t1)}, {v(sc + 2 * idx + 1)}, {s(C_SCALE)}, {v(NEGM)}")
         if masked:
-            e(f"v_cndmask_b32 {v(T[4])}, {v(NEGINF)}, {v(T[4])}, {s(MASKS[0], 2)}")
-            e(f"v_cndmask_b32 {v(T[5])}, {v(NEGINF)}, {v(T[5])}, {s(MASKS[1], 2)}")
-        e(f"v_exp_f32 {v(T[4])}, {v(T[4])}")
-        e(f"v_exp_f32 {v(T[5])}, {v(T[5])}")
-        if pending:
-            flush_sum()
-        else:
-            e("s_nop 0")
-        e(f"v_cvt_pk_bf16_f32 {v(pb + idx)}, {v(T[4])}, {v(T[5])}")
-        pending.append(pb + idx)
-        if not DEFER_SUM:
-            flush_sum()
+            e(f"v_cndmask_b32 {v(t0)}, {v(NEGINF)}, {v(t0)}, {s(MASKS[0], 2)}")
+            e(f"v_cndmask_b32 {v(t1)}, {v(NEGINF)}, {v(t1)}, {s(MASKS[1], 2)}")
+        e(f"v_exp_f32 {v(t0)}, {v(t0)}")
+        e(f"v_exp_f32 {v(t1)}, {v(t1)}")
+        late.append((pb + idx, t0, t1))
+        if len(late) > 1:
+            convert()
 
     def end_of_sums(f):
-        """The last row-sum step of a key block, and then three instructions before anything but another such step
-        reads the sum (the result of a dot-product instruction reaches other ALU instructions three issue slots
-        late, and the hardware does not wait for it): the LDS reads this MFMA slot (fragment f) still owes and the
-        wait that the next MFMA needs anyway."""
-        flush_sum()
-        n0 = len(st.lines)
+        """What the MFMA slot of fragment f still owes, the row sum of a key block (all its dot products in a row, see above),
+        and then three instructions before anything but another such step reads the sum (the result of a dot-product
+        instruction reaches other ALU instructions three issue slots late, and the hardware does not wait for it): the
+        wait that the next MFMA needs anyway among them."""
         read_frag(f + PD)
+        while late:
+            convert()
+        while to_sum:
+            e(f"v_dot2c_f32_bf16 {v(LSUM)}, {ONES}, {v(to_sum.pop(0))}")
+        n0 = len(st.lines)
         st.wait_lds(last[f + 2])
         while len(st.lines) - n0 < 3:
             e("s_nop 0")
