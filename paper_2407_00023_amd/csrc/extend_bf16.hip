@@ -1,4 +1,4 @@
-// Extend attention on the bf16 matrix cores (MFMA 32x32x16, fp32 accumulate), gfx950.
+// Extend attention on the bf16 matrix cores (MFMA 16x16x32, fp32 accumulate), gfx950.
 //
 // What is computed (Sec. 3.2 and Sec. 5 of the paper: only the missed tokens of a prompt
 // are prefilled, the cached prefix KV is reused losslessly): extend row i of request r
@@ -21,11 +21,12 @@
 // fetches the row's chunk c ^ swizzle(row).
 //
 // MFMA formulation.  Scores are produced TRANSPOSED, S^T = K * Q^T, so that in the
-// accumulator layout every lane holds one query row (column l % 32) and 16 of the 32
-// keys of a block: row statistics of the online softmax are per-lane scalars plus one
-// exchange between lane l and l ^ 32, and the probabilities are already laid out as the
+// accumulator layout every lane holds two query rows (l % 16 and 16 more of the wave's 32) and 8 of the 32
+// keys of a block for each: row statistics of the online softmax are per-lane scalars plus two
+// exchanges between the lanes l, l ^ 16, l ^ 32, l ^ 48, and the probabilities are already laid out as the
 // B operand of the second product O^T = V^T * P^T.  The V^T fragments are read from the
-// row-major V tile with the transposing LDS read of gfx950.
+// row-major V tile with the transposing LDS read of gfx950.  (16x16x32 rather than 32x32x16: less energy for the same
+// product, see gen_fast_run.py.)
 //
 // Two kinds of tile.  The general tile (general_block below) takes any mix of pool and extend rows, masks and
 // ragged ends, and moves the running maximum; it runs where nothing else applies (heads of 64 on the fp8 pool or on
@@ -49,7 +50,7 @@ namespace pa {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -77,41 +78,40 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 }
 
 // XOR swizzles of the 16-byte chunks of a K/V row in LDS, chosen so that the two read patterns of the
-// arithmetic are free of bank conflicts for 256-byte rows: K is read 16 bytes per lane down 16
-// consecutive rows, V is read 8 bytes per lane across 64 bytes of 4 consecutive rows.
+// arithmetic are free of bank conflicts: K is read 16 bytes per lane down 16 consecutive rows, V is read 8 bytes per lane across
+// 32 bytes of 8 consecutive rows (by half a wave).
 template <int D>
 __device__ __forceinline__ int swz_k(int row) {
     return D == 128 ? (row & 15) : ((row >> 1) & 7);
 }
 template <int D>
 __device__ __forceinline__ int swz_v(int row) {
-    return D == 128 ? (((row & 3) << 2) | ((row >> 2) & 3)) : ((((row >> 1) & 1) << 2) | ((row >> 2) & 3));
+    return ((D == 128 ? row & 3 : (row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1) | ((row >> 3) & 1);
 }
 
 // The V^T fragments come from the transposing LDS read ds_read_b64_tr_b16: within each group of 16 lanes the
 // 16 x 4 16-bit values addressed by the lanes form a flat array F (lane-major); lane i of the group receives
 // F[i], F[16 + i], F[32 + i], F[48 + i].
 
-// Both halves of a query row (lanes l and l ^ 32) combined, in every lane, without going through LDS.
-// v_permlane32_swap exchanges lanes 32..63 of its first operand with lanes 0..31 of its second: fed the
-// same value x twice it leaves (x of the low half, x of the high half) in every lane.  Written as
-// inline assembly (the compiler builtin folded its two results into one); the s_nop pairs cover the
-// wait states the instruction needs after a VALU write of its operands and before a VALU read of them.
-__device__ __forceinline__ void row_halves(float x, float& lo, float& hi) {
+// The largest of a query row's values, which lie in the lanes l, l ^ 16, l ^ 32 and l ^ 48, in all of them, without going through
+// LDS.  v_permlane32_swap exchanges lanes 32..63 of its first operand with lanes 0..31 of its second, v_permlane16_swap the odd
+// rows of 16 lanes of the first with the even ones of the second: fed the same value twice they leave both values of a pair in
+// every lane.  Written as inline assembly (the compiler builtin folded its two results into one); the s_nop pairs cover the
+// wait states the instructions need after a VALU write of their operands and before a VALU read of them.
+__device__ __forceinline__ float row_max(float x) {
     float a = x, b = x;
     asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
-    lo = a;
-    hi = b;
+    a = b = fmaxf(a, b);
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+    return fmaxf(a, b);
 }
-__device__ __forceinline__ float row_max(float x) {
-    float lo, hi;
-    row_halves(x, lo, hi);
-    return fmaxf(lo, hi);
-}
+// ... and their sum.
 __device__ __forceinline__ float row_sum(float x) {
-    float lo, hi;
-    row_halves(x, lo, hi);
-    return lo + hi;
+    float a = x, b = x;
+    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+    a = b = a + b;
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+    return a + b;
 }
 
 // Workgroup barrier without the memory fence of __syncthreads(): the fence would make the compiler wait
@@ -157,29 +157,29 @@ __device__ __forceinline__ unsigned lds_address(const void* p) {
 // The K fragments of a block of 32 keys, all asked for before the first product, so that their LDS round trips overlap
 // instead of following one another (the compiler, short of registers, reads one fragment at a time into the same four
 // registers).  The wait stands in the same statement: no register of a read in flight is ever the compiler's to use.
+// kf[2 s + kb]: k-slice s of the keys 16 kb .. 16 kb + 15, which lie half_off bytes apart.
 template <int KS>
-__device__ __forceinline__ void read_k_block(bf16x8 (&kf)[KS], const unsigned (&at)[KS], unsigned off) {
-    static_assert(KS == 8 || KS == 4, "head dimension 128 or 64");
-    if constexpr (KS == 8)
+__device__ __forceinline__ void read_k_block(bf16x8 (&kf)[2 * KS], const unsigned (&at)[KS], unsigned off, unsigned half_off) {
+    static_assert(KS == 4 || KS == 2, "head dimension 128 or 64");
+    if constexpr (KS == 4)
         asm volatile(
             "ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
             "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\ts_waitcnt lgkmcnt(0)"
             : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3]), "=&v"(kf[4]), "=&v"(kf[5]), "=&v"(kf[6]), "=&v"(kf[7])
-            : "v"(at[0] + off), "v"(at[1] + off), "v"(at[2] + off), "v"(at[3] + off), "v"(at[4] + off), "v"(at[5] + off),
-              "v"(at[6] + off), "v"(at[7] + off)
+            : "v"(at[0] + off), "v"(at[0] + off + half_off), "v"(at[1] + off), "v"(at[1] + off + half_off), "v"(at[2] + off),
+              "v"(at[2] + off + half_off), "v"(at[3] + off), "v"(at[3] + off + half_off)
             : "memory");
     else
         asm volatile(
             "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
             : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3])
-            : "v"(at[0] + off), "v"(at[1] + off), "v"(at[2] + off), "v"(at[3] + off)
+            : "v"(at[0] + off), "v"(at[0] + off + half_off), "v"(at[1] + off), "v"(at[1] + off + half_off)
             : "memory");
 }
 
 // A store of 16 bytes that goes through to memory: the workgroup that joins the parts of a tile may run on another XCD, whose
 // L2 does not see this one's.  (The s_nop: a vector-ALU write of the data registers must stay two slots away.)
 __device__ __forceinline__ void store_through_16(float* p, float4 v) {
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
     const f32x4 x = {v.x, v.y, v.z, v.w};
     asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(x) : "memory");
 }
@@ -260,19 +260,23 @@ constexpr int kLdsTail = kLdsMl + 4 * kNarrowRows * 8;
 
 // KV8: the pool holds one-byte codes and row exponents (fp8_rows.h) instead of bfloat16; its rows are decoded into the
 // bfloat16 tiles in LDS, and everything from there on is the same arithmetic.
-// kDirect: a launch without a work list (DirectArgs, direct_item); a kernel of its own, so that the other keeps its registers and code.
-template <int D, bool KV8, bool kDirect>
+// kForm: a launch with a work list, or one without (DirectArgs, direct_item), of tiles of 128 rows (narrow where a tile has few) or of
+// narrow ones only.  Kernels of their own, so that none of them keeps the registers and code of the others.
+constexpr int kList = 0, kDirectWide = 1, kDirectNarrow = 2;
+template <int D, bool KV8, int kForm>
 __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_kernel(
     const __hip_bfloat16* __restrict__ q_ext, const __hip_bfloat16* __restrict__ k_ext,
     const __hip_bfloat16* __restrict__ v_ext, const __hip_bfloat16* __restrict__ pool, const signed char* __restrict__ pool_exp,
     const int32_t* __restrict__ slot_idx, int Hq, int Hkv, int page_size, int page_shift, unsigned page_magic,
     int page_mshift, int num_slots, int fast_ok, float scale_log2e, __hip_bfloat16* __restrict__ out, const int32_t* __restrict__ hdr,
     const int4* __restrict__ item_tab, const int4* __restrict__ member_tab, float* __restrict__ part_o,
-    float* __restrict__ part_ml, unsigned long long* __restrict__ clk, std::conditional_t<kDirect, DirectArgs, NoArgs> direct) {
+    float* __restrict__ part_ml, unsigned long long* __restrict__ clk, std::conditional_t<kForm != kList, DirectArgs, NoArgs> direct) {
+    constexpr bool kDirect = kForm != kList;
     constexpr int NW = 4;                    // waves
     constexpr int MT = kTileRows;            // packed query rows per wide row tile, 32 per wave
-    constexpr int NB = D / 32;               // MFMA row blocks of the head dimension in O^T
-    constexpr int KS = D / 16;               // k-slices of the QK^T product
+    constexpr int RB = 2;                    // row blocks of a wave: its rows 0..15 and 16..31
+    constexpr int NB = D / 16;               // MFMA row blocks of the head dimension in O^T
+    constexpr int KS = D / 32;               // k-slices of the QK^T product
     constexpr int CPR = D / 8;               // 16-byte chunks per K/V row
     constexpr int ROWB = D * 2;              // bytes per row
     constexpr int TILEB = kKT * ROWB;        // bytes of one K (or V) tile
@@ -302,26 +306,34 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     const int prow = rec1.x;  // first row of this item's partial result; -1: the item covers all keys and writes the output
     const int P = rec1.y;  // keys of the prefix; in a shared tile: of the part of it that all members have in common
     const int G = Hq / Hkv;
+    // packed rows by the size of the group: a shift where that is a power of two, as it mostly is (a division by a number that is
+    // not known at compile time is thirty instructions)
+    const int g_shift = (G & (G - 1)) == 0 ? __builtin_ctz(static_cast<unsigned>(G)) : -1;
+    auto by_group = [&](int x) __attribute__((always_inline)) { return g_shift >= 0 ? x >> g_shift : x / G; };
     // a shared tile: rows of n_members requests with this prefix, laid end to end; after the common keys come the members'
     // extend tokens, member after member (unless only the first part of their prefixes is common: the tile ends there)
     const int member0 = __builtin_amdgcn_readfirstlane(rec2.z), n_members = kDirect ? 0 : __builtin_amdgcn_readfirstlane(rec2.w);
-    const bool narrow = __builtin_amdgcn_readfirstlane(rec2.y) != 0;
     const bool shared = n_members > 0;
+    // Wide and narrow tiles have nothing but this in common, not even the code of their set-up: written once, compiled for each (values
+    // of the one kept across the assembly of the other were spilled, and reloaded in the narrow tiles' loop behind its loads: 256
+    // decode requests 69 -> 73 us).
+    auto tile = [&](auto narrow_c) __attribute__((always_inline)) {
+    constexpr bool narrow = decltype(narrow_c)::value;
     const int rows_total = shared ? rec1.z : rec1.z * G;
     const int rows_here = min(narrow ? kNarrowRows : MT, rows_total - row0);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n = lane & 31, hh = lane >> 5;
+    const int n = lane & 15, g4 = lane >> 4;
     const int64_t e0 = rec1.w;
     const int32_t* __restrict__ slots = slot_idx + slot_off;
 
-    // this lane's query row (a narrow tile: the same rows in every wave)
+    // this lane's query rows are wave_row0 + 16 rb + n (a narrow tile: the same rows in every wave)
     const int wave_row0 = narrow ? 0 : wave * 32;
     const bool wave_on = wave_row0 < rows_here;
     // (the rows of a shared tile are their requests' last ones: no tile of its key range is skipped)
-    const int wave_i_last = shared ? max(0, kv_hi - P) : (row0 + min(rows_here, wave_row0 + 32) - 1) / G;
+    const int wave_i_last = shared ? max(0, kv_hi - P) : by_group(row0 + min(rows_here, wave_row0 + 32) - 1);
     // the members of a shared tile: where a member's extend tokens begin on the tile's key axis (and, one past the last
     // member, where they end) and its first extend token counted from this item's
     // (behind the K/V ring in the dynamic LDS, which thereby keeps its alignment)
@@ -350,41 +362,55 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         }
         __syncthreads();
     }
-    bf16x8 qreg[KS];
-    int rho = row0 + wave_row0 + n;
-    const bool row_ok = wave_row0 + n < rows_here;
-    int64_t e0_row = e0;         // first extend token of the row's request
-    int vis_lo = P;              // in a shared tile: the keys [P, vis_lo) are other members' and hidden from the row
+    bf16x8 qreg[RB][KS];
+    int qi[RB], qh[RB];          // extend index and query head of the row
+    int64_t e0_row[RB];          // first extend token of the row's request
+    int vis_lo[RB], vis_end[RB]; // keys [.., vis_end) are visible to the row; in a shared tile [P, vis_lo) are other members' and hidden
+    bool row_ok[RB];
+    const int blk_vis_min = shared ? min(kv_hi, P) : min(kv_hi, P + by_group(row0 + wave_row0) + 1);  // every row of the wave sees keys [.., this)
+    int rho[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        rho[rb] = row0 + wave_row0 + 16 * rb + n;
+        row_ok[rb] = wave_row0 + 16 * rb + n < rows_here;
+        e0_row[rb] = e0;
+        vis_lo[rb] = P;
+    }
     if (shared) {
-        // whose row this is: the last member that starts at or before it; its place in that request; where
+        // whose rows these are: the last member that starts at or before a row; its place in that request; where
         // that member's extend tokens begin on the tile's key axis
-        const int want = row_ok ? rho : member_tab[2 * member0].x;
+        const int first = member_tab[2 * member0].x;
+        const int want[RB] = {row_ok[0] ? rho[0] : first, row_ok[1] ? rho[1] : first};
         for (int k = 0; k < n_members; ++k) {
             const int4 mem = member_tab[2 * (member0 + k)];  // (same address in every lane)
-            if (mem.x <= want) {
-                e0_row = mem.y;
-                rho = mem.z + (want - mem.x);
-                vis_lo = s_mseg[k];
-            }
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+                if (mem.x <= want[rb]) {
+                    e0_row[rb] = mem.y;
+                    rho[rb] = mem.z + (want[rb] - mem.x);
+                    vis_lo[rb] = s_mseg[k];
+                }
         }
     }
-    const int qi = row_ok ? rho / G : 0, qh = g * G + (row_ok ? rho % G : 0);   // extend index and query head of the row
-    const int vis_end = min(kv_hi, vis_lo + qi + 1);                            // keys [.., vis_end) are visible to the row
-    const int blk_vis_min = shared ? min(kv_hi, P) : min(kv_hi, P + (row0 + wave_row0) / G + 1);  // every row of the wave sees keys [.., this)
-    {
-        const uint4* qp = reinterpret_cast<const uint4*>(q_ext + ((e0_row + qi) * Hq + qh) * static_cast<int64_t>(D));
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        const int r = row_ok[rb] ? rho[rb] : 0;
+        qi[rb] = by_group(r);
+        qh[rb] = g * G + (r - qi[rb] * G);
+        vis_end[rb] = min(kv_hi, vis_lo[rb] + qi[rb] + 1);
+        const uint4* qp = reinterpret_cast<const uint4*>(q_ext + ((e0_row[rb] + qi[rb]) * Hq + qh[rb]) * static_cast<int64_t>(D));
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             uint4 v = make_uint4(0, 0, 0, 0);
-            if (row_ok) v = qp[2 * s + hh];
-            qreg[s] = __builtin_bit_cast(bf16x8, v);
+            if (row_ok[rb]) v = qp[4 * s + g4];
+            qreg[rb][s] = __builtin_bit_cast(bf16x8, v);
         }
     }
 
     // In a shared tile the keys past the common part concern one member each: the wave skips the arithmetic of a tile
     // that holds no key of the members its rows belong to (uniform over the wave).
     if (shared) {
-        int wave_own_lo = vis_lo, wave_own_hi = vis_end;
+        int wave_own_lo = min(vis_lo[0], vis_lo[1]), wave_own_hi = max(vis_end[0], vis_end[1]);
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             wave_own_lo = min(wave_own_lo, __shfl_xor(wave_own_lo, off));
@@ -407,7 +433,20 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     const unsigned char* vx_g = reinterpret_cast<const unsigned char*>(v_ext) + (e0 * Hkv + g) * static_cast<int64_t>(ROWB);
     const size_t x_stride = static_cast<size_t>(Hkv) * ROWB;  // bytes from one extend token to the next
     const unsigned smem_addr = __builtin_amdgcn_readfirstlane(lds_address(smem));
-    int32_t sl_next[UPW];  // pool slots of the rows this lane loads in the tile after the one in flight
+    // Pool slots of rows of the tile after the one in flight.  Heads of 128: of one row of the wave's sixteen, 4 (lane % 4) + lane / 16; the
+    // lanes 16 j .. 16 j + 15, which load row 4 u + j in block u, have it from lane 16 j + u.  Heads of 64: of the rows that the lane loads.
+    constexpr int NSL = D == 128 ? 1 : UPW;
+    int32_t sl_next[NSL];
+    const int sl_row = D == 128 ? 4 * (lane & 3) + (lane >> 4) : ld_rowl;
+    auto slot_of = [&](int u) __attribute__((always_inline)) -> int {  // (all lanes; u known at compile time)
+        if constexpr (D == 128)
+            return u == 0   ? __builtin_amdgcn_update_dpp(0, sl_next[0], 0x150, 0xf, 0xf, false)
+                   : u == 1 ? __builtin_amdgcn_update_dpp(0, sl_next[0], 0x151, 0xf, 0xf, false)
+                   : u == 2 ? __builtin_amdgcn_update_dpp(0, sl_next[0], 0x152, 0xf, 0xf, false)
+                            : __builtin_amdgcn_update_dpp(0, sl_next[0], 0x153, 0xf, 0xf, false);
+        else
+            return sl_next[u];
+    };
 
     // (first member of a shared tile whose own keys reach the tile asked for; the tiles are asked for in order)
     int cur_member = 0;
@@ -418,15 +457,15 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     };
     auto load_slots = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < UPW; ++u) {
-            // positions past the end of the key range repeat the last valid one (see issue_tile)
-            const int p = min(p0 + (wave * UPW + u) * RPB + ld_rowl, kv_hi - 1);
+        for (int u = 0; u < NSL; ++u) {
+            // positions past the end of the key range repeat the last valid one (see issue)
+            const int p = min(p0 + (wave * UPW + u) * RPB + sl_row, kv_hi - 1);
             sl_next[u] = p < P ? slots[p] : 0;
         }
     };
     // Byte offset, inside its K (V) row, of the 16 bytes this lane fetches for block u.  Block u of the wave holds
     // rows 16 w + 4 u + lane / 16 (D = 128), so its swizzle differs from that of block 0 by an XOR with 4 u (K) or
-    // u (V); for D = 64 (rows 16 w + 8 u + lane / 8) by an XOR with 4 u (K) or 2 u (V).
+    // 2 (u % 2) + u / 2 (V); for D = 64 (rows 16 w + 8 u + lane / 8) by an XOR with 4 u (K) or u (V).
     const unsigned ld_koff0 = (ld_pos ^ swz_k<D>(wave * UPW * RPB + ld_rowl)) * 16;
     const unsigned ld_voff0 = (ld_pos ^ swz_v<D>(wave * UPW * RPB + ld_rowl)) * 16;
     // (Worked out where they are used, from a value the compiler cannot see through: left to itself it keeps all eight
@@ -437,7 +476,8 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         return x;
     };
     auto ld_koff = [&](int u) __attribute__((always_inline)) { return opaque(ld_koff0) ^ (64u * u); };
-    auto ld_voff = [&](int u) __attribute__((always_inline)) { return opaque(ld_voff0) ^ ((D == 128 ? 16u : 32u) * u); };
+    auto v_swizzle = [](int u) __attribute__((always_inline)) { return 16u * (D == 128 ? 2 * (u & 1) + (u >> 1) : u); };
+    auto ld_voff = [&](int u) __attribute__((always_inline)) { return opaque(ld_voff0) ^ v_swizzle(u); };
     // The next tile's loads, general: every lane takes its row from the pool (through the slot prefetched for it) or
     // from the extend tensors, by position; rows past the end of the key range repeat the last valid row (finite
     // values that the mask zeroes).  The page of a slot: a shift where the page size is a power of two
@@ -451,7 +491,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
             const int blk = wave * UPW + u;
             const int p = min(p0 + blk * RPB + ld_rowl, kv_hi - 1);
             const bool ext = p >= P;
-            const unsigned sl = static_cast<unsigned>(min(max(sl_next[u], 0), num_slots - 1));  // never outside the pool
+            const unsigned sl = static_cast<unsigned>(min(max(slot_of(u), 0), num_slots - 1));  // never outside the pool
             const unsigned pg = page_shift >= 0 ? sl >> page_shift : __umulhi(sl, page_magic) >> page_mshift;
             const size_t pool_off = static_cast<size_t>(pg) * page_stride +
                                     (sl - pg * static_cast<unsigned>(page_size)) * static_cast<unsigned>(ROWB);
@@ -493,7 +533,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
             const int blk = wave * UPW + u;
             const int p = min(p0 + blk * RPB + ld_rowl, kv_hi - 1);
             const bool ext = p >= P;
-            const unsigned sl = static_cast<unsigned>(min(max(sl_next[u], 0), num_slots - 1));  // never outside the pool
+            const unsigned sl = static_cast<unsigned>(min(max(slot_of(u), 0), num_slots - 1));  // never outside the pool
             const unsigned pg = page_shift >= 0 ? sl >> page_shift : __umulhi(sl, page_magic) >> page_mshift;
             const unsigned o = sl - pg * static_cast<unsigned>(page_size);
             int64_t xrow = p - P;
@@ -512,11 +552,20 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                     load_to_lds_16(ka, sk + blk * 1024);
                     load_to_lds_16(ka + v_off8, sk + TILEB + blk * 1024);
                 }
-                if (ld_pos == 0) {
+                if (D == 64 && ld_pos == 0) {
                     const signed char* ea = exp_g + static_cast<size_t>(pg) * exp_page + o;
                     load_to_lds_1(ea, ex + (2 * u) * 256);
                     load_to_lds_1(ea + exp_v, ex + (2 * u + 1) * 256);
                 }
+            }
+        }
+        if constexpr (D == 128) {  // (lane 16 j + u those of row 4 u + j, as the assembly does)
+            if (ld_pos < UPW && min(p0 + wave * UPW * RPB + sl_row, kv_hi - 1) < P) {
+                const unsigned sl = static_cast<unsigned>(min(max(sl_next[0], 0), num_slots - 1));
+                const unsigned pg = page_shift >= 0 ? sl >> page_shift : __umulhi(sl, page_magic) >> page_mshift;
+                const signed char* ea = exp_g + static_cast<size_t>(pg) * exp_page + (sl - pg * static_cast<unsigned>(page_size));
+                load_to_lds_1(ea, ex);
+                load_to_lds_1(ea + exp_v, ex + 256);
             }
         }
     };
@@ -532,8 +581,8 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                 const unsigned char* row = sk + (wave * UPW + u) * 1024 + ld_rowl * ROWB;
                 kraw[u] = *reinterpret_cast<const uint2*>(row + (ld_koff(u) >> 1));
                 vraw[u] = *reinterpret_cast<const uint2*>(row + TILEB + (ld_voff(u) >> 1));
-                ke[u] = ex[(2 * u) * 64 + (lane & ~(CPR - 1))];
-                ve[u] = ex[(2 * u + 1) * 64 + (lane & ~(CPR - 1))];
+                ke[u] = D == 128 ? ex[(lane & ~15) + u] : ex[(2 * u) * 64 + (lane & ~(CPR - 1))];
+                ve[u] = D == 128 ? ex[64 + (lane & ~15) + u] : ex[(2 * u + 1) * 64 + (lane & ~(CPR - 1))];
             }
         }
 #pragma unroll
@@ -555,37 +604,35 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         else issue(p0, ring);
     };
 
-    f32x16 oacc[NB];
-    float m_run = -INFINITY, l_run = 0.f;  // running maximum (scaled, log2 domain) and this lane's share of the sum
+    f32x4 oacc[RB][NB];
+    float m_run[RB] = {-INFINITY, -INFINITY}, l_run[RB] = {0.f, 0.f};  // running maximum (scaled, log2 domain) and this lane's share of the sum
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[b][i] = 0.f;
+        for (int b = 0; b < NB; ++b) oacc[rb][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // ---- LDS read addresses of this lane in the ring slot that holds the current tile (toggled after every tile).
-    // K: row n (+32 for the second key block), 16-byte chunk 2 s + hh of the row.
-    // V, transposing read: group lane i = 4 e + c reads key row 8 h2 + 4 hh + e (+ 16 cs + 32 mb) and 8 bytes at
-    // head-dim offset 32 b + 16 par + 4 c.  The swizzles do not depend on mb / cs, which become immediates.
+    // K: row n (+16 for the second half of a block, +32 for the second block), 16-byte chunk 4 s + g4 of the row.
+    // V, transposing read: group lane i = 4 e + c reads key row 4 g4 + e (+ 16 for the second half, + 32 for the second block) and
+    // 8 bytes at head-dim offset 16 b + 4 c.  The swizzles do not depend on halves and blocks, which become immediates.
     typedef __attribute__((address_space(3))) const unsigned char lds_cbyte;
     lds_cbyte* lds = (lds_cbyte*)nullptr;  // k_rd / v_rd hold absolute LDS addresses
-    unsigned k_rd[KS], v_rd[NB][2];
+    unsigned k_rd[KS], v_rd[NB];
     {
-        const int tr_e = (lane >> 2) & 3, tr_c = lane & 3, tr_par = (lane >> 4) & 1;
+        const int tr_e = (lane >> 2) & 3, tr_c = lane & 3;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            k_rd[s] = smem_addr + n * ROWB + (((2 * s + hh) ^ swz_k<D>(n)) * 16);
+            k_rd[s] = smem_addr + n * ROWB + (((4 * s + g4) ^ swz_k<D>(n)) * 16);
             asm volatile("" : "+v"(k_rd[s]));  // keep it in a register instead of recomputing it every tile
         }
+        const int vrow = 4 * g4 + tr_e;
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2) {
-                const int vrow = 8 * h2 + 4 * hh + tr_e;
-                const int chunk16 = 4 * b + 2 * tr_par + (tr_c >> 1);
-                v_rd[b][h2] = smem_addr + TILEB + vrow * ROWB + ((chunk16 ^ swz_v<D>(vrow)) * 16) + (tr_c & 1) * 8;
-                asm volatile("" : "+v"(v_rd[b][h2]));
-            }
+        for (int b = 0; b < NB; ++b) {
+            v_rd[b] = smem_addr + TILEB + vrow * ROWB + (((2 * b + (tr_c >> 1)) ^ swz_v<D>(vrow)) * 16) + (tr_c & 1) * 8;
+            asm volatile("" : "+v"(v_rd[b]));
+        }
     }
+
     const bf16x2_t ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
 
     // ---- One block of 32 keys of the current tile, general: masks, any running maximum.  Kept small in registers
@@ -593,78 +640,103 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     // it runs wherever the assembly tiles do not apply.  mb = 0 / 1: first / second block of the tile.
     auto general_block = [&](int p0, int mb, bool need_mask) __attribute__((always_inline)) {
         const unsigned off = static_cast<unsigned>(mb) * (32 * ROWB);
-        const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        f32x16 sacc;
+        const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+        f32x4 sacc[2][RB];  // [half of the block's keys][row block]
         // S^T = K Q^T
-        bf16x8 kf[KS];
-        read_k_block<KS>(kf, k_rd, off);
+        bf16x8 kf[2 * KS];
+        read_k_block<KS>(kf, k_rd, off, 16 * ROWB);
 #pragma unroll
-        for (int s = 0; s < KS; ++s) sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qreg[s], s == 0 ? zero16 : sacc, 0, 0, 0);
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)
+                    sacc[kb][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[2 * s + kb], qreg[rb][s], s == 0 ? zero4 : sacc[kb][rb], 0, 0, 0);
         const int pb0 = p0 + 32 * mb;
-        uint32_t pb[8];
         // the keys a row must not see (only where the block crosses a visibility limit)
-        // (register i of the lane holds the key at offset 8 (i / 4) + i % 4 from the lane's first key of the block:
+        // (register i of half kb holds the key at offset 16 kb + i from the lane's first key of the block:
         // compared, without branches, against the row's limits counted from that key)
         if (need_mask && pb0 + 32 > blk_vis_min) {
-            const int first = pb0 + 4 * hh;
-            const int lim_end = vis_end - first;
+            const int first = pb0 + 4 * g4;
             if (!shared) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) sacc[i] = (8 * (i / 4) + (i % 4) < lim_end) ? sacc[i] : -INFINITY;
-            } else {
-                const int lim_p = P - first, lim_lo = vis_lo - first;
+                for (int rb = 0; rb < RB; ++rb) {
+                    const int lim_end = vis_end[rb] - first;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int o = 8 * (i / 4) + (i % 4);
-                    const bool hide = (o >= lim_end) | ((o >= lim_p) & (o < lim_lo));
-                    sacc[i] = hide ? -INFINITY : sacc[i];
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) sacc[kb][rb][i] = (16 * kb + i < lim_end) ? sacc[kb][rb][i] : -INFINITY;
+                }
+            } else {
+                const int lim_p = P - first;
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    const int lim_end = vis_end[rb] - first, lim_lo = vis_lo[rb] - first;
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int o = 16 * kb + i;
+                            const bool hide = (o >= lim_end) | ((o >= lim_p) & (o < lim_lo));
+                            sacc[kb][rb][i] = hide ? -INFINITY : sacc[kb][rb][i];
+                        }
                 }
             }
         }
-        // row maximum of the block, in every lane of the row
-        float mx = fmaxf(sacc[0], sacc[1]);
+        // row maxima of the block, in every lane of the row
+        float m_blk[RB];
 #pragma unroll
-        for (int i = 2; i < 16; ++i) mx = fmaxf(mx, sacc[i]);
-        const float m_blk = row_max(mx) * scale_log2e;  // log2 domain (scale > 0)
+        for (int rb = 0; rb < RB; ++rb) {
+            float mx = fmaxf(sacc[0][rb][0], sacc[1][rb][0]);
+#pragma unroll
+            for (int i = 1; i < 4; ++i) mx = fmaxf(mx, fmaxf(sacc[0][rb][i], sacc[1][rb][i]));
+            m_blk[rb] = row_max(mx) * scale_log2e;  // log2 domain (scale > 0)
+        }
         // The running maximum may lag the true one by kRescaleThreshold (probabilities then reach 2^threshold,
         // harmless in bf16/fp32).  If some row of the wave outgrew it by more, raise it and rescale what was
         // accumulated so far.  With a stable maximum this happens for the first block only.
-        if (__any(m_blk > m_run + kRescaleThreshold)) {
-            const float m_new = fmaxf(m_run, m_blk);
-            const float alpha = __builtin_amdgcn_exp2f(m_run - ((m_new == -INFINITY) ? 0.f : m_new));
-            l_run *= alpha;
+        if (__any(m_blk[0] > m_run[0] + kRescaleThreshold || m_blk[1] > m_run[1] + kRescaleThreshold)) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+            for (int rb = 0; rb < RB; ++rb) {
+                const float m_new = fmaxf(m_run[rb], m_blk[rb]);
+                const float alpha = __builtin_amdgcn_exp2f(m_run[rb] - ((m_new == -INFINITY) ? 0.f : m_new));
+                l_run[rb] *= alpha;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
-            m_run = m_new;
-        }
-        // probabilities, packed to bf16 pairs (the B operand of the second product); the row sum takes the
-        // ROUNDED probabilities, the values the numerator uses
-        const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
-        float acc = 0.f;
+                for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int i = 0; i < 16; i += 2) {
-            const float a = __builtin_amdgcn_exp2f(fmaf(sacc[i], scale_log2e, neg_m));
-            const float b = __builtin_amdgcn_exp2f(fmaf(sacc[i + 1], scale_log2e, neg_m));
-            const uint32_t pk = pack_bf16x2(a, b);
-            pb[i / 2] = pk;
-            acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, pk), ones, acc, false);
-        }
-        l_run += acc;
-        // O^T += V^T P^T, 16 keys per MFMA
-#pragma unroll
-        for (int cs = 0; cs < 2; ++cs) {
-            const bf16x8 pop = __builtin_bit_cast(bf16x8, make_uint4(pb[cs * 4 + 0], pb[cs * 4 + 1], pb[cs * 4 + 2], pb[cs * 4 + 3]));
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                s16x4 frag[2];
-#pragma unroll
-                for (int h2 = 0; h2 < 2; ++h2)
-                    frag[h2] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds + (v_rd[b][h2] + off + cs * 16 * ROWB)));
-                const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(frag[0], frag[1], 0, 1, 2, 3, 4, 5, 6, 7));
-                oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pop, oacc[b], 0, 0, 0);
+                    for (int i = 0; i < 4; ++i) oacc[rb][b][i] *= alpha;
+                m_run[rb] = m_new;
             }
+        }
+        // probabilities, packed to bf16 pairs (the B operand of the second product: its k-slots of lane group g4 are the keys
+        // 4 g4 .. 4 g4 + 3 of the block's halves, and so are those of the V^T fragments); the row sum takes the
+        // ROUNDED probabilities, the values the numerator uses
+        bf16x8 pop[RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const float neg_m = (m_run[rb] == -INFINITY) ? 0.f : -m_run[rb];
+            uint32_t pb[4];
+            float acc = 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float a = __builtin_amdgcn_exp2f(fmaf(sacc[k / 2][rb][2 * (k % 2)], scale_log2e, neg_m));
+                const float b = __builtin_amdgcn_exp2f(fmaf(sacc[k / 2][rb][2 * (k % 2) + 1], scale_log2e, neg_m));
+                pb[k] = pack_bf16x2(a, b);
+                acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, pb[k]), ones, acc, false);
+            }
+            pop[rb] = __builtin_bit_cast(bf16x8, make_uint4(pb[0], pb[1], pb[2], pb[3]));
+            l_run[rb] += acc;
+        }
+        // O^T += V^T P^T
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            s16x4 frag[2];
+#pragma unroll
+            for (int h2 = 0; h2 < 2; ++h2)
+                frag[h2] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds + (v_rd[b] + off + h2 * 16 * ROWB)));
+            const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(frag[0], frag[1], 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) oacc[rb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pop[rb], oacc[rb][b], 0, 0, 0);
         }
     };
 
@@ -821,7 +893,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     // results are joined.  What bounds them is memory (a few rows make little arithmetic): eight waves of a compute unit have
     // 16 KB each on the way.  (As a wide tile, one wave at work between two barriers per 64 keys, they took three times as
     // long.) ----
-    if (narrow) {
+    if constexpr (narrow) {
         constexpr int NLB = 32 / RPB;           // 1 KB load blocks of 32 rows, per tensor
         constexpr int VOFF = 32 * ROWB;         // the V rows lie behind the K rows
         constexpr int WB = kStages * STAGEB / NW;
@@ -830,13 +902,11 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
 #pragma unroll
         for (int s = 0; s < KS; ++s) k_rd[s] += wave * WB;
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2) v_rd[b][h2] += wave * WB + VOFF - TILEB;
+        for (int b = 0; b < NB; ++b) v_rd[b] += wave * WB + VOFF - TILEB;
         // (rows RPB u + lane / CPR: the swizzles repeat after 4 (D = 128) or 2 (D = 64) load blocks)
         const unsigned koff0 = (ld_pos ^ swz_k<D>(ld_rowl)) * 16, voff0 = (ld_pos ^ swz_v<D>(ld_rowl)) * 16;
         auto koff = [&](int u) __attribute__((always_inline)) { return opaque(koff0) ^ (64u * (u & (D == 128 ? 3 : 1))); };
-        auto voff = [&](int u) __attribute__((always_inline)) { return opaque(voff0) ^ ((D == 128 ? 16u : 32u) * (u & (D == 128 ? 3 : 1))); };
+        auto voff = [&](int u) __attribute__((always_inline)) { return opaque(voff0) ^ v_swizzle(u & (D == 128 ? 3 : 1)); };
         int32_t sl[NLB];
         auto ask_slots = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
@@ -920,19 +990,22 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         // ---- join the waves: each leaves its sums in its quarter of the ring (16-byte pieces of a row XORed with the row's
         // number, so that the lanes of a store meet different banks) ----
         constexpr int V4 = D / 4;  // pieces per row
-        const float l_wave = row_sum(l_run);
-        if (row_ok) {
-            float4* mine = reinterpret_cast<float4*>(smem + wave * WB) + n * V4;
+        const float l_row[RB] = {row_sum(l_run[0]), row_sum(l_run[1])};
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            if (!row_ok[rb]) continue;
+            const int row = 16 * rb + n;
+            float4* mine = reinterpret_cast<float4*>(smem + wave * WB) + row * V4;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-                    mine[(8 * b + 2 * q4 + hh) ^ (n & (V4 - 1))] = make_float4(oacc[b][4 * q4], oacc[b][4 * q4 + 1], oacc[b][4 * q4 + 2], oacc[b][4 * q4 + 3]);
-            if (hh == 0) s_ml[wave * kNarrowRows + n] = make_float2(m_run, l_wave);
+                mine[(4 * b + g4) ^ (row & (V4 - 1))] = make_float4(oacc[rb][b][0], oacc[rb][b][1], oacc[rb][b][2], oacc[rb][b][3]);
+            if (g4 == 0) s_ml[wave * kNarrowRows + row] = make_float2(m_run[rb], l_row[rb]);
         }
-        const int64_t my_out = (e0_row + qi) * Hq + qh;
+        // (a row of the output: fewer than 2^31 of 64 elements and more fit the memory)
+        const int my_out[RB] = {(static_cast<int>(e0_row[0]) + qi[0]) * Hq + qh[0], (static_cast<int>(e0_row[1]) + qi[1]) * Hq + qh[1]};
         const int jr = tid >> 3, sub = tid & 7;  // eight threads per row
-        const int64_t out_row = __shfl(my_out, jr);
+        const int out_a = __shfl(my_out[0], jr & 15), out_b = __shfl(my_out[1], jr & 15);
+        const int64_t out_row = jr < 16 ? out_a : out_b;
         __syncthreads();
         if (jr < rows_here) {
         float2 ml[NW];
@@ -977,9 +1050,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         }
         if constexpr (kDirect)
             if (prow >= 0) join_parts();
-        return;
-    }
-
+    } else {
     // ---- prologue: first tile into ring slot 0 ----
     load_slots(kv_lo);
     issue_any(kv_lo, 0);
@@ -1001,10 +1072,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
 #pragma unroll
         for (int s = 0; s < KS; ++s) k_rd[s] += d;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            v_rd[b][0] += d;
-            v_rd[b][1] += d;
-        }
+        for (int b = 0; b < NB; ++b) v_rd[b] += d;
     };
     // this wave's part of the next tile has landed, and so has everyone else's; nobody still reads the tile just
     // finished; then on to the next tile
@@ -1021,9 +1089,10 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     // tokens (2); it issues its tiles' loads itself.  A single tile: arithmetic only, with the keys a row must not see
     // hidden if there are any (5, else 4), the next tile's loads issued from here by the general code - for the tiles
     // that no run takes because of what their successor is (prefix and extend rows mixed) or because they touch the
-    // causal diagonal; not in shared tiles (a second visibility bound).  Neither before the running maximum exists.
+    // causal diagonal; in shared tiles only where all keys are common (a second visibility bound otherwise).  Neither before the
+    // running maximum exists.  (Last tiles of common first parts so, 256 decode requests: 3.5 us in the general tile.)
     auto single_tile_ok = [&](int p0) __attribute__((always_inline)) -> bool {
-        return (fast_ok || KV8) && kAsm && (smem_addr & 255u) == 0 && !shared && wave_on && p0 <= P + wave_i_last;
+        return (fast_ok || KV8) && kAsm && (smem_addr & 255u) == 0 && (!shared || min(p0 + kKT, kv_hi) <= P) && wave_on && p0 <= P + wave_i_last;
     };
     // The assembly tiles want a running maximum to start from, and any lower bound of the true one will do as long as it
     // is not 2^40 short (then the tile is handed to the general code, as always): the largest score of the first 32 keys,
@@ -1032,16 +1101,22 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     if constexpr (kAsm) {
         // (also in shared tiles: the keys of the common prefix are visible to every row)
         if ((fast_ok || KV8) && (smem_addr & 255u) == 0 && wave_on && kv_lo <= P + wave_i_last && kv_lo + 32 <= blk_vis_min && kv_lo + 32 <= kv_hi) {
-            const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            bf16x8 kf[KS];
-            read_k_block<KS>(kf, k_rd, 0);
-            f32x16 sacc = zero16;
+            const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+            bf16x8 kf[2 * KS];
+            read_k_block<KS>(kf, k_rd, 0, 16 * ROWB);
 #pragma unroll
-            for (int s = 0; s < KS; ++s) sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qreg[s], sacc, 0, 0, 0);
-            float mx = fmaxf(sacc[0], sacc[1]);
+            for (int rb = 0; rb < RB; ++rb) {
+                f32x4 s0 = zero4, s1 = zero4;
 #pragma unroll
-            for (int i = 2; i < 16; ++i) mx = fmaxf(mx, sacc[i]);
-            m_run = row_max(mx) * scale_log2e;
+                for (int s = 0; s < KS; ++s) {
+                    s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[2 * s], qreg[rb][s], s0, 0, 0, 0);
+                    s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[2 * s + 1], qreg[rb][s], s1, 0, 0, 0);
+                }
+                float mx = fmaxf(s0[0], s1[0]);
+#pragma unroll
+                for (int i = 1; i < 4; ++i) mx = fmaxf(mx, fmaxf(s0[i], s1[i]));
+                m_run[rb] = row_max(mx) * scale_log2e;
+            }
         }
     }
     bool fast_allowed = true;
@@ -1051,7 +1126,13 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         int from = 0;
         bool issue_next = true;
         int mode = 0, kind = 0;
-        if (fast_allowed && __all(m_run != -INFINITY)) {  // (every row has a running maximum)
+        const bool idle = !wave_on || p0 > P + wave_i_last;
+        if (idle && fast_ok && kAsm && (smem_addr & 255u) == 0) {
+            // Nothing to compute, in this tile or any later one: only its share of the loads.  (In the general code they held up the other
+            // waves: 16 questions to long documents, items of 68 to 92 rows 110 us instead of 90, with the fp8 pool 210 instead of 100.)
+            kind = min(p0 + 2 * kKT - 1, kv_hi - 1) < P ? (!KV8 || (fast_ok & 2) ? 1 : 0) : min(p0 + kKT, kv_hi - 1) >= P && !shared && (!KV8 || (fast_ok & 1)) ? 2 : 0;
+            mode = kind == 0 ? 0 : kind == 2 ? 8 : KV8 ? 10 : fast_ok == 2 ? 9 : 7;
+        } else if (fast_allowed && __all(m_run[0] != -INFINITY && m_run[1] != -INFINITY)) {  // (every row has a running maximum)
             kind = tile_kind(p0);
             mode = kind == 1 ? (KV8 ? 6 : fast_ok == 2 ? 3 : 1) : kind == 2 ? 2 : single_tile_ok(p0) ? (p0 + kKT > blk_vis_min ? 5 : 4) : 0;
         }
@@ -1060,8 +1141,12 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                 // Against the running maximum as it stands: scores never move it in there (a row's probabilities may
                 // reach 2^40 instead), the output accumulators are touched by MFMAs only.
                 int p_end = p0 + kKT;
-                if (mode <= 3 || mode == 6) {
-                    while (tile_kind(p_end) == kind) p_end += kKT;
+                if (mode != 4 && mode != 5) {
+                    // (as far as tile_kind() stays what it is: every condition in it, once it fails, fails for all later tiles.  Asked
+                    // tile by tile this took 2 us of a workgroup's 60.)
+                    int last = idle ? kv_hi - 1 : min(P + wave_i_last, blk_vis_min - kKT);
+                    if (kind == 1 && kv_hi > P) last = min(last, P - 2 * kKT);
+                    p_end += (last - p0) & ~(kKT - 1);
                     raw_mask = 0;  // (fp8 pool: a run decodes what it loads itself)
                 } else if (p0 + kKT < kv_hi) {
                     issue_any(p0 + kKT, ring ^ 1);
@@ -1071,11 +1156,15 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                 }
                 const int p_start = p0, ring_start = ring;
                 int st = 0;
-                auto quad = [&](int k) __attribute__((always_inline)) {  // the query fragments k .. k + 3 in a row
-                    const bf16x16 a = __builtin_shufflevector(qreg[k], qreg[k + 1], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
-                    const bf16x16 b = __builtin_shufflevector(qreg[k + 2], qreg[k + 3], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
-                    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18, 19, 20, 21, 22, 23, 24,
-                                                   25, 26, 27, 28, 29, 30, 31);
+                auto fragments = [&](int rb) __attribute__((always_inline)) {  // the query fragments of a row block in a row
+                    const bf16x16 a = __builtin_shufflevector(qreg[rb][0], qreg[rb][1], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+                    if constexpr (KS == 2) {
+                        return a;
+                    } else {
+                        const bf16x16 b = __builtin_shufflevector(qreg[rb][2], qreg[rb][3], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+                        return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18, 19, 20, 21, 22, 23, 24,
+                                                       25, 26, 27, 28, 29, 30, 31);
+                    }
                 };
                 // wave-uniform values, said so to the compiler (they go to scalar registers)
                 auto uni = [](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(x); };
@@ -1087,35 +1176,34 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                 // (mode 3: the pool is too large for 32-bit byte offsets; rows are then counted in units of 256 bytes)
                 // (mode 6, the fp8 pool: strides of the codes and of the row exponents, and where the latter lie)
                 const uint64_t exp_addr = reinterpret_cast<uint64_t>(exp_g);
+                const bool is8 = mode == 6 || mode == 10;
                 const i32x8 c = {uni(page_shift), uni(page_size - 1),
-                                 uni(static_cast<int>(mode == 6 ? page_stride8 : mode == 3 ? page_stride / ROWB : page_stride)), uni(num_slots - 1),
-                                 uni(P - 1), uni(static_cast<int>(mode == 6 ? exp_page : x_stride)),
-                                 uni(mode == 6 ? static_cast<int>(exp_v) : kv_hi - 1 - P),
+                                 uni(static_cast<int>(is8 ? page_stride8 : mode == 3 || mode == 9 ? page_stride / ROWB : page_stride)), uni(num_slots - 1),
+                                 uni(P - 1), uni(static_cast<int>(is8 ? exp_page : x_stride)),
+                                 uni(is8 ? static_cast<int>(exp_v) : kv_hi - 1 - P),
                                  uni(static_cast<int>(smem_addr) + wave * (UPW * 1024))};
-                const i32x4 c2 = {uni(mode == 6 ? static_cast<int>(exp_addr) : 128), uni(mode == 6 ? static_cast<int>(exp_addr >> 32) : 192), uni(P),
+                const i32x4 c2 = {uni(is8 ? static_cast<int>(exp_addr) : 128), uni(is8 ? static_cast<int>(exp_addr >> 32) : 192), uni(P),
                                   uni(__float_as_int(scale_log2e))};
                 p0 = uni(p0);
                 ring = uni(ring);
                 p_end = uni(p_end);
-                const int row_in_tile = wave * (UPW * RPB) + ld_rowl;
-                const void* base_k = mode == 2 ? static_cast<const void*>(kx_g) : mode == 6 ? static_cast<const void*>(pool8_g) : static_cast<const void*>(pool_g);
-                const void* base_v = mode == 2 ? static_cast<const void*>(vx_g) : mode == 6 ? static_cast<const void*>(pool8_g + v_off8) : static_cast<const void*>(pool_g + v_off32);
-                const int lim = vis_end - p0 - 4 * hh;
+                const int row_in_tile = wave * (UPW * RPB) + sl_row;
+                const void* base_k = kind == 2 ? static_cast<const void*>(kx_g) : is8 ? static_cast<const void*>(pool8_g) : static_cast<const void*>(pool_g);
+                const void* base_v = kind == 2 ? static_cast<const void*>(vx_g) : is8 ? static_cast<const void*>(pool8_g + v_off8) : static_cast<const void*>(pool_g + v_off32);
+                const int lim[RB] = {vis_end[0] - p0 - 4 * g4, vis_end[1] - p0 - 4 * g4};
                 if constexpr (KV8)  // (single tiles only; they end with this wave's loads landed and leave the barrier to the caller)
-                    fast_tiles_d128_kv8(uni(mode), oacc[0], oacc[1], oacc[2], oacc[3], quad(0), quad(4), l_run, -m_run, sl_next,
-                                        k_rd[0], v_rd[0][0], ld_koff0, ld_voff0, row_in_tile, p0, ring, st, p_end, uni_ptr(slots),
-                                        uni_ptr(base_k), uni_ptr(base_v), lim, c, c2, uni(static_cast<int>(smem_addr) + EX_OFF + wave * EXPB));
+                    fast_tiles_d128_kv8(uni(mode), oacc, fragments(0), fragments(1), l_run, -m_run[0], -m_run[1], sl_next, k_rd[0], v_rd[0], ld_koff0,
+                                        ld_voff0, row_in_tile, p0, ring, st, p_end, uni_ptr(slots), uni_ptr(base_k), uni_ptr(base_v), lim[0], lim[1], c, c2,
+                                        uni(static_cast<int>(smem_addr) + EX_OFF + wave * EXPB));
                 else if constexpr (D == 128)
-                    fast_tiles_d128(uni(mode), oacc[0], oacc[1], oacc[2], oacc[3], quad(0), quad(4), l_run, -m_run, sl_next,
-                                    k_rd[0], v_rd[0][0], ld_koff0, ld_voff0, row_in_tile, p0, ring, st, p_end, uni_ptr(slots),
-                                    uni_ptr(base_k), uni_ptr(base_v), lim, c, c2);
+                    fast_tiles_d128(uni(mode), oacc, fragments(0), fragments(1), l_run, -m_run[0], -m_run[1], sl_next, k_rd[0], v_rd[0], ld_koff0,
+                                    ld_voff0, row_in_tile, p0, ring, st, p_end, uni_ptr(slots), uni_ptr(base_k), uni_ptr(base_v), lim[0], lim[1], c, c2);
                 else
-                    fast_tiles_d64(uni(mode), oacc[0], oacc[1], quad(0), l_run, -m_run, sl_next,
-                                   k_rd[0], v_rd[0][0], ld_koff0, ld_voff0, row_in_tile, p0, ring, st, p_end, uni_ptr(slots),
-                                   uni_ptr(base_k), uni_ptr(base_v), lim, c, c2);
+                    fast_tiles_d64(uni(mode), oacc, fragments(0), fragments(1), l_run, -m_run[0], -m_run[1], sl_next, k_rd[0], v_rd[0], ld_koff0,
+                                   ld_voff0, row_in_tile, p0, ring, st, p_end, uni_ptr(slots), uni_ptr(base_k), uni_ptr(base_v), lim[0], lim[1], c, c2);
                 if constexpr (KV8) {
                     if (mode == 6 && st != 0) raw_mask = (1 << UPW) - 1;  // left inside a tile: the next one's rows are still codes
-                    if (st == 0 && mode != 6 && mode >= 4) {
+                    if (st == 0 && (mode == 4 || mode == 5)) {
                         landed8(ring);
                         wg_barrier();
                     }
@@ -1137,43 +1225,41 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         atomicAdd(clk + 1, static_cast<unsigned long long>(wall_clock64() - clk_w0));
     }
     claim_word();
-    // ---- epilogue: lane holds, for block b and register i, head-dim element 32 b + 8 (i / 4) + 4 hh + i % 4 ----
-    const float l_row = row_sum(l_run);
-    if (!row_ok) {
-        // (no row of its own: helps to join the parts, below)
-    } else if (prow < 0) {
-        const float inv = 1.f / l_row;
-        __hip_bfloat16* orow = out + ((e0_row + qi) * Hq + qh) * static_cast<int64_t>(D);
+    // ---- epilogue: lane holds, for block b and register i, head-dim element 16 b + 4 g4 + i of its rows ----
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+    for (int rb = 0; rb < RB; ++rb) {
+        const int row = wave_row0 + 16 * rb + n;
+        const float l_row = row_sum(l_run[rb]);
+        if (!row_ok[rb]) {
+            // (no row of its own: helps to join the parts, below)
+        } else if (prow < 0) {
+            const float inv = 1.f / l_row;
+            __hip_bfloat16* orow = out + ((e0_row[rb] + qi[rb]) * Hq + qh[rb]) * static_cast<int64_t>(D);
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
+            for (int b = 0; b < NB; ++b) {
                 uint2 v;
-                v.x = pack_bf16x2(oacc[b][4 * q4 + 0] * inv, oacc[b][4 * q4 + 1] * inv);
-                v.y = pack_bf16x2(oacc[b][4 * q4 + 2] * inv, oacc[b][4 * q4 + 3] * inv);
-                *reinterpret_cast<uint2*>(orow + 32 * b + 8 * q4 + 4 * hh) = v;
+                v.x = pack_bf16x2(oacc[rb][b][0] * inv, oacc[rb][b][1] * inv);
+                v.y = pack_bf16x2(oacc[rb][b][2] * inv, oacc[rb][b][3] * inv);
+                *reinterpret_cast<uint2*>(orow + 16 * b + 4 * g4) = v;
             }
-    } else {
-        const size_t part_row = static_cast<size_t>(prow) * Hkv + static_cast<size_t>(g) * rows_here + (wave * 32 + n);
-        if constexpr (kDirect) {
-            // (through LDS, the pieces of a row XORed with its number as where narrow tiles join their waves: the stores that go
-            // through to memory then write whole lines; the ring is free, the last tile ended with a barrier)
-            float4* const mine = reinterpret_cast<float4*>(smem) + (wave * 32 + n) * (D / 4);
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-                    mine[(8 * b + 2 * q4 + hh) ^ (n & (D / 4 - 1))] = make_float4(oacc[b][4 * q4], oacc[b][4 * q4 + 1], oacc[b][4 * q4 + 2], oacc[b][4 * q4 + 3]);
-            if (hh == 0) store_through_8(part_ml + 2 * part_row, make_float2(m_run, l_row));
         } else {
-            float* po = part_o + part_row * D;
+            const size_t part_row = static_cast<size_t>(prow) * Hkv + static_cast<size_t>(g) * rows_here + row;
+            const float2 ml = make_float2(m_run[rb], l_row);
+            if constexpr (kDirect) {
+                // (through LDS, the pieces of a row XORed with its number as where narrow tiles join their waves: the stores that go
+                // through to memory then write whole lines; the ring is free, the last tile ended with a barrier)
+                float4* const mine = reinterpret_cast<float4*>(smem) + row * (D / 4);
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+                for (int b = 0; b < NB; ++b)
+                    mine[(4 * b + g4) ^ (row & 31 & (D / 4 - 1))] = make_float4(oacc[rb][b][0], oacc[rb][b][1], oacc[rb][b][2], oacc[rb][b][3]);
+                if (g4 == 0) store_through_8(part_ml + 2 * part_row, ml);
+            } else {
+                float* po = part_o + part_row * D;
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-                    *reinterpret_cast<float4*>(po + 32 * b + 8 * q4 + 4 * hh) = make_float4(
-                        oacc[b][4 * q4 + 0], oacc[b][4 * q4 + 1], oacc[b][4 * q4 + 2], oacc[b][4 * q4 + 3]);
-            if (hh == 0) reinterpret_cast<float2*>(part_ml)[part_row] = make_float2(m_run, l_row);
+                for (int b = 0; b < NB; ++b)
+                    *reinterpret_cast<float4*>(po + 16 * b + 4 * g4) = make_float4(oacc[rb][b][0], oacc[rb][b][1], oacc[rb][b][2], oacc[rb][b][3]);
+                if (g4 == 0) reinterpret_cast<float2*>(part_ml)[part_row] = ml;
+            }
         }
     }
     if constexpr (kDirect) {
@@ -1185,6 +1271,14 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
             store_through_16(po + 4 * static_cast<size_t>(x), reinterpret_cast<const float4*>(smem)[row * (D / 4) + (c ^ (row & 31 & (D / 4 - 1)))]);
         }
         join_parts();
+    }
+    }
+    };
+    if constexpr (kForm == kDirectNarrow) {
+        tile(std::true_type{});
+    } else {
+        if (__builtin_amdgcn_readfirstlane(rec2.y) != 0) tile(std::true_type{});
+        else tile(std::false_type{});
     }
 }
 
@@ -1330,9 +1424,10 @@ static int launch_extend(const ExtendPlan& p, const PlanTables& t, const void* q
                            scale_log2e, static_cast<__hip_bfloat16*>(out), t.hdr, t.item, t.member, t.part_o, t.part_ml, clk, args);
     };
     if (direct.parts > 0) {
-        launch(extend_bf16_kernel<D, KV8, true>, direct);
+        if (direct.tile_rows == kNarrowRows) launch(extend_bf16_kernel<D, KV8, kDirectNarrow>, direct);
+        else launch(extend_bf16_kernel<D, KV8, kDirectWide>, direct);
     } else {
-        launch(extend_bf16_kernel<D, KV8, false>, NoArgs{});
+        launch(extend_bf16_kernel<D, KV8, kList>, NoArgs{});
         // whether any tile was split is known on the device only: otherwise the merge's blocks leave at once
         ProfScope prof(kProfMerge, stream);
         const int64_t most = static_cast<int64_t>(p.chunks_cap) * Hkv;
