@@ -679,6 +679,16 @@ def test_extend_cuts_tiles_or_not_around_a_round_of_workgroups(pa, gpu_device, B
                    kv_more=1000000, cut=B != 16) <= TOL["bf16"]
 
 
+# lists ordered by length: 16 slots per KV head and just more items than one round, six rounds and just beyond, several threads of the
+# planner to a tile and one, cut tiles among them; the last: the planner of more than 256 requests (64 slots, 300 tiles)
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hkv,D,E,longest", [(17, 32, 128, 60, 900), (17, 32, 128, 128, 3000), (60, 32, 64, 40, 700), (96, 32, 64, 40, 700),
+                                               (97, 32, 64, 40, 700), (300, 8, 64, 33, 800)])
+def test_extend_lists_of_mixed_lengths(pa, gpu_device, B, Hkv, D, E, longest):
+    P = [(40, longest // 2, longest, 130, longest // 3)[r % 5] + r % 3 for r in range(B)]
+    assert _extend(pa, gpu_device, "bf16", P, [E - r % 2 for r in range(B)], Hkv, Hkv, D, 16, kv_more=1000000) <= TOL["bf16"]
+
+
 # narrow tiles in a list: uncut only where every round of workgroups is at least half full (8, 4 and 2 KV heads: 64, 128 and 256 slots)
 @pytest.mark.gpu
 @pytest.mark.parametrize("B,Hkv,D,P,cut", [(12, 8, 128, 1000, True), (12, 8, 64, 1000, True), (32, 4, 64, 1000, True), (70, 2, 128, 1000, True),
