@@ -689,6 +689,17 @@ def test_extend_lists_of_mixed_lengths(pa, gpu_device, B, Hkv, D, E, longest):
     assert _extend(pa, gpu_device, "bf16", P, [E - r % 2 for r in range(B)], Hkv, Hkv, D, 16, kv_more=1000000) <= TOL["bf16"]
 
 
+# wide tiles of which one to three waves (of 32 rows) have no rows, or a single row: runs over the pool and over the new tokens
+@pytest.mark.usefixtures("both_forms")
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_kv8"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("E,G", [(64, 1), (65, 1), (96, 1), (97, 1), (193, 1), (12, 4), (40, 4)])
+def test_extend_waves_without_rows(pa, gpu_device, dtype, D, E, G):
+    P = [0, 63, 64, 200, 1090]
+    assert _extend(pa, gpu_device, dtype, P, [E] * len(P), 2 * G, 2, D, 16) <= TOL[dtype]
+
+
 # narrow tiles in a list: uncut only where every round of workgroups is at least half full (8, 4 and 2 KV heads: 64, 128 and 256 slots)
 @pytest.mark.gpu
 @pytest.mark.parametrize("B,Hkv,D,P,cut", [(12, 8, 128, 1000, True), (12, 8, 64, 1000, True), (32, 4, 64, 1000, True), (70, 2, 128, 1000, True),
