@@ -45,10 +45,6 @@ four phases 1.65 (3,130 at 1,900); this order 1.60 (2,970 at 1,860).
 Run:  python gen_fast_run.py  (the build does)."""
 import os
 
-NFR = 8                  # fragment buffers (K and V^T fragments share them: the two kinds are read in different phases)
-PD = 5                   # LDS fragments in flight ahead of their MFMA
-PAIRWAIT = True          # (switch for experiments)
-
 
 def shape(D):
     """Sizes and vector registers for one head dimension.  D = 128 fills 256 registers (two waves on a SIMD), D = 64 keeps to
@@ -125,7 +121,6 @@ class Stream:
         self.lines = []
         self.lds = []      # ids of LDS reads in flight, oldest first
         self.next_id = 0
-        self.tail = []     # code placed behind the loop (rarely taken paths)
 
     def emit(self, text):
         self.lines.append(text)
@@ -522,8 +517,6 @@ def gen(upw, kinds, no_barrier=()):
             tile(st, kind, ring, uid, upw)
             e(f"s_cbranch_scc0 Ldone{end}" if ring == 0 else f"s_cbranch_scc1 Lring0{uid}")
         e(f"s_branch Ldone{end}")
-    for ln in st.tail:
-        e(ln)
     e(f"Lover1{end}:")
     e(f"s_mov_b32 {s(STATUS)}, 1")
     e(f"s_branch Ldone{end}")
