@@ -262,13 +262,9 @@ constexpr int kLdsTail = kLdsMl + 4 * kNarrowRows * 8;
 // bfloat16 tiles in LDS, and everything from there on is the same arithmetic.
 // kForm: a launch with a work list, or one without (DirectArgs, direct_item), of tiles of 128 rows (narrow where a tile has few) or of
 // narrow ones only.  Kernels of their own, so that none of them keeps the registers and code of the others.
-// Waves on a SIMD: two with heads of 128 (256 registers), three with heads of 64 (168); heads of 64 on the fp8 pool, which run the general
-// tile, wait for its loads and gain from a fourth where a list fills the chip (17 documents' questions behind 19,000 keys, 4 | 3 waves: 188 | 220
-// us) although it spills; in a launch without one, of two workgroups on a compute unit at most, three spill nothing (2 requests of 218 to
-// 1,861 new tokens 47.6 | 45.2 us, 11 of 40 to 100 39.3 | 37.7).
 constexpr int kList = 0, kDirectWide = 1, kDirectNarrow = 2;
 template <int D, bool KV8, int kForm>
-__global__ __launch_bounds__(256, D == 64 ? (KV8 && kForm == kList ? 4 : 3) : 2) void extend_bf16_kernel(
+__global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_kernel(
     const __hip_bfloat16* __restrict__ q_ext, const __hip_bfloat16* __restrict__ k_ext,
     const __hip_bfloat16* __restrict__ v_ext, const __hip_bfloat16* __restrict__ pool, const signed char* __restrict__ pool_exp,
     const int32_t* __restrict__ slot_idx, int Hq, int Hkv, int page_size, int page_shift, unsigned page_magic,
