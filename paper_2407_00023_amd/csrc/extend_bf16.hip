@@ -114,6 +114,13 @@ __device__ __forceinline__ float row_sum(float x) {
     return a + b;
 }
 
+// The lane's number, worked out anew: what is derived from it here is held by no register before.
+__device__ __forceinline__ unsigned lane_here() {
+    unsigned x;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
+    return x;
+}
+
 // Workgroup barrier without the memory fence of __syncthreads(): the fence would make the compiler wait
 // for every outstanding global->LDS load, including the ones meant to stay in flight.  Completion of
 // the loads that must be visible is awaited explicitly (wait_vm_all) before the barrier.
@@ -256,7 +263,8 @@ __device__ __forceinline__ bool direct_item(const DirectArgs& a, int item, int G
 // LDS behind the K/V ring: the table of a shared tile's members (two ints each, one int more), two ints per wave, and, from
 // kLdsMl on, what the waves of a narrow tile leave for one another.
 constexpr int kLdsMl = ((2 * kTileRows + 1 + 2 * 4) * 4 + 15) & ~15;
-constexpr int kLdsTail = kLdsMl + 4 * kNarrowRows * 8;
+constexpr int kLdsRows = kLdsMl + 4 * kNarrowRows * 8;
+constexpr int kLdsTail = kLdsRows + kTileRows * 4;
 
 // KV8: the pool holds one-byte codes and row exponents (fp8_rows.h) instead of bfloat16; its rows are decoded into the
 // bfloat16 tiles in LDS, and everything from there on is the same arithmetic.
@@ -341,6 +349,9 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     int* const s_mx0 = s_mseg + (MT + 1);
     int* const s_wave_own = s_mx0 + MT;  // per wave: the key range that holds the extend tokens of its rows' members
     float2* const s_ml = reinterpret_cast<float2*>(smem + kStages * STAGEB + kLdsMl);  // narrow tiles: (maximum, sum) per wave and row
+    // the tile's rows of q and of the output; -1: none.  (Needed again behind the key loop only: kept in LDS, since a register
+    // held across the loop was spilled, and asked back from memory.)
+    int* const s_row = reinterpret_cast<int*>(smem + kStages * STAGEB + kLdsRows);
     // (a launch without a work list has no members: what is needed to join the parts of the tile, read behind the key loop)
     if constexpr (kDirect) {
         if (tid == 0) {
@@ -363,17 +374,15 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         __syncthreads();
     }
     bf16x8 qreg[RB][KS];
-    int qi[RB], qh[RB];          // extend index and query head of the row
-    int64_t e0_row[RB];          // first extend token of the row's request
     int vis_lo[RB], vis_end[RB]; // keys [.., vis_end) are visible to the row; in a shared tile [P, vis_lo) are other members' and hidden
-    bool row_ok[RB];
     const int blk_vis_min = shared ? min(kv_hi, P) : min(kv_hi, P + by_group(row0 + wave_row0) + 1);  // every row of the wave sees keys [.., this)
-    int rho[RB];
+    int rho[RB], e0_row[RB];     // packed row of its request; that one's first extend token
+    bool row_ok[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         rho[rb] = row0 + wave_row0 + 16 * rb + n;
         row_ok[rb] = wave_row0 + 16 * rb + n < rows_here;
-        e0_row[rb] = e0;
+        e0_row[rb] = static_cast<int>(e0);
         vis_lo[rb] = P;
     }
     if (shared) {
@@ -395,10 +404,12 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         const int r = row_ok[rb] ? rho[rb] : 0;
-        qi[rb] = by_group(r);
-        qh[rb] = g * G + (r - qi[rb] * G);
-        vis_end[rb] = min(kv_hi, vis_lo[rb] + qi[rb] + 1);
-        const uint4* qp = reinterpret_cast<const uint4*>(q_ext + ((e0_row[rb] + qi[rb]) * Hq + qh[rb]) * static_cast<int64_t>(D));
+        const int qi = by_group(r), qh = g * G + (r - qi * G);  // extend index and query head
+        vis_end[rb] = min(kv_hi, vis_lo[rb] + qi + 1);
+        // (q and the output, of 64 elements a row and more, both have to fit the memory: fewer than 2^31 rows)
+        const int q_row = (e0_row[rb] + qi) * Hq + qh;
+        s_row[wave_row0 + 16 * rb + n] = row_ok[rb] ? q_row : -1;
+        const uint4* qp = reinterpret_cast<const uint4*>(q_ext + q_row * static_cast<int64_t>(D));
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             uint4 v = make_uint4(0, 0, 0, 0);
@@ -431,13 +442,24 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     const unsigned v_off32 = static_cast<unsigned>(Hkv) * page_size * ROWB;      // from a K row to its V row
     const unsigned char* kx_g = reinterpret_cast<const unsigned char*>(k_ext) + (e0 * Hkv + g) * static_cast<int64_t>(ROWB);
     const unsigned char* vx_g = reinterpret_cast<const unsigned char*>(v_ext) + (e0 * Hkv + g) * static_cast<int64_t>(ROWB);
-    const size_t x_stride = static_cast<size_t>(Hkv) * ROWB;  // bytes from one extend token to the next
+    // (strides within a page and a token fit 31 bits, checked on the host: products with them are one 32 x 32 bit multiplication)
+    const int x_stride = Hkv * ROWB;  // bytes from one extend token to the next
     const unsigned smem_addr = __builtin_amdgcn_readfirstlane(lds_address(smem));
     // Pool slots of rows of the tile after the one in flight.  Heads of 128: of one row of the wave's sixteen, 4 (lane % 4) + lane / 16; the
     // lanes 16 j .. 16 j + 15, which load row 4 u + j in block u, have it from lane 16 j + u.  Heads of 64: of the rows that the lane loads.
     constexpr int NSL = D == 128 ? 1 : UPW;
     int32_t sl_next[NSL];
     const int sl_row = D == 128 ? 4 * (lane & 3) + (lane >> 4) : ld_rowl;
+    // The lane's number where a tile's general loads and slot ids need it: asked for anew in the kernels with assembly tiles, whose
+    // registers that fills.  (What the loads derive from it was kept from tile to tile, spilled, and each reload waited for the loads
+    // issued just before it: 16 questions to long documents on the fp8 pool 281 us a step, so 278.  Heads of 64 on the fp8 pool run
+    // this code for every tile and have the registers: 17 questions to a document 232, so 236.)
+    auto lane_again = [&]() __attribute__((always_inline)) { return kAsm ? static_cast<int>(lane_here() & 63) : lane; };
+    auto slot_row = [&]() __attribute__((always_inline)) {
+        if constexpr (!kAsm) return sl_row;
+        const int l = lane_again();
+        return D == 128 ? 4 * (l & 3) + (l >> 4) : l / CPR;
+    };
     auto slot_of = [&](int u) __attribute__((always_inline)) -> int {  // (all lanes; u known at compile time)
         if constexpr (D == 128)
             return u == 0   ? __builtin_amdgcn_update_dpp(0, sl_next[0], 0x150, 0xf, 0xf, false)
@@ -456,10 +478,11 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         return k;
     };
     auto load_slots = [&](int p0) __attribute__((always_inline)) {
+        const int row = slot_row();
 #pragma unroll
         for (int u = 0; u < NSL; ++u) {
             // positions past the end of the key range repeat the last valid one (see issue)
-            const int p = min(p0 + (wave * UPW + u) * RPB + sl_row, kv_hi - 1);
+            const int p = min(p0 + (wave * UPW + u) * RPB + row, kv_hi - 1);
             sl_next[u] = p < P ? slots[p] : 0;
         }
     };
@@ -486,22 +509,23 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         const unsigned sk = __builtin_amdgcn_readfirstlane(smem_addr + ring * STAGEB);  // wave-uniform (goes to M0)
         if (shared)
             while (cur_member + 1 < n_members && s_mseg[cur_member + 1] <= p0) ++cur_member;
+        const int rowl = lane_again() / CPR;
 #pragma unroll
         for (int u = 0; u < UPW; ++u) {
             const int blk = wave * UPW + u;
-            const int p = min(p0 + blk * RPB + ld_rowl, kv_hi - 1);
+            const int p = min(p0 + blk * RPB + rowl, kv_hi - 1);
             const bool ext = p >= P;
             const unsigned sl = static_cast<unsigned>(min(max(slot_of(u), 0), num_slots - 1));  // never outside the pool
             const unsigned pg = page_shift >= 0 ? sl >> page_shift : __umulhi(sl, page_magic) >> page_mshift;
             const size_t pool_off = static_cast<size_t>(pg) * page_stride +
                                     (sl - pg * static_cast<unsigned>(page_size)) * static_cast<unsigned>(ROWB);
-            int64_t xrow = p - P;  // extend token, counted from the first one of the request of this item
+            int xrow = p - P;  // extend token, counted from the first one of the request of this item
             if (shared && ext) {
                 // the member whose extend tokens hold key p, and that token relative to e0
                 const int k = member_at(cur_member, p);
-                xrow = static_cast<int64_t>(s_mx0[k]) + (p - s_mseg[k]);
+                xrow = s_mx0[k] + (p - s_mseg[k]);
             }
-            const size_t off = ext ? static_cast<size_t>(xrow) * x_stride : pool_off;
+            const size_t off = ext ? static_cast<size_t>(static_cast<int64_t>(xrow) * x_stride) : pool_off;
             const unsigned char* ka = (ext ? kx_g : pool_g) + off + ld_koff(u);
             const unsigned char* va = (ext ? vx_g : pool_g + v_off32) + off + ld_voff(u);
             load_to_lds_16(ka, sk + blk * 1024);
@@ -517,10 +541,10 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     constexpr int EXPB = 256 * 2 * UPW;  // staging bytes per wave: one 32-bit word per lane, load block and tensor
     constexpr int EX_OFF = (kStages * STAGEB + kLdsTail + 255) & ~255;
     const unsigned char* pool8_g = reinterpret_cast<const unsigned char*>(pool) + static_cast<size_t>(g) * page_size * D;
-    const size_t page_stride8 = static_cast<size_t>(2) * Hkv * page_size * D;
-    const size_t v_off8 = static_cast<size_t>(Hkv) * page_size * D;
+    const unsigned page_stride8 = 2u * Hkv * page_size * D;
+    const unsigned v_off8 = static_cast<unsigned>(Hkv) * page_size * D;
     const signed char* exp_g = pool_exp + static_cast<size_t>(g) * page_size;
-    const size_t exp_page = static_cast<size_t>(2) * Hkv * page_size, exp_v = static_cast<size_t>(Hkv) * page_size;
+    const unsigned exp_page = 2u * Hkv * page_size, exp_v = static_cast<unsigned>(Hkv) * page_size;
     int raw_mask = 0;  // bit u: this lane's row of load block u is a pool row (codes to be decoded)
     auto issue8 = [&](int p0, int ring) __attribute__((always_inline)) {
         const unsigned sk = __builtin_amdgcn_readfirstlane(smem_addr + ring * STAGEB);
@@ -528,31 +552,32 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         if (shared)
             while (cur_member + 1 < n_members && s_mseg[cur_member + 1] <= p0) ++cur_member;
         raw_mask = 0;
+        const int l_here = lane_again(), pos = l_here % CPR, rowl = l_here / CPR;
 #pragma unroll
         for (int u = 0; u < UPW; ++u) {
             const int blk = wave * UPW + u;
-            const int p = min(p0 + blk * RPB + ld_rowl, kv_hi - 1);
+            const int p = min(p0 + blk * RPB + rowl, kv_hi - 1);
             const bool ext = p >= P;
             const unsigned sl = static_cast<unsigned>(min(max(slot_of(u), 0), num_slots - 1));  // never outside the pool
             const unsigned pg = page_shift >= 0 ? sl >> page_shift : __umulhi(sl, page_magic) >> page_mshift;
             const unsigned o = sl - pg * static_cast<unsigned>(page_size);
-            int64_t xrow = p - P;
+            int xrow = p - P;
             if (shared && ext) {
                 const int k = member_at(cur_member, p);
-                xrow = static_cast<int64_t>(s_mx0[k]) + (p - s_mseg[k]);
+                xrow = s_mx0[k] + (p - s_mseg[k]);
             }
             if (ext) {
-                const size_t off = static_cast<size_t>(xrow) * x_stride;
+                const size_t off = static_cast<size_t>(static_cast<int64_t>(xrow) * x_stride);
                 load_to_lds_16(kx_g + off + ld_koff(u), sk + blk * 1024);
                 load_to_lds_16(vx_g + off + ld_voff(u), sk + TILEB + blk * 1024);
             } else {
                 raw_mask |= 1 << u;
-                if (ld_pos < CPR / 2) {
-                    const unsigned char* ka = pool8_g + static_cast<size_t>(pg) * page_stride8 + o * static_cast<unsigned>(D) + ld_pos * 16;
+                if (pos < CPR / 2) {
+                    const unsigned char* ka = pool8_g + static_cast<size_t>(pg) * page_stride8 + o * static_cast<unsigned>(D) + pos * 16;
                     load_to_lds_16(ka, sk + blk * 1024);
                     load_to_lds_16(ka + v_off8, sk + TILEB + blk * 1024);
                 }
-                if (D == 64 && ld_pos == 0) {
+                if (D == 64 && pos == 0) {
                     const signed char* ea = exp_g + static_cast<size_t>(pg) * exp_page + o;
                     load_to_lds_1(ea, ex + (2 * u) * 256);
                     load_to_lds_1(ea + exp_v, ex + (2 * u + 1) * 256);
@@ -560,7 +585,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
             }
         }
         if constexpr (D == 128) {  // (lane 16 j + u those of row 4 u + j, as the assembly does)
-            if (ld_pos < UPW && min(p0 + wave * UPW * RPB + sl_row, kv_hi - 1) < P) {
+            if (pos < UPW && min(p0 + wave * UPW * RPB + 4 * (l_here & 3) + (l_here >> 4), kv_hi - 1) < P) {
                 const unsigned sl = static_cast<unsigned>(min(max(sl_next[0], 0), num_slots - 1));
                 const unsigned pg = page_shift >= 0 ? sl >> page_shift : __umulhi(sl, page_magic) >> page_mshift;
                 const signed char* ea = exp_g + static_cast<size_t>(pg) * exp_page + (sl - pg * static_cast<unsigned>(page_size));
@@ -573,22 +598,23 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     auto landed8 = [&](int ring) __attribute__((always_inline)) {
         unsigned char* const sk = smem + ring * STAGEB;
         const int* const ex = reinterpret_cast<const int*>(smem + EX_OFF + wave * EXPB);
+        const int l_here = lane_again();
         uint2 kraw[UPW], vraw[UPW];
         int ke[UPW], ve[UPW];
 #pragma unroll
         for (int u = 0; u < UPW; ++u) {
             if ((raw_mask >> u) & 1) {
-                const unsigned char* row = sk + (wave * UPW + u) * 1024 + ld_rowl * ROWB;
+                const unsigned char* row = sk + (wave * UPW + u) * 1024 + l_here / CPR * ROWB;
                 kraw[u] = *reinterpret_cast<const uint2*>(row + (ld_koff(u) >> 1));
                 vraw[u] = *reinterpret_cast<const uint2*>(row + TILEB + (ld_voff(u) >> 1));
-                ke[u] = D == 128 ? ex[(lane & ~15) + u] : ex[(2 * u) * 64 + (lane & ~(CPR - 1))];
-                ve[u] = D == 128 ? ex[64 + (lane & ~15) + u] : ex[(2 * u + 1) * 64 + (lane & ~(CPR - 1))];
+                ke[u] = D == 128 ? ex[(l_here & ~15) + u] : ex[(2 * u) * 64 + (l_here & ~(CPR - 1))];
+                ve[u] = D == 128 ? ex[64 + (l_here & ~15) + u] : ex[(2 * u + 1) * 64 + (l_here & ~(CPR - 1))];
             }
         }
 #pragma unroll
         for (int u = 0; u < UPW; ++u) {
             if ((raw_mask >> u) & 1) {
-                unsigned char* dst = sk + (wave * UPW + u) * 1024 + lane * 16;
+                unsigned char* dst = sk + (wave * UPW + u) * 1024 + l_here * 16;
                 const float ks = fp8_scale(static_cast<int>(static_cast<signed char>(ke[u] & 0xFF)));
                 const float vs = fp8_scale(static_cast<int>(static_cast<signed char>(ve[u] & 0xFF)));
                 const uint2 ka = fp8_decode4(kraw[u].x, ks), kb = fp8_decode4(kraw[u].y, ks);
@@ -928,17 +954,17 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                 const unsigned slot = static_cast<unsigned>(min(max(sl[u], 0), num_slots - 1));  // never outside the pool
                 const unsigned pg = page_shift >= 0 ? slot >> page_shift : __umulhi(slot, page_magic) >> page_mshift;
                 const unsigned o = slot - pg * static_cast<unsigned>(page_size);
-                int64_t xrow = pr - P;
+                int xrow = pr - P;
                 if (shared && ext) {
                     const int k = member_at(0, pr);
-                    xrow = static_cast<int64_t>(s_mx0[k]) + (pr - s_mseg[k]);
+                    xrow = s_mx0[k] + (pr - s_mseg[k]);
                 }
                 if constexpr (KV8) {
                     const signed char* ea = exp_g + static_cast<size_t>(pg) * exp_page + o;  // (slot 0 where the row is no pool row)
                     ke[u] = ea[0];
                     ve[u] = ea[exp_v];
                     if (ext) {
-                        const size_t off = static_cast<size_t>(xrow) * x_stride;
+                        const size_t off = static_cast<size_t>(static_cast<int64_t>(xrow) * x_stride);
                         load_to_lds_16(kx_g + off + koff(u), wbase + u * 1024);
                         load_to_lds_16(vx_g + off + voff(u), wbase + VOFF + u * 1024);
                     } else {
@@ -950,7 +976,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                         }
                     }
                 } else {
-                    const size_t off = ext ? static_cast<size_t>(xrow) * x_stride
+                    const size_t off = ext ? static_cast<size_t>(static_cast<int64_t>(xrow) * x_stride)
                                            : static_cast<size_t>(pg) * page_stride + o * static_cast<unsigned>(ROWB);
                     load_to_lds_16((ext ? kx_g : pool_g) + off + koff(u), wbase + u * 1024);
                     load_to_lds_16((ext ? vx_g : pool_g + v_off32) + off + voff(u), wbase + VOFF + u * 1024);
@@ -993,20 +1019,17 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         const float l_row[RB] = {row_sum(l_run[0]), row_sum(l_run[1])};
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            if (!row_ok[rb]) continue;
             const int row = 16 * rb + n;
+            if (row >= rows_here) continue;
             float4* mine = reinterpret_cast<float4*>(smem + wave * WB) + row * V4;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
                 mine[(4 * b + g4) ^ (row & (V4 - 1))] = make_float4(oacc[rb][b][0], oacc[rb][b][1], oacc[rb][b][2], oacc[rb][b][3]);
             if (g4 == 0) s_ml[wave * kNarrowRows + row] = make_float2(m_run[rb], l_row[rb]);
         }
-        // (a row of the output: fewer than 2^31 of 64 elements and more fit the memory)
-        const int my_out[RB] = {(static_cast<int>(e0_row[0]) + qi[0]) * Hq + qh[0], (static_cast<int>(e0_row[1]) + qi[1]) * Hq + qh[1]};
         const int jr = tid >> 3, sub = tid & 7;  // eight threads per row
-        const int out_a = __shfl(my_out[0], jr & 15), out_b = __shfl(my_out[1], jr & 15);
-        const int64_t out_row = jr < 16 ? out_a : out_b;
         __syncthreads();
+        const int64_t out_row = s_row[jr];
         if (jr < rows_here) {
         float2 ml[NW];
         float m = -INFINITY, l = 0.f;
@@ -1187,7 +1210,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                 p0 = uni(p0);
                 ring = uni(ring);
                 p_end = uni(p_end);
-                const int row_in_tile = wave * (UPW * RPB) + sl_row;
+                const int row_in_tile = wave * (UPW * RPB) + slot_row();
                 const void* base_k = kind == 2 ? static_cast<const void*>(kx_g) : is8 ? static_cast<const void*>(pool8_g) : static_cast<const void*>(pool_g);
                 const void* base_v = kind == 2 ? static_cast<const void*>(vx_g) : is8 ? static_cast<const void*>(pool8_g + v_off8) : static_cast<const void*>(pool_g + v_off32);
                 const int lim[RB] = {vis_end[0] - p0 - 4 * g4, vis_end[1] - p0 - 4 * g4};
@@ -1230,11 +1253,12 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
     for (int rb = 0; rb < RB; ++rb) {
         const int row = wave_row0 + 16 * rb + n;
         const float l_row = row_sum(l_run[rb]);
-        if (!row_ok[rb]) {
+        const int64_t q_row = s_row[row];
+        if (q_row < 0) {
             // (no row of its own: helps to join the parts, below)
         } else if (prow < 0) {
             const float inv = 1.f / l_row;
-            __hip_bfloat16* orow = out + ((e0_row[rb] + qi[rb]) * Hq + qh[rb]) * static_cast<int64_t>(D);
+            __hip_bfloat16* orow = out + q_row * D;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 uint2 v;
