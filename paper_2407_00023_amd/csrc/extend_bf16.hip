@@ -65,6 +65,7 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kStages = 2;               // LDS ring: one tile being read, one being filled
 constexpr float kRescaleThreshold = 8.f; // log2 units: the running maximum may lag the true one by this much
+constexpr float kLargest = 3.4028234663852886e38f;  // the largest finite float
 // The steady-state tiles (fast_run_*.inc) never move the running maximum: a run is left, for the general tile, when
 // the probabilities of one lane and key block sum to more than 2^40.  The exponent range of fp32 and bf16 leaves that
 // much room: a probability of 2^40 is as precise as one of 1, and what then underflows next to it is < 2^-100 of it.
@@ -164,23 +165,24 @@ __device__ __forceinline__ unsigned lds_address(const void* p) {
 // The K fragments of a block of 32 keys, all asked for before the first product, so that their LDS round trips overlap
 // instead of following one another (the compiler, short of registers, reads one fragment at a time into the same four
 // registers).  The wait stands in the same statement: no register of a read in flight is ever the compiler's to use.
-// kf[2 s + kb]: k-slice s of the keys 16 kb .. 16 kb + 15, which lie half_off bytes apart.
-template <int KS>
-__device__ __forceinline__ void read_k_block(bf16x8 (&kf)[2 * KS], const unsigned (&at)[KS], unsigned off, unsigned half_off) {
+// kf[2 s + kb]: k-slice s of the keys 16 kb .. 16 kb + 15, which lie kHalf bytes apart.
+template <int kHalf, int KS>
+__device__ __forceinline__ void read_k_block(bf16x8 (&kf)[2 * KS], const unsigned (&at)[KS], unsigned off) {
     static_assert(KS == 4 || KS == 2, "head dimension 128 or 64");
     if constexpr (KS == 4)
         asm volatile(
-            "ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
-            "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\ts_waitcnt lgkmcnt(0)"
+            "ds_read_b128 %0, %8\n\tds_read_b128 %1, %8 offset:%12\n\tds_read_b128 %2, %9\n\tds_read_b128 %3, %9 offset:%12\n\t"
+            "ds_read_b128 %4, %10\n\tds_read_b128 %5, %10 offset:%12\n\tds_read_b128 %6, %11\n\tds_read_b128 %7, %11 offset:%12\n\t"
+            "s_waitcnt lgkmcnt(0)"
             : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3]), "=&v"(kf[4]), "=&v"(kf[5]), "=&v"(kf[6]), "=&v"(kf[7])
-            : "v"(at[0] + off), "v"(at[0] + off + half_off), "v"(at[1] + off), "v"(at[1] + off + half_off), "v"(at[2] + off),
-              "v"(at[2] + off + half_off), "v"(at[3] + off), "v"(at[3] + off + half_off)
+            : "v"(at[0] + off), "v"(at[1] + off), "v"(at[2] + off), "v"(at[3] + off), "n"(kHalf)
             : "memory");
     else
         asm volatile(
-            "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+            "ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:%6\n\tds_read_b128 %2, %5\n\tds_read_b128 %3, %5 offset:%6\n\t"
+            "s_waitcnt lgkmcnt(0)"
             : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3])
-            : "v"(at[0] + off), "v"(at[0] + off + half_off), "v"(at[1] + off), "v"(at[1] + off + half_off)
+            : "v"(at[0] + off), "v"(at[1] + off), "n"(kHalf)
             : "memory");
 }
 
@@ -670,7 +672,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         f32x4 sacc[2][RB];  // [half of the block's keys][row block]
         // S^T = K Q^T
         bf16x8 kf[2 * KS];
-        read_k_block<KS>(kf, k_rd, off, 16 * ROWB);
+        read_k_block<16 * ROWB>(kf, k_rd, off);
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
@@ -709,22 +711,27 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                 }
             }
         }
-        // row maxima of the block, in every lane of the row
-        float m_blk[RB];
+        // largest score of the block that this lane holds, by row
+        float mx[RB], neg_m[RB];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            float mx = fmaxf(sacc[0][rb][0], sacc[1][rb][0]);
+            mx[rb] = sacc[0][rb][0];
 #pragma unroll
-            for (int i = 1; i < 4; ++i) mx = fmaxf(mx, fmaxf(sacc[0][rb][i], sacc[1][rb][i]));
-            m_blk[rb] = row_max(mx) * scale_log2e;  // log2 domain (scale > 0)
+            for (int i = 1; i < 8; ++i) mx[rb] = fmaxf(mx[rb], sacc[i / 4][rb][i % 4]);
+            // (no maximum yet: any finite score exceeds it, and of hidden keys, -inf, the probability is 0 whatever stands here)
+            neg_m[rb] = fminf(-m_run[rb], kLargest);
         }
         // The running maximum may lag the true one by kRescaleThreshold (probabilities then reach 2^threshold,
         // harmless in bf16/fp32).  If some row of the wave outgrew it by more, raise it and rescale what was
-        // accumulated so far.  With a stable maximum this happens for the first block only.
-        if (__any(m_blk[0] > m_run[0] + kRescaleThreshold || m_blk[1] > m_run[1] + kRescaleThreshold)) {
+        // accumulated so far.  With a stable maximum this happens for the first block only, so only there are the lanes of a row
+        // brought together.  (What bounds heads of 64 on the fp8 pool, which run this code for every tile with four waves a SIMD, is
+        // its vector instructions: 78 a block, exponentials aside, with the maxima of all rows, the dot products and one address per fragment,
+        // now 46.)
+        const float over = fmaxf(fmaf(mx[0], scale_log2e, neg_m[0]), fmaf(mx[1], scale_log2e, neg_m[1]));  // log2 domain (scale > 0)
+        if (__builtin_amdgcn_ballot_w64(over > kRescaleThreshold) != 0) {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
-                const float m_new = fmaxf(m_run[rb], m_blk[rb]);
+                const float m_new = fmaxf(m_run[rb], row_max(mx[rb]) * scale_log2e);
                 const float alpha = __builtin_amdgcn_exp2f(m_run[rb] - ((m_new == -INFINITY) ? 0.f : m_new));
                 l_run[rb] *= alpha;
 #pragma unroll
@@ -732,26 +739,36 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
 #pragma unroll
                     for (int i = 0; i < 4; ++i) oacc[rb][b][i] *= alpha;
                 m_run[rb] = m_new;
+                neg_m[rb] = fminf(-m_new, kLargest);
             }
         }
         // probabilities, packed to bf16 pairs (the B operand of the second product: its k-slots of lane group g4 are the keys
         // 4 g4 .. 4 g4 + 3 of the block's halves, and so are those of the V^T fragments); the row sum takes the
         // ROUNDED probabilities, the values the numerator uses
+        // ... wide tiles that have no others (heads of 64 on the fp8 pool): by a product with a row of ones, two matrix instructions in
+        // place of twelve vector ones.  (In narrow tiles, which wait for memory, it costs registers: 103 decode requests 57.0 -> 58.4 us.)
+        constexpr bool kSumProduct = !kAsm && !narrow;
         bf16x8 pop[RB];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const float neg_m = (m_run[rb] == -INFINITY) ? 0.f : -m_run[rb];
             uint32_t pb[4];
             float acc = 0.f;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const float a = __builtin_amdgcn_exp2f(fmaf(sacc[k / 2][rb][2 * (k % 2)], scale_log2e, neg_m));
-                const float b = __builtin_amdgcn_exp2f(fmaf(sacc[k / 2][rb][2 * (k % 2) + 1], scale_log2e, neg_m));
+                const float a = __builtin_amdgcn_exp2f(fmaf(sacc[k / 2][rb][2 * (k % 2)], scale_log2e, neg_m[rb]));
+                const float b = __builtin_amdgcn_exp2f(fmaf(sacc[k / 2][rb][2 * (k % 2) + 1], scale_log2e, neg_m[rb]));
                 pb[k] = pack_bf16x2(a, b);
-                acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, pb[k]), ones, acc, false);
+                if constexpr (!kSumProduct) acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, pb[k]), ones, acc, false);
             }
             pop[rb] = __builtin_bit_cast(bf16x8, make_uint4(pb[0], pb[1], pb[2], pb[3]));
-            l_run[rb] += acc;
+            if constexpr (!kSumProduct) l_run[rb] += acc;
+        }
+        f32x4 sums[RB];
+        if constexpr (kSumProduct) {
+            const uint32_t one2 = n == 0 ? 0x3f803f80u : 0u;
+            const bf16x8 one = __builtin_bit_cast(bf16x8, make_uint4(one2, one2, one2, one2));
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) sums[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(one, pop[rb], zero4, 0, 0, 0);
         }
         // O^T += V^T P^T
 #pragma unroll
@@ -763,6 +780,10 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
             const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(frag[0], frag[1], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) oacc[rb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pop[rb], oacc[rb][b], 0, 0, 0);
+        }
+        if constexpr (kSumProduct) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) l_run[rb] += sums[rb][0];
         }
     };
 
@@ -1126,7 +1147,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
         if ((fast_ok || KV8) && (smem_addr & 255u) == 0 && wave_on && kv_lo <= P + wave_i_last && kv_lo + 32 <= blk_vis_min && kv_lo + 32 <= kv_hi) {
             const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
             bf16x8 kf[2 * KS];
-            read_k_block<KS>(kf, k_rd, 0, 16 * ROWB);
+            read_k_block<16 * ROWB>(kf, k_rd, 0);
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
                 f32x4 s0 = zero4, s1 = zero4;

@@ -209,10 +209,11 @@ def test_captured_matches_beside_eager_ones(pa, gpu_device):
             check(small, pls[k], sis[k])
 
 
-def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None, kv_more=0, cut=None, direct=None):
+def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None, kv_more=0, cut=None, direct=None, louder_from=None):
     """Largest error against the oracle for requests with P[r] cached tokens, the first `common` of them the same for all.
     tiles: how many row tiles the work list has to hold; kv_more: how many more keys than it has the call is told of (1,000,000: it
-    builds a list whatever the batch); cut, direct: whether any tile has to be cut into parts, and the call to go without a list."""
+    builds a list whatever the batch); cut, direct: whether any tile has to be cut into parts, and the call to go without a list;
+    louder_from: the key of every request from which on keys are 48 times as large (no common tokens then)."""
     import oracle
     rng = np.random.default_rng(seed)
     P, E = np.asarray(P, np.int32), np.asarray(E, np.int32)
@@ -239,6 +240,13 @@ def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None
     mk = lambda s, n, h: W._normal(s, n * h * D, el).reshape(n, h, D)
     T = int(eo[-1])
     q, k, v, pk, pv = mk(ss[0], T, Hq), mk(ss[1], T, Hkv), mk(ss[2], T, Hkv), mk(ss[3], len(backed), Hkv), mk(ss[4], len(backed), Hkv)
+    if louder_from is not None:
+        assert common == 0 and el == "bf16"
+        fk, fpk = W.bf16_bits_to_f32(k).copy(), W.bf16_bits_to_f32(pk).copy()
+        for r in range(B):
+            fk[eo[r] + max(louder_from - P[r], 0):eo[r + 1]] *= 48
+            fpk[np.searchsorted(backed, slots[r][louder_from:])] *= 48
+        k, pk = W.f32_to_bf16_bits(fk), W.f32_to_bf16_bits(fpk)
     tdt, kv8 = (torch.float32 if dtype == "f32" else torch.bfloat16), dtype == "bf16_kv8"
     kw = dict(page_size=page, num_slots=nslots, kv8=kv8)
     pool = torch.zeros(pa.kv_pool_bytes(nslots, Hkv, D, tdt, page, kv8), dtype=torch.uint8, device=dev)
@@ -698,6 +706,18 @@ def test_extend_lists_of_mixed_lengths(pa, gpu_device, B, Hkv, D, E, longest):
 def test_extend_waves_without_rows(pa, gpu_device, dtype, D, E, G):
     P = [0, 63, 64, 200, 1090]
     assert _extend(pa, gpu_device, dtype, P, [E] * len(P), 2 * G, 2, D, 16) <= TOL[dtype]
+
+
+# scores that outgrow the running maximum by far more than 2^40 (in probability) from one key on, in the first or the second block of a
+# tile: a run over the pool, or over the new tokens, is left there (the fp8 pool: with the next tile's rows still codes), single tiles on the diagonal too
+@pytest.mark.usefixtures("both_forms")
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_kv8"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("at", [64 * 9 + 5, 64 * 9 + 37])
+@pytest.mark.parametrize("P,E", [([1300, 1257], [150, 70]), ([320, 300], [700, 450])], ids=["pool", "new tokens"])
+def test_extend_scores_that_outgrow_the_running_maximum(pa, gpu_device, dtype, D, at, P, E):
+    assert _extend(pa, gpu_device, dtype, P, E, 8, 2, D, 16, louder_from=at) <= TOL[dtype]
 
 
 # narrow tiles in a list: uncut only where every round of workgroups is at least half full (8, 4 and 2 KV heads: 64, 128 and 256 slots)
