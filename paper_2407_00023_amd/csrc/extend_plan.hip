@@ -42,7 +42,10 @@ constexpr int kMinChunkTiles = 16;       // never split below this many key tile
 constexpr int kMinChunkCommon = 8;       // ... unless the tile leaves partial results anyway (or is narrow: kMinChunkNarrow)
 constexpr int kItemOverhead = 4;         // fixed cost of a work item, in key tiles (its prologue and epilogue)
 constexpr int kItemFixed = 6;            // ... as the time of a workgroup goes: 9 us, a key tile 1.6
-constexpr int kLengthRounds = 6;         // lists of up to this many rounds of workgroups are ordered by length (more: 41 rounds, nothing)
+constexpr int kLengthRounds = 6;         // lists of up to this many rounds of workgroups are ordered by length (7 to 41: nothing either way):
+constexpr float kLengthFirst = 1.1f;     // first the items longer than so many times the average, last those shorter than so many
+constexpr float kLengthLast = 0.75f;
+constexpr float kLengthNarrow = 0.7f;    // what a key tile of a narrow item counts there
 constexpr int kMergeCost = 4;            // what partial results cost a launch, in key tiles
 constexpr int kMaxParts = 64;            // parts of one tile at most
 constexpr int kSortMax = 1024;           // ... and up to this many are ordered
@@ -401,16 +404,21 @@ __device__ __forceinline__ void emit_items(const PlanArgs& a, int n_rows, int n_
         __syncthreads();
     }
     // ---- where a tile's items stand: workgroups start in the list's order, and what starts last alone decides when the launch ends.
-    // In up to kLengthRounds rounds of them the longest come first (half as long again as the average; a tenth; the others), so that the
-    // last to start are short.  Attention of 190 tiles for 64 slots, 24 to 98 key tiles long, in order | by length: 272 | 244 us; 202 tiles
-    // of 44 to 132 408 | 403; 85 items of decode requests 64.2 | 62.4.  Longer lists stay in order: their last items are a small part,
-    // and requests with a common prefix, which find each other's keys in the L2, stay together.  Lists of one length skip the scan
-    // (1 us), and so do those of more tiles than the planner has threads, whose tiles would be described once more (2 us). ----
+    // In up to kLengthRounds rounds of them the items of more than the average length come first, the short ones last.  Longer lists stay
+    // in order: their last items are a small part.  So do those of more tiles than the planner has threads, whose tiles would be described
+    // once more (2 us).  Only three classes, because requests with a common prefix find each other's keys in the L2 while they run together.
+    // The average is that of the planner's costs, where a narrow item counts half its key tiles, as where it has the memory to itself;
+    // beside wide ones it takes nearly all of their time, and in the classes counts more.  (With half there, too, three whole new problems
+    // beside 61 requests of a few new tokens, 190 tiles of 24 to 98 key tiles for 64 slots, gain nothing: 315.6.)
+    // Steps in us, in order | so: these 313.6 | 285.8, a video of 8,192 keys 489.2 | 484.8, 256 decode requests 109.1 | 107.5, 80 of 500 to
+    // 6,200 keys 221.4 | 217.7, 6 documents of 2,000 to 16,000 keys 212.1 | 204.6, 4 of 4,000 to 20,000 213.6 | 220.4, on the fp8 pool
+    // 258.3 | 255.4.  572 random lists: 1.007 times as fast in the mean, with new problems 1.022, documents of unlike length 1.003.  Lists of
+    // one length gain nothing and pay the scan (0.4 us); asking for the longest item first costs all others a reduction. ----
     const float average = static_cast<float>(W - n_all * kItemOverhead) / static_cast<float>(max(total[0], 1));
-    const bool by_length = per == 1 && total[0] > a.slots && total[0] <= kLengthRounds * a.slots && static_cast<float>(longest - kItemOverhead) >= 1.1f * average;
+    const bool by_length = per == 1 && total[0] > a.resident && total[0] <= kLengthRounds * a.resident;
     auto class_of = [&](const TileDesc& d, int n) {
-        const float len = static_cast<float>(key_tiles(d)), scale = average * static_cast<float>(n);
-        return len >= 1.5f * scale ? 0 : len >= 1.1f * scale ? 1 : 2;
+        const float len = static_cast<float>(key_tiles(d)) * (narrow(d) ? kLengthNarrow : 1.f), scale = average * static_cast<float>(n);
+        return len >= kLengthFirst * scale ? 0 : len >= kLengthLast * scale ? 1 : 2;
     };
     int c[2] = {0, 0}, c_total[2] = {0, 0};
     if (by_length) {

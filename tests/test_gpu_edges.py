@@ -209,11 +209,21 @@ def test_captured_matches_beside_eager_ones(pa, gpu_device):
             check(small, pls[k], sis[k])
 
 
-def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None, kv_more=0, cut=None, direct=None, louder_from=None):
+def _items(ws, B, rows, D):
+    """The item records of a work list, 12 ints each: behind the header, the tile table and the member table (extend_plan.h)."""
+    up = lambda n: -(-n // 256) * 256
+    own = min(rows, B * (48 if D == 128 else 64)) // 32 + B if 1 < B <= 256 else 0
+    at = 256 + up(8 * (-(-rows // 128) + B + own)) + (up(32 * B) if B <= 256 else 0)
+    return ws[at:at + 48 * ws[4:8].view(torch.int32).item()].view(torch.int32).reshape(-1, 12).tolist()
+
+
+def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None, kv_more=0, cut=None, direct=None, louder_from=None,
+            records=None):
     """Largest error against the oracle for requests with P[r] cached tokens, the first `common` of them the same for all.
     tiles: how many row tiles the work list has to hold; kv_more: how many more keys than it has the call is told of (1,000,000: it
     builds a list whatever the batch); cut, direct: whether any tile has to be cut into parts, and the call to go without a list;
-    louder_from: the key of every request from which on keys are 48 times as large (no common tokens then)."""
+    louder_from: the key of every request from which on keys are 48 times as large (no common tokens then); records: a list that gets
+    the item records of the work list."""
     import oracle
     rng = np.random.default_rng(seed)
     P, E = np.asarray(P, np.int32), np.asarray(E, np.int32)
@@ -262,6 +272,8 @@ def _extend(pa, dev, dtype, P, E, Hq, Hkv, D, page, common=0, seed=0, tiles=None
         assert ws[12:16].view(torch.int32).item() == 0  # (the work list fitted)
         assert tiles is None or ws[:4].view(torch.int32).item() == tiles
         assert direct is None or (ws[20:24].view(torch.int32).item() > 0) == direct
+        if records is not None:
+            records.extend(_items(ws, B, T * (Hq // Hkv), D))
         assert cut is None or (ws[4:8].view(torch.int32).item() > ws[:4].view(torch.int32).item()) == cut
     opk, opv = oracle.new_pool(nslots, Hkv, D, dtype)
     oracle.append_kv(opk, opv, backed, pk, pv, dtype)
@@ -695,6 +707,34 @@ def test_extend_cuts_tiles_or_not_around_a_round_of_workgroups(pa, gpu_device, B
 def test_extend_lists_of_mixed_lengths(pa, gpu_device, B, Hkv, D, E, longest):
     P = [(40, longest // 2, longest, 130, longest // 3)[r % 5] + r % 3 for r in range(B)]
     assert _extend(pa, gpu_device, "bf16", P, [E - r % 2 for r in range(B)], Hkv, Hkv, D, 16, kv_more=1000000) <= TOL["bf16"]
+
+
+# The order of a list's items.  By length: new prompts (long and short tiles in each), narrow tiles only, narrow ones beside wide
+# ones.  As the requests stand: one length; one round of workgroups (heads of 64: 24, three on a compute unit); more than six rounds.
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,P,E,by_length", [
+    (128, [0] * 4, [1500] * 4, True), (64, [0] * 5, [1100] * 5, True), (128, [300 + 977 * r % 2700 for r in range(40)], [4] * 40, True),
+    (128, [200 + 331 * r % 1500 for r in range(24)] + [100] * 2, [3] * 24 + [1400, 900], True),
+    (128, [1000] * 40, [60] * 40, False), (64, [0] * 2, [1400] * 2, False), (128, [0] * 9, [1500] * 9, False)])
+def test_extend_order_of_a_list(pa, gpu_device, D, P, E, by_length):
+    records = []
+    assert _extend(pa, gpu_device, "bf16", P, E, 32, 32, D, 16, kv_more=1000000, records=records) <= TOL["bf16"]
+    tiles = {}  # (request, first row): key tiles, items, narrow
+    for r, row0, lo, hi, *rest in records:
+        k, n, _ = tiles.get((r, row0), (0, 0, 0))
+        tiles[r, row0] = k + -(-(hi - lo) // 64), n + 1, rest[5]
+    average = sum((k + 1) // 2 if narrow else k for k, _, narrow in tiles.values()) / len(records)
+    if by_length:
+        ranks = []
+        for r, row0, *_ in records:
+            k, n, narrow = tiles[r, row0]
+            length = k / n * (0.7 if narrow else 1.0) / average
+            if min(abs(length - 1.1), abs(length - 0.75)) > 1e-3:  # (not as good as on a bound)
+                ranks.append(0 if length > 1.1 else 1 if length > 0.75 else 2)
+        assert ranks == sorted(ranks) and {0, 2} <= set(ranks)
+    else:
+        seen = [r for i, (r, *_) in enumerate(records) if i == 0 or records[i - 1][0] != r]
+        assert len(seen) == len(set(seen)) == len(P)
 
 
 # wide tiles of which one to three waves (of 32 rows) have no rows, or a single row: runs over the pool and over the new tokens
