@@ -66,8 +66,8 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 constexpr int kStages = 2;               // LDS ring: one tile being read, one being filled
 constexpr float kRescaleThreshold = 8.f; // log2 units: the running maximum may lag the true one by this much
 constexpr float kLargest = 3.4028234663852886e38f;  // the largest finite float
-// The steady-state tiles (fast_run_*.inc) never move the running maximum: a run is left, for the general tile, when
-// the probabilities of one lane and key block sum to more than 2^40.  The exponent range of fp32 and bf16 leaves that
+// The steady-state tiles (fast_run.inc) never move the running maximum: a run is left, for the general tile, when
+// the probabilities of one row and key block sum to more than 2^40.  The exponent range of fp32 and bf16 leaves that
 // much room: a probability of 2^40 is as precise as one of 1, and what then underflows next to it is < 2^-100 of it.
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {

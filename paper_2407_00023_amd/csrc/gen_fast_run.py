@@ -32,10 +32,10 @@ four cycles (an exponential two as well): two vector instructions behind every M
 the schedule is written for few of them, spread evenly: a row's place is worked out by one lane and broadcast to the others that
 fetch it, row sums are products with ones (dot products wait for the matrix pipe to run dry, and the pipe for them).
 LDS reads are awaited two fragments at a time by counting them (they return in order).  Wait states the hardware does not
-interlock are written out, other work standing in them where there is any: the last MFMA of a score block and the
-first ALU read of it (seven slots), a transcendental and a use of its result (one), a write of M0 and the load that uses it (one), a
-vector write of a register and a broadcast from it (two).  The
-loop is written out for both ring slots, so that every LDS offset is an immediate and no address register changes
+interlock are written out, other work standing in them where there is any: an MFMA and an ALU read of its result (eight slots of four
+cycles), a transcendental and a use of its result (one instruction), a write of M0 and the load that uses it (one), a
+vector write of a register and a broadcast from it (two), a comparison and a selection by it (two); check_waits() holds the tiles to them.
+The loop is written out for both ring slots, so that every LDS offset is an immediate and no address register changes
 between tiles.
 
 Measured, the loop alone with rows from the L2s, all of the chip, per 256 rows and 64 keys on a compute unit: phases of 32x32x16 MFMAs
@@ -44,6 +44,7 @@ four phases 1.65 (3,130 at 1,900); this order 1.60 (2,970 at 1,860).
 
 Run:  python gen_fast_run.py  (the build does)."""
 import os
+import re
 
 
 def shape(D):
@@ -98,7 +99,7 @@ C_128, C_192, C_P, C_SCALE = range(C2, C2 + 4)
 C_EXPPAGE, C_EXPV = C_XSTRIDE, C_EXTMAX   # bytes from one page's row exponents to the next page's; from a K row's exponent to its V row's
 EXP_BASE = C_128                          # s[60:61]: the row exponents of this KV head
 EXST = 51                                 # LDS address of this wave's staging area for row exponents
-LIMIT = "0x53800000"   # 2^40: a lane's probabilities of one key block may sum to this much before the run is left
+LIMIT = "0x53800000"   # 2^40: a row's probabilities of one key block may sum to this much before the run is left
 ONES = "0x3f803f80"    # bf16 (1, 1)
 
 
@@ -140,7 +141,7 @@ class Stream:
         self.lds = self.lds[len(self.lds) - after:] if after else []
 
 
-def tile(st, kind, ring, uid, upw):
+def tile(st, kind, ring, upw):
     """One tile that sits in ring slot `ring`; the next tile is loaded into the other slot.  st.lds: the reads of its first
     fragments, under way already (not for the kinds in st.no_prefetch)."""
     e = st.emit
@@ -449,6 +450,52 @@ KINDS = ["pool", "ext", "pool64", "plain", "masked", "pool8", "pool_idle", "ext_
 MODE = 50                                                # scalar register of the mode operand
 
 
+def registers(operand):
+    """{"v7", ...} for v7, v[4:7], s[72:73]; vcc; nothing for anything else."""
+    m = re.fullmatch(r"-?([vs])(?:(\d+)|\[(\d+):(\d+)\])", operand)
+    if not m:
+        return {operand} if operand in ("vcc", "m0") else set()
+    lo, hi = (int(m[2]), int(m[2])) if m[2] else (int(m[3]), int(m[4]))
+    return {f"{m[1]}{i}" for i in range(lo, hi + 1)}
+
+
+def check_waits(kind, lines):
+    """Tiles of a kind in a row: nothing reads a result before it may (the wait states above).  Time in cycles, four an instruction; an
+    MFMA waits for the pipe, which the one before holds for sixteen; what other waves do only adds to it."""
+    now, pipe, n = 0, 0, 0
+    made = {}   # register -> (instruction that wrote it, its number, when it was issued)
+    for text in lines:
+        op, _, rest = text.partition(" ")
+        args = [registers(a.split()[0]) for a in rest.split(", ") if a]
+        if op in ("s_waitcnt", "s_barrier") or op.startswith("s_cbranch"):
+            continue
+        if op == "s_nop":
+            now, n = now + 4 * (int(rest) + 1), n + int(rest) + 1
+            continue
+        stores = op.startswith(("ds_write", "global_load_lds"))
+        reads = set().union(*args) if stores else set().union(*args[1:]) if len(args) > 1 else set()
+        if op.startswith("global_load_lds"):
+            reads.add("m0")
+        if op.startswith("v_mfma"):
+            now = max(now, pipe)
+            pipe = now + 16
+            reads -= args[0]   # (an accumulator that goes on)
+        for reg in reads & made.keys():
+            by, at, when = made[reg]
+            if by.startswith("v_mfma") and op.startswith("v_") and not op.startswith("v_mfma"):
+                assert now - when >= 36, (kind, text, now - when)
+            wait = 1 if by.startswith("v_exp") or (reg == "m0" and op.startswith("global_load_lds")) else 0
+            if "_dpp" in op and reg in args[1] and by.startswith("v_"):   # (the operand that is broadcast)
+                wait = 2
+            if by.startswith("v_cmp") and op.startswith("v_cndmask"):
+                wait = 2
+            assert n - at > wait, (kind, text, by, n - at)
+        if not stores and args:
+            for reg in args[0]:
+                made[reg] = (op, n, now)
+        now, n = now + 4, n + 1
+
+
 def gen(upw, kinds, no_barrier=()):
     """All kinds of run in one statement (one set of register constraints for the compiler to meet), chosen by the mode
     operand.  Labels of a kind carry its name; Lover1 / Lover2 / Ldone are common.  A tile of a kind in no_barrier ends
@@ -510,12 +557,16 @@ def gen(upw, kinds, no_barrier=()):
                     off = ring * STAGEB + kb * 16 * ROWB
                     e(f"ds_read_b128 {v(FR[f], 4)}, {v(KRD[sl])}" + (f" offset:{off}" if off else ""))
             e(f"s_branch Lring{ring}{uid}")
+        body = []
         for ring in range(2):
             e(f"Lring{ring}{uid}:")
             st.lds = list(range(st.next_id, st.next_id + (0 if kind in st.no_prefetch else NB)))
             st.next_id += len(st.lds)
-            tile(st, kind, ring, uid, upw)
+            at = len(st.lines)
+            tile(st, kind, ring, upw)
+            body.append(st.lines[at:])
             e(f"s_cbranch_scc0 Ldone{end}" if ring == 0 else f"s_cbranch_scc1 Lring0{uid}")
+        check_waits(kind, body[0] + body[1] + body[0])
         e(f"s_branch Ldone{end}")
     e(f"Lover1{end}:")
     e(f"s_mov_b32 {s(STATUS)}, 1")
