@@ -403,8 +403,8 @@ int pa_profile_clock(void* workspace, int reset, double* shader_mhz);
  * a loop of nothing but bf16 MFMAs, to set a kernel's distance from the published peaks against.  Both are
  * asynchronous on the stream and are recorded by the per-kernel timing above as "calib_copy" and "calib_mfma".
  * pa_calib_copy: dst[0..bytes) = src[0..bytes) (device pointers, 16-byte aligned, bytes a multiple of 16); it moves
- * 2 * bytes.  pa_calib_mfma: 512 workgroups of four waves (two per compute unit) each run `iters` rounds of four
- * independent 32x32x16 bf16 MFMAs per wave; *flops (host) receives the flops of the launch.  out: device, 16-byte
+ * 2 * bytes.  pa_calib_mfma: 512 workgroups of four waves (two per compute unit) each run `iters` rounds of eight
+ * independent 16x16x32 bf16 MFMAs per wave; *flops (host) receives the flops of the launch.  out: device, 16-byte
  * aligned, at least 16,400 bytes; its first two 64-bit words receive the shader cycles and the ticks of the 100 MHz
  * constant counter that one wave spent in its loop (clock in MHz = 100 * cycles / ticks).  PA_EINVAL on bad arguments. */
 int pa_calib_copy(void* dst, const void* src, size_t bytes, void* stream);

@@ -6,7 +6,7 @@
 namespace pa {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Four 16-byte loads in flight per thread, streaming (non-temporal) in both directions.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -23,13 +23,12 @@ __global__ __launch_bounds__(256) void calib_copy_kernel(u32x4* __restrict__ dst
     for (; x < n_vec; x += stride) dst[x] = src[x];
 }
 
-// Every wave runs iters rounds of kChains independent 32x32x16 bf16 MFMAs (each chain waits only for itself, so the
-// matrix pipe always has an independent instruction to take).  out[0], out[1] (64-bit): shader cycles and ticks of the
+// Every wave runs iters rounds of kChains independent 16x16x32 bf16 MFMAs, the form that the attention kernel is made of (each
+// chain waits only for itself, so the matrix pipe always has an independent instruction to take).  out[0], out[1] (64-bit): shader cycles and ticks of the
 // 100 MHz constant counter that wave 0 of workgroup 0 spent in its loop; behind them every lane leaves one float so
 // that the arithmetic cannot be dropped.
-constexpr int kChains = 4;
+constexpr int kChains = 8;
 __global__ __launch_bounds__(256, 2) void calib_mfma_kernel(float* __restrict__ out, int iters) {
-    const int lane = threadIdx.x & 63;
     bf16x8 a, b;
     for (int i = 0; i < 8; ++i) {  // operands with busy bit patterns, in [-1, 1): what toggles costs power
         const unsigned ha = (static_cast<unsigned>(threadIdx.x * 8 + i) + 1u) * 2654435761u;
@@ -37,17 +36,16 @@ __global__ __launch_bounds__(256, 2) void calib_mfma_kernel(float* __restrict__ 
         a[i] = static_cast<__bf16>(static_cast<float>(ha >> 16) * (1.f / 32768.f) - 1.f);
         b[i] = static_cast<__bf16>(static_cast<float>(hb >> 16) * (1.f / 32768.f) - 1.f);
     }
-    f32x16 acc[kChains];
-    for (int c = 0; c < kChains; ++c)
-        for (int i = 0; i < 16; ++i) acc[c][i] = 0.f;
+    f32x4 acc[kChains];
+    for (int c = 0; c < kChains; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
     const long long c0 = clock64(), w0 = wall_clock64();
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int c = 0; c < kChains; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[c], 0, 0, 0);
+        for (int c = 0; c < kChains; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[c], 0, 0, 0);
     }
     float sum = 0.f;
     for (int c = 0; c < kChains; ++c)
-        for (int i = 0; i < 16; ++i) sum += acc[c][i];
+        for (int i = 0; i < 4; ++i) sum += acc[c][i];
     const long long c1 = clock64(), w1 = wall_clock64();
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         reinterpret_cast<unsigned long long*>(out)[0] = static_cast<unsigned long long>(c1 - c0);
@@ -80,7 +78,7 @@ extern "C" int pa_calib_mfma(void* out, size_t out_bytes, int iters, int64_t* fl
                (4 + 4096) * sizeof(float));
     PA_REQUIRE(iters > 0 && iters <= (1 << 24), "pa_calib_mfma: iters out of range");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    *flops = static_cast<int64_t>(pa::kCalibBlocks) * 4 * iters * pa::kChains * (2ll * 32 * 32 * 16);
+    *flops = static_cast<int64_t>(pa::kCalibBlocks) * 4 * iters * pa::kChains * (2ll * 16 * 16 * 32);
     {
         pa::ProfScope prof(pa::kProfCalibMfma, s);
         hipLaunchKernelGGL(pa::calib_mfma_kernel, dim3(pa::kCalibBlocks), dim3(256), 0, s, static_cast<float*>(out), iters);
