@@ -35,9 +35,9 @@ FP8_POOL_CONFIGS = ["long_doc_qa"]   # measured once more with the KV pool held 
 # run cannot share a process with the timed one): FETCH_SIZE x the factor that the same counter shows for append_kv, a
 # plain copy of known size, + WRITE_SIZE x its factor (KiB).  The runs are summarised in
 # profiles/extend_attention_<workload>.md, which is the source named beside each figure.  None = not measured.
-MEASURED_TRAFFIC_BYTES = {"tool_use": 200_199_944, "agent_tree": 2_483_411_547, "long_doc_qa": 538_408_316,
-                          "video_qa": 347_014_323, "programming": 231_973_593, "decode": 275_858_130,
-                          "long_doc_qa_fp8_pool": 322_742_165}
+MEASURED_TRAFFIC_BYTES = {"tool_use": 204_243_296, "agent_tree": 2_319_688_533, "long_doc_qa": 504_178_560,
+                          "video_qa": 347_469_047, "programming": 237_305_966, "decode": 275_244_406,
+                          "long_doc_qa_fp8_pool": 316_209_838}
 
 
 def algorithmic_work(wl, prefix_len):
