@@ -10,8 +10,8 @@ next tile's loads themselves (its rows in the pool through slot ids, 32-bit or 6
 pool, or in the extend tokens), and single tiles, plain or with keys hidden from rows, whose loads the caller issues.
 
 The products are 16x16x32 MFMAs: what bounds the large launches is the chip's power, and these take less of it than 32x32x16 ones
-for the same work (loops of nothing else, operands with random bits, all of the chip: 2,205 to 2,260 TFLOP/s at 2.2 GHz against
-1,905 to 1,940 at 1.9).  A lane then holds two query rows (l % 16 and 16 more) and, of a block of 32 keys, 4 (l / 16) .. + 3 of
+for the same work (loops of nothing else, operands with busy bits, all of the chip, TFLOP/s: 2,205 to 2,260 against 1,905 to 1,940 on one
+box, 1,880 to 2,130 against 1,640 to 1,810 on another).  A lane then holds two query rows (l % 16 and 16 more) and, of a block of 32 keys, 4 (l / 16) .. + 3 of
 each half.
 
 A tile is 64 MFMAs (32 at head dimension 64), in four phases of NB fragments, each multiplied with the rows 0..15 first and,
