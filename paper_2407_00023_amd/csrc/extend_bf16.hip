@@ -1220,9 +1220,11 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                 // (mode 3: the pool is too large for 32-bit byte offsets; rows are then counted in units of 256 bytes)
                 // (mode 6, the fp8 pool: strides of the codes and of the row exponents, and where the latter lie)
                 const uint64_t exp_addr = reinterpret_cast<uint64_t>(exp_g);
+                // (the single tiles look at none of the bases and strides: the fp8 pool's kernels need not keep those of a bf16 pool for them,
+                // 18 scalars that were spilled around the statement)
                 const bool is8 = mode == 6 || mode == 10;
                 const i32x8 c = {uni(page_shift), uni(page_size - 1),
-                                 uni(static_cast<int>(is8 ? page_stride8 : mode == 3 || mode == 9 ? page_stride / ROWB : page_stride)), uni(num_slots - 1),
+                                 uni(static_cast<int>(KV8 ? page_stride8 : mode == 3 || mode == 9 ? page_stride / ROWB : page_stride)), uni(num_slots - 1),
                                  uni(P - 1), uni(static_cast<int>(is8 ? exp_page : x_stride)),
                                  uni(is8 ? static_cast<int>(exp_v) : kv_hi - 1 - P),
                                  uni(static_cast<int>(smem_addr) + wave * (UPW * 1024))};
@@ -1232,8 +1234,8 @@ __global__ __launch_bounds__(256, D == 64 ? (KV8 ? 4 : 3) : 2) void extend_bf16_
                 ring = uni(ring);
                 p_end = uni(p_end);
                 const int row_in_tile = wave * (UPW * RPB) + slot_row();
-                const void* base_k = kind == 2 ? static_cast<const void*>(kx_g) : is8 ? static_cast<const void*>(pool8_g) : static_cast<const void*>(pool_g);
-                const void* base_v = kind == 2 ? static_cast<const void*>(vx_g) : is8 ? static_cast<const void*>(pool8_g + v_off8) : static_cast<const void*>(pool_g + v_off32);
+                const void* base_k = kind == 2 ? static_cast<const void*>(kx_g) : KV8 ? static_cast<const void*>(pool8_g) : static_cast<const void*>(pool_g);
+                const void* base_v = kind == 2 ? static_cast<const void*>(vx_g) : KV8 ? static_cast<const void*>(pool8_g + v_off8) : static_cast<const void*>(pool_g + v_off32);
                 const int lim[RB] = {vis_end[0] - p0 - 4 * g4, vis_end[1] - p0 - 4 * g4};
                 if constexpr (KV8)  // (single tiles only; they end with this wave's loads landed and leave the barrier to the caller)
                     fast_tiles_d128_kv8(uni(mode), oacc, fragments(0), fragments(1), l_run, -m_run[0], -m_run[1], sl_next, k_rd[0], v_rd[0], ld_koff0,
